@@ -12,6 +12,7 @@
 #include <new>
 #include <vector>
 
+size_t f32_lora_linear_ws_floats(int T, int r);
 int f32_lora_linear_fwd(int T, int n_in, int n_out, int r, float s, const float *x, const float *W,
                         const float *bias, const float *A, const float *B, float *y, float *ws, hipStream_t st);
 int f32_lora_linear_bwd(int T, int n_in, int n_out, int r, float s, const float *x, const float *dy,
@@ -939,7 +940,7 @@ bool lin_args_ok(int dtype, int T, int n_in, int n_out, int r)
 size_t slora_lora_linear_ws_bytes(int dtype, int T, int n_in, int n_out, int r)
 {
     if (!lin_args_ok(dtype, T, n_in, n_out, r)) return 0;
-    if (dtype == SLORA_DTYPE_F32) return al256(2 * sizeof(float) * (size_t)T * r);
+    if (dtype == SLORA_DTYPE_F32) return al256(sizeof(float) * f32_lora_linear_ws_floats(T, r));
     return lin_ws(T, n_in, n_out).total;
 }
 

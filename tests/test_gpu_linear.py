@@ -79,6 +79,25 @@ def test_fp32_ragged_shapes(T, n_in, n_out, r, bias):
         assert relerr(g, ref) <= F32_TOL, name
 
 
+# Where the fp32 products change kernel, and ragged edges on both sides of each line: 16 x 16 outputs per block up to 95
+# tiles of 64 x 64, 64 x 64 tiles up to 511 tiles of 128 x 128, float4 loads only for rows of a multiple of 4 floats.
+# Sums of up to 16 400 fp32 products in whatever order: 1e-4 is the bar of the fp32 path.
+@pytest.mark.parametrize("T,n_in,n_out,r,bias", [
+    (1, 768, 768, 4, True),
+    (17, 1280, 1288, 5, False),
+    (500, 768, 704, 2, False),       # 88 and 96 tiles of 64 x 64
+    (333, 259, 130, 3, True),        # odd rows, direct
+    (700, 331, 1027, 9, True),       # odd rows, 64 x 64 tiles
+    (8200, 64, 1030, 16, True),      # 585 tiles of 128 x 128 forward, odd columns
+    (16400, 512, 36, 4, False),      # 516 tiles of 128 x 128 in the input gradient
+])
+def test_fp32_dispatch_edges(T, n_in, n_out, r, bias):
+    c = synth.make_single_layer(T, n_in, n_out, r, seed=17 + T, bias=bias)
+    say("fp32 single layer", T, n_in, n_out, r)
+    for name, g, ref in zip(("y", "dx", "dA", "dB"), _run_f32(c), _oracle(c)):
+        assert relerr(g, ref) <= F32_TOL, name
+
+
 def test_fp32_zero_B_is_bitwise_base():
     import torch
     c = synth.make_single_layer(300, 128, 192, 4, seed=11)
