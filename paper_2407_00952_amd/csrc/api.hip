@@ -908,7 +908,7 @@ int slora_adamw(size_t n, float *p, const float *g, float *m, float *v, float lr
 
 // ---- single layer -----------------------------------------------------------------------------
 namespace {
-struct LinWs { size_t A16, B16, B16T, A16T, zs, ps, WT, ytmp, part, total; };
+struct LinWs { size_t A16, B16, B16T, A16T, zs, ps, WT, part_a, part_b, cnt, split, total; bool can_split; };
 LinWs lin_ws(int T, int n_in, int n_out)
 {
     LinWs w;
@@ -921,10 +921,28 @@ LinWs lin_ws(int T, int n_in, int n_out)
     w.zs = take(2 * (size_t)T * 16);
     w.ps = take(2 * (size_t)T * 16);
     w.WT = take(2 * (size_t)n_in * n_out);
-    w.ytmp = take(2 * (size_t)T * n_out);
-    w.part = take(4 * lora_grad_partial_floats(T, n_in > n_out ? n_in : n_out));
+    w.part_a = take(4 * lora_grad_layer_floats(T, n_in, n_out));
+    w.part_b = take(4 * lora_grad_layer_floats(T, n_out, n_in));
+    // scratch for products that split their contraction, unless it alone would put the layer beyond what the library's own
+    // array holds
+    const size_t more = al256(gemm_split_bytes()) + al256(gemm_split_counter_bytes());
+    w.can_split = off + more <= (size_t)SLORA_NOALLOC_SCRATCH_BYTES || off > (size_t)SLORA_NOALLOC_SCRATCH_BYTES;
+    w.cnt = w.split = 0;
+    if (w.can_split) {
+        w.cnt = take(gemm_split_counter_bytes());
+        w.split = take(gemm_split_bytes());
+    }
     w.total = off;
     return w;
+}
+// the product of a layer call, with its split scratch; the counters are zeroed by the same call's front kernel
+void lin_split(const LinWs &w, char *base, GemmArgs &a, LayerFront &f)
+{
+    if (!w.can_split) return;
+    a.split_part = (float *)(base + w.split);
+    a.split_cnt = (unsigned *)(base + w.cnt);
+    f.zero = a.split_cnt;
+    f.n_zero = (int)(gemm_split_counter_bytes() / 4);
 }
 bool lin_args_ok(int dtype, int T, int n_in, int n_out, int r)
 {
@@ -960,11 +978,16 @@ int slora_lora_linear_fwd(int dtype, int T, int n_in, int n_out, int r, float al
     const LinWs w = lin_ws(T, n_in, n_out);
     char *base = (char *)ws;
     int rc;
-    if ((rc = launch_cast_pad(A, r, n_in, (bf16 *)(base + w.A16), 16, n_in, 0, st))) return rc;
-    if ((rc = launch_cast_pad(B, n_out, r, (bf16 *)(base + w.B16), n_out, 32, 0, st))) return rc;
+    LayerFront f;
+    memset(&f, 0, sizeof(f));
+    f.n_copies = 2;
+    f.copy[0] = {A, (bf16 *)(base + w.A16), r, n_in, 0, 16, n_in};
+    f.copy[1] = {B, (bf16 *)(base + w.B16), n_out, r, 0, n_out, 32};
     GemmArgs a = gemm_base((const bf16 *)x, n_in, (const bf16 *)W, T, n_out, n_in, (const bf16 *)bias, s);
-    a.zmat[0] = (bf16 *)(base + w.A16); a.tmat[0] = (bf16 *)(base + w.B16); a.zspill[0] = (bf16 *)(base + w.zs);
+    a.zmat[0] = (bf16 *)(base + w.A16); a.tmat[0] = (bf16 *)(base + w.B16);
     a.out0 = y;
+    lin_split(w, base, a, f);
+    if ((rc = launch_layer_front(f, st))) return rc;
     return launch_gemm(a, EPI_STORE, 16, st);
 }
 
@@ -997,21 +1020,28 @@ int slora_lora_linear_bwd(int dtype, int T, int n_in, int n_out, int r, float al
     const LinWs w = lin_ws(T, n_in, n_out);
     char *base = (char *)ws;
     int rc;
-    // the forward's rank-space activations zs = s x A^T are needed by dB: rerun the fused forward
-    if ((rc = slora_lora_linear_fwd(dtype, T, n_in, n_out, r, alpha, x, W, nullptr, A, B, base + w.ytmp, ws, ws_bytes,
-                                    stream)))
-        return rc;
-    if ((rc = launch_cast_pad(B, n_out, r, (bf16 *)(base + w.B16T), 16, n_out, 1, st))) return rc;
-    if ((rc = launch_cast_pad(A, r, n_in, (bf16 *)(base + w.A16T), n_in, 32, 1, st))) return rc;
-    if ((rc = launch_transpose_bf16((const bf16 *)W, n_out, n_in, (bf16 *)(base + w.WT), st))) return rc;
+    // zs = s x A^T (for dB), the transposed weight and the padded adapter operands; then dx with ps = s dy B as its
+    // rank-space activations; then both adapter gradients
+    LayerFront f;
+    memset(&f, 0, sizeof(f));
+    f.n_copies = 2;
+    f.copy[0] = {B, (bf16 *)(base + w.B16T), n_out, r, 1, 16, n_out};
+    f.copy[1] = {A, (bf16 *)(base + w.A16T), r, n_in, 1, n_in, 32};
+    f.x = (const bf16 *)x; f.A = A; f.zs = (bf16 *)(base + w.zs); f.scale = s;
+    f.W = (const bf16 *)W; f.WT = (bf16 *)(base + w.WT);
+    f.T = T; f.n_in = n_in; f.n_out = n_out; f.r = r;
+    f.project_blocks = (T + 15) / 16;
+    f.transpose_blocks = ((n_out + 63) / 64) * ((n_in + 63) / 64);
     GemmArgs a = gemm_base((const bf16 *)dy, n_out, (bf16 *)(base + w.WT), T, n_in, n_out, nullptr, s);
     a.zmat[0] = (bf16 *)(base + w.B16T); a.tmat[0] = (bf16 *)(base + w.A16T); a.zspill[0] = (bf16 *)(base + w.ps);
     a.out0 = dx;
+    lin_split(w, base, a, f);
+    if ((rc = launch_layer_front(f, st))) return rc;
     if ((rc = launch_gemm(a, EPI_STORE, 16, st))) return rc;
-    float *part = (float *)(base + w.part);
-    if ((rc = launch_lora_grad((const bf16 *)x, n_in, n_in, (bf16 *)(base + w.ps), 16, r, T, part, dA, 1, st)))
-        return rc;
-    return launch_lora_grad((const bf16 *)dy, n_out, n_out, (bf16 *)(base + w.zs), 16, r, T, part, dB, 0, st);
+    const LoraGradDesc jobs[2] = {
+        {(const bf16 *)x, (bf16 *)(base + w.ps), (float *)(base + w.part_a), dA, nullptr, n_in, 16, n_in, false, 1},
+        {(const bf16 *)dy, (bf16 *)(base + w.zs), (float *)(base + w.part_b), dB, nullptr, n_out, 16, n_out, false, 0}};
+    return launch_lora_grad_jobs(jobs, 2, r, T, st);
 }
 
 // ---- the same backward for callers that cannot allocate ------------------------------------------

@@ -97,10 +97,20 @@ struct GemmArgs {
     // codes [M,ldo] + scales [M,ldo/32], so that the product that consumes it needs no conversion pass
     unsigned char *oq, *os;
     static constexpr bool kEmitCodes = false;   // the bf16 kernel never does
+    // scratch for launches that share the contraction over blocks (null: they do not; contexts never do, so that a
+    // sequence's results do not depend on its batch): gemm_split_bytes() of partial
+    // sums, and gemm_split_counter_bytes() of counters, zero before the launch and left zero by it
+    float *split_part; unsigned *split_cnt;
     unsigned long long *clk;         // measurement hook: four words for clock stamps of this launch, or null
 };
 
 int launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st);
+// the product on 64 x 64 or 128 x 128 tiles (gemm_tile.hip), for launches with too few 256-row tiles
+struct TilePlan { int tile, waves, splits; };            // tile 0: the 256-row kernels
+TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int nz, bool can_split);
+int launch_gemm_tile(const GemmArgs &a, int epi, int nz, const TilePlan &p, hipStream_t st);
+size_t gemm_split_bytes();
+size_t gemm_split_counter_bytes();
 // the same call with the frozen product in MXFP8 (a.mx set): converts X, forms the rank-space activations
 // of the adapted segments with a separate projection kernel (into a.zspill), then one fp8 GEMM launch
 int launch_gemm_mx_stack(const GemmArgs &a, int epi, int nz, hipStream_t st);
@@ -122,13 +132,10 @@ int launch_attn_fwd(const bf16 *qkv, bf16 *o, bf16 *o_lo, float *lse, int n_seq,
 bool attn_bwd_takes_delta(int S);
 int launch_attn_bwd(const bf16 *qkv, const bf16 *o, const bf16 *o_lo, const bf16 *dout, const float *lse,
                     float *delta, bf16 *dqkv, int n_seq, int S, int H, hipStream_t st, bool delta_ready = false);
-// G[c, j] = sum_t X[t, c] * Y[t, j], j < r; written transposed ([r, C]) when out_is_rxC.
-int launch_lora_grad(const bf16 *X, int ldx, int C, const bf16 *Y, int ldy, int r, int T,
-                     float *partials, float *out, int out_is_rxC, hipStream_t st);
-int launch_lora_grad_pair(const bf16 *X, int ldx, int C, const bf16 *Y, int ldy, int r, int T,
-                          float *partials, float *out_a, float *out_b, int out_is_rxC, hipStream_t st);
 size_t lora_grad_partial_floats(int T, int C);
-// several of them in one launch pair (same T and r; each with partial-sum scratch of its own)
+size_t lora_grad_layer_floats(int T, int C, int c_other);
+// G[c, j] = sum_t X[t, c] * Y[t, j], j < r, written transposed ([r, C]) when out_is_rxC; several of them in one launch pair
+// (same T and r; each with partial-sum scratch of its own)
 struct LoraGradDesc {
     const bf16 *X; const bf16 *Y;    // tall operand [T,C] (pitch ldx); skinny operand [T,16] (or [T,32] when dual)
     float *partials;                 // lora_grad_partial_floats(T, C) floats
@@ -140,8 +147,21 @@ int launch_fedavg(int K, const float *const *x, const float *w, size_t n, float 
 int launch_sgd(float *p, const float *g, float lr, size_t n, hipStream_t st);
 int launch_adamw(float *p, const float *g, float *m, float *v, size_t n, float b1, float b2, float eps, float decay,
                  float a, float c, float o1, float o2, hipStream_t st);
-int launch_cast_pad(const float *src, int rows, int cols, bf16 *dst, int drows, int dcols, int transpose,
-                    hipStream_t st);
+// what a single-layer call does before its product, in one launch (layer_front_kernel)
+struct LayerFront {
+    static constexpr int kMaxCopies = 3;
+    struct Copy {                    // fp32 [rows, cols] (optionally transposed) -> bf16 [drows, dcols], zero padded
+        const float *src; bf16 *dst;
+        int rows, cols, transpose, drows, dcols;
+    };
+    Copy copy[kMaxCopies];
+    const bf16 *x; const float *A; bf16 *zs; float scale;   // zs [T,16] = scale x A^T, A [r,n_in]
+    const bf16 *W; bf16 *WT;                                // W [n_out,n_in] -> WT [n_in,n_out]
+    unsigned *zero;
+    int T, n_in, n_out, r;
+    int n_copies, n_zero, project_blocks, transpose_blocks; // project_blocks: (T + 15) / 16 or 0; transpose_blocks: 64 x 64 tiles or 0
+};
+int launch_layer_front(LayerFront f, hipStream_t st);
 int launch_transpose_bf16(const bf16 *src, int rows, int cols, bf16 *dst, hipStream_t st);
 int launch_fill_zero(void *p, size_t bytes, hipStream_t st);
 

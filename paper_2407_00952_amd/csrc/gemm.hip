@@ -15,6 +15,7 @@
 // by asynchronous global->LDS copies (no staging registers), 16-byte XOR-swizzled LDS rows
 // so that both the copies and the MFMA operand reads are bank-conflict free.
 #include "common.h"
+#include "gemm_copy.h"
 #include "gemm_epilogue.h"
 #include "prof.h"
 #include <algorithm>
@@ -26,26 +27,6 @@ constexpr int ROWB = BK * 2;                 // bytes per LDS row (one k-slab of
 constexpr int XB = BM * ROWB, WB = BN * ROWB;
 
 #define SL_WAIT_VM0() __builtin_amdgcn_s_waitcnt(0x0F70)   // vmcnt(0): this wave's copies have landed
-
-// Asynchronous global -> LDS copy of 16 bytes per lane (the 64 lanes fill 1 KB) with a scalar 64-bit base
-// and a 32-bit per-lane byte offset, which keeps the address down to one VGPR per row.  `lds` is the
-// wave-uniform LDS byte address the 1 KB lands at.  Waiting for completion (SL_WAIT_VM0 + barrier) is
-// the caller's job.
-__device__ __forceinline__ void glds_soff(const void *sbase, unsigned voff, unsigned lds)
-{
-    // M0 carries the LDS address; one wait state is required between its write and the copy.  The compiler
-    // treats M0 as reserved and does not accept it on a clobber list, so nothing else in this file may
-    // depend on M0: tests/test_kernel_isa.py checks in the compiled code that every write of M0 is the one
-    // below and that nothing but these copies reads it.
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds), "v"(voff), "s"(sbase)
-                 : "memory");
-}
-__device__ __forceinline__ unsigned lds_addr(const void *p)
-{
-    return (unsigned)(unsigned long long)(const __attribute__((address_space(3))) char *)p;
-}
 
 // NZ = number of rank-space columns handled in the K loop: 16 per adapter whose down-projection
 // spans this K range (0, 16, 32 or 48).  K2P = NZ rounded up to the MFMA k-step of 32.
@@ -630,14 +611,16 @@ static int launch_gemm_inner(const GemmArgs &a, int epi, int nz, hipStream_t st)
     if ((unsigned long long)a.M * a.ldx * 2ull >= (1ull << 32) || (unsigned long long)a.N * a.ldw * 2ull >= (1ull << 32))
         return SL_EINVAL;
     if (nz > 0 && (a.K2 != nz || (a.ldt % 8) || a.ldt < (nz + 31) / 32 * 32 || (a.ldz % 8))) return SL_EINVAL;
+    if (epi == EPI_STORE_DELTA && (nz != 0 || !a.dl_o || !a.dl_lo || !a.dl_out || !a.out0 || (a.N % 64) || a.nseg != 1))
+        return SL_EINVAL;                                // no rank-space branch, whole heads of 64 columns
+    const TilePlan plan = plan_gemm_tile(a.M, a.seg_n, a.nseg, a.K, nz, a.split_part != nullptr && a.split_cnt != nullptr);
+    if (plan.tile) return launch_gemm_tile(a, epi, nz, plan, st);
     switch (epi) {
     case EPI_STORE: return launch_e<EPI_STORE>(a, nz, st);
     case EPI_RESID: return launch_e<EPI_RESID>(a, nz, st);
     case EPI_GELU: return launch_e<EPI_GELU>(a, nz, st);
     case EPI_DGELU: return launch_e<EPI_DGELU>(a, nz, st);
-    case EPI_STORE_DELTA:                                // 4-wave kernel only, whole heads of 64 columns
-        if (nz != 0 || !a.dl_o || !a.dl_lo || !a.dl_out || !a.out0 || (a.N % 64) || a.nseg != 1) return SL_EINVAL;
-        return launch_t4<EPI_STORE_DELTA>(a, st);
+    case EPI_STORE_DELTA: return launch_t4<EPI_STORE_DELTA>(a, st);
     }
     return SL_EINVAL;
 }

@@ -12,10 +12,16 @@
 //  * FedAvg (Sec. III-B step b2, Eq. 8-9): acc = fmaf(w_i, x_i[j], acc), i = 0..K-1.
 #include "common.h"
 #include "prof.h"
+#include "rank_project.h"
+#include <algorithm>
 
 namespace {
 
-constexpr int GR_ROWS = 512;   // token rows per block: 8 tiles of 64
+// Token rows per block: 8 tiles of 64, which keeps the partial sums small beside the operands; 2 tiles where blocks of 8
+// would not fill the chip (fewer than 128 of them for the widest operand: T = 5376, C = 1024 ran 13 us on 44 blocks).
+constexpr int GR_ROWS = 512, GR_ROWS_FEW = 128;
+constexpr long GR_FEW = 128l * GR_ROWS * 256;            // T * C below which that is so
+inline int grad_rows(int T, int C) { return (long)T * C < GR_FEW ? GR_ROWS_FEW : GR_ROWS; }
 constexpr int GR_COLS = 256;   // columns of X per block: 64 per wavefront (two MFMA row tiles)
 constexpr int GX_TILE = 64 * GR_COLS * 2;   // bytes of one 64-token X tile in LDS
 
@@ -64,7 +70,7 @@ __device__ __forceinline__ bf16x8 yfrag_tr(const unsigned char *t, int tok0, int
 template <bool DUAL>
 __device__ __forceinline__ void lora_grad_partial_body(const bf16 *__restrict__ X, int ldx, int C,
                                                        const bf16 *__restrict__ Y, int ldy, int r, int T,
-                                                       float *__restrict__ partials, unsigned char *X0,
+                                                       int rows, float *__restrict__ partials, unsigned char *X0,
                                                        unsigned char *X1, unsigned char *Y0, unsigned char *Y1)
 {
     constexpr int YP = DUAL ? 96 : 32;
@@ -72,8 +78,8 @@ __device__ __forceinline__ void lora_grad_partial_body(const bf16 *__restrict__ 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c_blk = blockIdx.x * GR_COLS;
     const int chunk = blockIdx.y;
-    const int t_begin = chunk * GR_ROWS;
-    const int ntile = (min(T, t_begin + GR_ROWS) - t_begin + 63) >> 6;
+    const int t_begin = chunk * rows;
+    const int ntile = (min(T, t_begin + rows) - t_begin + 63) >> 6;
     const bool wave_ok = c_blk + wave * 64 < C;          // C is a multiple of 64
 
     // X copy: each instruction moves 2 token rows x 512 B; lane l -> row l>>5, physical 16-byte slot
@@ -167,14 +173,14 @@ struct LoraGradJob {
 constexpr int LG_MAX_JOBS = 6;
 struct LoraGradJobs { LoraGradJob j[LG_MAX_JOBS]; };
 
-__global__ __launch_bounds__(256) void lora_grad_partial_kernel(LoraGradJobs jobs, int r, int T)
+__global__ __launch_bounds__(256) void lora_grad_partial_kernel(LoraGradJobs jobs, int r, int T, int rows)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char X0[GX_TILE], X1[GX_TILE];
     __shared__ __attribute__((aligned(16))) unsigned char Y0[64 * 96], Y1[64 * 96];
     const LoraGradJob &jb = jobs.j[blockIdx.z];
     if ((int)blockIdx.x * GR_COLS >= jb.C) return;       // this job's operand is narrower than the widest one
-    if (jb.dual) lora_grad_partial_body<true>(jb.X, jb.ldx, jb.C, jb.Y, jb.ldy, r, T, jb.partials, X0, X1, Y0, Y1);
-    else lora_grad_partial_body<false>(jb.X, jb.ldx, jb.C, jb.Y, jb.ldy, r, T, jb.partials, X0, X1, Y0, Y1);
+    if (jb.dual) lora_grad_partial_body<true>(jb.X, jb.ldx, jb.C, jb.Y, jb.ldy, r, T, rows, jb.partials, X0, X1, Y0, Y1);
+    else lora_grad_partial_body<false>(jb.X, jb.ldx, jb.C, jb.Y, jb.ldy, r, T, rows, jb.partials, X0, X1, Y0, Y1);
 }
 
 // out[j, c] = sum over chunks, in a fixed order: each of the 4 wavefronts of a block sums a
@@ -260,36 +266,94 @@ __global__ __launch_bounds__(256) void adamw_kernel(float *__restrict__ p, const
     }
 }
 
-// src fp32 [rows, cols] -> dst bf16 [drows, dcols], zero padded; optionally transposed first
-__global__ __launch_bounds__(256) void cast_pad_kernel(const float *__restrict__ src, int rows, int cols,
-                                                       bf16 *__restrict__ dst, int drows, int dcols, int transpose)
+// 64 x 64 tile (br, bc) of a bf16 matrix, transposed through LDS; 256 threads, 16-byte accesses on both sides where rows
+// and columns allow them (multiples of 8)
+constexpr int TR_PITCH = 66;                 // elements: column reads of 8 rows fall into different banks
+__device__ __forceinline__ void transpose_tile(const bf16 *__restrict__ src, int rows, int cols, bf16 *__restrict__ dst,
+                                               int br, int bc, bf16 *tile, int tid)
 {
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= drows * dcols) return;
-    const int i = idx / dcols, j = idx - i * dcols;
-    float v = 0.f;
-    if (!transpose) {
-        if (i < rows && j < cols) v = src[(size_t)i * cols + j];
-    } else {
-        if (j < rows && i < cols) v = src[(size_t)j * cols + i];
+    const int r0 = br * 64, c0 = bc * 64;
+    if (((rows | cols) & 7) == 0) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int r = p * 32 + (tid >> 3), c = (tid & 7) * 8;
+            if (r0 + r < rows && c0 + c < cols) {
+                const bf16x8 v = *(const bf16x8 *)(src + (size_t)(r0 + r) * cols + c0 + c);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) tile[r * TR_PITCH + c + i] = v[i];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int c = p * 32 + (tid >> 3), r = (tid & 7) * 8;
+            if (r0 + r < rows && c0 + c < cols) {
+                bf16x8 v;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = tile[(r + i) * TR_PITCH + c];
+                *(bf16x8 *)(dst + (size_t)(c0 + c) * rows + r0 + r) = v;
+            }
+        }
+        return;
     }
-    dst[idx] = f2bf(v);
+    for (int i = tid; i < 64 * 64; i += 256) {
+        const int r = i >> 6, c = i & 63;
+        if (r0 + r < rows && c0 + c < cols) tile[r * TR_PITCH + c] = src[(size_t)(r0 + r) * cols + c0 + c];
+    }
+    __syncthreads();
+    for (int i = tid; i < 64 * 64; i += 256) {
+        const int c = i >> 6, r = i & 63;
+        if (r0 + r < rows && c0 + c < cols) dst[(size_t)(c0 + c) * rows + r0 + r] = tile[r * TR_PITCH + c];
+    }
 }
 
 __global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16 *__restrict__ src, int rows, int cols,
                                                              bf16 *__restrict__ dst)
 {
-    __shared__ bf16 tile[64][66];
-    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-    for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-        const int r = i >> 6, c = i & 63;
-        if (r0 + r < rows && c0 + c < cols) tile[r][c] = src[(size_t)(r0 + r) * cols + c0 + c];
+    __shared__ bf16 tile[64 * TR_PITCH];
+    transpose_tile(src, rows, cols, dst, blockIdx.y, blockIdx.x, tile, threadIdx.x);
+}
+
+// Everything a single-layer call needs before its product, in one launch (each part alone is a few microseconds of
+// latency): bf16 copies of the adapter padded to the MFMA tile, the rank-space activations zs = s x A^T, the transposed
+// frozen weight, and zeroed counters.  blockIdx.x picks the part: projection blocks first (the longest), then the
+// transpose, then the copies.
+__global__ __launch_bounds__(256) void layer_front_kernel(LayerFront f)
+{
+    __shared__ __attribute__((aligned(16))) unsigned char mem[RP_LDS];
+    static_assert(64 * TR_PITCH * 2 <= RP_LDS, "a transposed tile fits too");
+    const int tid = threadIdx.x;
+    int b = blockIdx.x;
+    if (b < f.project_blocks) {
+        rank_project_rows<false, true>(f.x, f.T, f.n_in, f.A, f.r, f.scale, f.zs, nullptr, nullptr, b * 16, mem);
+        return;
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-        const int c = i >> 6, r = i & 63;
-        if (r0 + r < rows && c0 + c < cols) dst[(size_t)(c0 + c) * rows + r0 + r] = tile[r][c];
+    b -= f.project_blocks;
+    if (b < f.transpose_blocks) {
+        const int tc = (f.n_in + 63) >> 6;
+        transpose_tile(f.W, f.n_out, f.n_in, f.WT, b / tc, b % tc, (bf16 *)mem, tid);
+        return;
     }
+    b -= f.transpose_blocks;
+    for (int c = 0; c < f.n_copies; ++c) {
+        const LayerFront::Copy &k = f.copy[c];
+        const int total = k.drows * k.dcols, nb = (total + 1023) >> 10;
+        if (b < nb) {
+            for (int idx = b * 1024 + tid; idx < min(total, (b + 1) * 1024); idx += 256) {
+                const int i = idx / k.dcols, j = idx - i * k.dcols;
+                float v = 0.f;
+                if (!k.transpose) {
+                    if (i < k.rows && j < k.cols) v = k.src[(size_t)i * k.cols + j];
+                } else {
+                    if (j < k.rows && i < k.cols) v = k.src[(size_t)j * k.cols + i];
+                }
+                k.dst[idx] = f2bf(v);
+            }
+            return;
+        }
+        b -= nb;
+    }
+    for (int i = tid; i < f.n_zero; i += 256) f.zero[i] = 0u;
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t *__restrict__ p, size_t nwords)
@@ -343,10 +407,19 @@ __global__ __launch_bounds__(256) void fedavg_kernel(FedTable t, size_t n, float
 
 }  // namespace
 
+// enough for every token count up to T (the larger number of chunks may belong to a smaller count), room for two adapters
+// reduced together
 size_t lora_grad_partial_floats(int T, int C)
 {
-    const size_t nchunk = (size_t)(T + GR_ROWS - 1) / GR_ROWS;
-    return nchunk * 2 * SL_RP * (size_t)C;               // room for two adapters reduced together
+    const long few = std::min<long>((T + GR_ROWS_FEW - 1) / GR_ROWS_FEW, GR_FEW / C / GR_ROWS_FEW + 1);
+    return (size_t)std::max<long>((T + GR_ROWS - 1) / GR_ROWS, few) * 2 * SL_RP * (size_t)C;
+}
+
+// the same for one token count and single adapters, launched together with a job of width c_other
+size_t lora_grad_layer_floats(int T, int C, int c_other)
+{
+    const int rows = grad_rows(T, std::max(C, c_other));
+    return (size_t)((T + rows - 1) / rows) * SL_RP * (size_t)C;
 }
 
 int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStream_t st)
@@ -365,30 +438,15 @@ int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStr
         max_red = red > max_red ? red : max_red;
         bytes += 2.0 * T * (double)q.C;                  // the streaming pass: the tall operand once
     }
-    const int nchunk = (T + GR_ROWS - 1) / GR_ROWS;
+    const int rows = grad_rows(T, max_c), nchunk = (T + rows - 1) / rows;
     const bool rec = prof_begin(PK_LORA_GRAD, st);
     hipLaunchKernelGGL(lora_grad_partial_kernel, dim3((max_c + GR_COLS - 1) / GR_COLS, nchunk, njobs), dim3(256), 0, st,
-                       jobs, r, T);
+                       jobs, r, T, rows);
     prof_end(rec, PK_LORA_GRAD, bytes, st);
     SL_CHECK_LAUNCH("lora_grad_partial");
     hipLaunchKernelGGL(lora_grad_reduce_kernel, dim3((max_red + 63) / 64, 1, njobs), dim3(256), 0, st, jobs, nchunk, r);
     SL_CHECK_LAUNCH("lora_grad_reduce");
     return 0;
-}
-
-int launch_lora_grad(const bf16 *X, int ldx, int C, const bf16 *Y, int ldy, int r, int T, float *partials,
-                     float *out, int out_is_rxC, hipStream_t st)
-{
-    const LoraGradDesc d = {X, Y, partials, out, nullptr, ldx, ldy, C, false, out_is_rxC};
-    return launch_lora_grad_jobs(&d, 1, r, T, st);
-}
-
-// Two adapters that share X: Y carries their rank-space columns in [0,16) and [16,32) of each row.
-int launch_lora_grad_pair(const bf16 *X, int ldx, int C, const bf16 *Y, int ldy, int r, int T, float *partials,
-                          float *out_a, float *out_b, int out_is_rxC, hipStream_t st)
-{
-    const LoraGradDesc d = {X, Y, partials, out_a, out_b, ldx, ldy, C, true, out_is_rxC};
-    return launch_lora_grad_jobs(&d, 1, r, T, st);
 }
 
 int launch_sgd(float *p, const float *g, float lr, size_t n, hipStream_t st)
@@ -413,13 +471,13 @@ int launch_adamw(float *p, const float *g, float *m, float *v, size_t n, float b
     return 0;
 }
 
-int launch_cast_pad(const float *src, int rows, int cols, bf16 *dst, int drows, int dcols, int transpose,
-                    hipStream_t st)
+int launch_layer_front(LayerFront f, hipStream_t st)
 {
-    const int n = drows * dcols;
-    hipLaunchKernelGGL(cast_pad_kernel, dim3((n + 255) / 256), dim3(256), 0, st, src, rows, cols, dst, drows, dcols,
-                       transpose);
-    SL_CHECK_LAUNCH("cast_pad");
+    if ((f.project_blocks && (f.n_in % 32)) || f.n_copies > LayerFront::kMaxCopies) return SL_EINVAL;
+    long blocks = (long)f.project_blocks + f.transpose_blocks + (f.n_zero > 0 ? 1 : 0);
+    for (int c = 0; c < f.n_copies; ++c) blocks += (f.copy[c].drows * f.copy[c].dcols + 1023) / 1024;
+    hipLaunchKernelGGL(layer_front_kernel, dim3((unsigned)blocks), dim3(256), 0, st, f);
+    SL_CHECK_LAUNCH("layer_front");
     return 0;
 }
 

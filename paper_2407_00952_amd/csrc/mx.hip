@@ -21,6 +21,8 @@
 #include "common.h"
 #include "gemm_epilogue.h"
 #include "mx_codec.h"
+#include "rank_project.h"
+#include <cstring>
 
 namespace {
 
@@ -62,6 +64,17 @@ __global__ __launch_bounds__(128) void mx_quantize_kernel(const bf16 *__restrict
         *(uint2 *)(codes + row * (long long)K + ch * 8) = make_uint2(out[0], out[1]);
         if ((ch & 3) == 0) scales[row * (long long)(K >> 5) + (ch >> 2)] = (unsigned char)scode;
     }
+}
+
+// Codes, scales and rank-space activations of a layer's operand in one pass (see rank_project.h)
+__global__ __launch_bounds__(256) void mx_quantize_project_kernel(const bf16 *__restrict__ x, int M, int K,
+                                                                  unsigned char *__restrict__ codes,
+                                                                  unsigned char *__restrict__ scales,
+                                                                  const bf16 *__restrict__ Z, float scale,
+                                                                  bf16 *__restrict__ out)
+{
+    __shared__ __attribute__((aligned(16))) unsigned char lds[RP_LDS];
+    rank_project_rows<true, false>(x, M, K, Z, SL_RP, scale, out, codes, scales, blockIdx.x * 16, lds);
 }
 
 // The same for FP4 E2M1 elements (frozen weights): emax 2, so the scale code is the biased exponent - 2;
@@ -455,6 +468,15 @@ int launch_quantize(const bf16 *x, long long ldx, long long M, int K, unsigned c
     return 0;
 }
 
+int launch_quantize_project(const bf16 *x, int M, int K, unsigned char *codes, unsigned char *scales, const bf16 *Z,
+                            float scale, bf16 *out, hipStream_t st)
+{
+    hipLaunchKernelGGL(mx_quantize_project_kernel, dim3((M + 15) / 16), dim3(256), 0, st, x, M, K, codes, scales, Z, scale,
+                       out);
+    SL_CHECK_LAUNCH("mx_quantize_project");
+    return 0;
+}
+
 int launch_gemm_mx(const MxArgs &a, hipStream_t st, bool w4 = false, int epi = EPI_STORE)
 {
     const int nb = ((a.M + BM - 1) / BM) * (((a.seg_n + BN - 1) / BN) * a.nseg);
@@ -528,7 +550,7 @@ MxPack mx_pack(int n_in, int n_out)
     return p;
 }
 
-struct MxLinWs { size_t A16, B32, B16T, A32T, zs, ps, q, qs, part, total; };
+struct MxLinWs { size_t A16, B32, B16T, A32T, zs, ps, q, qs, part_a, part_b, total; };
 MxLinWs mx_lin_ws(int T, int n_in, int n_out)
 {
     MxLinWs w;
@@ -543,7 +565,8 @@ MxLinWs mx_lin_ws(int T, int n_in, int n_out)
     w.ps = take(2 * (size_t)T * 16);
     w.q = take((size_t)T * nmax);
     w.qs = take((size_t)T * nmax / 32);
-    w.part = take(4 * lora_grad_partial_floats(T, (int)nmax));
+    w.part_a = take(4 * lora_grad_layer_floats(T, n_in, n_out));
+    w.part_b = take(4 * lora_grad_layer_floats(T, n_out, n_in));
     w.total = off;
     return w;
 }
@@ -708,12 +731,15 @@ int slora_mx_lora_linear_fwd(int32_t T, int32_t n_in, int32_t n_out, int32_t r, 
     const unsigned char *pw = (const unsigned char *)packed_w;
     const float s = alpha / (float)r;
     int rc;
-    if ((rc = launch_cast_pad(A, r, n_in, (bf16 *)(base + w.A16), 16, n_in, 0, st))) return rc;
-    if ((rc = launch_cast_pad(B, n_out, r, (bf16 *)(base + w.B32), n_out, 32, 0, st))) return rc;
-    if ((rc = launch_rank_project((const bf16 *)x, n_in, T, n_in, (const bf16 *)(base + w.A16), n_in, 16, s,
-                                  (bf16 *)(base + w.zs), st)))
+    LayerFront f;
+    memset(&f, 0, sizeof(f));
+    f.n_copies = 2;
+    f.copy[0] = {A, (bf16 *)(base + w.A16), r, n_in, 0, 16, n_in};
+    f.copy[1] = {B, (bf16 *)(base + w.B32), n_out, r, 0, n_out, 32};
+    if ((rc = launch_layer_front(f, st))) return rc;
+    if ((rc = launch_quantize_project((const bf16 *)x, T, n_in, base + w.q, base + w.qs, (const bf16 *)(base + w.A16), s,
+                                      (bf16 *)(base + w.zs), st)))
         return rc;
-    if ((rc = launch_quantize((const bf16 *)x, n_in, T, n_in, base + w.q, base + w.qs, st))) return rc;
     MxArgs a = mx_plain(base + w.q, base + w.qs, pw + p.wq, pw + p.ws, bias, y, T, n_out, n_in);
     a.zs[0] = (const bf16 *)(base + w.zs); a.tmat[0] = (const bf16 *)(base + w.B32);
     return launch_gemm_mx(a, st);
@@ -735,22 +761,25 @@ int slora_mx_lora_linear_bwd(int32_t T, int32_t n_in, int32_t n_out, int32_t r, 
     const unsigned char *pw = (const unsigned char *)packed_w;
     const float s = alpha / (float)r;
     int rc;
-    // zs = s x A^T (for dB) and ps = s dy B (for dA and for the low-rank part of dx)
-    if ((rc = launch_cast_pad(A, r, n_in, (bf16 *)(base + w.A16), 16, n_in, 0, st))) return rc;
-    if ((rc = launch_rank_project((const bf16 *)x, n_in, T, n_in, (const bf16 *)(base + w.A16), n_in, 16, s,
-                                  (bf16 *)(base + w.zs), st)))
+    // zs = s x A^T (for dB) and the padded adapter operands; then the codes of dy with ps = s dy B (for dA and for the
+    // low-rank part of dx) in one pass; then dx; then both adapter gradients
+    LayerFront f;
+    memset(&f, 0, sizeof(f));
+    f.n_copies = 2;
+    f.copy[0] = {B, (bf16 *)(base + w.B16T), n_out, r, 1, 16, n_out};
+    f.copy[1] = {A, (bf16 *)(base + w.A32T), r, n_in, 1, n_in, 32};
+    f.x = (const bf16 *)x; f.A = A; f.zs = (bf16 *)(base + w.zs); f.scale = s;
+    f.T = T; f.n_in = n_in; f.n_out = n_out; f.r = r;
+    f.project_blocks = (T + 15) / 16;
+    if ((rc = launch_layer_front(f, st))) return rc;
+    if ((rc = launch_quantize_project((const bf16 *)dy, T, n_out, base + w.q, base + w.qs, (const bf16 *)(base + w.B16T), s,
+                                      (bf16 *)(base + w.ps), st)))
         return rc;
-    if ((rc = launch_cast_pad(B, n_out, r, (bf16 *)(base + w.B16T), 16, n_out, 1, st))) return rc;
-    if ((rc = launch_cast_pad(A, r, n_in, (bf16 *)(base + w.A32T), n_in, 32, 1, st))) return rc;
-    if ((rc = launch_rank_project((const bf16 *)dy, n_out, T, n_out, (const bf16 *)(base + w.B16T), n_out, 16, s,
-                                  (bf16 *)(base + w.ps), st)))
-        return rc;
-    if ((rc = launch_quantize((const bf16 *)dy, n_out, T, n_out, base + w.q, base + w.qs, st))) return rc;
     MxArgs a = mx_plain(base + w.q, base + w.qs, pw + p.tq, pw + p.ts, nullptr, dx, T, n_in, n_out);
     a.zs[0] = (const bf16 *)(base + w.ps); a.tmat[0] = (const bf16 *)(base + w.A32T);
     if ((rc = launch_gemm_mx(a, st))) return rc;
-    float *part = (float *)(base + w.part);
-    if ((rc = launch_lora_grad((const bf16 *)x, n_in, n_in, (const bf16 *)(base + w.ps), 16, r, T, part, dA, 1, st)))
-        return rc;
-    return launch_lora_grad((const bf16 *)dy, n_out, n_out, (const bf16 *)(base + w.zs), 16, r, T, part, dB, 0, st);
+    const LoraGradDesc jobs[2] = {
+        {(const bf16 *)x, (bf16 *)(base + w.ps), (float *)(base + w.part_a), dA, nullptr, n_in, 16, n_in, false, 1},
+        {(const bf16 *)dy, (bf16 *)(base + w.zs), (float *)(base + w.part_b), dB, nullptr, n_out, 16, n_out, false, 0}};
+    return launch_lora_grad_jobs(jobs, 2, r, T, st);
 }

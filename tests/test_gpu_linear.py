@@ -167,3 +167,44 @@ def test_frozen_linear_bf16(T, n_in, n_out, bias):
     say("frozen linear", T, n_in, n_out, "rel err %.2e" % e)
     # fp32 accumulation and one rounding to bf16: half a bf16 ulp of the largest output
     assert e <= 2.0 ** -8
+
+
+# Where the bf16 products change kernel (64 x 64 tiles up to 512 of them, 128 x 128 tiles with 8 waves up to 256, with 4
+# where they beat the 256-row tiles), with ragged rows and columns on both sides; one slab and odd numbers of slabs.
+@pytest.mark.parametrize("T,n_in,n_out,bias", [
+    (1, 1152, 64, True),             # one tile
+    (130, 2432, 72, False),          # six tiles, columns past a tile
+    (300, 1216, 776, True),          # 65 tiles
+    (1020, 64, 2040, True),          # 512 tiles of 64 x 64, one slab
+    (1030, 192, 2040, False),        # 544: 128 x 128 with 8 waves, three slabs
+    (2050, 320, 2056, True),         # 289 tiles of 128 x 128, five slabs
+])
+def test_frozen_linear_dispatch_edges(T, n_in, n_out, bias):
+    import torch
+    c = synth.make_single_layer(T, n_in, n_out, 1, seed=400 + T + n_in, quant=True, bias=bias)
+    x, W = B.to_device_bf16(c["x"]), B.to_device_bf16(c["W"])
+    b = None if c["b"] is None else B.to_device_bf16(c["b"])
+    y = torch.full((T, n_out), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.slora_frozen_linear_bf16(T, n_in, n_out, x, W, b, y)
+    torch.cuda.synchronize()
+    ref, _ = so.lora_linear_fwd(c["x"], c["W"], c["b"], np.zeros_like(c["A"]), np.zeros_like(c["B"]), 1.0)
+    e = relerr(B.from_device_bf16(y), ref)
+    say("frozen linear", T, n_in, n_out, "rel err %.2e" % e)
+    assert e <= 2.0 ** -8                # as above: one rounding to bf16
+
+
+@pytest.mark.parametrize("T,n_in,n_out,r", [
+    (3, 2432, 128, 16),              # contraction shared over four blocks (9 and 10 slabs), forward; one row of tiles
+    (130, 128, 2432, 3),             # the same in the input gradient
+    (1100, 192, 1984, 5),            # 128 x 128 tiles, 8 waves; odd number of slabs
+    (260, 1216, 832, 2),             # 65 tiles, two shares
+    (2100, 2048, 320, 8),            # 289 tiles of 128 x 128 in the input gradient
+])
+def test_bf16_layer_dispatch_edges(T, n_in, n_out, r):
+    c = synth.make_single_layer(T, n_in, n_out, r, seed=500 + T + r, quant=True, bias=True)
+    c["B"] = synth.round_bf16(c["B"] * 10)
+    say("bf16 single layer", T, n_in, n_out, r)
+    for name, g, rf in zip(("y", "dx", "dA", "dB"), _run_bf16(c), _oracle(c)):
+        e = relerr(g, rf)
+        say("   %s rel err %.2e" % (name, e))
+        assert e <= BF16_TOL, (name, e)

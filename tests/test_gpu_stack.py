@@ -262,6 +262,21 @@ def test_workload5_sampled():
     _sampled_parity(synth.CONFIGS[5], [50, 9])
 
 
+# The kernels a product of a context may run on, chosen by its tile counts: one sequence alone (64 x 64 tiles throughout), three
+# (128 x 128 tiles with 8 waves for q|k|v and the MLP's wide products) and eleven (with 4 waves, or 256-row tiles).
+# Sequences do not interact, so each one's results must be the same bits whichever kernels its batch ran on.
+@pytest.mark.parametrize("proj", [(), synth.PROJ_NAMES])
+def test_results_do_not_depend_on_the_batch(proj):
+    cfg = synth.tiny_config(d_model=768, n_head=12, d_ff=3072, n_blocks=1, lora_r=5, lora_proj=proj,
+                            n_clients=11, batch=1, seq_len=512, seed=synth.BASE_SEED + 130)
+    inp = _boost_B(synth.make_stack_inputs(cfg), cfg, target=16.0)
+    srv, Y, dX, _ = gpu_round(cfg, inp)
+    for n in (1, 3):
+        _, y, dx, _ = gpu_round(cfg, inp, clients=inp["clients"][:n], dY=inp["dY"][:n], server=srv)
+        assert np.array_equal(y, Y[:n]) and all(np.array_equal(a, b) for a, b in zip(dx, dX[:n])), n
+    srv.close()
+
+
 # Token counts at which a wavefront of the adapter-gradient reduction sums eight or more 512-token chunks
 # (T >= 14337: the path with eight loads in flight, which workloads 3-5 take), on a stack narrow enough for
 # the oracle to run the whole batch: 33 sequences x 512 tokens = 33 chunks, i.e. 9 + 9 + 9 + 6 per wavefront
