@@ -82,9 +82,66 @@ __device__ __forceinline__ bf16x8 frag_tr(const unsigned char *t, int col0, int 
     return u.v;
 }
 
-// ------------------------------------------------------------------------------------------
+// The lane's byte offsets of both kinds of fragment inside a 32-row piece of a tile (neither swizzle looks above bit 2
+// of the row): row-major fragment of k-step ks at rm[ks]; transposed fragment of columns 32 dt .. and rows 16 hh .. at
+// tr[dt] + 2048 hh.
+__device__ __forceinline__ void frag_offsets(int lane, int (&rm)[4], int (&tr)[2])
+{
+    const int r32 = lane & 31, g = lane >> 5, q = lane & 3, e = (lane >> 2) & 3, half = (lane >> 4) & 1;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) rm[ks] = swz128(r32, ks * 2 + g);
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt) {
+        const int col = 32 * dt + 16 * half + 4 * q;
+        tr[dt] = swz128(4 * g + e, col >> 3) + (col & 7) * 2;
+    }
+}
+__device__ __forceinline__ bf16x8 read_tr(const unsigned char *p)
+{
+    union { v4s s[2]; bf16x8 v; } u;
+    u.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)p);
+    u.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)(p + 1024));
+    return u.v;
+}
+
 constexpr int OST_PITCH = 144;                                // bytes per staged output row (128 + pad: see fwd_store)
 constexpr int OST_B = 32 * OST_PITCH;
+
+// One wave's asynchronous copy of 32 rows of 128 bytes (global pitch ld) into a swizzled row-major piece of its own: whole
+// lines, where reading the MFMA fragments straight from memory touches 32 lines with 32 bytes each per instruction.
+__device__ __forceinline__ void rows32_copy_async(unsigned char *dst, const bf16 *src, int ld, int lane)
+{
+    const int lrow = lane >> 3, lch = (lane & 7) ^ swm(lane >> 3);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) AT_GLDS(src + (size_t)(p * 8 + lrow) * ld + lch * 8, dst + p * 1024);
+}
+
+// 32 rows x 64 columns held as two MFMA accumulators (a lane has 4 consecutive columns of row r32 per register group)
+// leave through the wave's staging area as whole lines (see fwd_store)
+__device__ __forceinline__ void store_rows32(unsigned char *stg, const f32x16 (&acc)[2], float scale, bf16 *dst, int ld, int lane)
+{
+    const int r32 = lane & 31, g = lane >> 5, orow = lane >> 3, och = lane & 7;
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+            bf16x4 w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = f2bf(acc[dt][4 * e4 + i] * scale);
+            *(bf16x4 *)(stg + r32 * OST_PITCH + (32 * dt + 8 * e4 + 4 * g) * 2) = w;
+        }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    bf16x8 rows[4];
+#pragma unroll
+    for (int it = 0; it < 4; ++it) rows[it] = *(const bf16x8 *)(stg + (8 * it + orow) * OST_PITCH + och * 16);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) *(bf16x8 *)(dst + (size_t)(8 * it + orow) * ld + och * 8) = rows[it];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// ------------------------------------------------------------------------------------------
 
 __global__ __launch_bounds__(256, 3) void attn_fwd_kernel(const bf16 *__restrict__ qkv, bf16 *__restrict__ o,
                                                        bf16 *__restrict__ o_lo, float *__restrict__ lse, int S,
@@ -286,13 +343,19 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_kernel(const bf16 *__restrict
 
 // ------------------------------------------------------------------------------------------
 // dQ (and delta = rowsum(dO * O), which the dK/dV kernel reads afterwards)
-__global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(const bf16 *__restrict__ qkv, const bf16 *__restrict__ o,
+// Bound by the vector work between the products and by the operand rows of each query tile, which nothing hides but
+// the CU's other block.  So: one copy of the 32 x 32 body (all operand reads of a product issued before its first MFMA;
+// a copy per case spilled), LDS offsets formed once per lane, -delta carried into dP as the accumulator's start, the
+// mask only on the diagonal half, and Q, dO, O and dQ moved as whole 128-byte lines.  S = 1024, 32 x 16 heads, with the
+// dK/dV kernel: 412 -> 372 us; three blocks per CU instead of two spill and take 4 us more.
+__global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16 *__restrict__ qkv, const bf16 *__restrict__ o,
                                                           const bf16 *__restrict__ o_lo,
                                                           const bf16 *__restrict__ dout,
                                                           const float *__restrict__ lse, float *__restrict__ delta,
                                                           bf16 *__restrict__ dqkv, int S, int H, int n_seq)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char K0[TILE_B], V0[TILE_B], K1[TILE_B], V1[TILE_B];
+    __shared__ __attribute__((aligned(1024))) unsigned char KV[2][2 * TILE_B];
+    __shared__ __attribute__((aligned(1024))) unsigned char Ost[4 * OST_B];
     // block ids decoded as in the forward: the query tiles of a (sequence, head) share an XCD, and a block
     // takes the tiles j and nqt-1-j one after the other so that every block has the same work
     const int nqt = (S + 127) >> 7, npb = (nqt + 1) >> 1;
@@ -304,6 +367,8 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(const bf16 *__restr
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bf16 *base = qkv + (size_t)n * S * ld + a * 64;
+    int rm[4], tr[2];
+    frag_offsets(lane, rm, tr);
 #pragma clang loop unroll(disable)
     for (int ph = 0; ph < 2; ++ph) {
     const int qt = ph == 0 ? nqt - 1 - idx % npb : idx % npb;
@@ -315,106 +380,126 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(const bf16 *__restr
     const bool active = qb < S;
     const int q = qb + r32;
 
+    // first tile, and this wave's rows of Q (its staging area) and dO (the second buffer, still free) as whole lines
+    const bf16 *kg = base + d, *vg = base + 2 * d;
+    unsigned char *stg = Ost + wave * OST_B, *dO_s = KV[1] + wave * 4096;
+    tile_copy_async(KV[0], kg, ld, wave, lane);
+    tile_copy_async(KV[0] + TILE_B, vg, ld, wave, lane);
     bf16x8 qf[4], dof[4];
     float lse_q = 0.f, dl = 0.f;
     if (active) {
-        const bf16 *orow = o + ((size_t)n * S + q) * d + a * 64;
-        const bf16 *lrow = o_lo + ((size_t)n * S + q) * d + a * 64;
-        const bf16 *drow = dout + ((size_t)n * S + q) * d + a * 64;
+        rows32_copy_async(stg, base + (size_t)qb * ld, ld, lane);
+        rows32_copy_async(dO_s, dout + ((size_t)n * S + qb) * d + a * 64, d, lane);
         // delta = rowsum(dO * O) with O to ~16 bits (o + o_lo): when the value rows of a head share a
-        // large common component, dP - delta cancels it, and a delta built from bf16 O alone would not
+        // large common component, dP - delta cancels it, and a delta built from bf16 O alone would not.
+        // 8 lanes per row, 8 rows per pass
+        const size_t off = ((size_t)n * S + qb + (lane >> 3)) * d + a * 64 + (lane & 7) * 8;
+        bf16x8 ov[4], lv[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            ov[p] = *(const bf16x8 *)(o + off + (size_t)(8 * p) * d);
+            lv[p] = *(const bf16x8 *)(o_lo + off + (size_t)(8 * p) * d);
+        }
+        lse_q = lse[((size_t)n * H + a) * S + q];
+        AT_WAIT_VM0();
+        asm volatile("" ::: "memory");
+        float t[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const bf16x8 dv = *(const bf16x8 *)(dO_s + swz128(8 * p + (lane >> 3), lane & 7));
+            t[p] = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t[p] += bf2f(dv[i]) * (bf2f(ov[p][i]) + bf2f(lv[p][i]));
+            t[p] += __shfl_xor(t[p], 1, 64);
+            t[p] += __shfl_xor(t[p], 2, 64);
+            t[p] += __shfl_xor(t[p], 4, 64);
+        }
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const float v = __shfl(t[p], (r32 & 7) * 8, 64);
+            if ((r32 >> 3) == p) dl = v;
+        }
+        if (g == 0) delta[((size_t)n * H + a) * S + q] = dl;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-            qf[ks] = *(const bf16x8 *)(base + (size_t)q * ld + ks * 16 + g * 8);
-            dof[ks] = *(const bf16x8 *)(drow + ks * 16 + g * 8);
-            bf16x8 of = *(const bf16x8 *)(orow + ks * 16 + g * 8);
-            bf16x8 ol = *(const bf16x8 *)(lrow + ks * 16 + g * 8);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) dl += bf2f(dof[ks][i]) * (bf2f(of[i]) + bf2f(ol[i]));
+            qf[ks] = *(const bf16x8 *)(stg + rm[ks]);
+            dof[ks] = *(const bf16x8 *)(dO_s + rm[ks]);
         }
-        dl += __shfl_xor(dl, 32, 64);
-        lse_q = lse[((size_t)n * H + a) * S + q];
-        if (g == 0) delta[((size_t)n * H + a) * S + q] = dl;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // read before the second buffer is filled
     }
     f32x16 dqacc[2] = {zero16(), zero16()};
     const int kv_end = min(S, qt * 128 + 128);
     const int ntile = kv_end >> 6;
 
-#define DQ_TILE(Ks, Vs, k0)                                                                            \
-    if (active && (k0) <= qb + 31) {                                                                   \
-        const bool need_mask = (k0) + 63 > qb;                                                         \
-        _Pragma("unroll") for (int mt = 0; mt < 2; ++mt) {                                             \
-            f32x16 sacc = zero16(), dpacc = zero16();                                                  \
-            _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {                                         \
-                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rm(Ks, mt * 32 + r32, ks, g),      \
-                                                                qf[ks], sacc, 0, 0, 0);                \
-                dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rm(Vs, mt * 32 + r32, ks, g),     \
-                                                                 dof[ks], dpacc, 0, 0, 0);             \
-            }                                                                                          \
-            _Pragma("unroll") for (int e = 0; e < 16; ++e) {                                           \
-                const int key = (k0) + 32 * mt + 8 * (e >> 2) + 4 * g + (e & 3);                       \
-                float p = __builtin_amdgcn_exp2f(fmaf(sacc[e], kScaleLog2, -lse_q));                   \
-                if (need_mask && key > q) p = 0.f;                                                     \
-                sacc[e] = p * (dpacc[e] - dl);                                                         \
-            }                                                                                          \
-            _Pragma("unroll") for (int hh = 0; hh < 2; ++hh) {                                         \
-                bf16x8 dsb;                                                                            \
-                _Pragma("unroll") for (int i = 0; i < 8; ++i) dsb[i] = f2bf(sacc[8 * hh + i]);         \
-                _Pragma("unroll") for (int dt = 0; dt < 2; ++dt)                                       \
-                    dqacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                               \
-                        frag_tr(Ks, 32 * dt, 32 * mt + 16 * hh, lane), dsb, dqacc[dt], 0, 0, 0);       \
-            }                                                                                          \
-        }                                                                                              \
-    }
-
-    const bf16 *kg = base + d, *vg = base + 2 * d;
-    tile_copy_async(K0, kg, ld, wave, lane);
-    tile_copy_async(V0, vg, ld, wave, lane);
-    AT_WAIT_VM0();
-    __syncthreads();
-    int j = 0;
-    for (; j + 2 <= ntile; j += 2) {
-        tile_copy_async(K1, kg + (size_t)(j + 1) * 64 * ld, ld, wave, lane);
-        tile_copy_async(V1, vg + (size_t)(j + 1) * 64 * ld, ld, wave, lane);
-        DQ_TILE(K0, V0, j * 64)
+    // -delta as the addend of the dP product: dP - delta leaves the matrix cores ready
+    f32x16 ndl;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) ndl[e] = -dl;
+    for (int j = 0; j < ntile; ++j) {
         AT_WAIT_VM0();
-        __syncthreads();
-        if (j + 2 < ntile) {
-            tile_copy_async(K0, kg + (size_t)(j + 2) * 64 * ld, ld, wave, lane);
-            tile_copy_async(V0, vg + (size_t)(j + 2) * 64 * ld, ld, wave, lane);
+        __syncthreads();                                 // tile j has landed and nobody reads the other buffer any more
+        if (j + 1 < ntile) {
+            tile_copy_async(KV[(j + 1) & 1], kg + (size_t)(j + 1) * 64 * ld, ld, wave, lane);
+            tile_copy_async(KV[(j + 1) & 1] + TILE_B, vg + (size_t)(j + 1) * 64 * ld, ld, wave, lane);
         }
-        DQ_TILE(K1, V1, (j + 1) * 64)
-        AT_WAIT_VM0();
-        __syncthreads();
-    }
-    if (j < ntile) DQ_TILE(K0, V0, j * 64)
-#undef DQ_TILE
-
-    if (active) {
-        bf16 *drow = dqkv + ((size_t)n * S + q) * ld + a * 64;
+        // the tile's 32-key halves at or below the diagonal, one copy of the body for all of them; all operand reads of
+        // a product go out before its first MFMA
+        const int nhalf = active ? min(max((qb + 32 - j * 64) >> 5, 0), 2) : 0;
+#pragma clang loop unroll(disable)
+        for (int mt = 0; mt < nhalf; ++mt) {
+            const unsigned char *kt_ = KV[j & 1] + mt * 4096, *vt_ = kt_ + TILE_B;
+            bf16x8 fk[4], fv[4];
 #pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-                bf16x4 w;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) w[i] = f2bf(dqacc[dt][4 * e4 + i] * 0.125f);
-                *(bf16x4 *)(drow + 32 * dt + 8 * e4 + 4 * g) = w;
+            for (int ks = 0; ks < 4; ++ks) {
+                fk[ks] = *(const bf16x8 *)(kt_ + rm[ks]);
+                fv[ks] = *(const bf16x8 *)(vt_ + rm[ks]);
             }
+            __builtin_amdgcn_sched_barrier(0);
+            f32x16 sacc = zero16(), dpacc = ndl;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk[ks], qf[ks], sacc, 0, 0, 0);
+                dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv[ks], dof[ks], dpacc, 0, 0, 0);
+            }
+            bf16x8 ft[2][2];
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+                for (int dt = 0; dt < 2; ++dt) ft[hh][dt] = read_tr(kt_ + hh * 2048 + tr[dt]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (j * 64 + mt * 32 == qb) {                // the half on the diagonal: keys behind the query leave nothing
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (8 * (e >> 2) + 4 * g + (e & 3) > r32) sacc[e] = -INFINITY;
+            }
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                bf16x8 dsb;
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    dsb[i] = f2bf(__builtin_amdgcn_exp2f(fmaf(sacc[8 * hh + i], kScaleLog2, -lse_q)) * dpacc[8 * hh + i]);
+#pragma unroll
+                for (int dt = 0; dt < 2; ++dt)
+                    dqacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ft[hh][dt], dsb, dqacc[dt], 0, 0, 0);
+            }
+        }
     }
+
+    if (active) store_rows32(stg, dqacc, 0.125f, dqkv + ((size_t)n * S + qb) * ld + a * 64, ld, lane);
     }   // pass
 }
 
 // ------------------------------------------------------------------------------------------
-// dK, dV: each wavefront owns 32 keys and walks the query tiles that can see them
+// dK, dV: each wavefront owns 32 keys and walks the query tiles that can see them (bound and layout as in the dQ kernel)
 __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(const bf16 *__restrict__ qkv,
                                                            const bf16 *__restrict__ dout,
                                                            const float *__restrict__ lse,
                                                            const float *__restrict__ delta,
                                                            bf16 *__restrict__ dqkv, int S, int H, int n_seq)
 {
-    __shared__ __attribute__((aligned(1024))) unsigned char Q0[TILE_B], D0[TILE_B], Q1[TILE_B], D1[TILE_B];
-    __shared__ __align__(16) float st0[128], st1[128];   // lse | delta of the 64 queries of a tile
+    __shared__ __attribute__((aligned(1024))) unsigned char QD[2][2 * TILE_B];
+    __shared__ __attribute__((aligned(1024))) unsigned char Ost[4 * OST_B];
+    __shared__ __align__(16) float st[2][128];           // lse | -delta of the 64 queries of a tile
     // block ids decoded as in the forward: the key tiles of a (sequence, head) share an XCD, and a block takes
     // the tiles j (most query tiles to walk) and nkt-1-j one after the other: equal work per block
     const int nkt = (S + 127) >> 7, npb = (nkt + 1) >> 1;
@@ -428,6 +513,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(const bf16 *__rest
     const bf16 *base = qkv + (size_t)n * S * ld + a * 64;
     const bf16 *dbase = dout + (size_t)n * S * d + a * 64;
     const float *lse_b = lse + ((size_t)n * H + a) * S, *dl_b = delta + ((size_t)n * H + a) * S;
+    int rm[4], tr[2];
+    frag_offsets(lane, rm, tr);
 #pragma clang loop unroll(disable)
     for (int ph = 0; ph < 2; ++ph) {
     const int kvt = ph == 0 ? idx % npb : nkt - 1 - idx % npb;
@@ -439,119 +526,109 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(const bf16 *__rest
     const bool active = kb < S;
     const int key = kb + r32;
 
-    bf16x8 kf[4], vf[4];
-    if (active) {
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            kf[ks] = *(const bf16x8 *)(base + d + (size_t)key * ld + ks * 16 + g * 8);
-            vf[ks] = *(const bf16x8 *)(base + 2 * d + (size_t)key * ld + ks * 16 + g * 8);
-        }
-    }
     f32x16 dkacc[2] = {zero16(), zero16()}, dvacc[2] = {zero16(), zero16()};
     const int q_first = kvt * 128;
     const int ntile = (S - q_first) >> 6;
 
-#define DKV_TILE(Qs, Ds, stt, q0)                                                                      \
-    if (active) {                                                                                      \
-        _Pragma("unroll") for (int st = 0; st < 2; ++st) {                                             \
-            const int qs = (q0) + 32 * st;                                                             \
-            if (qs + 31 >= kb) {                                                                       \
-                const bool need_mask = qs < kb + 31;                                                   \
-                f32x16 sacc = zero16(), dpacc = zero16();                                              \
-                _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {                                     \
-                    sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rm(Qs, 32 * st + r32, ks, g),  \
-                                                                    kf[ks], sacc, 0, 0, 0);            \
-                    dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rm(Ds, 32 * st + r32, ks, g), \
-                                                                     vf[ks], dpacc, 0, 0, 0);          \
-                }                                                                                      \
-                _Pragma("unroll") for (int e4 = 0; e4 < 4; ++e4) {                                     \
-                    const int ql = 32 * st + 8 * e4 + 4 * g;                                           \
-                    const f32x4 ls = *(const f32x4 *)((stt) + ql);                                     \
-                    const f32x4 dd = *(const f32x4 *)((stt) + 64 + ql);                                \
-                    if (need_mask) {                     /* sub-tiles that touch the diagonal */       \
-                        _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                \
-                            const int e = 4 * e4 + i;                                                  \
-                            float p = __builtin_amdgcn_exp2f(fmaf(sacc[e], kScaleLog2, -ls[i]));       \
-                            if (key > (q0) + ql + i) p = 0.f;                                          \
-                            sacc[e] = p;                                                               \
-                            dpacc[e] = p * (dpacc[e] - dd[i]);                                         \
-                        }                                                                              \
-                    } else {                                                                           \
-                        _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                \
-                            const int e = 4 * e4 + i;                                                  \
-                            const float p = __builtin_amdgcn_exp2f(fmaf(sacc[e], kScaleLog2, -ls[i])); \
-                            sacc[e] = p;                                                               \
-                            dpacc[e] = p * (dpacc[e] - dd[i]);                                         \
-                        }                                                                              \
-                    }                                                                                  \
-                }                                                                                      \
-                _Pragma("unroll") for (int hh = 0; hh < 2; ++hh) {                                     \
-                    bf16x8 pb, dsb;                                                                    \
-                    _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                    \
-                        pb[i] = f2bf(sacc[8 * hh + i]);                                                \
-                        dsb[i] = f2bf(dpacc[8 * hh + i]);                                              \
-                    }                                                                                  \
-                    _Pragma("unroll") for (int dt = 0; dt < 2; ++dt) {                                 \
-                        dvacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                           \
-                            frag_tr(Ds, 32 * dt, 32 * st + 16 * hh, lane), pb, dvacc[dt], 0, 0, 0);    \
-                        dkacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                           \
-                            frag_tr(Qs, 32 * dt, 32 * st + 16 * hh, lane), dsb, dkacc[dt], 0, 0, 0);   \
-                    }                                                                                  \
-                }                                                                                      \
-            }                                                                                          \
-        }                                                                                              \
-    }
-    // per-query statistics travel through a register so that their LDS store (which has to wait
-    // for the load) sits after the MFMA work of the current tile
+    // per-query statistics travel through a register so that their LDS store (which has to wait for the load) sits
+    // after the MFMA work of the current tile
     float stat = 0.f;
-#define DKV_ISSUE(Qs, Ds, q0)                                                                          \
-    {                                                                                                  \
-        tile_copy_async(Qs, base + (size_t)(q0) * ld, ld, wave, lane);                                 \
-        tile_copy_async(Ds, dbase + (size_t)(q0) * d, d, wave, lane);                                  \
-        if (tid < 64) stat = lse_b[(q0) + tid];                                                        \
-        else if (tid < 128) stat = dl_b[(q0) + tid - 64];                                              \
-    }
-#define DKV_COMMIT(stt) if (tid < 128) (stt)[tid] = stat;
-
-    DKV_ISSUE(Q0, D0, q_first)
-    DKV_COMMIT(st0)
-    AT_WAIT_VM0();
-    __syncthreads();
-    int j = 0;
-    for (; j + 2 <= ntile; j += 2) {
-        DKV_ISSUE(Q1, D1, q_first + (j + 1) * 64)
-        DKV_TILE(Q0, D0, st0, q_first + j * 64)
-        DKV_COMMIT(st1)
-        AT_WAIT_VM0();
-        __syncthreads();
-        const bool more = j + 2 < ntile;
-        if (more) DKV_ISSUE(Q0, D0, q_first + (j + 2) * 64)
-        DKV_TILE(Q1, D1, st1, q_first + (j + 1) * 64)
-        if (more) DKV_COMMIT(st0)
-        AT_WAIT_VM0();
-        __syncthreads();
-    }
-    if (j < ntile) DKV_TILE(Q0, D0, st0, q_first + j * 64)
-#undef DKV_ISSUE
-#undef DKV_COMMIT
-#undef DKV_TILE
-
+    auto issue = [&](int j) {
+        const int q0 = q_first + j * 64;
+        tile_copy_async(QD[j & 1], base + (size_t)q0 * ld, ld, wave, lane);
+        tile_copy_async(QD[j & 1] + TILE_B, dbase + (size_t)q0 * d, d, wave, lane);
+        if (tid < 64) stat = lse_b[q0 + tid];
+        else if (tid < 128) stat = -dl_b[q0 + tid - 64];
+    };
+    issue(0);
+    // this wave's rows of K (its staging area) and V (the second buffer, still free) as whole lines
+    unsigned char *stg = Ost + wave * OST_B, *v_s = QD[1] + wave * 4096;
+    bf16x8 kf[4], vf[4];
     if (active) {
-        bf16 *krow = dqkv + ((size_t)n * S + key) * ld + d + a * 64;
-        bf16 *vrow = krow + d;
+        rows32_copy_async(stg, base + d + (size_t)kb * ld, ld, lane);
+        rows32_copy_async(v_s, base + 2 * d + (size_t)kb * ld, ld, lane);
+    }
+    if (tid < 128) st[0][tid] = stat;
+    AT_WAIT_VM0();
+    asm volatile("" ::: "memory");
+    if (active) {
 #pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
+        for (int ks = 0; ks < 4; ++ks) {
+            kf[ks] = *(const bf16x8 *)(stg + rm[ks]);
+            vf[ks] = *(const bf16x8 *)(v_s + rm[ks]);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // read before the second buffer is filled
+    }
+    for (int j = 0; j < ntile; ++j) {
+        AT_WAIT_VM0();
+        __syncthreads();                                 // tile j has landed and nobody reads the other buffer any more
+        if (j + 1 < ntile) issue(j + 1);
+        // the tile's 32-query halves at or above this wave's keys, one copy of the body for all of them
+        const int h0 = active ? min(max((kb - q_first - j * 64) >> 5, 0), 2) : 2;
+#pragma clang loop unroll(disable)
+        for (int hf = h0; hf < 2; ++hf) {
+            const unsigned char *qt_ = QD[j & 1] + hf * 4096, *dt_ = qt_ + TILE_B;
+            const float *sl = st[j & 1] + 32 * hf + 4 * g;
+            bf16x8 fq[4], fd[4];
+            f32x4 ls[4];
+            f32x16 sacc = zero16(), dpacc;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                fq[ks] = *(const bf16x8 *)(qt_ + rm[ks]);
+                fd[ks] = *(const bf16x8 *)(dt_ + rm[ks]);
+            }
+            // -delta as the addend of the dP product: dP - delta leaves the matrix cores ready
 #pragma unroll
             for (int e4 = 0; e4 < 4; ++e4) {
-                bf16x4 wk, wv;
+                ls[e4] = *(const f32x4 *)(sl + 8 * e4);
+                const f32x4 dd = *(const f32x4 *)(sl + 64 + 8 * e4);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    wk[i] = f2bf(dkacc[dt][4 * e4 + i] * 0.125f);
-                    wv[i] = f2bf(dvacc[dt][4 * e4 + i]);
-                }
-                *(bf16x4 *)(krow + 32 * dt + 8 * e4 + 4 * g) = wk;
-                *(bf16x4 *)(vrow + 32 * dt + 8 * e4 + 4 * g) = wv;
+                for (int i = 0; i < 4; ++i) dpacc[4 * e4 + i] = dd[i];
             }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[ks], kf[ks], sacc, 0, 0, 0);
+                dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fd[ks], vf[ks], dpacc, 0, 0, 0);
+            }
+            bf16x8 tq[2][2], td[2][2];
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+                for (int dt = 0; dt < 2; ++dt) {
+                    td[hh][dt] = read_tr(dt_ + hh * 2048 + tr[dt]);
+                    tq[hh][dt] = read_tr(qt_ + hh * 2048 + tr[dt]);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            if (q_first + j * 64 + hf * 32 == kb) {      // the half on the diagonal
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (r32 > 8 * (e >> 2) + 4 * g + (e & 3)) sacc[e] = -INFINITY;
+            }
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                bf16x8 pb, dsb;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int e = 8 * hh + i;
+                    const float p = __builtin_amdgcn_exp2f(fmaf(sacc[e], kScaleLog2, -ls[e >> 2][e & 3]));
+                    pb[i] = f2bf(p);
+                    dsb[i] = f2bf(p * dpacc[e]);
+                }
+#pragma unroll
+                for (int dt = 0; dt < 2; ++dt) {
+                    dvacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(td[hh][dt], pb, dvacc[dt], 0, 0, 0);
+                    dkacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tq[hh][dt], dsb, dkacc[dt], 0, 0, 0);
+                }
+            }
+        }
+        if (j + 1 < ntile && tid < 128) st[(j + 1) & 1][tid] = stat;
+    }
+
+    if (active) {
+        bf16 *out = dqkv + ((size_t)n * S + kb) * ld + d + a * 64;
+        store_rows32(stg, dkacc, 0.125f, out, ld, lane);
+        store_rows32(stg, dvacc, 1.0f, out + d, ld, lane);
     }
     }   // pass
 }
