@@ -380,9 +380,11 @@ TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int nz, bool can_spli
     // against 44 with 4 waves and two stages, 54 on 128-row tiles of the 4-wave kernel).
     if (t128 <= 256) return {128, 8, 1};
     // Otherwise two such tiles share a CU; a round of 512 of them costs 0.58 of a round of 256-row tiles (85 against 128
-    // flop per operand byte), a partial one less.  256-row tiles lose whole rounds instead.
+    // flop per operand byte), 0.75 with a rank-space branch (its rows are copied and multiplied for every tile: 32768
+    // tokens of 1280, five rounds of 128 against three of 256: 141, 176 and 380 us against 124, 171 and 332); a partial one
+    // less.  256-row tiles lose whole rounds instead.
     const long full = t128 / 512, rem = t128 - 512 * full;
-    const double c128 = 0.58 * (full + (rem == 0 ? 0.0 : rem <= 256 ? 0.75 : 0.9));
+    const double c128 = (nz == 0 ? 0.58 : 0.75) * (full + (rem == 0 ? 0.0 : rem <= 256 ? 0.75 : 0.9));
     double c256 = (double)((t256 + 255) / 256);
     if (nz == 0 && M >= 1024) c256 = std::min(c256, 0.58 * ((t128x256 + 255) / 256));
     return c128 < c256 ? TilePlan{128, 4, 1} : TilePlan{0, 4, 1};
