@@ -332,6 +332,7 @@ def main():
         B.slora_loss_head_prepare(cfg.d_model, V, lh_Wv, lh_ws, lh_bytes, stream)
         lh_g, lh_b = B.to_device_bf16(lh["lnf_g"]), B.to_device_bf16(lh["lnf_b"])
         lh_labels = torch.from_numpy(lh["labels"]).cuda()
+        lh_labeled = int((lh["labels"] >= 0).sum())
         lh_tok = torch.empty(cfg.tokens, dtype=torch.float32, device="cuda")
         lh_loss = torch.empty(1, dtype=torch.float32, device="cuda")
         lh_dy = torch.empty_like(dy)
@@ -399,7 +400,8 @@ def main():
             loss_head()
         torch.cuda.synchronize()
         lh_ms = (time.perf_counter() - t1) / 5 * 1e3
-    lh_flop = 4.0 * cfg.tokens * cfg.d_model * V
+    # both products, over the labeled tokens (the others have neither loss nor gradient)
+    lh_flop = 4.0 * lh_labeled * cfg.d_model * V if not args.no_legs or args.loss_head else 0.0
 
     # one client's share of a round (embedding + client-side blocks forward, backward, SGD step), on its own
     n_cb = synth.FEDAVG_CLIENT_BLOCKS

@@ -363,10 +363,15 @@ __device__ __forceinline__ void epilogue4(const GemmArgs &a, f32x4 (&acc)[NI][8]
 
 // NI = 16-row MFMA tiles per wave along M: 8 (tile 256 x 256, wave tile 128 x 128) or 4 (tile 128 x 256, wave
 // tile 64 x 128) for launches that have fewer 256-row tiles than the chip has CUs.
-template <int EPI, int NI>
-__global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_kernel4(GemmArgs a)
+// COUNTED: the number of rows, and (EPI_PARTIAL) over how many blocks a tile's contraction is shared, are read from
+// device memory (a.rows); share s of a tile leaves its fp32 sums in the s-th [rows, ldo] block of out0.
+template <int EPI, int NI, bool COUNTED>
+__device__ __forceinline__ void gemm4_body(GemmArgs a)
 {
     constexpr int BM4 = 32 * NI;                         // rows of a block tile
+    constexpr bool SHARED = EPI == EPI_PARTIAL;
+    if constexpr (COUNTED) a.M = a.rows->rows;
+    const int shares = SHARED ? a.rows->shares : 1;
     __shared__ __attribute__((aligned(1024))) unsigned char ring[5 * HB];   // X: 0, HB, 2HB;  W: 3HB, 4HB
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -383,7 +388,7 @@ __global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const int tiles_n_seg = (a.seg_n + BN - 1) / BN;
     const int tiles_n = tiles_n_seg * a.nseg;
     const int tiles_m = (a.M + BM4 - 1) / BM4;
-    const int nb = tiles_m * tiles_n;
+    const int nt = tiles_m * tiles_n, nb = SHARED ? nt * shares : nt;    // shares of one tile are nt apart
     const int per_xcd = (nb + 7) >> 3;
     const int slots = gridDim.x >> 3;
     const int t_end = min(((int)(blockIdx.x & 7) + 1) * per_xcd, nb);
@@ -400,20 +405,34 @@ __global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const unsigned ringa_x = lds_addr(ring) + wave * (8 * NI) * ROWB, ringa_w = lds_addr(ring) + wave * 64 * ROWB;
     const int a_row = (wm * (16 * NI) + r16) * ROWB, b_row = (wn * 128 + r16) * ROWB;
     const int sw = r16 & 7;
-    const int nk = a.K / BK, klast = (nk - 1) * BK;
-    const int k1 = min(BK, klast), k2 = min(2 * BK, klast);
+    int nk = a.K / BK, klast = (nk - 1) * BK;
+    int k1 = min(BK, klast), k2 = min(2 * BK, klast);
+    const int nk_all = nk;
     // the epilogue's staging strips live in the third X buffer, the one the next tile's early copies leave alone
     float *stg = (float *)(ring + 2 * HB + wave * (16 * EP4 * 4));
 
-    int m0, n0, n_end;
+    int m0, n0, n_end, share = 0;
+    float *const part0 = (float *)a.out0;
     unsigned xo[8], wo[8];
     // tile `t` of the panel walk: its origin, and this wave's copy offsets (every wave copies a quarter of the
     // rows of each operand tile per slab -- 8 NI of X, 64 of W --, 8 rows = 1 KB per instruction; lane l fills
     // 16-byte slot l: row l>>3, physical k-chunk l&7 holding logical chunk (l&7) ^ (l>>3))
-#define G4_TILE(t)                                                                                     \
+#define G4_TILE(id)                                                                                    \
     {                                                                                                  \
         constexpr int PANEL = 4;                                                                       \
-        const int pidx = (t) / (PANEL * tiles_n), prem = (t) - pidx * (PANEL * tiles_n);               \
+        int t = (id);                                                                                  \
+        unsigned kb = 0;                                 /* byte offset of the share's first slab */   \
+        if constexpr (SHARED) {                                                                        \
+            share = t / nt;                                                                            \
+            t -= share * nt;                                                                           \
+            const int ks = (int)((long)share * nk_all / shares);                                       \
+            nk = (int)((long)(share + 1) * nk_all / shares) - ks;                                      \
+            klast = (nk - 1) * BK;                                                                     \
+            k1 = min(BK, klast);                                                                       \
+            k2 = min(2 * BK, klast);                                                                   \
+            kb = (unsigned)ks * ROWB;                                                                  \
+        }                                                                                              \
+        const int pidx = t / (PANEL * tiles_n), prem = t - pidx * (PANEL * tiles_n);                   \
         const int prow = min(PANEL, tiles_m - pidx * PANEL);                                           \
         const int tn = prem / prow, tm = pidx * PANEL + prem - tn * prow;                              \
         const int seg = tn / tiles_n_seg, tns = tn % tiles_n_seg;                                      \
@@ -423,8 +442,8 @@ __global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         _Pragma("unroll") for (int p = 0; p < 8; ++p) {                                                \
             const int row = min(m0 + wave * (8 * NI) + (p % NI) * 8 + lrow, a.M - 1);                  \
             const int n = min(n0 + wave * 64 + p * 8 + lrow, n_end - 1);                               \
-            xo[p] = ((unsigned)row * (unsigned)a.ldx + lch * 8) * 2u;                                  \
-            wo[p] = ((unsigned)n * (unsigned)a.ldw + lch * 8) * 2u;                                    \
+            xo[p] = ((unsigned)row * (unsigned)a.ldx + lch * 8) * 2u + kb;                             \
+            wo[p] = ((unsigned)n * (unsigned)a.ldw + lch * 8) * 2u + kb;                               \
         }                                                                                              \
     }
 #define G4_COPYX(k0, ldsb, p) glds_soff(Xb + (size_t)(k0) * 2, xo[p], ringa_x + (ldsb) + (p) * 1024);
@@ -515,6 +534,7 @@ __global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         __syncthreads();
         // the next tile's first four half stages are requested now and arrive under this tile's epilogue
         const int em0 = m0, en0 = n0, en_end = n_end;
+        if constexpr (SHARED) a.out0 = part0 + (size_t)share * a.M * a.ldo;
         const int next = logical + slots;
         if (next < t_end) {
             G4_TILE(next)
@@ -542,6 +562,17 @@ __global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 #undef G4_ROW
 #undef G4_STEP
 #undef G4_STEPC
+}
+
+template <int EPI, int NI>
+__global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_kernel4(GemmArgs a)
+{
+    gemm4_body<EPI, NI, false>(a);
+}
+template <int EPI, int NI>
+__global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_counted4(GemmArgs a)
+{
+    gemm4_body<EPI, NI, true>(a);
 }
 
 template <int EPI>
@@ -623,4 +654,26 @@ static int launch_gemm_inner(const GemmArgs &a, int epi, int nz, hipStream_t st)
     case EPI_STORE_DELTA: return launch_t4<EPI_STORE_DELTA>(a, st);
     }
     return SL_EINVAL;
+}
+
+// A product over the rows that a kernel before it counted (a.rows; a.M is their upper bound), without rank-space branch.
+// EPI_STORE or EPI_PARTIAL.  Its work is only known on the device, so it is not in the launch profile.
+int launch_gemm_counted(const GemmArgs &a, int epi, hipStream_t st)
+{
+    if (a.M <= 0 || a.N <= 0 || a.K <= 0 || (a.K % BK) != 0 || a.nseg != 1 || a.seg_n != a.N || (a.ldx % 8) ||
+        (a.ldw % 8) || (a.N % 8) || (a.ldo % 8) || !a.rows || !a.out0)
+        return SL_EINVAL;
+    if ((unsigned long long)a.M * a.ldx * 2ull >= (1ull << 32) || (unsigned long long)a.N * a.ldw * 2ull >= (1ull << 32))
+        return SL_EINVAL;
+    const int bm = gemm_counted_rows(a.M);
+    const int tiles = ((a.M + bm - 1) / bm) * ((a.N + BN - 1) / BN);
+    // shares are chosen where the rows are counted, so that launch always has a block for every CU
+    const dim3 grid(epi == EPI_PARTIAL ? 256 : std::min((tiles + 7) / 8 * 8, 256)), block(NTHR4);
+    if (epi == EPI_STORE && bm == 256) hipLaunchKernelGGL((gemm_counted4<EPI_STORE, 8>), grid, block, 0, st, a);
+    else if (epi == EPI_STORE) hipLaunchKernelGGL((gemm_counted4<EPI_STORE, 4>), grid, block, 0, st, a);
+    else if (epi == EPI_PARTIAL && bm == 256) hipLaunchKernelGGL((gemm_counted4<EPI_PARTIAL, 8>), grid, block, 0, st, a);
+    else if (epi == EPI_PARTIAL) hipLaunchKernelGGL((gemm_counted4<EPI_PARTIAL, 4>), grid, block, 0, st, a);
+    else return SL_EINVAL;
+    SL_CHECK_LAUNCH("gemm counted");
+    return 0;
 }

@@ -85,6 +85,9 @@ __device__ __forceinline__ void store_row8(const Args &a, int row, int col, floa
         p += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(p), 0x112, 0xF, 0xF, true));   // row_shr:2
         p += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(p), 0x114, 0xF, 0xF, true));   // row_shr:4
         if ((threadIdx.x & 7) == 7) a.dl_out[(size_t)row * (a.N >> 6) + (col >> 6)] = p;
+    } else if constexpr (EPI == EPI_PARTIAL) {
+        *(float4 *)((float *)a.out0 + o) = make_float4(v[0], v[1], v[2], v[3]);
+        *(float4 *)((float *)a.out0 + o + 4) = make_float4(v[4], v[5], v[6], v[7]);
     } else if (EPI == EPI_STORE) {
         bf16x8 w;
 #pragma unroll

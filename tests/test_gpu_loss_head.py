@@ -89,6 +89,42 @@ def test_loss_head_without_labels():
     assert np.all(loss_tok == 0.0) and np.all(dy == 0.0)
 
 
+# Where the listed rows and the shared contraction of the input gradient have their edges: one row, row tiles of 128 and
+# 256, one row more than either; a second chunk without a labeled row, with one, with a few; few slabs and many to share.
+@pytest.mark.parametrize("T,d,V,n_labeled", [
+    (1, 64, 4099, 1),
+    (128, 128, 50257, 127),
+    (129, 320, 20011, 129),
+    (257, 64, 64, 256),
+    (600, 192, 8001, 257),
+    (16640, 64, 520, 16384),
+    (16641, 64, 520, 16385),
+    (16700, 64, 1030, 16700),
+])
+def test_loss_head_listed_rows(T, d, V, n_labeled):
+    say("loss head T=%d d=%d V=%d, %d labeled" % (T, d, V, n_labeled))
+    inp = synth.make_loss_head_inputs(1, T, d, vocab=V, seed=synth.BASE_SEED + 79)
+    inp["Wv"] = synth.round_bf16(inp["Wv"] * np.float32(4.0))
+    rng = np.random.default_rng(T)
+    inp["labels"] = rng.integers(0, V, size=T).astype(inp["labels"].dtype)
+    inp["labels"][rng.permutation(T)[:T - n_labeled]] = -1
+    check_full(inp, d, V, "listed rows")
+
+
+def test_loss_head_nan_stays_in_its_row():
+    """A NaN in an unlabeled row of y reaches that row of dy (as the LayerNorm gradient has it) and nothing else."""
+    T, d, V = 300, 128, 1003
+    inp = synth.make_loss_head_inputs(1, T, d, vocab=V, seed=synth.BASE_SEED + 80)
+    inp["labels"][:] = np.arange(T) % V
+    inp["labels"][::3] = -1
+    loss, tok, dy = gpu_loss_head(inp, d, V)
+    inp["y"][150, 5] = np.nan
+    loss2, tok2, dy2 = gpu_loss_head(inp, d, V)
+    keep = np.arange(T) != 150
+    assert loss2 == loss and np.array_equal(tok2, tok) and np.array_equal(dy2[keep], dy[keep])
+    assert np.isnan(dy2[150]).all()
+
+
 def test_loss_head_workload3_sampled_rows():
     """Workload 3's shape: 64 x 512 tokens, d = 1024, GPT-2's vocabulary of 50257.  The oracle runs on a
     sample of rows; a row's loss term does not depend on the other rows and its gradient only through the

@@ -99,8 +99,18 @@ def gemm_asm():
 def test_four_wave_gemm_mfma_hazards(gemm_asm):
     funcs = {n: b for n, b in _functions(gemm_asm).items() if "gemm_kernel4" in n}
     assert len(funcs) == 10, sorted(funcs)         # five epilogues x two tile heights
+    _check_mfma_hazards(funcs)
+
+
+def test_counted_gemm_mfma_hazards(gemm_asm):
+    funcs = {n: b for n, b in _functions(gemm_asm).items() if "gemm_counted4" in n}
+    assert len(funcs) == 4, sorted(funcs)          # plain store and shared contraction x two tile heights
+    _check_mfma_hazards(funcs)
+
+
+def _check_mfma_hazards(funcs):
     for name, body in funcs.items():
-        ni = int(re.search(r"gemm_kernel4ILi\d+ELi(\d+)E", name).group(1))      # 16-row MFMA tiles per wave along M
+        ni = int(re.search(r"gemm_(?:kernel|counted)4ILi\d+ELi(\d+)E", name).group(1))      # 16-row MFMA tiles per wave along M
         assert ni in (4, 8), name
         mf = [(i, ins) for i, ins in enumerate(body) if ins.startswith("v_mfma")]
         # the unrolled loop body: 2 k-steps x (ni x 8) MFMAs
