@@ -924,15 +924,17 @@ LinWs lin_ws(int T, int n_in, int n_out)
     w.part_a = take(4 * lora_grad_layer_floats(T, n_in, n_out));
     w.part_b = take(4 * lora_grad_layer_floats(T, n_out, n_in));
     // scratch for products that split their contraction, unless it alone would put the layer beyond what the library's own
-    // array holds
+    // array holds; such a layer reports the array's size, so that the total never falls as T grows and a workspace taken
+    // for the most tokens serves fewer
     const size_t more = al256(gemm_split_bytes()) + al256(gemm_split_counter_bytes());
-    w.can_split = off + more <= (size_t)SLORA_NOALLOC_SCRATCH_BYTES || off > (size_t)SLORA_NOALLOC_SCRATCH_BYTES;
+    const size_t own = (size_t)SLORA_NOALLOC_SCRATCH_BYTES;
+    w.can_split = off + more <= own || off > own;
     w.cnt = w.split = 0;
     if (w.can_split) {
         w.cnt = take(gemm_split_counter_bytes());
         w.split = take(gemm_split_bytes());
     }
-    w.total = off;
+    w.total = w.can_split ? off : own;
     return w;
 }
 // the product of a layer call, with its split scratch; the counters are zeroed by the same call's front kernel

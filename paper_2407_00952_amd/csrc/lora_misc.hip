@@ -415,11 +415,12 @@ size_t lora_grad_partial_floats(int T, int C)
     return (size_t)std::max<long>((T + GR_ROWS - 1) / GR_ROWS, few) * 2 * SL_RP * (size_t)C;
 }
 
-// the same for one token count and single adapters, launched together with a job of width c_other
+// the same for single adapters, launched together with a job of width c_other (which has a say in the rows per chunk)
 size_t lora_grad_layer_floats(int T, int C, int c_other)
 {
-    const int rows = grad_rows(T, std::max(C, c_other));
-    return (size_t)((T + rows - 1) / rows) * SL_RP * (size_t)C;
+    const long t_few = std::min<long>(T, (GR_FEW - 1) / std::max(C, c_other));       // the largest count with short chunks
+    const long few = (t_few + GR_ROWS_FEW - 1) / GR_ROWS_FEW;
+    return (size_t)std::max<long>((T + GR_ROWS - 1) / GR_ROWS, few) * SL_RP * (size_t)C;
 }
 
 int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStream_t st)

@@ -163,6 +163,18 @@ def test_documented_size_limits_are_enforced():
     B.slora_destroy(_create(d_model=2048, n_head=32, d_ff=8192, max_seqs=255, seq_len=1024))
 
 
+@pytest.mark.parametrize("n_in,n_out", [(64, 64), (128, 128), (768, 3072), (4096, 1024)])
+def test_layer_workspace_for_the_most_tokens_serves_fewer(n_in, n_out):
+    # counts around where the scratch of a layer changes its make-up (rows of a partial sum, room for shared contractions)
+    T = sorted({t + k for b in range(18) for t in (1 << b, 3 << b, 5 << b) for k in (-1, 0, 1)
+                if 0 < t + k <= 200000} | set(range(997, 200000, 997)))
+    for f in ([lambda t: B.slora_lora_linear_ws_bytes(B.DTYPE_F32, t, n_in, n_out, 4),
+               lambda t: B.slora_lora_linear_ws_bytes(B.DTYPE_BF16, t, n_in, n_out, 4)]
+              + ([lambda t: B.slora_mx_lora_linear_ws_bytes(t, n_in, n_out, 4)] if n_in > 64 else [])):
+        n = [f(t) for t in T]
+        assert n[0] > 0 and all(a <= b for a, b in zip(n, n[1:]))
+
+
 def test_noalloc_backward_argument_checks():
     # checked before anything touches a GPU: sizes beyond the library's own scratch, bad pointers and sizes
     assert B.slora_lora_linear_ws_bytes(B.DTYPE_BF16, 65536, 4096, 4096, 4) > B.NOALLOC_SCRATCH_BYTES
