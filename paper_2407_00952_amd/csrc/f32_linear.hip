@@ -105,7 +105,8 @@ __global__ __launch_bounds__(512) void f32_project_kernel(ProjJobs jobs, int T, 
         float v = 0.f;
 #pragma unroll
         for (int w = 0; w < 8; ++w) v += red[w][m][j];
-        if (t0 + m < T && j < zp) jb.out[(size_t)(t0 + m) * zp + j] = v;
+        // zero beyond the rank also where an infinity met a zero of Z
+        if (t0 + m < T && j < zp) jb.out[(size_t)(t0 + m) * zp + j] = j < r ? v : 0.f;
     }
 }
 

@@ -98,6 +98,19 @@ def test_fp32_dispatch_edges(T, n_in, n_out, r, bias):
         assert relerr(g, ref) <= F32_TOL, name
 
 
+@pytest.mark.parametrize("T,n_in,n_out", [(20, 64, 96), (700, 768, 704)])       # direct, 64 x 64 tiles
+def test_fp32_infinity_stays_an_infinity(T, n_in, n_out):
+    # rank 3 is kept as 4 columns: the empty one must not turn inf * 0 into a NaN of the result
+    c = synth.make_single_layer(T, n_in, n_out, 3, seed=5, bias=False)
+    for k in ("W", "A", "B"):
+        c[k] = np.abs(c[k]) + np.float32(1e-3)
+    c["x"][7, 5] = c["dy"][9, 11] = np.inf
+    say("fp32 layer with an infinity", T, n_in, n_out)
+    y, dx = _run_f32(c)[:2]
+    assert np.all(y[7] == np.inf) and np.all(dx[9] == np.inf)
+    assert np.isfinite(np.delete(y, 7, 0)).all() and np.isfinite(np.delete(dx, 9, 0)).all()
+
+
 def test_fp32_zero_B_is_bitwise_base():
     import torch
     c = synth.make_single_layer(300, 128, 192, 4, seed=11)
