@@ -20,6 +20,16 @@ namespace {
 
 constexpr int MAXC = 8;   // 256-column chunks per row: d <= 2048
 
+// A row of whole 256-column chunks (every width that is a multiple of 256) runs on a kernel with that many chunks
+// and no column test.  With a test per chunk the compiler waits for each chunk's loads before it requests the next
+// chunk's, and one wave has a row to itself: the waits of a row add up to most of a small launch.  Without the tests
+// all loads of a row are in flight together, those that are used last (gains, residual gradient) behind the others.
+// [32768, 1024]: forward 40.8 -> 34.5 us (5.8 TB/s), backward 91.1 -> 84.8 us (6.3 TB/s); a round of 128 tokens and nine
+// blocks of 768, 36 such launches: 1279 -> 1199 us.
+// NC = 0 is the general kernel, up to MAXC chunks with a test each.
+template <int NC> __device__ __forceinline__ constexpr int chunks() { return NC ? NC : MAXC; }
+template <int NC> __device__ __forceinline__ bool in_row(int col, int d) { return NC != 0 || col < d; }
+
 __device__ __forceinline__ int client_of(const ClientTable &t, int row, int &local)
 {
     int c = 0, start = 0;
@@ -30,14 +40,14 @@ __device__ __forceinline__ int client_of(const ClientTable &t, int row, int &loc
 
 // MXFP8 copy of a row: each lane holds 4 consecutive bf16 values of a 256-column chunk, so a block of 32 columns
 // is 8 neighbouring lanes (three shuffles for its maximum).  Every lane of the wave must call this; lanes
-// whose columns are outside the row (`in_row` false) only take part in the shuffles.
-__device__ __forceinline__ void mx_store_row4(bf16x4 o, bool in_row, int lane, unsigned char *q_row,
+// whose columns are outside the row (`valid` false) only take part in the shuffles.
+__device__ __forceinline__ void mx_store_row4(bf16x4 o, bool valid, int lane, unsigned char *q_row,
                                               unsigned char *s_row, int col)
 {
     union { bf16x4 v; unsigned short s[4]; } bits;       // the four bit patterns
     bits.v = o;
     unsigned hb[4] = {0u, 0u, 0u, 0u}, mag = 0u;
-    if (in_row) {
+    if (valid) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             hb[i] = bits.s[i];
@@ -48,7 +58,7 @@ __device__ __forceinline__ void mx_store_row4(bf16x4 o, bool in_row, int lane, u
     mag = max(mag, (unsigned)__shfl_xor((int)mag, 2, 64));
     mag = max(mag, (unsigned)__shfl_xor((int)mag, 4, 64));
     const int scode = mx_scale_code(mag);
-    if (in_row) {
+    if (valid) {
         const unsigned q4 = mx_encode_pair_bf16(hb[0], hb[1], scode) | (mx_encode_pair_bf16(hb[2], hb[3], scode) << 16);
         *(unsigned *)(q_row + col) = q4;
         if ((lane & 7) == 0) s_row[col >> 5] = (unsigned char)scode;
@@ -57,7 +67,7 @@ __device__ __forceinline__ void mx_store_row4(bf16x4 o, bool in_row, int lane, u
 
 // SRC 0: fp32 rows of h; 1: bf16 rows gathered from the client buffers; 2: embedding lookup;
 // 3: MXFP8 rows (element codes + one scale code per 32 columns) gathered from the client buffers
-template <int SRC>
+template <int SRC, int NC>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ h, ClientTable tab, EmbedSrc emb,
                                                      float *__restrict__ hcopy, const bf16 *__restrict__ gamma,
                                                      const bf16 *__restrict__ beta, float eps,
@@ -68,7 +78,9 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ h
     const int lane = threadIdx.x & 63;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= T) return;
-    float v[MAXC][4];
+    constexpr int N = chunks<NC>();
+    float v[N][4];
+    bf16x4 gm[N], bt[N];
     const bf16 *src16 = nullptr, *pos16 = nullptr;
     const unsigned char *srcq = nullptr, *srcs = nullptr;
     if (SRC == 3) {
@@ -87,9 +99,9 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ h
     }
     float s = 0.f;
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
+    for (int c = 0; c < N; ++c) {
         const int col = c * 256 + lane * 4;
-        if (col < d) {
+        if (in_row<NC>(col, d)) {
             if (SRC == 3) {
                 const unsigned q4 = *(const unsigned *)(srcq + col);
                 const int sc = (int)srcs[col >> 5] - 127;
@@ -110,35 +122,50 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ h
                 float4 t = *(const float4 *)(h + (size_t)row * d + col);
                 v[c][0] = t.x; v[c][1] = t.y; v[c][2] = t.z; v[c][3] = t.w;
             }
+            if (NC == 0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s += v[c][i];
+            }
+        }
+    }
+    if (NC != 0) {
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            gm[c] = *(const bf16x4 *)(gamma + c * 256 + lane * 4);
+            bt[c] = *(const bf16x4 *)(beta + c * 256 + lane * 4);
+        }
+#pragma unroll
+        for (int c = 0; c < N; ++c)
 #pragma unroll
             for (int i = 0; i < 4; ++i) s += v[c][i];
-        }
     }
     const float mu = wave_sum(s) / (float)d;
     float q = 0.f;
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-        if (c * 256 + lane * 4 < d) {
+    for (int c = 0; c < N; ++c) {
+        if (in_row<NC>(c * 256 + lane * 4, d)) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) { v[c][i] -= mu; q += v[c][i] * v[c][i]; }
         }
     }
     const float rho = rsqrtf(wave_sum(q) / (float)d + eps);
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
+    for (int c = 0; c < N; ++c) {
         const int col = c * 256 + lane * 4;
         bf16x4 o;
 #pragma unroll
         for (int i = 0; i < 4; ++i) o[i] = f2bf(0.f);
-        if (col < d) {
-            bf16x4 gm = *(const bf16x4 *)(gamma + col);
-            bf16x4 bt = *(const bf16x4 *)(beta + col);
+        if (in_row<NC>(col, d)) {
+            if (NC == 0) {
+                gm[c] = *(const bf16x4 *)(gamma + col);
+                bt[c] = *(const bf16x4 *)(beta + col);
+            }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = f2bf(v[c][i] * rho * bf2f(gm[i]) + bf2f(bt[i]));
+            for (int i = 0; i < 4; ++i) o[i] = f2bf(v[c][i] * rho * bf2f(gm[c][i]) + bf2f(bt[c][i]));
             if (u != nullptr) *(bf16x4 *)(u + (size_t)row * d + col) = o;    // (null: only the codes are wanted)
         }
-        if (uq != nullptr && c * 256 < d)
-            mx_store_row4(o, col < d, lane, uq + (size_t)row * d, us + (size_t)row * (d >> 5), col);
+        if (uq != nullptr && (NC != 0 || c * 256 < d))
+            mx_store_row4(o, in_row<NC>(col, d), lane, uq + (size_t)row * d, us + (size_t)row * (d >> 5), col);
     }
     if (lane == 0) { stats[2 * row] = mu; stats[2 * row + 1] = rho; }
 }
@@ -147,7 +174,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ h
 // with DRES16 false a null `dres` means there is no residual gradient to add.
 // SCATTER 1: the bf16 output goes to the K client buffers; 2: it goes there as MXFP8 (the value is rounded
 // to bf16 first, then converted block by block: 8 neighbouring lanes hold one block of 32 columns).
-template <bool DRES16, int SCATTER>
+template <bool DRES16, int SCATTER, int NC>
 __global__ __launch_bounds__(256) void ln_bwd_kernel(const bf16 *__restrict__ du, const float *__restrict__ h,
                                                      const float *__restrict__ stats, const bf16 *__restrict__ gamma,
                                                      const void *__restrict__ dres, float *__restrict__ out32,
@@ -158,23 +185,49 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const bf16 *__restrict__ du
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= T) return;
     const float mu = stats[2 * row], rho = stats[2 * row + 1];
-    float gq[MAXC][4], xh[MAXC][4];
+    constexpr int N = chunks<NC>();
+    float gq[N][4], xh[N][4];
     float s1 = 0.f, s2 = 0.f;
+    auto load_dres = [&](int col) {
+        if (DRES16) {
+            const bf16x4 t = *(const bf16x4 *)((const bf16 *)dres + (size_t)row * d + col);
+            return make_float4(bf2f(t[0]), bf2f(t[1]), bf2f(t[2]), bf2f(t[3]));
+        }
+        if (dres != nullptr) return *(const float4 *)((const float *)dres + (size_t)row * d + col);
+        return make_float4(0.f, 0.f, 0.f, 0.f);          // no residual branch (the final LayerNorm)
+    };
+    auto take = [&](int c, bf16x4 t, bf16x4 gm, float4 hv) {
+        const float hh[4] = {hv.x, hv.y, hv.z, hv.w};
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-        const int col = c * 256 + lane * 4;
-        if (col < d) {
-            bf16x4 t = *(const bf16x4 *)(du + (size_t)row * d + col);
-            bf16x4 gm = *(const bf16x4 *)(gamma + col);
-            float4 hv = *(const float4 *)(h + (size_t)row * d + col);
-            const float hh[4] = {hv.x, hv.y, hv.z, hv.w};
+        for (int i = 0; i < 4; ++i) {
+            gq[c][i] = bf2f(t[i]) * bf2f(gm[i]);
+            xh[c][i] = (hh[i] - mu) * rho;
+            s1 += gq[c][i];
+            s2 += gq[c][i] * xh[c][i];
+        }
+    };
+    float4 res[N];
+    if (NC != 0) {
+        bf16x4 t[N], gm[N];
+        float4 hv[N];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                gq[c][i] = bf2f(t[i]) * bf2f(gm[i]);
-                xh[c][i] = (hh[i] - mu) * rho;
-                s1 += gq[c][i];
-                s2 += gq[c][i] * xh[c][i];
-            }
+        for (int c = 0; c < N; ++c) {
+            const int col = c * 256 + lane * 4;
+            t[c] = *(const bf16x4 *)(du + (size_t)row * d + col);
+            gm[c] = *(const bf16x4 *)(gamma + col);
+            hv[c] = *(const float4 *)(h + (size_t)row * d + col);
+        }
+#pragma unroll
+        for (int c = 0; c < N; ++c) res[c] = load_dres(c * 256 + lane * 4);
+#pragma unroll
+        for (int c = 0; c < N; ++c) take(c, t[c], gm[c], hv[c]);
+    } else {
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            const int col = c * 256 + lane * 4;
+            if (col < d)
+                take(c, *(const bf16x4 *)(du + (size_t)row * d + col), *(const bf16x4 *)(gamma + col),
+                     *(const float4 *)(h + (size_t)row * d + col));
         }
     }
     const float m1 = wave_sum(s1) / (float)d;
@@ -193,21 +246,12 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const bf16 *__restrict__ du
         }
     }
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
+    for (int c = 0; c < N; ++c) {
         const int col = c * 256 + lane * 4;
         float r_keep[4] = {0.f, 0.f, 0.f, 0.f};
-        if (col < d) {
-            float r[4];
-            if (DRES16) {
-                bf16x4 t = *(const bf16x4 *)((const bf16 *)dres + (size_t)row * d + col);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) r[i] = bf2f(t[i]);
-            } else if (dres != nullptr) {
-                float4 t = *(const float4 *)((const float *)dres + (size_t)row * d + col);
-                r[0] = t.x; r[1] = t.y; r[2] = t.z; r[3] = t.w;
-            } else {                                     // no residual branch (the final LayerNorm)
-                r[0] = r[1] = r[2] = r[3] = 0.f;
-            }
+        if (in_row<NC>(col, d)) {
+            if (NC == 0) res[c] = load_dres(col);
+            float r[4] = {res[c].x, res[c].y, res[c].z, res[c].w};
             bf16x4 o16;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -223,15 +267,29 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const bf16 *__restrict__ du
             bf16x4 o4;
 #pragma unroll
             for (int i = 0; i < 4; ++i) o4[i] = f2bf(r_keep[i]);
-            if (c * 256 < d) mx_store_row4(o4, col < d, lane, dstq, dsts, col);
-        } else if (oq != nullptr && c * 256 < d) {
+            if (NC != 0 || c * 256 < d) mx_store_row4(o4, in_row<NC>(col, d), lane, dstq, dsts, col);
+        } else if (oq != nullptr && (NC != 0 || c * 256 < d)) {
             bf16x4 o4;
 #pragma unroll
             for (int i = 0; i < 4; ++i) o4[i] = f2bf(r_keep[i]);
-            mx_store_row4(o4, col < d, lane, oq + (size_t)row * d, os + (size_t)row * (d >> 5), col);
+            mx_store_row4(o4, in_row<NC>(col, d), lane, oq + (size_t)row * d, os + (size_t)row * (d >> 5), col);
         }
     }
 }
+
+// NC of a row: its chunks if they are whole, else the general kernel
+#define LN_WIDTHS(d, CALL)                  \
+    switch ((d) % 256 == 0 ? (d) / 256 : 0) { \
+    case 1: CALL(1); break;                 \
+    case 2: CALL(2); break;                 \
+    case 3: CALL(3); break;                 \
+    case 4: CALL(4); break;                 \
+    case 5: CALL(5); break;                 \
+    case 6: CALL(6); break;                 \
+    case 7: CALL(7); break;                 \
+    case 8: CALL(8); break;                 \
+    default: CALL(0);                       \
+    }
 
 }  // namespace
 
@@ -253,17 +311,25 @@ int launch_ln_fwd(const float *h_f32, const ClientTable *gather, float *h_copy, 
     const bool rec = prof_begin(PK_LN_FWD, st);
     if (embed) {
         if (!embed->tokens || !embed->wte || !embed->wpe || embed->seq_len <= 0 || embed->vocab <= 0) return SL_EINVAL;
-        hipLaunchKernelGGL((ln_fwd_kernel<2>), grid, block, 0, st, nullptr, none, *embed, h_copy, gamma, beta, eps, u,
-                           stats, T, d, u_codes, u_scales);
+#define LN_CALL(NC) hipLaunchKernelGGL((ln_fwd_kernel<2, NC>), grid, block, 0, st, nullptr, none, *embed, h_copy, gamma, \
+                                       beta, eps, u, stats, T, d, u_codes, u_scales)
+        LN_WIDTHS(d, LN_CALL)
+#undef LN_CALL
     } else if (gather && gather->mx) {
-        hipLaunchKernelGGL((ln_fwd_kernel<3>), grid, block, 0, st, nullptr, *gather, noemb, h_copy, gamma, beta, eps,
-                           u, stats, T, d, u_codes, u_scales);
+#define LN_CALL(NC) hipLaunchKernelGGL((ln_fwd_kernel<3, NC>), grid, block, 0, st, nullptr, *gather, noemb, h_copy, gamma, \
+                                       beta, eps, u, stats, T, d, u_codes, u_scales)
+        LN_WIDTHS(d, LN_CALL)
+#undef LN_CALL
     } else if (gather) {
-        hipLaunchKernelGGL((ln_fwd_kernel<1>), grid, block, 0, st, nullptr, *gather, noemb, h_copy, gamma, beta, eps,
-                           u, stats, T, d, u_codes, u_scales);
+#define LN_CALL(NC) hipLaunchKernelGGL((ln_fwd_kernel<1, NC>), grid, block, 0, st, nullptr, *gather, noemb, h_copy, gamma, \
+                                       beta, eps, u, stats, T, d, u_codes, u_scales)
+        LN_WIDTHS(d, LN_CALL)
+#undef LN_CALL
     } else {
-        hipLaunchKernelGGL((ln_fwd_kernel<0>), grid, block, 0, st, h_f32, none, noemb, nullptr, gamma, beta, eps, u,
-                           stats, T, d, u_codes, u_scales);
+#define LN_CALL(NC) hipLaunchKernelGGL((ln_fwd_kernel<0, NC>), grid, block, 0, st, h_f32, none, noemb, nullptr, gamma, \
+                                       beta, eps, u, stats, T, d, u_codes, u_scales)
+        LN_WIDTHS(d, LN_CALL)
+#undef LN_CALL
     }
     prof_end(rec, PK_LN_FWD, row_bytes * (double)T * d, st);
     SL_CHECK_LAUNCH("ln_fwd");
@@ -285,26 +351,29 @@ int launch_ln_bwd(const bf16 *du, const float *h, const float *stats, const bf16
     const double el_bytes = 2 + 4 + (dres_bf16 ? 2 : dres_f32 ? 4 : 0) + (out_f32 ? 4 : 0) + (out_bf16 ? 2 : 0) +
                             (scatter ? (scatter->mx ? 1 : 2) : 0) + (o_codes ? 1 : 0);
     const bool rec = prof_begin(PK_LN_BWD, st);
+    if (scatter && scatter->mx && ((d % 32) || dres_bf16)) return SL_EINVAL;
+    const void *dres = dres_bf16 ? (const void *)dres_bf16 : (const void *)dres_f32;
+#define LN_BWD(D16, SCATTER, NC) hipLaunchKernelGGL((ln_bwd_kernel<D16, SCATTER, NC>), grid, block, 0, st, du, h, stats, \
+                                                    gamma, dres, out_f32, out_bf16, tab, T, d, o_codes, o_scales)
+#define LN_CALL_F2(NC) LN_BWD(false, 2, NC)
+#define LN_CALL_B1(NC) LN_BWD(true, 1, NC)
+#define LN_CALL_B0(NC) LN_BWD(true, 0, NC)
+#define LN_CALL_F1(NC) LN_BWD(false, 1, NC)
+#define LN_CALL_F0(NC) LN_BWD(false, 0, NC)
     if (scatter && scatter->mx) {
         // compressed activation gradients: only the first server block scatters, and its residual gradient is fp32
-        if ((d % 32) || dres_bf16) return SL_EINVAL;
-        hipLaunchKernelGGL((ln_bwd_kernel<false, 2>), grid, block, 0, st, du, h, stats, gamma, (const void *)dres_f32,
-                           out_f32, out_bf16, tab, T, d, o_codes, o_scales);
+        LN_WIDTHS(d, LN_CALL_F2)
     } else if (dres_bf16) {
-        if (scatter)
-            hipLaunchKernelGGL((ln_bwd_kernel<true, 1>), grid, block, 0, st, du, h, stats, gamma,
-                               (const void *)dres_bf16, out_f32, out_bf16, tab, T, d, o_codes, o_scales);
-        else
-            hipLaunchKernelGGL((ln_bwd_kernel<true, 0>), grid, block, 0, st, du, h, stats, gamma,
-                               (const void *)dres_bf16, out_f32, out_bf16, tab, T, d, o_codes, o_scales);
+        if (scatter) LN_WIDTHS(d, LN_CALL_B1) else LN_WIDTHS(d, LN_CALL_B0)
     } else {
-        if (scatter)
-            hipLaunchKernelGGL((ln_bwd_kernel<false, 1>), grid, block, 0, st, du, h, stats, gamma,
-                               (const void *)dres_f32, out_f32, out_bf16, tab, T, d, o_codes, o_scales);
-        else
-            hipLaunchKernelGGL((ln_bwd_kernel<false, 0>), grid, block, 0, st, du, h, stats, gamma,
-                               (const void *)dres_f32, out_f32, out_bf16, tab, T, d, o_codes, o_scales);
+        if (scatter) LN_WIDTHS(d, LN_CALL_F1) else LN_WIDTHS(d, LN_CALL_F0)
     }
+#undef LN_CALL_F2
+#undef LN_CALL_B1
+#undef LN_CALL_B0
+#undef LN_CALL_F1
+#undef LN_CALL_F0
+#undef LN_BWD
     prof_end(rec, PK_LN_BWD, el_bytes * (double)T * d, st);
     SL_CHECK_LAUNCH("ln_bwd");
     return 0;

@@ -277,6 +277,18 @@ def test_results_do_not_depend_on_the_batch(proj):
     srv.close()
 
 
+# LayerNorm of a width that is a multiple of 256 runs on a kernel of exactly that many chunks per row; both directions, fp32,
+# gathered and scattered rows of every such width (256 and 2048: test_small_stacks).
+@pytest.mark.parametrize("d", [512, 768, 1024, 1280, 1536, 1792])
+def test_widths_of_whole_chunks(d):
+    cfg = synth.tiny_config(d_model=d, n_head=d // 64, d_ff=128, n_blocks=2, lora_r=4, lora_proj=("q", "fc"),
+                            n_clients=3, batch=1, seq_len=64, seed=synth.BASE_SEED + 140)
+    inp = _boost_B(synth.make_stack_inputs(cfg), cfg)
+    srv, Y, dX, grads = gpu_round(cfg, inp)
+    compare_round(cfg, inp, Y, dX, grads, label="d%d" % d)
+    srv.close()
+
+
 # Token counts at which a wavefront of the adapter-gradient reduction sums eight or more 512-token chunks
 # (T >= 14337: the path with eight loads in flight, which workloads 3-5 take), on a stack narrow enough for
 # the oracle to run the whole batch: 33 sequences x 512 tokens = 33 chunks, i.e. 9 + 9 + 9 + 6 per wavefront
