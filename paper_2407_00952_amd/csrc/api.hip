@@ -908,7 +908,7 @@ int slora_adamw(size_t n, float *p, const float *g, float *m, float *v, float lr
 
 // ---- single layer -----------------------------------------------------------------------------
 namespace {
-struct LinWs { size_t A16, B16, B16T, A16T, zs, ps, WT, part_a, part_b, cnt, split, total; bool can_split; };
+struct LinWs { size_t A16, B16, B16T, A16T, zs, ps, WT, part_a, part_b, cnt, split, total; bool can_split, long_chunks; };
 LinWs lin_ws(int T, int n_in, int n_out)
 {
     LinWs w;
@@ -921,20 +921,29 @@ LinWs lin_ws(int T, int n_in, int n_out)
     w.zs = take(2 * (size_t)T * 16);
     w.ps = take(2 * (size_t)T * 16);
     w.WT = take(2 * (size_t)n_in * n_out);
-    w.part_a = take(4 * lora_grad_layer_floats(T, n_in, n_out));
-    w.part_b = take(4 * lora_grad_layer_floats(T, n_out, n_in));
+    // Short chunks of the adapter gradients' partial sums take up to four times the scratch of long ones.  A layer that the
+    // library's own array holds only with long ones takes those (a wide input into a narrow output: 273 tokens, 61888 -> 128
+    // need 39 MiB, with long chunks 27).
+    const size_t own = (size_t)SLORA_NOALLOC_SCRATCH_BYTES, at = off;
+    auto gradients = [&](bool long_chunks) {
+        off = at;
+        w.long_chunks = long_chunks;
+        w.part_a = take(4 * lora_grad_layer_floats(T, n_in, n_out, long_chunks));
+        w.part_b = take(4 * lora_grad_layer_floats(T, n_out, n_in, long_chunks));
+        return off <= own;
+    };
+    if (!gradients(false) && !gradients(true)) gradients(false);
     // scratch for products that split their contraction, unless it alone would put the layer beyond what the library's own
     // array holds; such a layer reports the array's size, so that the total never falls as T grows and a workspace taken
     // for the most tokens serves fewer
     const size_t more = al256(gemm_split_bytes()) + al256(gemm_split_counter_bytes());
-    const size_t own = (size_t)SLORA_NOALLOC_SCRATCH_BYTES;
     w.can_split = off + more <= own || off > own;
     w.cnt = w.split = 0;
     if (w.can_split) {
         w.cnt = take(gemm_split_counter_bytes());
         w.split = take(gemm_split_bytes());
     }
-    w.total = w.can_split ? off : own;
+    w.total = w.can_split && !w.long_chunks ? off : own;
     return w;
 }
 // the product of a layer call, with its split scratch; the counters are zeroed by the same call's front kernel
@@ -1043,7 +1052,7 @@ int slora_lora_linear_bwd(int dtype, int T, int n_in, int n_out, int r, float al
     const LoraGradDesc jobs[2] = {
         {(const bf16 *)x, (bf16 *)(base + w.ps), (float *)(base + w.part_a), dA, nullptr, n_in, 16, n_in, false, 1},
         {(const bf16 *)dy, (bf16 *)(base + w.zs), (float *)(base + w.part_b), dB, nullptr, n_out, 16, n_out, false, 0}};
-    return launch_lora_grad_jobs(jobs, 2, r, T, st);
+    return launch_lora_grad_jobs(jobs, 2, r, T, st, w.long_chunks);
 }
 
 // ---- the same backward for callers that cannot allocate ------------------------------------------

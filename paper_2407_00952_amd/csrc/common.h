@@ -142,7 +142,7 @@ bool attn_bwd_takes_delta(int S);
 int launch_attn_bwd(const bf16 *qkv, const bf16 *o, const bf16 *o_lo, const bf16 *dout, const float *lse,
                     float *delta, bf16 *dqkv, int n_seq, int S, int H, hipStream_t st, bool delta_ready = false);
 size_t lora_grad_partial_floats(int T, int C);
-size_t lora_grad_layer_floats(int T, int C, int c_other);
+size_t lora_grad_layer_floats(int T, int C, int c_other, bool long_chunks);
 // G[c, j] = sum_t X[t, c] * Y[t, j], j < r, written transposed ([r, C]) when out_is_rxC; several of them in one launch pair
 // (same T and r; each with partial-sum scratch of its own)
 struct LoraGradDesc {
@@ -151,7 +151,7 @@ struct LoraGradDesc {
     float *out_a, *out_b;            // out_b: the second adapter of a dual job, else null
     int ldx, ldy, C; bool dual; int out_is_rxC;
 };
-int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStream_t st);
+int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStream_t st, bool long_chunks = false);
 int launch_fedavg(int K, const float *const *x, const float *w, size_t n, float *out, hipStream_t st);
 int launch_sgd(float *p, const float *g, float lr, size_t n, hipStream_t st);
 int launch_adamw(float *p, const float *g, float *m, float *v, size_t n, float b1, float b2, float eps, float decay,

@@ -415,15 +415,17 @@ size_t lora_grad_partial_floats(int T, int C)
     return (size_t)std::max<long>((T + GR_ROWS - 1) / GR_ROWS, few) * 2 * SL_RP * (size_t)C;
 }
 
-// the same for single adapters, launched together with a job of width c_other (which has a say in the rows per chunk)
-size_t lora_grad_layer_floats(int T, int C, int c_other)
+// The same for single adapters, launched together with a job of width c_other (which has a say in the rows per chunk).
+// long_chunks: what launch_lora_grad_jobs needs with that argument set, for this token count alone.
+size_t lora_grad_layer_floats(int T, int C, int c_other, bool long_chunks)
 {
+    if (long_chunks) return (size_t)((T + GR_ROWS - 1) / GR_ROWS) * SL_RP * (size_t)C;
     const long t_few = std::min<long>(T, (GR_FEW - 1) / std::max(C, c_other));       // the largest count with short chunks
     const long few = (t_few + GR_ROWS_FEW - 1) / GR_ROWS_FEW;
     return (size_t)std::max<long>((T + GR_ROWS - 1) / GR_ROWS, few) * SL_RP * (size_t)C;
 }
 
-int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStream_t st)
+int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStream_t st, bool long_chunks)
 {
     if (njobs < 1 || njobs > LG_MAX_JOBS || T <= 0 || r < 1 || r > 16) return SL_EINVAL;
     LoraGradJobs jobs;
@@ -439,7 +441,7 @@ int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStr
         max_red = red > max_red ? red : max_red;
         bytes += 2.0 * T * (double)q.C;                  // the streaming pass: the tall operand once
     }
-    const int rows = grad_rows(T, max_c), nchunk = (T + rows - 1) / rows;
+    const int rows = long_chunks ? GR_ROWS : grad_rows(T, max_c), nchunk = (T + rows - 1) / rows;
     const bool rec = prof_begin(PK_LORA_GRAD, st);
     hipLaunchKernelGGL(lora_grad_partial_kernel, dim3((max_c + GR_COLS - 1) / GR_COLS, nchunk, njobs), dim3(256), 0, st,
                        jobs, r, T, rows);

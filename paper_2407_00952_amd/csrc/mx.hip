@@ -565,8 +565,8 @@ MxLinWs mx_lin_ws(int T, int n_in, int n_out)
     w.ps = take(2 * (size_t)T * 16);
     w.q = take((size_t)T * nmax);
     w.qs = take((size_t)T * nmax / 32);
-    w.part_a = take(4 * lora_grad_layer_floats(T, n_in, n_out));
-    w.part_b = take(4 * lora_grad_layer_floats(T, n_out, n_in));
+    w.part_a = take(4 * lora_grad_layer_floats(T, n_in, n_out, false));
+    w.part_b = take(4 * lora_grad_layer_floats(T, n_out, n_in, false));
     w.total = off;
     return w;
 }

@@ -175,6 +175,22 @@ def test_layer_workspace_for_the_most_tokens_serves_fewer(n_in, n_out):
         assert n[0] > 0 and all(a <= b for a, b in zip(n, n[1:]))
 
 
+# Layers that the library's own array holds with 512-token partial sums and not with 128-token ones: a wide input into a narrow output,
+# 257 to 1023 tokens.  The workspace is then the array's size, from there on up to the tokens that no longer fit.
+@pytest.mark.parametrize("T,n_in,n_out", [(273, 61888, 128), (311, 54656, 192), (511, 30400, 384), (763, 19840, 640)])
+def test_noalloc_backward_takes_wide_inputs(T, n_in, n_out):
+    al = lambda n: -(-n // 256) * 256
+    need = (al(32 * n_in) + al(64 * n_out) + al(32 * n_out) + al(64 * n_in) + 2 * al(32 * T) + al(2 * n_in * n_out)
+            + -(-T // 512) * 64 * (n_in + n_out))
+    assert need <= B.NOALLOC_SCRATCH_BYTES
+    n = [B.slora_lora_linear_ws_bytes(B.DTYPE_BF16, t, n_in, n_out, 4) for t in range(1, 2048)]
+    assert need <= n[T - 1] <= B.NOALLOC_SCRATCH_BYTES and all(a <= b for a, b in zip(n, n[1:]))
+    with pytest.raises(B.SloraError) as e:               # the size is checked before the alignment
+        B.slora_lora_linear_bwd_noalloc(T, n_in, n_out, 4, 32.0, FAKE + 8, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE,
+                                        stream=0)
+    assert e.value.code == B.SLORA_EINVAL
+
+
 def test_noalloc_backward_argument_checks():
     # checked before anything touches a GPU: sizes beyond the library's own scratch, bad pointers and sizes
     assert B.slora_lora_linear_ws_bytes(B.DTYPE_BF16, 65536, 4096, 4096, 4) > B.NOALLOC_SCRATCH_BYTES

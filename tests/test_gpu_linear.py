@@ -135,6 +135,7 @@ def test_fp32_zero_B_is_bitwise_base():
     # nine chunks (the body with eight loads in flight plus its tail), the last wavefront seven (tail only)
     (16960, 256, 64, 4, True),
     (16960, 64, 256, 16, False),
+    (700, 19840, 640, 4, False),     # scratch with 512-token partial sums only, the last one ragged
 ])
 def test_bf16_layer(T, n_in, n_out, r, bias):
     c = synth.make_single_layer(T, n_in, n_out, r, seed=100 + T + r, quant=True, bias=bias)

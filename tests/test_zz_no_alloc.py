@@ -50,6 +50,11 @@ def test_noalloc_backward_equals_the_workspace_backward():
     _both(700, 320, 448, 3, seed=902)          # smaller, ragged tiles, lower rank
 
 
+def test_noalloc_backward_of_a_wide_input():
+    # fits the scratch with 512-token partial sums only
+    _both(273, 61888, 128, 4, seed=903)
+
+
 def test_noalloc_rejects_sizes_beyond_its_scratch():
     import torch
     t = torch.zeros(64, dtype=torch.float32, device="cuda")
