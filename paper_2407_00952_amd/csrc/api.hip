@@ -933,17 +933,25 @@ LinWs lin_ws(int T, int n_in, int n_out)
         return off <= own;
     };
     if (!gradients(false) && !gradients(true)) gradients(false);
-    // scratch for products that split their contraction, unless it alone would put the layer beyond what the library's own
-    // array holds; such a layer reports the array's size, so that the total never falls as T grows and a workspace taken
-    // for the most tokens serves fewer
-    const size_t more = al256(gemm_split_bytes()) + al256(gemm_split_counter_bytes());
-    w.can_split = off + more <= own || off > own;
+    // Scratch for products that share their contraction, up to the tokens at which one of the layer's two does, unless it
+    // alone would put the layer beyond what the library's own array holds.  The total never falls as T grows, so that
+    // a workspace taken for the most tokens serves fewer.
+    const int t_split = std::max(gemm_split_rows(n_out, n_in), gemm_split_rows(n_in, n_out));
+    w.can_split = false;
     w.cnt = w.split = 0;
-    if (w.can_split) {
-        w.cnt = take(gemm_split_counter_bytes());
-        w.split = take(gemm_split_bytes());
+    w.total = w.long_chunks ? own : off;
+    if (T <= t_split) {
+        const size_t bytes = std::max(gemm_split_bytes(T, n_out, n_in, SL_RP), gemm_split_bytes(T, n_in, n_out, SL_RP));
+        const size_t end = off + al256(gemm_split_counter_bytes()) + al256(bytes);
+        w.can_split = bytes > 0 && (end <= own || off > own);
+        if (w.can_split) {
+            w.cnt = take(gemm_split_counter_bytes());
+            w.split = take(bytes);
+        }
+        w.total = end <= own || off > own ? std::max(w.total, end) : own;
+    } else if (t_split > 0) {
+        w.total = std::max(w.total, lin_ws(t_split, n_in, n_out).total);
     }
-    w.total = w.can_split && !w.long_chunks ? off : own;
     return w;
 }
 // the product of a layer call, with its split scratch; the counters are zeroed by the same call's front kernel

@@ -103,7 +103,7 @@ struct GemmArgs {
     unsigned char *oq, *os;
     static constexpr bool kEmitCodes = false;   // the bf16 kernel never does
     // scratch for launches that share the contraction over blocks (null: they do not; contexts never do, so that a
-    // sequence's results do not depend on its batch): gemm_split_bytes() of partial
+    // sequence's results do not depend on its batch): gemm_split_bytes(M, N, K, nz) of partial
     // sums, and gemm_split_counter_bytes() of counters, zero before the launch and left zero by it
     float *split_part; unsigned *split_cnt;
     const CountedRows *rows;         // launch_gemm_counted: in device memory
@@ -118,7 +118,8 @@ inline int gemm_counted_rows(int max_rows) { return max_rows <= 128 ? 128 : 256;
 struct TilePlan { int tile, waves, splits; };            // tile 0: the 256-row kernels
 TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int nz, bool can_split);
 int launch_gemm_tile(const GemmArgs &a, int epi, int nz, const TilePlan &p, hipStream_t st);
-size_t gemm_split_bytes();
+int gemm_split_rows(int N, int K);                       // the most rows at which a launch may do so (0: none does)
+size_t gemm_split_bytes(int M, int N, int K, int nz);    // enough for M rows or fewer
 size_t gemm_split_counter_bytes();
 // the same call with the frozen product in MXFP8 (a.mx set): converts X, forms the rank-space activations
 // of the adapted segments with a separate projection kernel (into a.zspill), then one fp8 GEMM launch

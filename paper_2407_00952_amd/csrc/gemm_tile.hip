@@ -19,6 +19,7 @@
 namespace {
 
 constexpr int BK = 64, ROWB = BK * 2;
+constexpr int SPLIT_TILES = 128;                         // most 64 x 64 tiles of a launch that shares its contraction
 
 // Partial sums cross XCDs (each has its own L2), so they are written and read at device scope: relaxed 8-byte atomics
 // go through to the memory side and need no cache flush; the order is kept by the vmcnt wait before the counter.
@@ -361,6 +362,14 @@ int launch_te(const GemmArgs &a, int nz, const TilePlan &p, hipStream_t st)
 
 }  // namespace
 
+// Over how many blocks a launch of t64 tiles of 64 x 64 and nk slabs shares its contraction, if it has scratch for that.
+// Combining the partial sums costs about 3 us, so a block keeps 9 slabs or more.
+static int split_shares(long t64, int nk)
+{
+    const int s = t64 > SPLIT_TILES ? 1 : t64 > 64 ? 2 : t64 > 32 ? 3 : 4;
+    return std::max(1, std::min(s, nk / 9));
+}
+
 // What this launch should run on: tile 64 or 128 (with the number of wave groups and of blocks per tile), or 0 for the
 // 256-row kernels of gemm.hip.  Costs are in units of a round of 256 x 256 tiles over the 256 CUs.
 TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int nz, bool can_split)
@@ -368,14 +377,9 @@ TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int nz, bool can_spli
     auto tiles = [&](int tm, int tn) { return (long)((M + tm - 1) / tm) * ((seg_n + tn - 1) / tn) * nseg; };
     const long t64 = tiles(64, 64), t128 = tiles(128, 128), t256 = tiles(256, 256), t128x256 = tiles(128, 256);
     // Up to two 64 x 64 tiles per CU: all of them run at once, and the smallest tile gives the most CUs work (M = 128,
-    // 768 x 768: 5.4 us against 10 on 128-row tiles and 24 on 256-row ones).  With fewer than 128 tiles a long
-    // contraction is shared out too; combining the partial sums costs about 3 us, so a block keeps 9 slabs or more.
-    if (t64 <= 512) {
-        const int nk = K / BK;
-        int s = !can_split || t64 > 128 ? 1 : t64 > 64 ? 2 : t64 > 32 ? 3 : 4;
-        s = std::max(1, std::min(s, nk / 9));
-        return {64, 4, s};
-    }
+    // 768 x 768: 5.4 us against 10 on 128-row tiles and 24 on 256-row ones).  With 128 tiles or fewer a long
+    // contraction is shared out too.
+    if (t64 <= 512) return {64, 4, can_split ? split_shares(t64, K / BK) : 1};
     // One 128 x 128 tile per CU at most: 8 waves, so that each SIMD has two, and four stages (T = 4096, 4096 -> 1024: 34.5 us
     // against 44 with 4 waves and two stages, 54 on 128-row tiles of the 4-wave kernel).
     if (t128 <= 256) return {128, 8, 1};
@@ -390,9 +394,22 @@ TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int nz, bool can_spli
     return c128 < c256 ? TilePlan{128, 4, 1} : TilePlan{0, 4, 1};
 }
 
-// scratch of a launch whose contraction is shared over blocks: at most 128 tiles with 2 shares (or fewer tiles with more)
-size_t gemm_split_bytes() { return (size_t)256 * (4 + 3) * 16 * 256; }
-size_t gemm_split_counter_bytes() { return 128 * sizeof(unsigned); }
+int gemm_split_rows(int N, int K)
+{
+    return split_shares(1, K / BK) > 1 ? SPLIT_TILES / ((N + 63) / 64) * 64 : 0;
+}
+// a block leaves its 64 x 64 fp32 sums and its 64 rows of rank-space ones
+size_t gemm_split_bytes(int M, int N, int K, int nz)
+{
+    const int cols = (N + 63) / 64, rows = std::min((M + 63) / 64, SPLIT_TILES / cols);
+    long blocks = 0;
+    for (int r = 1; r <= rows; ++r) {
+        const int s = split_shares((long)r * cols, K / BK);
+        if (s > 1) blocks = std::max(blocks, (long)r * cols * s);
+    }
+    return (size_t)blocks * 64 * (64 + nz) * sizeof(float);
+}
+size_t gemm_split_counter_bytes() { return SPLIT_TILES * sizeof(unsigned); }
 
 int launch_gemm_tile(const GemmArgs &a, int epi, int nz, const TilePlan &p, hipStream_t st)
 {

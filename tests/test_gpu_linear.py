@@ -222,3 +222,33 @@ def test_bf16_layer_dispatch_edges(T, n_in, n_out, r):
         e = relerr(g, rf)
         say("   %s rel err %.2e" % (name, e))
         assert e <= BF16_TOL, (name, e)
+
+
+# Products that share their contraction over blocks: the blocks of a tile finish in any order, and their sums are added in
+# share order all the same; the counters are left as the next call expects them; nothing behind the workspace is written.
+@pytest.mark.parametrize("T,n_in,n_out,r", [
+    (3, 2432, 128, 16),              # forward: two tiles, four shares
+    (130, 128, 2432, 3),             # input gradient: six tiles, four shares
+    (260, 1216, 832, 2),             # forward: 65 tiles, two shares
+    (2048, 2048, 256, 4),            # forward: 128 tiles, two shares
+])
+def test_bf16_layer_shared_contraction_repeats_itself(T, n_in, n_out, r):
+    import torch
+    c = synth.make_single_layer(T, n_in, n_out, r, seed=600 + T + r, quant=True, bias=False)
+    x, W, dy = (B.to_device_bf16(c[k]) for k in ("x", "W", "dy"))
+    A, Bm = torch.from_numpy(c["A"]).cuda(), torch.from_numpy(c["B"]).cuda()
+    nws = B.slora_lora_linear_ws_bytes(B.DTYPE_BF16, T, n_in, n_out, r)
+    ws = torch.full((nws + 4096,), 0xFF, dtype=torch.uint8, device="cuda")       # NaN in either type
+    first = None
+    for k in range(4):
+        out = [torch.full(sh, float("nan"), dtype=dt, device="cuda") for sh, dt in
+               (((T, n_out), torch.bfloat16), ((T, n_in), torch.bfloat16), ((r, n_in), torch.float32), ((n_out, r), torch.float32))]
+        if k == 2:
+            ws[:nws].fill_(0xFF)
+        B.slora_lora_linear_fwd(B.DTYPE_BF16, T, n_in, n_out, r, c["alpha"], x, W, None, A, Bm, out[0], ws, nws)
+        B.slora_lora_linear_bwd(B.DTYPE_BF16, T, n_in, n_out, r, c["alpha"], x, dy, W, A, Bm, *out[1:], ws, nws)
+        torch.cuda.synchronize()
+        assert all(bool(torch.isfinite(t).all()) for t in out)
+        first = first or out
+        assert all(torch.equal(a, b) for a, b in zip(out, first)), k
+    assert bool((ws[nws:] == 0xFF).all())

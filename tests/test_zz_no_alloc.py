@@ -1,7 +1,7 @@
 """The allocation-free variant of the single layer's backward (for callers that cannot allocate device
 memory) against the entry point it is a variant of: same kernels, so the outputs must agree bit for bit
-(and thereby to the 2e-2 bar of the bf16 path).  Two calls in a row on the library's own scratch array, the
-second with a smaller input, so that whatever the first call left there is in the way of the second."""
+(and thereby to the 2e-2 bar of the bf16 path).  Calls in a row on the library's own scratch array, the
+later ones with a smaller input, so that whatever the first call left there is in the way of the others."""
 import numpy as np
 import pytest
 
@@ -45,9 +45,10 @@ def _both(T, n_in, n_out, r, seed):
 
 
 def test_noalloc_backward_equals_the_workspace_backward():
-    say("allocation-free single-layer backward, two calls in a row")
+    say("allocation-free single-layer backward, calls in a row")
     _both(2048, 512, 768, 8, seed=901)
     _both(700, 320, 448, 3, seed=902)          # smaller, ragged tiles, lower rank
+    _both(130, 128, 2432, 3, seed=904)         # the input gradient's contraction shared over four blocks
 
 
 def test_noalloc_backward_of_a_wide_input():
