@@ -98,6 +98,35 @@ def test_fp32_dispatch_edges(T, n_in, n_out, r, bias):
         assert relerr(g, ref) <= F32_TOL, name
 
 
+# The low-rank term may not cost the fp32 product precision: error (2-norm, against fp64) of y no larger than that of the sums
+# taken one after the other, the frozen product and the low-rank one each on its own (the 5 % cover the sample: some 1e5
+# independent roundings).  Short contractions, where 16 more roundings at the size of the result show most.
+# A low-rank term that is small beside the frozen product, and one that is larger.
+@pytest.mark.parametrize("boost", [1, 30])
+@pytest.mark.parametrize("T,n_in,n_out", [(20, 16, 768), (700, 32, 704), (8200, 16, 1030)])     # direct, 64 and 128 tiles
+def test_fp32_low_rank_term_costs_no_precision(T, n_in, n_out, boost):
+    c = synth.make_single_layer(T, n_in, n_out, 16, seed=23 + T, bias=True)
+    c["B"] = c["B"] * np.float32(boost)
+    rows = slice(0, min(T, 256))
+    f32, f64 = np.float32, np.float64
+    s = c["alpha"] / c["r"]
+
+    def one_by_one(X, Y):                                # sum_k X[:, k] Y[:, k]^T, a fused multiply-add each
+        acc = np.zeros((X.shape[0], Y.shape[0]), f32)
+        for k in range(X.shape[1]):
+            acc = (X[:, k, None].astype(f64) * Y[None, :, k].astype(f64) + acc).astype(f32)
+        return acc
+    x = c["x"][rows]
+    plain = one_by_one(x, c["W"]) + c["b"]
+    plain = plain + f32(s) * one_by_one(one_by_one(x, c["A"]), c["B"])
+    got = _run_f32(c)[0][rows]
+    x, W, A, Bm = (v.astype(f64) for v in (x, c["W"], c["A"], c["B"]))
+    ref = x @ W.T + c["b"].astype(f64) + s * (x @ A.T) @ Bm.T
+    e_got, e_plain = (np.linalg.norm(v - ref) / np.linalg.norm(ref) for v in (got, plain))
+    say("fp32 layer", T, n_in, n_out, boost, "error %.3e, one by one %.3e, ratio %.3f" % (e_got, e_plain, e_got / e_plain))
+    assert e_got <= 1.05 * e_plain
+
+
 @pytest.mark.parametrize("T,n_in,n_out", [(20, 64, 96), (700, 768, 704)])       # direct, 64 x 64 tiles
 def test_fp32_infinity_stays_an_infinity(T, n_in, n_out):
     # rank 3 is kept as 4 columns: the empty one must not turn inf * 0 into a NaN of the result
