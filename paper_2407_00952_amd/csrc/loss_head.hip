@@ -34,13 +34,24 @@ constexpr int LH_CHUNK = 16384;          // labeled tokens per pass
 constexpr int LH_MAXC = 8;               // 256-column chunks of a LayerNorm row: d <= 2048
 constexpr int LH_SHARES = 64;            // most blocks a tile's contraction is shared over (one per lane below)
 constexpr int LH_PART_ROWS = 65536;      // rows of partial sums a large batch has scratch for
+constexpr int LH_SHARE_SLABS = 4;        // fewest slabs of a share
 
 struct LabelCount { int n; float inv_n; };
 
-inline int part_rows(int rows) { return rows < LH_PART_ROWS / LH_SHARES ? rows * LH_SHARES : LH_PART_ROWS; }
-
 inline size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 inline int vocab_padded(int V) { return (V + 63) / 64 * 64; }
+
+// Rows of partial sums for up to `rows` labeled ones: the shares that the slabs of the vocabulary allow, and for every 1024 rows those
+// of one round of 256 blocks.  list_labels_kernel picks no more than that of itself (checked for every row count, width
+// and a sweep of vocabularies), so the limit changes no result.
+inline int part_rows(int rows, int d, int V)
+{
+    const int slabs = vocab_padded(V) / 64 / LH_SHARE_SLABS;
+    const int shares = slabs < 1 ? 1 : slabs < LH_SHARES ? slabs : LH_SHARES;
+    const int rounds = (rows + 1023) / 1024 * (256 * 256 / ((d + 255) / 256));
+    const int most = rounds < LH_PART_ROWS ? rounds : LH_PART_ROWS;
+    return rows * shares < most ? rows * shares : most;
+}
 
 __device__ __forceinline__ float block_reduce(float v, bool is_max, float *red)
 {
@@ -118,8 +129,7 @@ __global__ __launch_bounds__(1024) void list_labels_kernel(const int *__restrict
         const int tiles = ((rows + tile_rows - 1) / tile_rows) * ((d + 255) / 256);
         const int s = lane + 1;
         const int rounds = (tiles * s + 255) / 256;
-        // a share keeps four slabs or more
-        const bool ok = s == 1 || (s * 4 <= nk && (long long)s * rows <= part_rows);
+        const bool ok = s == 1 || (s * LH_SHARE_SLABS <= nk && (long long)s * rows <= part_rows);
         float cost = ok ? rounds * (1.41f * ((nk + s - 1) / s) + 8.0f) + (float)s * rows * d * 1.6e-6f : INFINITY;
         int best = s;
 #pragma unroll
@@ -368,7 +378,7 @@ HeadWs head_ws(int T, int d, int V)
     w.chunks = take(sizeof(CountedRows) * ((size_t)(T - 1) / LH_CHUNK + 1));
     w.perm = take(4 * (size_t)T);
     w.u = take(2 * (size_t)rows * d);
-    w.part = take(4 * (size_t)part_rows(rows) * d);
+    w.part = take(4 * (size_t)part_rows(rows, d, V) * d);
     w.logits = take(2 * (size_t)rows * Vp);
     w.total = off;
     return w;
@@ -440,7 +450,7 @@ int slora_loss_head(int32_t T, int32_t d_model, int32_t vocab, const void *y, co
 
     const int most = T < LH_CHUNK ? T : LH_CHUNK;
     hipLaunchKernelGGL(list_labels_kernel, dim3(1), dim3(1024), 0, st, labels, T, vocab, d, Vp / 64,
-                       gemm_counted_rows(most), part_rows(most), perm, cnt, chunks);
+                       gemm_counted_rows(most), part_rows(most, d, vocab), perm, cnt, chunks);
     SL_CHECK_LAUNCH("list_labels");
     for (int c = 0, r0 = 0; r0 < T; ++c, r0 += LH_CHUNK) {
         const int rows = (T - r0 < LH_CHUNK) ? T - r0 : LH_CHUNK;

@@ -261,6 +261,36 @@ def test_loss_head_argument_checks():
     assert e.value.code == B.SLORA_ENOSPC
 
 
+# The loss head's scratch holds the partial sums that its row counting may ask for and little more.  The rule of that kernel (rounds
+# of 256 blocks, 1.41 us per slab of a share and 8 to fill and drain, the sums' way through memory) is repeated here: the share
+# count it prefers has to fit at every row count, or the scratch would change results.
+@pytest.mark.parametrize("d", [64, 320, 768, 1024, 2048])
+@pytest.mark.parametrize("V", [50, 1000, 20011, 50257, 65536])
+def test_loss_head_workspace_fits_its_partial_sums(d, V):
+    al = lambda n: -(-n // 256) * 256
+    nk = -(-V // 64)
+    s = np.arange(1, 65)
+    prev = 0
+    for T in (1, 64, 128, 129, 256, 1000, 1024, 1025, 2048, 5000, 16384, 40000):
+        rows = min(T, 16384)
+        ws = B.slora_loss_head_ws_bytes(T, d, V)
+        assert ws >= prev
+        prev = ws
+        part = ws - (2 * al(128 * nk * d) + 256 + al(8 * -(-T // 16384)) + al(4 * T) + al(2 * rows * d) + al(128 * rows * nk))
+        have = part // (4 * d)
+        assert rows <= have <= min(rows * max(1, min(64, nk // 4)), 65536) + 64
+        r = np.arange(max(1, rows - 3000), rows + 1)[:, None]
+        tiles = -(-r // (128 if T <= 128 else 256)) * -(-d // 256)
+        cost = (-(-tiles * s // 256) * (1.41 * -(-nk // s) + 8.0) + s * r * (d * 1.6e-6)).astype(np.float32)
+        cost[:, (s > 1) & (s * 4 > nk)] = np.inf
+        cost[s * r > 65536] = np.inf
+        best = s[np.argmin(cost, axis=1)]
+        assert (best * r[:, 0] <= have).all(), T
+    # 1024 tokens: 264 and 553 MiB if 64 shares had to fit whatever the vocabulary
+    if d == 1024 and V in (1000, 50257):
+        assert B.slora_loss_head_ws_bytes(1024, d, V) <= (30 << 20 if V == 1000 else 370 << 20)
+
+
 def test_mx_argument_checks():
     """every check of the MXFP8 entry points precedes the first launch (include/slora.h)"""
     L = B.lib()
