@@ -30,6 +30,10 @@ namespace {
 // threads and two, 604 here = 5.5 TB/s)
 constexpr int CE_THR = 1024;
 constexpr int CE_MAXCH = 8;              // 16-byte chunks per thread: padded vocabulary <= 65536
+// short rows, most of whose 1024 threads would only wait at the reductions (16384 rows of 1000: 94 us with 512 threads, 101 with
+// 1024, 24 here; the whole head of 4096 tokens, width 1024, vocabulary 2000: 96, 111 and 93 us)
+constexpr int CE_SHORT_THR = 256;
+constexpr int CE_SHORT_MAXCH = 2;        // padded vocabulary <= 4096
 constexpr int LH_CHUNK = 16384;          // labeled tokens per pass
 constexpr int LH_MAXC = 8;               // 256-column chunks of a LayerNorm row: d <= 2048
 constexpr int LH_SHARES = 64;            // most blocks a tile's contraction is shared over (one per lane below)
@@ -53,6 +57,7 @@ inline int part_rows(int rows, int d, int V)
     return rows * shares < most ? rows * shares : most;
 }
 
+template <int THR>
 __device__ __forceinline__ float block_reduce(float v, bool is_max, float *red)
 {
 #pragma unroll
@@ -66,7 +71,7 @@ __device__ __forceinline__ float block_reduce(float v, bool is_max, float *red)
     __syncthreads();
     float r = red[0];
 #pragma unroll
-    for (int i = 1; i < CE_THR / 64; ++i) r = is_max ? fmaxf(r, red[i]) : r + red[i];
+    for (int i = 1; i < THR / 64; ++i) r = is_max ? fmaxf(r, red[i]) : r + red[i];
     return r;
 }
 
@@ -256,14 +261,15 @@ __device__ __forceinline__ float pair_max(unsigned w) { return fmaxf(lo_f(w), hi
 
 // One block per listed row.  logits [rows, ldl] bf16 in; the same memory receives
 // d loss / d logits = (softmax - onehot) * inv_n (zero in the padding columns).  Rows past the labeled ones have none.
-__global__ __launch_bounds__(CE_THR) __attribute__((amdgpu_waves_per_eu(8, 8))) void softmax_ce_kernel(bf16 *__restrict__ logits, int ldl, int V,
+template <int THR, int MAXCH>
+__global__ __launch_bounds__(THR) __attribute__((amdgpu_waves_per_eu(8, 8))) void softmax_ce_kernel(bf16 *__restrict__ logits, int ldl, int V,
                                                             const int *__restrict__ labels,
                                                             const int *__restrict__ perm,
                                                             const CountedRows *__restrict__ chunk,
                                                             const LabelCount *__restrict__ cnt,
                                                             float *__restrict__ loss_tok)
 {
-    __shared__ float red[CE_THR / 64];
+    __shared__ float red[THR / 64];
     const int tid = threadIdx.x, row = perm[blockIdx.x];
     if ((int)blockIdx.x >= chunk->rows) {
         if (tid == 0) loss_tok[row] = 0.f;
@@ -274,16 +280,16 @@ __global__ __launch_bounds__(CE_THR) __attribute__((amdgpu_waves_per_eu(8, 8))) 
     const int nch = ldl >> 3;
     const float picked = bf2f(p[label]);     // read before any thread overwrites the row (barriers below)
     const float l2e = 1.4426950408889634f;
-    uint4 v[CE_MAXCH];                       // the row's bf16 values, two to a dword
+    uint4 v[MAXCH];                       // the row's bf16 values, two to a dword
     float m = -INFINITY;
 #pragma unroll
-    for (int c = 0; c < CE_MAXCH; ++c) {
-        const int ch = tid + c * CE_THR;
+    for (int c = 0; c < MAXCH; ++c) {
+        const int ch = tid + c * THR;
         if (ch < nch) v[c] = *(const uint4 *)(p + ch * 8);
     }
 #pragma unroll
-    for (int c = 0; c < CE_MAXCH; ++c) {
-        const int ch = tid + c * CE_THR;
+    for (int c = 0; c < MAXCH; ++c) {
+        const int ch = tid + c * THR;
         if (ch < nch) {
             if (ch * 8 + 8 > V) {            // padding columns become -inf: no probability, no gradient
                 unsigned *w = (unsigned *)&v[c];
@@ -296,15 +302,15 @@ __global__ __launch_bounds__(CE_THR) __attribute__((amdgpu_waves_per_eu(8, 8))) 
             m = fmaxf(m, fmaxf(fmaxf(pair_max(v[c].x), pair_max(v[c].y)), fmaxf(pair_max(v[c].z), pair_max(v[c].w))));
         }
     }
-    m = block_reduce(m, true, red);
+    m = block_reduce<THR>(m, true, red);
     // The unpacked values would not all fit in registers beside the packed ones: without this the compiler keeps
     // them from pass to pass and half the waves have no room.
 #pragma unroll
-    for (int c = 0; c < CE_MAXCH; ++c) asm volatile("" : "+v"(v[c].x), "+v"(v[c].y), "+v"(v[c].z), "+v"(v[c].w));
+    for (int c = 0; c < MAXCH; ++c) asm volatile("" : "+v"(v[c].x), "+v"(v[c].y), "+v"(v[c].z), "+v"(v[c].w));
     float s = 0.f;
 #pragma unroll
-    for (int c = 0; c < CE_MAXCH; ++c) {
-        const int ch = tid + c * CE_THR;
+    for (int c = 0; c < MAXCH; ++c) {
+        const int ch = tid + c * THR;
         if (ch < nch) {
             const unsigned w[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
 #pragma unroll
@@ -314,15 +320,15 @@ __global__ __launch_bounds__(CE_THR) __attribute__((amdgpu_waves_per_eu(8, 8))) 
             }
         }
     }
-    s = block_reduce(s, false, red);
+    s = block_reduce<THR>(s, false, red);
 #pragma unroll
-    for (int c = 0; c < CE_MAXCH; ++c) asm volatile("" : "+v"(v[c].x), "+v"(v[c].y), "+v"(v[c].z), "+v"(v[c].w));
+    for (int c = 0; c < MAXCH; ++c) asm volatile("" : "+v"(v[c].x), "+v"(v[c].y), "+v"(v[c].z), "+v"(v[c].w));
     const float lse = m + __logf(s);
     if (tid == 0) loss_tok[row] = lse - picked;
     const float inv_n = cnt->inv_n;
 #pragma unroll
-    for (int c = 0; c < CE_MAXCH; ++c) {
-        const int ch = tid + c * CE_THR;
+    for (int c = 0; c < MAXCH; ++c) {
+        const int ch = tid + c * THR;
         if (ch < nch) {
             const unsigned w[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
             bf16x8 o;
@@ -468,8 +474,12 @@ int slora_loss_head(int32_t T, int32_t d_model, int32_t vocab, const void *y, co
             a.rows = cr;
             if ((rc = launch_gemm_counted(a, EPI_STORE, st))) return rc;
         }
-        hipLaunchKernelGGL(softmax_ce_kernel, dim3(rows), dim3(CE_THR), 0, st, logits, Vp, vocab, labels, list, cr, cnt,
-                           loss_tok);
+        if (Vp <= CE_SHORT_MAXCH * CE_SHORT_THR * 8)
+            hipLaunchKernelGGL((softmax_ce_kernel<CE_SHORT_THR, CE_SHORT_MAXCH>), dim3(rows), dim3(CE_SHORT_THR), 0, st, logits,
+                               Vp, vocab, labels, list, cr, cnt, loss_tok);
+        else
+            hipLaunchKernelGGL((softmax_ce_kernel<CE_THR, CE_MAXCH>), dim3(rows), dim3(CE_THR), 0, st, logits, Vp, vocab,
+                               labels, list, cr, cnt, loss_tok);
         SL_CHECK_LAUNCH("softmax_ce");
         GemmArgs b = plain_gemm(logits, Vp, (const bf16 *)(base + w.WvT), Vp, most, d, Vp, part, d);
         b.rows = cr;

@@ -100,6 +100,10 @@ def test_loss_head_without_labels():
     (16640, 64, 520, 16384),
     (16641, 64, 520, 16385),
     (16700, 64, 1030, 16700),
+    (70, 64, 2048, 70),              # one 16-byte chunk per thread of a short row, and one more
+    (70, 64, 2049, 69),
+    (70, 64, 4096, 70),              # the longest short row, the shortest long one
+    (70, 64, 4097, 69),
 ])
 def test_loss_head_listed_rows(T, d, V, n_labeled):
     say("loss head T=%d d=%d V=%d, %d labeled" % (T, d, V, n_labeled))
