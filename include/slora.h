@@ -304,7 +304,8 @@ int slora_mx_lora_linear_bwd(int32_t T, int32_t n_in, int32_t n_out, int32_t r, 
  * recorded events (it BLOCKS the host) and returns, for one kind, the summed kernel time in milliseconds, the
  * summed algorithmic work of those launches and their number.  Work is in flop for the matrix-core kinds --
  * GEMM: 2*M*N*K of the frozen product (Sec. II-C); attention: 2*S*d per token forward, 4*S*d backward, lower
- * triangle only -- and in bytes for the HBM-bound kinds: each tensor the kernel must read or write, once.
+ * triangle only -- and in bytes for the HBM-bound kinds: each tensor the kernel must read or write, once.  The loss
+ * head's launches count the labeled rows, whose number is only known on the device (and read by this call).
  * At most 16384 launches are recorded between two calls of slora_prof_enable, which also clears the record.
  * slora_prof_read is slora_prof_read_kind(SLORA_PROF_GEMM, ...).  Process-wide, not thread-safe.
  * SLORA_EINVAL for an unknown kind, SLORA_EHIP if an event call fails. */
@@ -324,7 +325,8 @@ int slora_prof_read(double *h_gemm_ms, double *h_gemm_flop, int *h_launches);
  * while SLORA_PROF_GEMM is selected, the launches that run the 4-wave kernel store the shader-clock counter and
  * the 100 MHz reference counter at their start and end; this call synchronises the device (it BLOCKS), and
  * returns sum of shader ticks / sum of reference ticks x 100 over those launches and their number (0 MHz with no
- * sample).  Uses 512 KB of device memory of the library's own (a static array). */
+ * sample).  Uses 576 KB of device memory of the library's own (static arrays, the row counts of
+ * the loss head's launches included). */
 int slora_prof_read_clock(double *h_mhz, int *h_samples);
 
 const char *slora_strerror(int code);

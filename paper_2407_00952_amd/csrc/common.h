@@ -68,7 +68,7 @@ struct EmbedSrc {
 // ---- GEMM ---------------------------------------------------------------------------------
 // EPI_STORE_DELTA: plain store of a [M, 64 H] tensor that is the gradient of an attention output, plus
 // delta[row][head] = sum over the head's 64 columns of out * (dl_o + dl_lo) (4-wave kernel only)
-// EPI_PARTIAL: fp32 sums of a share of the contraction (launch_gemm_counted only)
+// EPI_PARTIAL: fp32 sums of a share of the contraction (products over counted rows only)
 enum { EPI_STORE = 0, EPI_RESID = 1, EPI_GELU = 2, EPI_DGELU = 3, EPI_STORE_DELTA = 4, EPI_PARTIAL = 5 };
 
 // Row count of a product as an earlier kernel found it, and over how many blocks a tile's contraction is shared
@@ -106,13 +106,14 @@ struct GemmArgs {
     // sequence's results do not depend on its batch): gemm_split_bytes(M, N, K, nz) of partial
     // sums, and gemm_split_counter_bytes() of counters, zero before the launch and left zero by it
     float *split_part; unsigned *split_cnt;
-    const CountedRows *rows;         // launch_gemm_counted: in device memory
+    // in device memory, or null: how many of the M rows are wanted, as an earlier kernel counted them (no rank-space branch; one
+    // segment).  EPI_PARTIAL needs it; EPI_STORE may compute rows past them on the kernels for few tiles
+    const CountedRows *rows;
     unsigned long long *clk;         // measurement hook: four words for clock stamps of this launch, or null
 };
 
 int launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st);
-int launch_gemm_counted(const GemmArgs &a, int epi, hipStream_t st);
-// rows of its tiles (256 columns): 128 only where no more rows can come
+// rows of the tiles (256 columns) of a product over counted rows: 128 only where no more can come
 inline int gemm_counted_rows(int max_rows) { return max_rows <= 128 ? 128 : 256; }
 // the product on 64 x 64 or 128 x 128 tiles (gemm_tile.hip), for launches with too few 256-row tiles
 struct TilePlan { int tile, waves, splits; };            // tile 0: the 256-row kernels

@@ -619,16 +619,20 @@ int launch_e(const GemmArgs &a, int nz, hipStream_t st)
 }  // namespace
 
 static int launch_gemm_inner(const GemmArgs &a, int epi, int nz, hipStream_t st);
+static int launch_gemm_counted(const GemmArgs &a, int epi, hipStream_t st);
 
 int launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st)
 {
-    const bool rec = prof_begin(PK_GEMM, st);
+    const bool rec = prof_begin(PK_GEMM, st, a.rows ? &a.rows->rows : nullptr);
     GemmArgs b = a;
     b.clk = prof_clock_words(rec);
-    const int rc = launch_gemm_inner(b, epi, nz, st);
+    const int rc = epi == EPI_PARTIAL || (a.rows && !plan_gemm_tile(a.M, a.N, 1, a.K, 0, false).tile)
+                       ? launch_gemm_counted(b, epi, st)
+                       : launch_gemm_inner(b, epi, nz, st);
     // algorithmic work of this launch: the frozen product only (the rank-r branch adds < 1 % and is left
     // out, which understates the achieved rate slightly)
-    prof_end(rec, PK_GEMM, 2.0 * a.M * (double)a.N * a.K, st);
+    const double row = 2.0 * (double)a.N * a.K;
+    prof_end(rec, PK_GEMM, a.rows ? 0.0 : row * a.M, st, a.rows ? row : 0.0);
     return rc;
 }
 
@@ -657,8 +661,8 @@ static int launch_gemm_inner(const GemmArgs &a, int epi, int nz, hipStream_t st)
 }
 
 // A product over the rows that a kernel before it counted (a.rows; a.M is their upper bound), without rank-space branch.
-// EPI_STORE or EPI_PARTIAL.  Its work is only known on the device, so it is not in the launch profile.
-int launch_gemm_counted(const GemmArgs &a, int epi, hipStream_t st)
+// EPI_STORE or EPI_PARTIAL.
+static int launch_gemm_counted(const GemmArgs &a, int epi, hipStream_t st)
 {
     if (a.M <= 0 || a.N <= 0 || a.K <= 0 || (a.K % BK) != 0 || a.nseg != 1 || a.seg_n != a.N || (a.ldx % 8) ||
         (a.ldw % 8) || (a.N % 8) || (a.ldo % 8) || !a.rows || !a.out0)

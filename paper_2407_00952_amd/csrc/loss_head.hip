@@ -20,6 +20,7 @@
 // the two products run at 1.09 and 1.48 PFLOP/s); 1098 tokens 952 -> 239 us; 65 tokens of 768 902 -> 118 us.
 #include "../../include/slora.h"
 #include "common.h"
+#include "prof.h"
 
 #include <cstring>
 
@@ -462,18 +463,14 @@ int slora_loss_head(int32_t T, int32_t d_model, int32_t vocab, const void *y, co
         const int rows = (T - r0 < LH_CHUNK) ? T - r0 : LH_CHUNK;
         const CountedRows *cr = chunks + c;
         const int *list = perm + r0;
+        bool rec = prof_begin(PK_LN_FWD, st, &cr->rows);
         hipLaunchKernelGGL(head_ln_fwd_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, (const bf16 *)y, list, cr, gamma,
                            beta, eps, u, d);
+        prof_end(rec, PK_LN_FWD, 0.0, st, 4.0 * d);
         SL_CHECK_LAUNCH("head_ln_fwd");
         GemmArgs a = plain_gemm(u, d, (const bf16 *)(base + w.WvP), d, rows, Vp, d, logits, Vp);
-        // few tiles: the kernels for those, over all rows of the chunk (a row's logits depend on that row alone, and
-        // those past the labeled rows are not read)
-        if (plan_gemm_tile(rows, Vp, 1, d, 0, false).tile) {
-            if ((rc = launch_gemm(a, EPI_STORE, 0, st))) return rc;
-        } else {
-            a.rows = cr;
-            if ((rc = launch_gemm_counted(a, EPI_STORE, st))) return rc;
-        }
+        a.rows = cr;
+        if ((rc = launch_gemm(a, EPI_STORE, 0, st))) return rc;
         if (Vp <= CE_SHORT_MAXCH * CE_SHORT_THR * 8)
             hipLaunchKernelGGL((softmax_ce_kernel<CE_SHORT_THR, CE_SHORT_MAXCH>), dim3(rows), dim3(CE_SHORT_THR), 0, st, logits,
                                Vp, vocab, labels, list, cr, cnt, loss_tok);
@@ -483,9 +480,11 @@ int slora_loss_head(int32_t T, int32_t d_model, int32_t vocab, const void *y, co
         SL_CHECK_LAUNCH("softmax_ce");
         GemmArgs b = plain_gemm(logits, Vp, (const bf16 *)(base + w.WvT), Vp, most, d, Vp, part, d);
         b.rows = cr;
-        if ((rc = launch_gemm_counted(b, EPI_PARTIAL, st))) return rc;
+        if ((rc = launch_gemm(b, EPI_PARTIAL, 0, st))) return rc;
+        rec = prof_begin(PK_LN_BWD, st, &cr->rows);
         hipLaunchKernelGGL(head_ln_bwd_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, (const bf16 *)y, list, rows, cr,
                            part, gamma, eps, (bf16 *)dy, d);
+        prof_end(rec, PK_LN_BWD, 4.0 * rows * (double)d, st, 4.0 * d);
         SL_CHECK_LAUNCH("head_ln_bwd");
     }
     hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(1024), 0, st, loss_tok, T, cnt, loss);

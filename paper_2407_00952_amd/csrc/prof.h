@@ -6,8 +6,10 @@
 
 enum { PK_GEMM = 0, PK_LN_FWD, PK_LN_BWD, PK_LORA_GRAD, PK_SGD, PK_ATTN_FWD, PK_ATTN_BWD, PK_FEDAVG, PK_COUNT };
 
-bool prof_begin(int kind, hipStream_t st);               // true if this launch is being recorded
-void prof_end(bool recording, int kind, double work, hipStream_t st);
+// true if this launch is being recorded.  `rows`: a row count in device memory that the launch's work depends on, written by
+// work queued on the stream before; its value is noted there and multiplies work_per_row.
+bool prof_begin(int kind, hipStream_t st, const int *rows = nullptr);
+void prof_end(bool recording, int kind, double work, hipStream_t st, double work_per_row = 0.0);
 int prof_enable(unsigned mask);                          // bit k = record kind k; resets what was recorded
 int prof_read(int kind, double *ms, double *work, int *launches);   // blocks until the events have happened
 // Shader clock under load: while the GEMM kind is being recorded, the 4-wave GEMM kernel stores the shader

@@ -1,4 +1,4 @@
-// Event-based timing of kernel launches (see prof.h).  Host code only.
+// Event-based timing of kernel launches (see prof.h).
 #include "prof.h"
 #include "common.h"
 #include <vector>
@@ -6,6 +6,8 @@
 // clock stamps of the recorded GEMM launches: [pair][4] = shader clock at start, reference clock at start,
 // shader clock at end, reference clock at end (written by block 0 of the 4-wave GEMM kernel)
 static __device__ unsigned long long clock_words[16384 * 4];
+// row counts of the recorded launches that are given one in device memory
+static __device__ int row_words[16384];
 
 namespace {
 struct Prof {
@@ -13,10 +15,14 @@ struct Prof {
     std::vector<hipEvent_t> ev;      // pairs: start, stop
     std::vector<int> kind;           // per pair
     std::vector<double> work;        // per pair
+    std::vector<double> per_row;     // per pair: work for each of its noted rows
     size_t used = 0;                 // pairs recorded
     unsigned long long *clk = nullptr;   // device address of clock_words on the device profiling was enabled on
+    int *rows = nullptr;                 // and of row_words
 } g;
 constexpr size_t kMaxPairs = 16384;
+
+__global__ void note_rows_kernel(const int *rows, int *word) { *word = *rows; }
 }  // namespace
 
 int prof_enable(unsigned mask)
@@ -27,11 +33,14 @@ int prof_enable(unsigned mask)
             if (hipEventCreate(&e) != hipSuccess) { g.ev.clear(); return SL_EHIP; }
         g.kind.resize(kMaxPairs);
         g.work.resize(kMaxPairs);
+        g.per_row.resize(kMaxPairs);
     }
     if (mask && !g.clk) {
         void *p = nullptr;
         if (hipGetSymbolAddress(&p, HIP_SYMBOL(clock_words)) != hipSuccess) return SL_EHIP;
         g.clk = (unsigned long long *)p;
+        if (hipGetSymbolAddress(&p, HIP_SYMBOL(row_words)) != hipSuccess) { g.clk = nullptr; return SL_EHIP; }
+        g.rows = (int *)p;
     }
     if (mask && hipMemset(g.clk, 0, sizeof(unsigned long long) * 4 * kMaxPairs) != hipSuccess) return SL_EHIP;
     g.mask = mask;
@@ -39,19 +48,22 @@ int prof_enable(unsigned mask)
     return SL_OK;
 }
 
-bool prof_begin(int kind, hipStream_t st)
+bool prof_begin(int kind, hipStream_t st, const int *rows)
 {
     if (!((g.mask >> kind) & 1u) || g.used >= kMaxPairs) return false;
+    // in front of the start event: outside the time taken, and done when the stop event has happened
+    if (rows) hipLaunchKernelGGL(note_rows_kernel, dim3(1), dim3(1), 0, st, rows, g.rows + g.used);
     (void)hipEventRecord(g.ev[2 * g.used], st);
     return true;
 }
 
-void prof_end(bool recording, int kind, double work, hipStream_t st)
+void prof_end(bool recording, int kind, double work, hipStream_t st, double work_per_row)
 {
     if (!recording) return;
     (void)hipEventRecord(g.ev[2 * g.used + 1], st);
     g.kind[g.used] = kind;
     g.work[g.used] = work;
+    g.per_row[g.used] = work_per_row;
     ++g.used;
 }
 
@@ -66,6 +78,11 @@ int prof_read(int kind, double *ms, double *work, int *launches)
         if (hipEventElapsedTime(&t, g.ev[2 * i], g.ev[2 * i + 1]) != hipSuccess) return SL_EHIP;
         tot += t;
         w += g.work[i];
+        if (g.per_row[i] != 0.0) {
+            int rows = 0;
+            if (hipMemcpy(&rows, g.rows + i, sizeof(rows), hipMemcpyDeviceToHost) != hipSuccess) return SL_EHIP;
+            w += g.per_row[i] * rows;
+        }
         ++n;
     }
     if (ms) *ms = tot;

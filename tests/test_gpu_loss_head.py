@@ -129,6 +129,26 @@ def test_loss_head_nan_stays_in_its_row():
     assert np.isnan(dy2[150]).all()
 
 
+# The measurement hook counts the head's products and LayerNorms over the labeled rows: logits on the kernels for few tiles and on those for
+# many, two chunks of rows, no labeled row at all.
+@pytest.mark.parametrize("T,d,V,n_labeled", [(300, 128, 1003, 170), (4000, 256, 8001, 2500), (16700, 64, 520, 16500), (300, 64, 520, 0)])
+def test_loss_head_is_in_the_launch_profile(T, d, V, n_labeled):
+    inp = synth.make_loss_head_inputs(1, T, d, vocab=V, seed=synth.BASE_SEED + 81)
+    inp["labels"][:] = -1
+    inp["labels"][:n_labeled] = np.arange(n_labeled) % V
+    chunks, Vp = -(-T // 16384), -(-V // 64) * 64
+    B.slora_prof_enable(1 << B.PROF_GEMM | 1 << B.PROF_LN_FWD | 1 << B.PROF_LN_BWD)
+    try:
+        gpu_loss_head(inp, d, V)
+        got = {k: B.slora_prof_read_kind(k) for k in (B.PROF_GEMM, B.PROF_LN_FWD, B.PROF_LN_BWD)}
+    finally:
+        B.slora_prof_enable(0)
+    for k, n, work in ((B.PROF_GEMM, 2, 2 * 2.0 * n_labeled * Vp * d), (B.PROF_LN_FWD, 1, 4.0 * n_labeled * d),
+                       (B.PROF_LN_BWD, 1, 4.0 * (T + n_labeled) * d)):
+        ms, w, launches = got[k]
+        assert launches == n * chunks and w == work and ms > 0, (k, got[k], work)
+
+
 def test_loss_head_workload3_sampled_rows():
     """Workload 3's shape: 64 x 512 tokens, d = 1024, GPT-2's vocabulary of 50257.  The oracle runs on a
     sample of rows; a row's loss term does not depend on the other rows and its gradient only through the
