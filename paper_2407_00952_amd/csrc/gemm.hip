@@ -673,8 +673,8 @@ static int launch_gemm_counted(const GemmArgs &a, int epi, hipStream_t st)
     const int tiles = ((a.M + bm - 1) / bm) * ((a.N + BN - 1) / BN);
     // shares are chosen where the rows are counted, so that launch always has a block for every CU
     const dim3 grid(epi == EPI_PARTIAL ? 256 : std::min((tiles + 7) / 8 * 8, 256)), block(NTHR4);
+    // (up to 128 rows of the widest vocabulary, 512 tiles of 128 x 128, plan_gemm_tile has the plain store on small tiles)
     if (epi == EPI_STORE && bm == 256) hipLaunchKernelGGL((gemm_counted4<EPI_STORE, 8>), grid, block, 0, st, a);
-    else if (epi == EPI_STORE) hipLaunchKernelGGL((gemm_counted4<EPI_STORE, 4>), grid, block, 0, st, a);
     else if (epi == EPI_PARTIAL && bm == 256) hipLaunchKernelGGL((gemm_counted4<EPI_PARTIAL, 8>), grid, block, 0, st, a);
     else if (epi == EPI_PARTIAL) hipLaunchKernelGGL((gemm_counted4<EPI_PARTIAL, 4>), grid, block, 0, st, a);
     else return SL_EINVAL;
