@@ -160,7 +160,7 @@ int launch_adamw(float *p, const float *g, float *m, float *v, size_t n, float b
                  float a, float c, float o1, float o2, hipStream_t st);
 // what a single-layer call does before its product, in one launch (layer_front_kernel)
 struct LayerFront {
-    static constexpr int kMaxCopies = 3;
+    static constexpr int kMaxCopies = 2;
     struct Copy {                    // fp32 [rows, cols] (optionally transposed) -> bf16 [drows, dcols], zero padded
         const float *src; bf16 *dst;
         int rows, cols, transpose, drows, dcols;

@@ -170,8 +170,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float *__restrict__ h
     if (lane == 0) { stats[2 * row] = mu; stats[2 * row + 1] = rho; }
 }
 
-// DRES16: the residual gradient arrives as bf16 (last block: the caller's dY) instead of fp32;
-// with DRES16 false a null `dres` means there is no residual gradient to add.
+// DRES16: the residual gradient arrives as bf16 (last block: the caller's dY) instead of fp32.
 // SCATTER 1: the bf16 output goes to the K client buffers; 2: it goes there as MXFP8 (the value is rounded
 // to bf16 first, then converted block by block: 8 neighbouring lanes hold one block of 32 columns).
 template <bool DRES16, int SCATTER, int NC>
@@ -193,8 +192,7 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const bf16 *__restrict__ du
             const bf16x4 t = *(const bf16x4 *)((const bf16 *)dres + (size_t)row * d + col);
             return make_float4(bf2f(t[0]), bf2f(t[1]), bf2f(t[2]), bf2f(t[3]));
         }
-        if (dres != nullptr) return *(const float4 *)((const float *)dres + (size_t)row * d + col);
-        return make_float4(0.f, 0.f, 0.f, 0.f);          // no residual branch (the final LayerNorm)
+        return *(const float4 *)((const float *)dres + (size_t)row * d + col);
     };
     auto take = [&](int c, bf16x4 t, bf16x4 gm, float4 hv) {
         const float hh[4] = {hv.x, hv.y, hv.z, hv.w};
@@ -342,34 +340,34 @@ int launch_ln_bwd(const bf16 *du, const float *h, const float *stats, const bf16
 {
     if (T <= 0 || d <= 0 || (d % 4) || d > MAXC * 256) return SL_EINVAL;
     if (o_codes && (!o_scales || (d % 32) || scatter)) return SL_EINVAL;
+    // one residual gradient; only the first block scatters, and its residual gradient is fp32
+    if (!dres_bf16 == !dres_f32 || (scatter && dres_bf16) || (scatter && scatter->mx && (d % 32))) return SL_EINVAL;
     dim3 grid((T + 3) / 4), block(256);
     ClientTable tab;
     tab.K = 0;
     tab.mx = 0;
     if (scatter) tab = *scatter;
     // algorithmic bytes per element: du (bf16), h (fp32), the residual gradient, and each output written
-    const double el_bytes = 2 + 4 + (dres_bf16 ? 2 : dres_f32 ? 4 : 0) + (out_f32 ? 4 : 0) + (out_bf16 ? 2 : 0) +
+    const double el_bytes = 2 + 4 + (dres_bf16 ? 2 : 4) + (out_f32 ? 4 : 0) + (out_bf16 ? 2 : 0) +
                             (scatter ? (scatter->mx ? 1 : 2) : 0) + (o_codes ? 1 : 0);
     const bool rec = prof_begin(PK_LN_BWD, st);
-    if (scatter && scatter->mx && ((d % 32) || dres_bf16)) return SL_EINVAL;
     const void *dres = dres_bf16 ? (const void *)dres_bf16 : (const void *)dres_f32;
 #define LN_BWD(D16, SCATTER, NC) hipLaunchKernelGGL((ln_bwd_kernel<D16, SCATTER, NC>), grid, block, 0, st, du, h, stats, \
                                                     gamma, dres, out_f32, out_bf16, tab, T, d, o_codes, o_scales)
 #define LN_CALL_F2(NC) LN_BWD(false, 2, NC)
-#define LN_CALL_B1(NC) LN_BWD(true, 1, NC)
 #define LN_CALL_B0(NC) LN_BWD(true, 0, NC)
 #define LN_CALL_F1(NC) LN_BWD(false, 1, NC)
 #define LN_CALL_F0(NC) LN_BWD(false, 0, NC)
     if (scatter && scatter->mx) {
-        // compressed activation gradients: only the first server block scatters, and its residual gradient is fp32
-        LN_WIDTHS(d, LN_CALL_F2)
+        LN_WIDTHS(d, LN_CALL_F2)                         // compressed activation gradients
+    } else if (scatter) {
+        LN_WIDTHS(d, LN_CALL_F1)
     } else if (dres_bf16) {
-        if (scatter) LN_WIDTHS(d, LN_CALL_B1) else LN_WIDTHS(d, LN_CALL_B0)
+        LN_WIDTHS(d, LN_CALL_B0)
     } else {
-        if (scatter) LN_WIDTHS(d, LN_CALL_F1) else LN_WIDTHS(d, LN_CALL_F0)
+        LN_WIDTHS(d, LN_CALL_F0)
     }
 #undef LN_CALL_F2
-#undef LN_CALL_B1
 #undef LN_CALL_B0
 #undef LN_CALL_F1
 #undef LN_CALL_F0
