@@ -80,7 +80,6 @@ __global__ __launch_bounds__(512) void f32_project_kernel(ProjJobs jobs, int T, 
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     const int steps = (K + 15) >> 4, per = (steps + 7) >> 3;
     const int s0 = wave * per, s1 = min(s0 + per, steps);
-#pragma unroll 4
     for (int s = s0; s < s1; ++s) {
         const int k = s * 16 + 4 * g;
         const float4 a = load4_lim<VEC>(xr, k, K);
@@ -331,7 +330,6 @@ __global__ __launch_bounds__(512) void f32_gemm_direct_kernel(GemmF32 a)
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     const int steps = (a.K + 15) >> 4, per = (steps + 7) >> 3;
     const int s0 = wave * per, s1 = min(s0 + per, steps);
-#pragma unroll 4
     for (int s = s0; s < s1; ++s) {
         const int k = s * 16 + 4 * g;
         const float4 x = load4_lim<VEC>(xr, k, a.K);
