@@ -2,7 +2,7 @@
 sources with the library's own flags; nothing runs on a GPU).
 
 The 4-wave GEMM kernel writes its MFMAs as inline assembly, so the compiler no longer sees their data
-hazards, and both GEMM sources write the M0 register behind the compiler's back for their asynchronous
+hazards, and the GEMM sources write the M0 register behind the compiler's back for their asynchronous
 global -> LDS copies.  What the source guarantees by construction is checked here in the instruction stream
 of every instantiation, so that a compiler upgrade or a changed flag that breaks an assumption fails the
 test suite instead of corrupting results:
@@ -16,7 +16,7 @@ test suite instead of corrupting results:
      longest, 16-pass, matrix instruction; the 16x16x32 bf16 one needs fewer) pass before the first
      instruction other than an MFMA that reads or writes an accumulation register;
   4. M0 is written only by the copy sequence (s_mov_b32 m0 / s_nop 0 / global_load_lds_*) and read by
-     nothing else, in gemm.hip and mx.hip;
+     nothing else, in gemm.hip, gemm_tile.hip and mx.hip;
   5. no vector memory instruction reads a scalar register that a vector instruction (v_readlane,
      v_readfirstlane, a compare with a scalar destination) wrote fewer than 5 wait states earlier.  The
      compiler keeps that distance for its own instructions but does not look into inline assembly, and the
@@ -94,6 +94,13 @@ def _agprs(ins):
 @pytest.fixture(scope="module")
 def gemm_asm():
     return _assembly("gemm.hip")
+
+
+@pytest.fixture(scope="module")
+def tile_asm():
+    text = _assembly("gemm_tile.hip")
+    assert sum("gemm_tile_kernel" in n for n in _functions(text)) == 33     # 11 epilogues and ranks x three tile forms
+    return text
 
 
 def test_four_wave_gemm_mfma_hazards(gemm_asm):
@@ -187,8 +194,9 @@ def _check_m0(text, what):
                     (what, name, code[max(i - 2, 0):i + 1])
 
 
-def test_m0_is_only_used_by_the_async_copies(gemm_asm):
+def test_m0_is_only_used_by_the_async_copies(gemm_asm, tile_asm):
     _check_m0(gemm_asm, "gemm.hip")
+    _check_m0(tile_asm, "gemm_tile.hip")
     _check_m0(_assembly("mx.hip"), "mx.hip")
 
 
@@ -231,8 +239,9 @@ def _check_valu_sgpr_to_vmem(text, what):
                 j -= 1
 
 
-def test_vector_written_scalars_are_settled_before_vector_memory_reads_them(gemm_asm):
+def test_vector_written_scalars_are_settled_before_vector_memory_reads_them(gemm_asm, tile_asm):
     _check_valu_sgpr_to_vmem(gemm_asm, "gemm.hip")
+    _check_valu_sgpr_to_vmem(tile_asm, "gemm_tile.hip")
     _check_valu_sgpr_to_vmem(_assembly("mx.hip"), "mx.hip")
     _check_valu_sgpr_to_vmem(_assembly("attention.hip"), "attention.hip")
 
