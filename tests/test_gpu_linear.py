@@ -160,10 +160,15 @@ def test_fp32_zero_B_is_bitwise_base():
     (64, 128, 128, 1, False),
     (512, 768, 768, 2, True),        # the remaining ranks of the paper's sweep r in {1, 2, 4, 8} (Sec. IV)
     (512, 768, 2304, 8, False),
-    # 34 chunks of 512 tokens, the last one ragged: each wavefront of the adapter-gradient reduction sums
-    # nine chunks (the body with eight loads in flight plus its tail), the last wavefront seven (tail only)
+    # 133 chunks of 128 tokens, the last one ragged: 34 for each wavefront of the adapter-gradient reduction, 31 for the
+    # last (the body with eight loads in flight, and its tail)
     (16960, 256, 64, 4, True),
     (16960, 64, 256, 16, False),
+    # both sides of tokens x the wider side = 2^24, where chunks of 128 tokens become chunks of 512 (for both gradients): 128 short
+    # chunks, the last one ragged; 33 long ones, the last of 16 tokens, nine for each wavefront and six for the last (tail only)
+    (16383, 1024, 64, 4, False),
+    (16400, 1024, 64, 4, True),
+    (16400, 64, 1024, 16, False),
     (700, 19840, 640, 4, False),     # scratch with 512-token partial sums only, the last one ragged
 ])
 def test_bf16_layer(T, n_in, n_out, r, bias):

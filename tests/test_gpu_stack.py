@@ -289,11 +289,11 @@ def test_widths_of_whole_chunks(d):
     srv.close()
 
 
-# Token counts at which a wavefront of the adapter-gradient reduction sums eight or more 512-token chunks
-# (T >= 14337: the path with eight loads in flight, which workloads 3-5 take), on a stack narrow enough for
-# the oracle to run the whole batch: 33 sequences x 512 tokens = 33 chunks, i.e. 9 + 9 + 9 + 6 per wavefront
-# (the eight-wide body, its tail, and a wavefront that only runs the tail), all six projections adapted (so
-# the paired pass over u for two of the q/k/v adapters runs too), at the smallest and the largest padded rank.
+# Token counts at which a wavefront of the adapter-gradient reduction sums many chunks (the path with eight loads in
+# flight, which workloads 3-5 take), on a stack narrow enough for the oracle to run the whole batch: 33 sequences x 512
+# tokens of at most 256 columns = 132 chunks of 128 tokens, 33 for each wavefront (the eight-wide body and its tail),
+# all six projections adapted (so the paired pass over u for two of the q/k/v adapters runs too), at the smallest and
+# the largest padded rank.
 @pytest.mark.parametrize("r", [4, 16])
 def test_adapter_gradients_of_a_long_batch(r):
     cfg = synth.tiny_config(d_model=128, n_head=2, d_ff=256, n_blocks=2, lora_r=r, lora_proj=synth.PROJ_NAMES,
@@ -307,6 +307,18 @@ def test_adapter_gradients_of_a_long_batch(r):
     inp = _boost_B(synth.make_stack_inputs(cfg), cfg, target=16.0)
     srv, Y, dX, grads = gpu_round(cfg, inp)
     compare_round(cfg, inp, Y, dX, grads, label="long-batch-r%d" % r)
+    srv.close()
+
+
+def test_adapter_gradients_in_long_chunks():
+    """Tokens x width of 2^24 or more, where the partial sums go over 512 tokens instead of 128: 1025 sequences x 64 tokens x
+    256 columns = 129 chunks, the last one of 64 tokens; all six projections adapted, paired pass included."""
+    cfg = synth.tiny_config(d_model=256, n_head=4, d_ff=64, n_blocks=1, lora_r=5, lora_proj=synth.PROJ_NAMES,
+                            n_clients=5, batch=205, seq_len=64, seed=synth.BASE_SEED + 150)
+    say("long chunks:", cfg)
+    inp = _boost_B(synth.make_stack_inputs(cfg), cfg, target=16.0)
+    srv, Y, dX, grads = gpu_round(cfg, inp)
+    compare_round(cfg, inp, Y, dX, grads, label="long-chunks")
     srv.close()
 
 
