@@ -180,9 +180,9 @@ def recorded_gemm_traffic():
     csrc = os.path.join(ROOT, "paper_2407_00952_amd", "csrc")
     try:
         text = open(path).read()
-        # the kernel's source: main loop and launcher, and the epilogue it shares with the fp8 kernel
+        # the kernel's source: main loop and launcher, the copies, and the epilogue it shares with the fp8 kernel
         h = hashlib.sha256()
-        for name in ("gemm.hip", "gemm_epilogue.h"):
+        for name in ("gemm.hip", "gemm_copy.h", "gemm_epilogue.h"):
             h.update(open(os.path.join(csrc, name), "rb").read())
         sha = h.hexdigest()
         m_sha = re.search(r"gemm_source_sha256:\s*([0-9a-f]{64})", text)

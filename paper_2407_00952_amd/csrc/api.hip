@@ -728,7 +728,7 @@ static int stack_bwd(slora_ctx *c, const void *dy, const ClientTable *tabp, hipS
             }
             MxOperands mxo;
             set_mx(c, l, MXW_OT, a, mxo, 1);
-            // where this product has no adapter branch (the 4-wave kernel, or the MXFP8 one) and the fused attention
+            // where this product has no adapter branch and the fused attention
             // backward follows, the epilogue also forms delta = rowsum(dO * O) per head, [T, H]
             gemm_delta = !ad && attn_bwd_takes_delta(c->S);
             if (gemm_delta) {

@@ -67,7 +67,7 @@ struct EmbedSrc {
 
 // ---- GEMM ---------------------------------------------------------------------------------
 // EPI_STORE_DELTA: plain store of a [M, 64 H] tensor that is the gradient of an attention output, plus
-// delta[row][head] = sum over the head's 64 columns of out * (dl_o + dl_lo) (4-wave kernel only)
+// delta[row][head] = sum over the head's 64 columns of out * (dl_o + dl_lo); no rank-space branch
 // EPI_PARTIAL: fp32 sums of a share of the contraction (products over counted rows only)
 enum { EPI_STORE = 0, EPI_RESID = 1, EPI_GELU = 2, EPI_DGELU = 3, EPI_STORE_DELTA = 4, EPI_PARTIAL = 5 };
 

@@ -6,7 +6,8 @@
 //
 // Only labeled tokens have a loss and a gradient (in prompt-completion records a quarter to a half of the tokens are
 // prompt), so everything runs on them alone: the device lists the labeled rows first and the others behind them, and the
-// kernels take the number of rows from memory; nothing synchronises the stream.  Per chunk of at most 16384 listed rows
+// kernels take the number of rows from memory; nothing synchronises the stream.  (Logits that fit a few small tiles are
+// formed for the chunk's other rows too, from whatever u holds there; nobody reads them.)  Per chunk of at most 16384 listed rows
 // (HBM is large: the chunk's logits are materialised once as bf16, 1.65 GB, instead of being recomputed):
 //   u      = LN(y)                                 wave-per-row LayerNorm of the listed rows
 //   logits = u . WvP^T            [rows, Vp]       bf16 MFMA GEMM (Vp = V rounded up to 64, zero rows)
