@@ -908,7 +908,7 @@ int slora_adamw(size_t n, float *p, const float *g, float *m, float *v, float lr
 
 // ---- single layer -----------------------------------------------------------------------------
 namespace {
-struct LinWs { size_t A16, B16, B16T, A16T, zs, ps, WT, part_a, part_b, cnt, split, total; bool can_split, long_chunks; };
+struct LinWs { size_t A16, B16, B16T, A16T, zs, ps, WT, part_a, part_b, total; bool share_fwd, share_bwd, long_chunks; };
 LinWs lin_ws(int T, int n_in, int n_out)
 {
     LinWs w;
@@ -933,33 +933,27 @@ LinWs lin_ws(int T, int n_in, int n_out)
         return off <= own;
     };
     if (!gradients(false) && !gradients(true)) gradients(false);
-    // Scratch for products that share their contraction, up to the tokens at which one of the layer's two does, unless it
-    // alone would put the layer beyond what the library's own array holds.  The total never falls as T grows, so that
-    // a workspace taken for the most tokens serves fewer.
-    const int t_split = std::max(gemm_split_rows(n_out, n_in), gemm_split_rows(n_in, n_out));
-    w.can_split = false;
-    w.cnt = w.split = 0;
+    // A product that shares its contraction has counters and partial sums where the call has no other use for the memory: the
+    // forward behind its two operand copies, the backward in place of the gradients' partial sums, which come later.  It does
+    // not where that alone would put the layer beyond the library's own array.  The total never falls as T grows, so
+    // that a workspace taken for the most tokens serves fewer.
     w.total = w.long_chunks ? own : off;
-    if (T <= t_split) {
-        const size_t bytes = std::max(gemm_split_bytes(T, n_out, n_in, SL_RP), gemm_split_bytes(T, n_in, n_out, SL_RP));
-        const size_t end = off + al256(gemm_split_counter_bytes()) + al256(bytes);
-        w.can_split = bytes > 0 && (end <= own || off > own);
-        if (w.can_split) {
-            w.cnt = take(gemm_split_counter_bytes());
-            w.split = take(bytes);
-        }
-        w.total = end <= own || off > own ? std::max(w.total, end) : own;
-    } else if (t_split > 0) {
-        w.total = std::max(w.total, lin_ws(t_split, n_in, n_out).total);
-    }
+    const size_t most = off <= own ? own : ~(size_t)0;
+    const int t_fwd = gemm_split_rows(n_out, n_in), t_bwd = gemm_split_rows(n_in, n_out);
+    auto end_of = [&](size_t begin, size_t bytes) { return bytes ? begin + al256(gemm_split_counter_bytes()) + al256(bytes) : 0; };
+    const int t = std::min(T, t_bwd);
+    const size_t fwd = end_of(w.B16T, gemm_split_bytes(T, n_out, n_in, SL_RP));
+    const size_t bwd = end_of(at - 2 * (al256(2 * (size_t)T * 16) - al256(2 * (size_t)t * 16)), gemm_split_bytes(T, n_in, n_out, SL_RP));
+    w.share_fwd = T <= t_fwd && fwd && fwd <= most;
+    w.share_bwd = T <= t_bwd && bwd && bwd <= most;
+    w.total = std::max(w.total, std::max(std::min(fwd, most), std::min(bwd, most)));
     return w;
 }
-// the product of a layer call, with its split scratch; the counters are zeroed by the same call's front kernel
-void lin_split(const LinWs &w, char *base, GemmArgs &a, LayerFront &f)
+// split scratch of the product of a layer call; its counters are zeroed by the same call's front kernel
+void lin_split(char *p, GemmArgs &a, LayerFront &f)
 {
-    if (!w.can_split) return;
-    a.split_part = (float *)(base + w.split);
-    a.split_cnt = (unsigned *)(base + w.cnt);
+    a.split_cnt = (unsigned *)p;
+    a.split_part = (float *)(p + al256(gemm_split_counter_bytes()));
     f.zero = a.split_cnt;
     f.n_zero = (int)(gemm_split_counter_bytes() / 4);
 }
@@ -1005,7 +999,7 @@ int slora_lora_linear_fwd(int dtype, int T, int n_in, int n_out, int r, float al
     GemmArgs a = gemm_base((const bf16 *)x, n_in, (const bf16 *)W, T, n_out, n_in, (const bf16 *)bias, s);
     a.zmat[0] = (bf16 *)(base + w.A16); a.tmat[0] = (bf16 *)(base + w.B16);
     a.out0 = y;
-    lin_split(w, base, a, f);
+    if (w.share_fwd) lin_split(base + w.B16T, a, f);
     if ((rc = launch_layer_front(f, st))) return rc;
     return launch_gemm(a, EPI_STORE, 16, st);
 }
@@ -1054,7 +1048,7 @@ int slora_lora_linear_bwd(int dtype, int T, int n_in, int n_out, int r, float al
     GemmArgs a = gemm_base((const bf16 *)dy, n_out, (bf16 *)(base + w.WT), T, n_in, n_out, nullptr, s);
     a.zmat[0] = (bf16 *)(base + w.B16T); a.tmat[0] = (bf16 *)(base + w.A16T); a.zspill[0] = (bf16 *)(base + w.ps);
     a.out0 = dx;
-    lin_split(w, base, a, f);
+    if (w.share_bwd) lin_split(base + w.part_a, a, f);
     if ((rc = launch_layer_front(f, st))) return rc;
     if ((rc = launch_gemm(a, EPI_STORE, 16, st))) return rc;
     const LoraGradDesc jobs[2] = {

@@ -175,23 +175,26 @@ def test_layer_workspace_for_the_most_tokens_serves_fewer(n_in, n_out):
         assert n[0] > 0 and all(a <= b for a, b in zip(n, n[1:]))
 
 
-# A layer asks for room for shared contractions only where one of its products has it: 18 slabs of 64 or more, and 128 tiles
-# of 64 x 64 or fewer.
-@pytest.mark.parametrize("T,n_in,n_out,shared", [
-    (1024, 768, 768, 0),                    # 12 slabs both ways
-    (1, 1088, 64, 0),                       # 17 slabs
-    (1, 1152, 64, 2),                       # 18: one tile, two shares
-    (130, 128, 2432, 6 * 4),                # the input gradient: six tiles, four shares
-    (2048, 2048, 256, 128 * 2),             # 128 tiles forward, two shares
-    (40000, 4096, 1024, 0),                 # far more tiles at this count, and more scratch than fewer tokens need
+# A layer asks for room for shared contractions only where one of its products has it (18 slabs of 64 or more, and 128 tiles of
+# 64 x 64 or fewer) and the call has none to spare: the forward's lies behind the operand copies it makes, the backward's where the
+# gradients' partial sums come to lie afterwards.
+@pytest.mark.parametrize("T,n_in,n_out,fwd,bwd", [
+    (1024, 768, 768, 0, 0),                 # 12 slabs both ways
+    (1, 1088, 64, 0, 0),                    # 17 slabs
+    (1, 1152, 64, 2, 0),                    # 18: one tile, two shares
+    (130, 128, 2432, 0, 6 * 4),             # the input gradient: six tiles, four shares
+    (2048, 2048, 256, 128 * 2, 0),          # 128 tiles forward, two shares
+    (64, 64, 8192, 0, 4),                   # one tile, four shares
+    (40000, 4096, 1024, 128 * 2, 0),        # far more tiles at this count, and more scratch than fewer tokens need
 ])
-def test_layer_workspace_holds_no_unused_split_scratch(T, n_in, n_out, shared):
+def test_layer_workspace_holds_no_unused_split_scratch(T, n_in, n_out, fwd, bwd):
     al = lambda n: -(-n // 256) * 256
     few = -(-min(T, (2 ** 24 - 1) // max(n_in, n_out)) // 128)
-    base = (al(32 * n_in) + al(64 * n_out) + al(32 * n_out) + al(64 * n_in) + 2 * al(32 * T) + al(2 * n_in * n_out)
-            + max(-(-T // 512), few) * 64 * (n_in + n_out))
-    split = al(shared * 64 * (64 + 16) * 4) + 512 if shared else 0
-    assert B.slora_lora_linear_ws_bytes(B.DTYPE_BF16, T, n_in, n_out, 4) == base + split
+    copies = al(32 * n_in) + al(64 * n_out)
+    grads = copies + al(32 * n_out) + al(64 * n_in) + 2 * al(32 * T) + al(2 * n_in * n_out)
+    need = [grads + max(-(-T // 512), few) * 64 * (n_in + n_out)]
+    need += [at + 512 + n * 64 * (64 + 16) * 4 for at, n in ((copies, fwd), (grads, bwd)) if n]
+    assert B.slora_lora_linear_ws_bytes(B.DTYPE_BF16, T, n_in, n_out, 4) == max(need)
 
 
 # Layers that the library's own array holds with 512-token partial sums and not with 128-token ones: a wide input into a narrow output,
