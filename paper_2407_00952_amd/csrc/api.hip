@@ -922,8 +922,8 @@ LinWs lin_ws(int T, int n_in, int n_out)
     w.ps = take(2 * (size_t)T * 16);
     w.WT = take(2 * (size_t)n_in * n_out);
     // Short chunks of the adapter gradients' partial sums take up to four times the scratch of long ones.  A layer that the
-    // library's own array holds only with long ones takes those (a wide input into a narrow output: 273 tokens, 61888 -> 128
-    // need 39 MiB, with long chunks 27).
+    // library's own array holds only with long ones takes those (a wide input into a narrow output: 311 tokens, 54656 -> 192
+    // need 35.1 MiB, with long chunks 28.4).
     const size_t own = (size_t)SLORA_NOALLOC_SCRATCH_BYTES, at = off;
     auto gradients = [&](bool long_chunks) {
         off = at;
