@@ -115,10 +115,12 @@ struct GemmArgs {
 int launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st);
 // rows of the tiles (256 columns) of a product over counted rows: 128 only where no more can come
 inline int gemm_counted_rows(int max_rows) { return max_rows <= 128 ? 128 : 256; }
-// the product on 64 x 64 or 128 x 128 tiles (gemm_tile.hip), for launches with too few 256-row tiles
-struct TilePlan { int tile, waves, splits; };            // tile 0: the 256-row kernels
-TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int nz, bool can_split);
+// the tile of a product's kernel and over how many blocks a tile's contraction is shared: 128 x 256 and 256 x 256 are those
+// of gemm.hip, 128 columns and more than 64 rows those of gemm_wide.hip, the others those of gemm_tile.hip
+struct TilePlan { int tm, tn, splits; };
+TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int epi, int nz, bool can_split, bool whole);
 int launch_gemm_tile(const GemmArgs &a, int epi, int nz, const TilePlan &p, hipStream_t st);
+int launch_gemm_wide(const GemmArgs &a, int epi, int nz, const TilePlan &p, hipStream_t st);
 int gemm_split_rows(int N, int K);                       // the most rows at which a launch may do so (0: none does)
 size_t gemm_split_bytes(int M, int N, int K, int nz);    // enough for M rows or fewer
 size_t gemm_split_counter_bytes();

@@ -576,17 +576,11 @@ __global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 }
 
 template <int EPI>
-int launch_t4(const GemmArgs &a, hipStream_t st)
+int launch_t4(const GemmArgs &a, int rows, hipStream_t st)
 {
-    const int tiles_n = ((a.seg_n + BN - 1) / BN) * a.nseg;
-    const int nb8 = ((a.M + 255) / 256) * tiles_n, nb4 = ((a.M + 127) / 128) * tiles_n;
-    // 128-row tiles where they fill the chip better: rounds of 256 tiles, a 128-row tile costing a good half of
-    // a 256-row one (e.g. the d x d products of a 10 240-token batch at d = 768: 120 tiles of 256 rows would leave
-    // half of the CUs idle); small problems stay on the 256-row tile, whichever way they fit
-    const bool half = a.M >= 1024 && 0.55 * ((nb4 + 255) / 256) < 1.0 * ((nb8 + 255) / 256);
-    const int nb = half ? nb4 : nb8;
+    const int nb = ((a.M + rows - 1) / rows) * ((a.seg_n + BN - 1) / BN) * a.nseg;
     const int grid = std::min(((nb + 7) / 8) * 8, 256);    // one block per CU, each walks its tiles
-    if (half) hipLaunchKernelGGL((gemm_kernel4<EPI, 4>), dim3(grid), dim3(NTHR4), 0, st, a);
+    if (rows == 128) hipLaunchKernelGGL((gemm_kernel4<EPI, 4>), dim3(grid), dim3(NTHR4), 0, st, a);
     else hipLaunchKernelGGL((gemm_kernel4<EPI, 8>), dim3(grid), dim3(NTHR4), 0, st, a);
     SL_CHECK_LAUNCH("gemm");
     return 0;
@@ -605,10 +599,10 @@ int launch_t(const GemmArgs &a, hipStream_t st)
 }
 
 template <int EPI>
-int launch_e(const GemmArgs &a, int nz, hipStream_t st)
+int launch_e(const GemmArgs &a, int nz, int rows, hipStream_t st)
 {
     switch (nz) {
-    case 0: return launch_t4<EPI>(a, st);                // no rank-space branch: the 4-wave kernel
+    case 0: return launch_t4<EPI>(a, rows, st);          // no rank-space branch: the 4-wave kernel
     case 16: return launch_t<EPI, 16>(a, st);
     case 32: return launch_t<EPI, 32>(a, st);
     case 48: return launch_t<EPI, 48>(a, st);
@@ -620,13 +614,14 @@ int launch_e(const GemmArgs &a, int nz, hipStream_t st)
 
 static int launch_gemm_inner(const GemmArgs &a, int epi, int nz, hipStream_t st);
 static int launch_gemm_counted(const GemmArgs &a, int epi, hipStream_t st);
+static bool counted_on_small_tiles(const GemmArgs &a);
 
 int launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st)
 {
     const bool rec = prof_begin(PK_GEMM, st, a.rows ? &a.rows->rows : nullptr);
     GemmArgs b = a;
     b.clk = prof_clock_words(rec);
-    const int rc = epi == EPI_PARTIAL || (a.rows && !plan_gemm_tile(a.M, a.N, 1, a.K, 0, false).tile)
+    const int rc = epi == EPI_PARTIAL || (a.rows && !counted_on_small_tiles(a))
                        ? launch_gemm_counted(b, epi, st)
                        : launch_gemm_inner(b, epi, nz, st);
     // algorithmic work of this launch: the frozen product only (the rank-r branch adds < 1 % and is left
@@ -648,16 +643,26 @@ static int launch_gemm_inner(const GemmArgs &a, int epi, int nz, hipStream_t st)
     if (nz > 0 && (a.K2 != nz || (a.ldt % 8) || a.ldt < (nz + 31) / 32 * 32 || (a.ldz % 8))) return SL_EINVAL;
     if (epi == EPI_STORE_DELTA && (nz != 0 || !a.dl_o || !a.dl_lo || !a.dl_out || !a.out0 || (a.N % 64) || a.nseg != 1))
         return SL_EINVAL;                                // no rank-space branch, whole heads of 64 columns
-    const TilePlan plan = plan_gemm_tile(a.M, a.seg_n, a.nseg, a.K, nz, a.split_part != nullptr && a.split_cnt != nullptr);
-    if (plan.tile) return launch_gemm_tile(a, epi, nz, plan, st);
+    // (a product over counted rows comes here only to run on the smaller tiles)
+    const TilePlan plan = plan_gemm_tile(a.M, a.seg_n, a.nseg, a.K, epi, nz, a.split_part != nullptr && a.split_cnt != nullptr,
+                                         a.rows == nullptr);
+    if (plan.tn < 256) return launch_gemm_tile(a, epi, nz, plan, st);
     switch (epi) {
-    case EPI_STORE: return launch_e<EPI_STORE>(a, nz, st);
-    case EPI_RESID: return launch_e<EPI_RESID>(a, nz, st);
-    case EPI_GELU: return launch_e<EPI_GELU>(a, nz, st);
-    case EPI_DGELU: return launch_e<EPI_DGELU>(a, nz, st);
-    case EPI_STORE_DELTA: return launch_t4<EPI_STORE_DELTA>(a, st);
+    case EPI_STORE: return launch_e<EPI_STORE>(a, nz, plan.tm, st);
+    case EPI_RESID: return launch_e<EPI_RESID>(a, nz, plan.tm, st);
+    case EPI_GELU: return launch_e<EPI_GELU>(a, nz, plan.tm, st);
+    case EPI_DGELU: return launch_e<EPI_DGELU>(a, nz, plan.tm, st);
+    case EPI_STORE_DELTA: return launch_t4<EPI_STORE_DELTA>(a, plan.tm, st);
     }
     return SL_EINVAL;
+}
+
+// Whether a plain-store product over counted rows runs on the smaller tiles, which compute all M rows: where one round of
+// them does.  (Larger ones would spend rounds on rows that nobody wants: 40 % of a loss head's are prompt tokens.)
+static bool counted_on_small_tiles(const GemmArgs &a)
+{
+    auto tiles = [&](int t) { return (long)((a.M + t - 1) / t) * ((a.N + t - 1) / t); };
+    return a.M <= 128 || tiles(64) <= 512 || tiles(128) <= 256;
 }
 
 // A product over the rows that a kernel before it counted (a.rows; a.M is their upper bound), without rank-space branch.
@@ -673,7 +678,7 @@ static int launch_gemm_counted(const GemmArgs &a, int epi, hipStream_t st)
     const int tiles = ((a.M + bm - 1) / bm) * ((a.N + BN - 1) / BN);
     // shares are chosen where the rows are counted, so that launch always has a block for every CU
     const dim3 grid(epi == EPI_PARTIAL ? 256 : std::min((tiles + 7) / 8 * 8, 256)), block(NTHR4);
-    // (up to 128 rows of the widest vocabulary, 512 tiles of 128 x 128, plan_gemm_tile has the plain store on small tiles)
+    // (up to 128 rows the plain store runs on the smaller tiles)
     if (epi == EPI_STORE && bm == 256) hipLaunchKernelGGL((gemm_counted4<EPI_STORE, 8>), grid, block, 0, st, a);
     else if (epi == EPI_PARTIAL && bm == 256) hipLaunchKernelGGL((gemm_counted4<EPI_PARTIAL, 8>), grid, block, 0, st, a);
     else if (epi == EPI_PARTIAL) hipLaunchKernelGGL((gemm_counted4<EPI_PARTIAL, 4>), grid, block, 0, st, a);

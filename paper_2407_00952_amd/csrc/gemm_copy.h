@@ -16,6 +16,14 @@ __device__ __forceinline__ void glds_soff(const void *sbase, unsigned voff, unsi
                  : "s"(lds), "v"(voff), "s"(sbase)
                  : "memory");
 }
+// the same with all lanes (mask -1) or none (mask 0: moves nothing, and still counts); all 64 are enabled around it
+__device__ __forceinline__ void glds_soff_if(const void *sbase, unsigned voff, unsigned lds, int mask)
+{
+    asm volatile("s_mov_b32 exec_lo, %3\n\ts_mov_b32 exec_hi, %3\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
+                 :
+                 : "s"(lds), "v"(voff), "s"(sbase), "s"(mask)
+                 : "memory");
+}
 __device__ __forceinline__ unsigned lds_addr(const void *p)
 {
     return (unsigned)(unsigned long long)(const __attribute__((address_space(3))) char *)p;

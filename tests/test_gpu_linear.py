@@ -241,6 +241,45 @@ def test_frozen_linear_dispatch_edges(T, n_in, n_out, bias):
     assert e <= 2.0 ** -8                # as above: one rounding to bf16
 
 
+# The tile forms of the bf16 products, each with ragged rows and columns and an odd number of slabs (forms with two slabs to
+# a barrier end on a single one).
+@pytest.mark.parametrize("T,n_in,n_out", [
+    (70, 704, 776),                  # 32 x 32
+    (33, 192, 104),                  # 32 x 64, three slabs
+    (200, 448, 4088),                # 64 x 64
+    (450, 192, 3080),                # 64 x 128
+    (1090, 320, 2056),               # 128 x 128
+    (1500, 1088, 3080),              # 192 x 128
+    (2000, 1088, 3080),              # 256 x 128
+    (2100, 192, 3080),               # 128 x 256
+])
+def test_frozen_linear_tile_forms(T, n_in, n_out):
+    test_frozen_linear_dispatch_edges(T, n_in, n_out, True)
+
+
+# The same with the rank-space branch (contraction n_in forward, n_out in the input gradient), and contractions long
+# enough to be shared over blocks in either direction, on repeated calls.
+@pytest.mark.parametrize("T,n_in,n_out,r", [
+    (70, 704, 768, 16),              # 32 x 32
+    (130, 704, 2048, 1),             # 32 x 64 forward
+    (450, 192, 3072, 5),             # 64 x 128 forward
+    (1400, 704, 3072, 8),            # 192 x 128 forward
+    (2000, 1088, 3072, 3),           # 256 x 128 forward
+])
+def test_bf16_layer_tile_forms(T, n_in, n_out, r):
+    test_bf16_layer_dispatch_edges(T, n_in, n_out, r)
+
+
+@pytest.mark.parametrize("T,n_in,n_out,r", [
+    (3, 5120, 128, 16),              # forward: two tiles of 64 x 64, four shares
+    (130, 128, 5120, 3),             # input gradient: six tiles, four shares
+    (1024, 5120, 512, 4),            # forward: 128 tiles, two shares
+])
+def test_bf16_layer_long_contractions_are_shared(T, n_in, n_out, r):
+    test_bf16_layer_dispatch_edges(T, n_in, n_out, r)
+    test_bf16_layer_shared_contraction_repeats_itself(T, n_in, n_out, r)
+
+
 @pytest.mark.parametrize("T,n_in,n_out,r", [
     (3, 2432, 128, 16),              # contraction shared over four blocks (9 and 10 slabs), forward; one row of tiles
     (130, 128, 2432, 3),             # the same in the input gradient

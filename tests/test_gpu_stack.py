@@ -277,6 +277,19 @@ def test_results_do_not_depend_on_the_batch(proj):
     srv.close()
 
 
+# The same for short records, from one (32 x 32 and 32 x 64 tiles) to 33 of 128 tokens (128 x 128 and 256 x 256).
+@pytest.mark.parametrize("proj", [("q", "v"), synth.PROJ_NAMES])
+def test_results_of_short_records_do_not_depend_on_the_batch(proj):
+    cfg = synth.tiny_config(d_model=768, n_head=12, d_ff=3072, n_blocks=1, lora_r=5, lora_proj=proj,
+                            n_clients=33, batch=1, seq_len=128, seed=synth.BASE_SEED + 131)
+    inp = _boost_B(synth.make_stack_inputs(cfg), cfg, target=16.0)
+    srv, Y, dX, _ = gpu_round(cfg, inp)
+    for n in (1, 2, 4, 8, 16, 24):
+        _, y, dx, _ = gpu_round(cfg, inp, clients=inp["clients"][:n], dY=inp["dY"][:n], server=srv)
+        assert np.array_equal(y, Y[:n]) and all(np.array_equal(a, b) for a, b in zip(dx, dX[:n])), n
+    srv.close()
+
+
 # LayerNorm of a width that is a multiple of 256 runs on a kernel of exactly that many chunks per row; both directions, fp32,
 # gathered and scattered rows of every such width (256 and 2048: test_small_stacks).
 @pytest.mark.parametrize("d", [512, 768, 1024, 1280, 1536, 1792])

@@ -239,6 +239,13 @@ def _check_valu_sgpr_to_vmem(text, what):
                 j -= 1
 
 
+def test_wide_tile_gemm_copies_and_scalars():
+    text = _assembly("gemm_wide.hip")
+    assert sum("gemm_wide_kernel" in n for n in _functions(text)) == 31     # 11 epilogues and ranks x three tile heights, less two
+    _check_m0(text, "gemm_wide.hip")
+    _check_valu_sgpr_to_vmem(text, "gemm_wide.hip")
+
+
 def test_vector_written_scalars_are_settled_before_vector_memory_reads_them(gemm_asm, tile_asm):
     _check_valu_sgpr_to_vmem(gemm_asm, "gemm.hip")
     _check_valu_sgpr_to_vmem(tile_asm, "gemm_tile.hip")
