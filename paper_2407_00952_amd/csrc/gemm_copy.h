@@ -24,6 +24,14 @@ __device__ __forceinline__ void glds_soff_if(const void *sbase, unsigned voff, u
                  : "s"(lds), "v"(voff), "s"(sbase), "s"(mask)
                  : "memory");
 }
+// 4 bytes per lane (256 bytes), by all lanes or none
+__device__ __forceinline__ void glds4_soff_if(const void *sbase, unsigned voff, unsigned lds, int mask)
+{
+    asm volatile("s_mov_b32 exec_lo, %3\n\ts_mov_b32 exec_hi, %3\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2\n\ts_mov_b64 exec, -1"
+                 :
+                 : "s"(lds), "v"(voff), "s"(sbase), "s"(mask)
+                 : "memory");
+}
 __device__ __forceinline__ unsigned lds_addr(const void *p)
 {
     return (unsigned)(unsigned long long)(const __attribute__((address_space(3))) char *)p;

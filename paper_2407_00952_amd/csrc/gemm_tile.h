@@ -40,8 +40,8 @@ __device__ __forceinline__ f32x4 get_partial(const float4 *p)
 
 // Epilogue of CR rows staged in LDS, so that memory sees 16-byte accesses.
 // INTERIOR: the rows and columns lie wholly inside the matrix, no branch (see epilogue4 in gemm.hip).
-template <int EPI, int TN, int CR, int NTHR, bool INTERIOR>
-__device__ __forceinline__ void epilogue_rows(const GemmArgs &a, const float *stg, int m0, int n0, int n_end,
+template <int EPI, int TN, int CR, int NTHR, bool INTERIOR, class Args>
+__device__ __forceinline__ void epilogue_rows(const Args &a, const float *stg, int m0, int n0, int n_end,
                                               const float (&bias8)[8])
 {
     constexpr int P = TN + 4, TPR = TN / 8, RPP = NTHR / TPR, NP = CR > RPP ? CR / RPP : 1;
@@ -78,8 +78,8 @@ constexpr int gemm_tile_lds()
 // Tile and share of the contraction of this block; consecutive logical ids land on one XCD and walk panels of PANEL row
 // tiles column by column (operands of the tiles in flight on an XCD stay in its L2).
 struct TileOf { int m0, n0, n_end, seg, tns, tile, split; bool any; };
-template <int TM, int TN>
-__device__ __forceinline__ TileOf gemm_tile_of(const GemmArgs &a, int splits)
+template <int TM, int TN, class Args>
+__device__ __forceinline__ TileOf gemm_tile_of(const Args &a, int splits)
 {
     TileOf t;
     const int tiles_n_seg = (a.seg_n + TN - 1) / TN;
@@ -103,6 +103,47 @@ __device__ __forceinline__ TileOf gemm_tile_of(const GemmArgs &a, int splits)
     return t;
 }
 
+// Epilogue of a block's tile, CR rows at a time; row tile i of a wave is tile (i + rot) mod MI of its rows.
+template <int EPI, int TM, int TN, int WM, int WN, class Args>
+__device__ __forceinline__ void gemm_tile_epilogue(const Args &a, const f32x4 (&acc)[TM / 16 / WM][TN / 16 / WN], unsigned char *lds,
+                                                   int m0, int n0, int n_end, int rot)
+{
+    constexpr int NTHR = 64 * WM * WN, MI = TM / 16 / WM, NI = TN / 16 / WN;
+    constexpr int P = TN + 4, CR = TM % 64 == 0 ? 64 : 32, CT = CR / 16;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN, r16 = lane & 15, kg = lane >> 4;
+    constexpr int TPR = TN / 8;
+    const int gcol = n0 + (tid % TPR) * 8;
+    float bias8[8];
+    {
+        bf16x8 b8;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b8[i] = f2bf(0.f);
+        if (a.bias && gcol < n_end) b8 = *(const bf16x8 *)(a.bias + gcol);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) bias8[i] = bf2f(b8[i]);
+    }
+    float *stg = (float *)lds;
+    const bool interior = m0 + TM <= a.M && n0 + TN <= n_end;
+#pragma unroll
+    for (int c = 0; c < TM / CR; ++c) {
+        if (c > 0) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const int rt = wm * MI + (i + rot) % MI - c * CT;         // 16-row tile within the chunk
+            if (rt >= 0 && rt < CT) {
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) stg[(rt * 16 + 4 * kg + e) * P + (wn * NI + j) * 16 + r16] = acc[i][j][e];
+            }
+        }
+        if (interior) epilogue_rows<EPI, TN, CR, NTHR, true>(a, stg, m0 + CR * c, n0, n_end, bias8);
+        else epilogue_rows<EPI, TN, CR, NTHR, false>(a, stg, m0 + CR * c, n0, n_end, bias8);
+    }
+}
+
 // TM x TN tile, WM x WN waves; a stage of the LDS ring holds NSUB slabs of 64 (one barrier per stage), NST stages.
 // SPLIT: `splits` blocks share a tile's contraction; their partial accumulators go to scratch memory and the block that
 // arrives last adds them in share order -- whichever block that is, so results are still reproducible.
@@ -119,7 +160,6 @@ __device__ __forceinline__ void gemm_tile_block(const GemmArgs &a, const TileOf 
     constexpr int NZT = NZ > 0 ? NZ / 16 : 1;
     constexpr int MZ = (MI + WN - 1) / WN;               // 16-row tiles of z that a wave forms
     constexpr int K2P = NZ > 0 ? (NZ + 31) / 32 * 32 : 32;
-    constexpr int P = TN + 4, CR = TM % 64 == 0 ? 64 : 32, CT = CR / 16;     // rows per epilogue chunk
     static_assert(EPI != EPI_STORE_DELTA || TN % 64 == 0, "a head's columns in one tile");
     static_assert(PX % NW == 0 && PW % NW == 0, "every wave copies as much");
     static_assert(NSUB * NC * NST < 64, "copies in flight fit the counter");
@@ -367,36 +407,7 @@ __device__ __forceinline__ void gemm_tile_block(const GemmArgs &a, const TileOf 
         __syncthreads();                                 // the z tile has been consumed
     }
 
-    // ---- epilogue, CR rows at a time ---------------------------------------------------------------------
-    constexpr int TPR = TN / 8;
-    const int gcol = n0 + (tid % TPR) * 8;
-    float bias8[8];
-    {
-        bf16x8 b8;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) b8[i] = f2bf(0.f);
-        if (a.bias && gcol < n_end) b8 = *(const bf16x8 *)(a.bias + gcol);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) bias8[i] = bf2f(b8[i]);
-    }
-    float *stg = (float *)lds;
-    const bool interior = m0 + TM <= a.M && n0 + TN <= n_end;
-#pragma unroll
-    for (int c = 0; c < TM / CR; ++c) {
-        if (c > 0) __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-            const int rt = wm * MI + (i + rot) % MI - c * CT;         // 16-row tile within the chunk
-            if (rt >= 0 && rt < CT) {
-#pragma unroll
-                for (int j = 0; j < NI; ++j)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) stg[(rt * 16 + 4 * kg + e) * P + (wn * NI + j) * 16 + r16] = acc[i][j][e];
-            }
-        }
-        if (interior) epilogue_rows<EPI, TN, CR, NTHR, true>(a, stg, m0 + CR * c, n0, n_end, bias8);
-        else epilogue_rows<EPI, TN, CR, NTHR, false>(a, stg, m0 + CR * c, n0, n_end, bias8);
-    }
+    gemm_tile_epilogue<EPI, TM, TN, WM, WN>(a, acc, lds, m0, n0, n_end, rot);
 }
 
 // the block's tile; a segment without adapter, which q|k|v has when not all three carry one, runs without the branch

@@ -19,15 +19,12 @@
 // rows 4g + e.
 #include "../../include/slora.h"
 #include "common.h"
-#include "gemm_epilogue.h"
+#include "gemm_mx_tile.h"
 #include "mx_codec.h"
 #include "rank_project.h"
 #include <cstring>
 
 namespace {
-
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------------------------------------
 // conversion kernels
@@ -141,39 +138,10 @@ constexpr int BM = 256, BN = 256, BKB = 128, NTHR = 512;   // BKB: bytes = fp8 e
 constexpr int XB = BM * BKB, WB = BN * BKB, SB = BM * 4;   // tile bytes; scale bytes per operand tile
 constexpr int STAGE = XB + WB + 2 * SB;                    // (fp8 weights; 4-bit weights need half of WB)
 
-struct MxArgs {
-    const unsigned char *X, *XS;     // codes [M,K], scales [M,K/32]
-    const unsigned char *W, *WS;     // codes [N,K], scales [N,K/32]   (N = nseg * seg_n)
-    const bf16 *bias;                // [N] or null
-    int M, N, K;
-    int nseg, seg_n;
-    // low-rank branch kept in bf16, per segment (null zs = segment not adapted): out += zs . tmat^T
-    const bf16 *zs[3];               // [M,K2]: scaled rank-space activations, zero beyond the rank(s)
-    const bf16 *tmat[3];             // [seg_n,ldt]: up-projection(s), ldt = K2 rounded up to 32, zero padded
-    int K2, ldt;
-    // epilogue (meaning as in GemmArgs)
-    void *out0; void *out1; const void *aux; int ldo;
-    const bf16 *dl_o, *dl_lo; float *dl_out;   // EPI_STORE_DELTA (meaning as in GemmArgs)
-    unsigned char *oq, *os;          // optional MXFP8 copy of the epilogue's bf16 tensor (see GemmArgs)
-    static constexpr bool kEmitCodes = true;
-};
 // With W4 the weight operand is MXFP4: W holds two E2M1 codes per byte ([N, K/2]), a tile row is 64 bytes
 // per slab, the lane's 32 elements are 16 consecutive bytes (k = 32g .. 32g+31) and the upper half of the
 // operand register is unused.
 
-__device__ __forceinline__ void glds16(const void *sbase, unsigned voff, unsigned lds)
-{
-    // M0 carries the LDS address; one wait state is required between its write and the copy
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(voff), "s"(sbase) : "memory");
-}
-__device__ __forceinline__ void glds4(const void *sbase, unsigned voff, unsigned lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds), "v"(voff), "s"(sbase) : "memory");
-}
-__device__ __forceinline__ unsigned lds_addr(const void *p)
-{
-    return (unsigned)(unsigned long long)(const __attribute__((address_space(3))) char *)p;
-}
 #define MX_WAIT_VM0() __builtin_amdgcn_s_waitcnt(0x0F70)
 
 template <bool W4, int EPI>
@@ -251,17 +219,17 @@ __global__ __launch_bounds__(NTHR) void gemm_mx_kernel(MxArgs a)
         int xr_ = xrow0, wr_ = wrow0;                                                     \
         asm volatile("" : "+v"(xr_), "+v"(wr_));                                          \
         const unsigned xo_ = (unsigned)min(xr_ + (p) * 8, a.M - 1) * (unsigned)a.K + lch16; \
-        glds16(a.X + (size_t)(kt) * BKB, xo_, lds_addr(st) + wofs + (p) * 1024);          \
+        glds_soff(a.X + (size_t)(kt) * BKB, xo_, lds_addr(st) + wofs + (p) * 1024);          \
         if (!W4) {                                                                        \
             const unsigned wo_ = (unsigned)min(wr_ + (p) * 8, n_end - 1) * (unsigned)a.K + lch16; \
-            glds16(a.W + (size_t)(kt) * BKB, wo_, lds_addr(st) + XB + wofs + (p) * 1024); \
+            glds_soff(a.W + (size_t)(kt) * BKB, wo_, lds_addr(st) + XB + wofs + (p) * 1024); \
         } else if ((p) < 2) {                                                             \
             int w4_ = w4row0;                                                             \
             asm volatile("" : "+v"(w4_));                                                 \
             const unsigned wo_ = (unsigned)min(w4_ + (p) * 16, n_end - 1) * (unsigned)(a.K >> 1) + w4ch16; \
-            glds16(a.W + (size_t)(kt) * 64, wo_, lds_addr(st) + XB + wave * 2048 + (p) * 1024); \
+            glds_soff(a.W + (size_t)(kt) * 64, wo_, lds_addr(st) + XB + wave * 2048 + (p) * 1024); \
         }                                                                                 \
-        if ((p) == 0) glds4(Sb + (size_t)(kt) * 4, so, lds_addr(st) + s_lds);             \
+        if ((p) == 0) glds4_soff_if(Sb + (size_t)(kt) * 4, so, lds_addr(st) + s_lds, -1);         \
     }
 #define MX_FRAG(dst, base, off)                                                           \
     {                                                                                     \
@@ -305,29 +273,8 @@ __global__ __launch_bounds__(NTHR) void gemm_mx_kernel(MxArgs a)
 
     const int nk = a.K / BKB;
     MX_ISSUE(st0, 0, 0) MX_ISSUE(st0, 0, 1) MX_ISSUE(st0, 0, 2) MX_ISSUE(st0, 0, 3)
-    MX_WAIT_VM0();
-    __syncthreads();
-    int kt = 0;
-    for (; kt + 2 <= nk; kt += 2) {
-        MX_PHASE(st0, st1, kt + 1, true)
-        MX_WAIT_VM0();
-        __syncthreads();
-        const bool more = kt + 2 < nk;
-        MX_PHASE(st1, st0, kt + 2, more)
-        MX_WAIT_VM0();
-        __syncthreads();
-    }
-    if (kt < nk) {
-        MX_PHASE(st0, st1, 0, false)
-        __syncthreads();
-    }
-#undef MX_ISSUE
-#undef MX_FRAG
-#undef MX_STEP
-#undef MX_PHASE
-
-    // ---- low-rank tail (SplitLoRA Sec. II-C: W + BA with the adapter kept in bf16): ldt / 32 bf16 MFMA
-    //      k-steps per tile on operands read straight from global memory (a few MB: cache hits); columns
+    // ---- low-rank part (SplitLoRA Sec. II-C: W + BA with the adapter kept in bf16), first as in gemm_mx_tile.h: ldt / 32 bf16
+    //      MFMA k-steps per tile on operands read straight from global memory (a few MB: cache hits); columns
     //      of the rank-space activations beyond K2 and of the up-projection beyond the ranks are zero
     if (a.zs[seg] != nullptr) {
         const bf16 *zs_ = a.zs[seg], *tm_ = a.tmat[seg];
@@ -352,6 +299,26 @@ __global__ __launch_bounds__(NTHR) void gemm_mx_kernel(MxArgs a)
             }
         }
     }
+    MX_WAIT_VM0();
+    __syncthreads();
+    int kt = 0;
+    for (; kt + 2 <= nk; kt += 2) {
+        MX_PHASE(st0, st1, kt + 1, true)
+        MX_WAIT_VM0();
+        __syncthreads();
+        const bool more = kt + 2 < nk;
+        MX_PHASE(st1, st0, kt + 2, more)
+        MX_WAIT_VM0();
+        __syncthreads();
+    }
+    if (kt < nk) {
+        MX_PHASE(st0, st1, 0, false)
+        __syncthreads();
+    }
+#undef MX_ISSUE
+#undef MX_FRAG
+#undef MX_STEP
+#undef MX_PHASE
 
     // ---- epilogue: each wave transposes its tiles through a private LDS strip (32 rows x 64 columns
     //      fp32) so that global memory sees 16-byte accesses; only the owning wave touches its strip.
@@ -479,6 +446,11 @@ int launch_quantize_project(const bf16 *x, int M, int K, unsigned char *codes, u
 
 int launch_gemm_mx(const MxArgs &a, hipStream_t st, bool w4 = false, int epi = EPI_STORE)
 {
+    if (epi == EPI_STORE_DELTA && (!a.dl_o || !a.dl_lo || !a.dl_out || !a.out0 || (a.N % 64) || a.nseg != 1)) return SL_EINVAL;
+    if (!w4) {
+        const TilePlan p = plan_gemm_mx(a);
+        if (p.tn < 256) return launch_gemm_mx_tile(a, epi, p, st);
+    }
     const int nb = ((a.M + BM - 1) / BM) * (((a.seg_n + BN - 1) / BN) * a.nseg);
     const dim3 grid(((nb + 7) / 8) * 8), block(NTHR);
     if (w4) {
@@ -490,10 +462,7 @@ int launch_gemm_mx(const MxArgs &a, hipStream_t st, bool w4 = false, int epi = E
         case EPI_RESID: hipLaunchKernelGGL((gemm_mx_kernel<false, EPI_RESID>), grid, block, 0, st, a); break;
         case EPI_GELU: hipLaunchKernelGGL((gemm_mx_kernel<false, EPI_GELU>), grid, block, 0, st, a); break;
         case EPI_DGELU: hipLaunchKernelGGL((gemm_mx_kernel<false, EPI_DGELU>), grid, block, 0, st, a); break;
-        case EPI_STORE_DELTA:
-            if (!a.dl_o || !a.dl_lo || !a.dl_out || !a.out0 || (a.N % 64) || a.nseg != 1) return SL_EINVAL;
-            hipLaunchKernelGGL((gemm_mx_kernel<false, EPI_STORE_DELTA>), grid, block, 0, st, a);
-            break;
+        case EPI_STORE_DELTA: hipLaunchKernelGGL((gemm_mx_kernel<false, EPI_STORE_DELTA>), grid, block, 0, st, a); break;
         default: return SL_EINVAL;
         }
     }

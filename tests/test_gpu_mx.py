@@ -114,6 +114,30 @@ def test_linear_on_oracle_codes(T, K, N, with_bias):
     assert rms < 0.06
 
 
+# The tile forms of the fp8 products, each with ragged rows and columns; odd and even numbers of slabs.
+@pytest.mark.parametrize("T,K,N", [
+    (70, 384, 200),               # 32 x 64
+    (300, 256, 4104),             # 64 x 64
+    (500, 640, 4000),             # 64 x 128
+    (1030, 384, 3080),            # 128 x 128
+    (1400, 640, 3080),            # 192 x 128
+    (2000, 640, 3080),            # 256 x 128
+    (5000, 384, 2056),            # 256 x 256
+])
+def test_linear_tile_forms(T, K, N):
+    test_linear_on_oracle_codes(T, K, N, True)
+
+
+@pytest.mark.parametrize("T,n_in,n_out,r", [
+    (70, 384, 256, 5),            # 32 x 64
+    (500, 640, 3968, 16),         # 64 x 128 forward
+    (1400, 640, 3072, 1),         # 192 x 128 forward
+    (5000, 384, 2048, 3),         # 256 x 256 forward
+])
+def test_lora_linear_tile_forms(T, n_in, n_out, r):
+    test_lora_linear_mxfp8(T, n_in, n_out, r, True)
+
+
 def test_linear_full_code_range():
     """every finite element code and a wide band of scales: the hardware's decode and block scaling"""
     say("mx linear, random codes")

@@ -244,6 +244,10 @@ def test_wide_tile_gemm_copies_and_scalars():
     assert sum("gemm_wide_kernel" in n for n in _functions(text)) == 31     # 11 epilogues and ranks x three tile heights, less two
     _check_m0(text, "gemm_wide.hip")
     _check_valu_sgpr_to_vmem(text, "gemm_wide.hip")
+    text = _assembly("gemm_mx.hip")
+    assert sum("gemm_mx_tile_kernel" in n for n in _functions(text)) == 30      # five epilogues x six tile forms
+    _check_m0(text, "gemm_mx.hip")
+    _check_valu_sgpr_to_vmem(text, "gemm_mx.hip")
 
 
 def test_vector_written_scalars_are_settled_before_vector_memory_reads_them(gemm_asm, tile_asm):
