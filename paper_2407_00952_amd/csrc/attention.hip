@@ -638,7 +638,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(const bf16 *__rest
 // produces dQ, dK and dV in one pass, so the scores, the probabilities and dP are formed once instead
 // of once per kernel, and K, V, Q, dO are read from memory once.
 //   * K of the whole sequence sits in LDS; every wave owns two 32-key blocks (w and nb-1-w, which
-//     balances the causal triangle), keeps their V fragments and their dK, dV accumulators in
+//     balances the causal triangle; one where there are no more blocks than waves: S = 128 with two blocks on two
+//     of the waves took 13.6 us), keeps their V fragments and their dK, dV accumulators in
 //     registers, and walks the 32-query tiles that can see them (phase 1, as in the dK/dV kernel).
 //   * dS of a query tile is written to LDS as dS^T [key][32 queries] bf16; after one barrier the 8
 //     waves each form one 16 x 16 piece of dQ = dS K over all visible keys (phase 2), in a fixed
@@ -691,8 +692,10 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16 *__restr
     // ---- prologue: first tile (Q, dO, K rows), log-sum-exp and delta of all rows, this wave's V fragments
     FB_COPY(Qb0, Db0, 0)
     if (tid < S) lse_s[tid] = lse[((size_t)n * H + a) * S + tid];
-    const bool owner = wave < (nb >> 1);                 // waves beyond the number of block pairs only do phase 2
-    const int jb[2] = {wave, nb - 1 - wave};
+    // up to 8 key blocks (256 tokens) every wave owns one at most; waves without a block only do phase 2
+    const bool single = nb <= 8;
+    const bool owner = wave < (single ? nb : nb >> 1);
+    const int jb[2] = {wave, single ? FB_MAXS : nb - 1 - wave};          // (no tile reaches block FB_MAXS)
     bf16x8 vf[2][4];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
@@ -847,6 +850,7 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16 *__restr
         const int orow = lane >> 3, och = lane & 7;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
+            if (b == 1 && single) break;
             bf16 *out = dqkv + ((size_t)n * S + 32 * jb[b] + orow) * ld + d + a * 64 + och * 8;
 #pragma unroll
             for (int which = 0; which < 2; ++which) {     // 0: dK (scaled), 1: dV
