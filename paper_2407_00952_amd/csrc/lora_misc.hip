@@ -62,6 +62,19 @@ __device__ __forceinline__ bf16x8 yfrag_tr(const unsigned char *t, int tok0, int
     return u.v;
 }
 
+// One launch for every adapter gradient that is due at one point of the backward pass (after the fused
+// q|k|v input-gradient product: dB of each adapted projection and dA of all of them): blockIdx.z picks the
+// job.  The jobs are a few dozen microseconds of streaming each, so launching them one by one (and their
+// reductions one by one) left the chip half idle between them.
+struct LoraGradJob {
+    const bf16 *X; const bf16 *Y;    // tall operand [T,C] (pitch ldx), skinny operand [T,16 or 32] (pitch ldy)
+    float *partials;                 // this job's chunk partial sums
+    float *out_a, *out_b;            // result(s); out_b only for a dual job
+    int ldx, ldy, C, dual, out_is_rxC;
+};
+constexpr int LG_MAX_JOBS = 6;
+struct LoraGradJobs { LoraGradJob j[LG_MAX_JOBS]; };
+
 // partial[chunk][j][c] = sum over the chunk's tokens of X[t,c] * Y[t,j]  on the matrix cores:
 // D[m = c][n = j] += X^T[c][t] * Y[t][j], both operands read along the token axis with the LDS
 // transpose read from row-major tiles that asynchronous copies (X) and plain loads (Y) fill.
@@ -70,9 +83,10 @@ __device__ __forceinline__ bf16x8 yfrag_tr(const unsigned char *t, int tok0, int
 template <bool DUAL>
 __device__ __forceinline__ void lora_grad_partial_body(const bf16 *__restrict__ X, int ldx, int C,
                                                        const bf16 *__restrict__ Y, int ldy, int r, int T,
-                                                       int rows, float *__restrict__ partials, unsigned char *X0,
+                                                       int rows, const LoraGradJob &jb, unsigned char *X0,
                                                        unsigned char *X1, unsigned char *Y0, unsigned char *Y1)
 {
+    float *__restrict__ partials = jb.partials;
     constexpr int YP = DUAL ? 96 : 32;
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -149,6 +163,16 @@ __device__ __forceinline__ void lora_grad_partial_body(const bf16 *__restrict__ 
     const int nrows = DUAL ? 2 * r : r;
     const int jrow = (DUAL && r32 >= 16) ? r + r32 - 16 : r32;
     if (wave_ok && (r32 & 15) < r && (DUAL || r32 < 16)) {
+        if (gridDim.y == 1) {                            // one chunk: the result itself, there is no reduction
+            float *dst = DUAL && r32 >= 16 ? jb.out_b : jb.out_a;
+            const size_t step = jb.out_is_rxC ? 1 : r, off = jb.out_is_rxC ? (size_t)(r32 & 15) * C : (r32 & 15);
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    dst[off + (size_t)(c_blk + wave * 64 + mt * 32 + 8 * (e >> 2) + 4 * g + (e & 3)) * step] = 0.f + acc[mt][e];
+            return;
+        }
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
@@ -160,27 +184,14 @@ __device__ __forceinline__ void lora_grad_partial_body(const bf16 *__restrict__ 
     }
 }
 
-// One launch for every adapter gradient that is due at one point of the backward pass (after the fused
-// q|k|v input-gradient product: dB of each adapted projection and dA of all of them): blockIdx.z picks the
-// job.  The jobs are a few dozen microseconds of streaming each, so launching them one by one (and their
-// reductions one by one) left the chip half idle between them.
-struct LoraGradJob {
-    const bf16 *X; const bf16 *Y;    // tall operand [T,C] (pitch ldx), skinny operand [T,16 or 32] (pitch ldy)
-    float *partials;                 // this job's chunk partial sums
-    float *out_a, *out_b;            // result(s); out_b only for a dual job
-    int ldx, ldy, C, dual, out_is_rxC;
-};
-constexpr int LG_MAX_JOBS = 6;
-struct LoraGradJobs { LoraGradJob j[LG_MAX_JOBS]; };
-
 __global__ __launch_bounds__(256) void lora_grad_partial_kernel(LoraGradJobs jobs, int r, int T, int rows)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char X0[GX_TILE], X1[GX_TILE];
     __shared__ __attribute__((aligned(16))) unsigned char Y0[64 * 96], Y1[64 * 96];
     const LoraGradJob &jb = jobs.j[blockIdx.z];
     if ((int)blockIdx.x * GR_COLS >= jb.C) return;       // this job's operand is narrower than the widest one
-    if (jb.dual) lora_grad_partial_body<true>(jb.X, jb.ldx, jb.C, jb.Y, jb.ldy, r, T, rows, jb.partials, X0, X1, Y0, Y1);
-    else lora_grad_partial_body<false>(jb.X, jb.ldx, jb.C, jb.Y, jb.ldy, r, T, rows, jb.partials, X0, X1, Y0, Y1);
+    if (jb.dual) lora_grad_partial_body<true>(jb.X, jb.ldx, jb.C, jb.Y, jb.ldy, r, T, rows, jb, X0, X1, Y0, Y1);
+    else lora_grad_partial_body<false>(jb.X, jb.ldx, jb.C, jb.Y, jb.ldy, r, T, rows, jb, X0, X1, Y0, Y1);
 }
 
 // out[j, c] = sum over chunks, in a fixed order: each of the 4 wavefronts of a block sums a
@@ -447,6 +458,7 @@ int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStr
                        jobs, r, T, rows);
     prof_end(rec, PK_LORA_GRAD, bytes, st);
     SL_CHECK_LAUNCH("lora_grad_partial");
+    if (nchunk == 1) return 0;                           // (one record of 128 tokens: 3.3 us of its 104 a block)
     hipLaunchKernelGGL(lora_grad_reduce_kernel, dim3((max_red + 63) / 64, 1, njobs), dim3(256), 0, st, jobs, nchunk, r);
     SL_CHECK_LAUNCH("lora_grad_reduce");
     return 0;

@@ -290,6 +290,19 @@ def test_results_of_short_records_do_not_depend_on_the_batch(proj):
     srv.close()
 
 
+# One short record: up to 128 tokens the adapter gradients are written without partial sums; up to 256 the attention backward
+# has one key block to a wave, beyond two to some (320: odd number of pairs).
+@pytest.mark.parametrize("S", [64, 128, 192, 256, 320])
+@pytest.mark.parametrize("proj", [("q", "v"), synth.PROJ_NAMES])
+def test_one_short_record(S, proj):
+    cfg = synth.tiny_config(d_model=128, n_head=2, d_ff=256, n_blocks=2, lora_r=3, lora_proj=proj,
+                            n_clients=1, batch=1, seq_len=S, seed=synth.BASE_SEED + 150 + S)
+    inp = _boost_B(synth.make_stack_inputs(cfg), cfg)
+    srv, Y, dX, grads = gpu_round(cfg, inp)
+    compare_round(cfg, inp, Y, dX, grads, label="S%d" % S)
+    srv.close()
+
+
 # LayerNorm of a width that is a multiple of 256 runs on a kernel of exactly that many chunks per row; both directions, fp32,
 # gathered and scattered rows of every such width (256 and 2048: test_small_stacks).
 @pytest.mark.parametrize("d", [512, 768, 1024, 1280, 1536, 1792])
