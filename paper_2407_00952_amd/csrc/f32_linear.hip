@@ -6,15 +6,17 @@
 // results are reproducible.
 //
 //   forward   z = x A^T                                 f32_project_kernel
-//             y = x W^T + bias + s z B^T                f32_gemm_kernel / f32_gemm_direct_kernel
+//             y = x W^T + bias + s z B^T                f32_tile_kernel / f32_gemm_kernel / f32_gemm_direct_kernel
 //   backward  z = x A^T, p = dy B                       f32_project_kernel (both in one launch)
 //             dx = dy W + s p A                         the same product kernels, W read as [k, n]
 //             dA = s p^T x, dB = s dy^T z               f32_grad_kernel (both in one launch)
 //
 // At T = 1024, 768 -> 768, r = 4 (2.5 GFLOP, 15 MB: 16 us at the fp32 matrix rate) forward + backward took 1113 us
 // as nine launches of one vector-FMA kernel: single floats moved one by one, the rank-4 products as mostly empty 64 x 64
-// tiles, the adapter gradients as 12 blocks that walk all tokens.  Five launches of the kernels below: 59 us.
+// tiles, the adapter gradients as 12 blocks that walk all tokens.  Five launches of the kernels below: 48 us (59 before the
+// products that fill the chip took the ring kernel).
 #include "common.h"
+#include "gemm_copy.h"
 
 namespace {
 
@@ -310,6 +312,174 @@ __global__ __launch_bounds__(256 * KS) void f32_gemm_kernel(GemmF32 a)
             }
 }
 
+// The same product where the contraction is a multiple of 64: TM x TN tile, two groups of WM x WN waves that take the slabs of
+// 32 in turn.  A stage of the LDS ring holds a slab for each group, filled by asynchronous copies NST - 1 stages ahead (a
+// slab's arithmetic is shorter than the round trip that the kernel above has one slab in flight for); operand rows of
+// 128 bytes with the 16-byte chunks XORed with the row, W read as [k, n] as rows of TN floats with the chunks rotated by the
+// k-group, so that the four k-groups of a read meet different banks.  Same sums in the same order.
+template <int TM, int TN, int WM, int WN, int NST, bool BT>
+__global__ __launch_bounds__(512) void f32_tile_kernel(GemmF32 a)
+{
+    static_assert(WM * WN == 4, "four waves in a group");
+    constexpr int MI = TM / 16 / WM, NI = TN / 16 / WN;
+    constexpr int ASZ = TM * 128, SUB = ASZ + TN * 128, STAGE = 2 * SUB;
+    constexpr int CA = 2 * TM / 64, PER = CA + (2 * TN + 63) / 64;    // 1 KB copies of a wave per stage
+    constexpr int RW = TN / 4;                           // 16-byte chunks of a row of W as [k, n]
+    static_assert((2 * TM) % 64 == 0 && NST * PER < 64, "copies");
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), grp = wv >> 2, wave = wv & 3;
+    const int wm = wave / WN, wn = wave % WN;
+    const int tiles_n = (a.N + TN - 1) / TN, tiles_m = (a.M + TM - 1) / TM, nb = tiles_m * tiles_n, per_xcd = (nb + 7) >> 3;
+    const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (tile >= nb || (int)(blockIdx.x >> 3) >= per_xcd) return;
+    const int panel = tile / (4 * tiles_n), rem = tile - panel * 4 * tiles_n, rows = min(4, tiles_m - 4 * panel);
+    const int m0 = (4 * panel + rem % rows) * TM, n0 = (rem / rows) * TN;
+
+    // operands of the low-rank term and the bias, needed after the loop: requested first, so that the waits below count
+    // copies only
+    float4 uz[MI], uu[NI];
+    float bias[NI];
+    if (grp == 0) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i) uz[i] = up_frag_z(a, min(m0 + (wm * MI + i) * 16 + r16, a.M - 1), g);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) uu[j] = up_frag_u(a, min(n0 + (wn * NI + j) * 16 + r16, a.N - 1), g);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) bias[j] = a.bias ? a.bias[min(n0 + (wn * NI + j) * 16 + r16, a.N - 1)] : 0.f;
+    }
+
+    // copies: piece p of a stage (1 KB), the pieces of both groups' slabs dealt over the 8 waves; lane l fills 16-byte slot l
+    const int nst = a.K / 64;                            // stages of the contraction
+    unsigned ao[CA], bo[PER - CA];
+    int al[CA], bl[PER - CA], blanes[PER - CA];
+#pragma unroll
+    for (int c = 0; c < CA; ++c) {
+        const int p = wv * CA + c, sub = p / (TM / 8), row = (p % (TM / 8)) * 8 + (lane >> 3);
+        ao[c] = (unsigned)min(m0 + row, a.M - 1) * (unsigned)a.K * 4u + sub * 128 + (((lane & 7) ^ (row & 7)) << 4);
+        al[c] = sub * SUB + (p % (TM / 8)) * 1024;
+    }
+#pragma unroll
+    for (int c = 0; c < PER - CA; ++c) {
+        constexpr int NB = 2 * (TN / 8);                 // pieces of B per stage
+        const int p = min(wv * (PER - CA) + c, NB - 1), sub = p / (TN / 8), q = p % (TN / 8);
+        blanes[c] = (wv * (PER - CA) + c - NB) >> 31;    // -1, or 0 where there is no such piece
+        bl[c] = sub * SUB + ASZ + q * 1024;
+        if (BT) {
+            const int row = q * 8 + (lane >> 3);
+            bo[c] = (unsigned)min(n0 + row, a.N - 1) * (unsigned)a.K * 4u + sub * 128 + (((lane & 7) ^ (row & 7)) << 4);
+        } else {
+            const int slot = q * 64 + lane, k = slot / RW, ch = (slot % RW + RW - 4 * ((k >> 2) & 3) % RW) % RW;
+            bo[c] = ((unsigned)(sub * 32 + k) * (unsigned)a.N + (unsigned)min(n0 + ch * 4, a.N - 4)) * 4u;
+        }
+    }
+    const unsigned base = lds_addr(lds);
+    const size_t bstep = BT ? 256 : 256 * (size_t)a.N;   // bytes of B per stage
+    // copies past the last stage repeat it (in bounds, never read)
+    auto copy1 = [&](int slot, int t, int c) {
+        const size_t tt = (size_t)min(t, nst - 1);
+        if (c < CA) glds_soff((const char *)a.A + tt * 256, ao[c < CA ? c : 0], base + slot * STAGE + al[c < CA ? c : 0]);
+        else {
+            const int b = c >= CA ? c - CA : 0;
+            glds_soff_if((const char *)a.B + tt * bstep, bo[b], base + slot * STAGE + bl[b], blanes[b]);
+        }
+    };
+
+    f32x4 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    struct Frags { float4 a[MI], b[NI]; } f[2];
+    const int sw = r16 & 7;
+    auto frags = [&](Frags &F, int slot, int ks) {
+        const unsigned char *S = lds + slot * STAGE + grp * SUB;
+        const int co = ((ks * 4 + g) ^ sw) << 4;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) F.a[i] = *(const float4 *)(S + ((wm * MI + i) * 16 + r16) * 128 + co);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int n = (wn * NI + j) * 16 + r16;
+            if (BT) F.b[j] = *(const float4 *)(S + ASZ + n * 128 + co);
+            else {
+                const float *q = (const float *)(S + ASZ) + (ks * 16 + 4 * g) * TN + (((n >> 2) + 4 * g) % RW) * 4 + (n & 3);
+                F.b[j] = make_float4(q[0], q[TN], q[2 * TN], q[3 * TN]);
+            }
+        }
+    };
+    // component by component, so that an accumulator is not needed again by the very next MFMA
+    auto mfmas = [&](const Frags &F) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32((&F.a[i].x)[c], (&F.b[j].x)[c], acc[i][j], 0, 0, 0);
+    };
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s)
+#pragma unroll
+        for (int c = 0; c < PER; ++c) copy1(s, s, c);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * PER) : "memory");
+    __syncthreads();
+    frags(f[0], 0, 0);
+    int slot = 0;
+    for (int t = 0; t < nst; ++t) {
+        const int next = slot + 1 == NST ? 0 : slot + 1, prev = slot == 0 ? NST - 1 : slot - 1;
+        frags(f[1], slot, 1);
+#pragma unroll
+        for (int c = 0; c < PER; ++c) copy1(prev, t + NST - 1, c);
+        __builtin_amdgcn_sched_barrier(0);
+        mfmas(f[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        // the wave's reads of the stage are done and its copies of the next one have landed
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NST - 2) * PER) : "memory");
+        __syncthreads();
+        frags(f[0], next, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        mfmas(f[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        slot = next;
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();                                     // the ring takes the second group's sums
+    float4 *part = (float4 *)lds;
+    if (grp == 1) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                part[(i * NI + j) * 256 + (tid & 255)] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+    }
+    __syncthreads();
+    if (grp == 1) return;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const float4 v = part[(i * NI + j) * 256 + (tid & 255)];
+            acc[i][j][0] += v.x; acc[i][j][1] += v.y; acc[i][j][2] += v.z; acc[i][j][3] += v.w;
+            f32x4 low = {0.f, 0.f, 0.f, 0.f};
+            mfma4(low, uz[i], uu[j]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][j][e] = fmaf(a.s, low[e], acc[i][j][e] + bias[j]);
+        }
+    float *cp = a.C + (size_t)(m0 + wm * MI * 16 + 4 * g) * a.N + n0 + wn * NI * 16 + r16;
+    const bool inside = m0 + TM <= a.M && n0 + TN <= a.N;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                const float v = acc[i][j][e];
+                if (inside) cp[(size_t)(i * 16 + e) * a.N + j * 16] = v;
+                else if (m0 + (wm * MI + i) * 16 + 4 * g + e < a.M && n0 + (wn * NI + j) * 16 + r16 < a.N)
+                    cp[(size_t)(i * 16 + e) * a.N + j * 16] = v;
+            }
+}
+
 // Few output tiles (small T): 16 x 16 outputs per block, the contraction split over 8 waves that read their fragments
 // straight from memory, partial tiles added in wave order.  Latency-bound; the operands are re-read N / 16 and
 // M / 16 times, which the caches carry up to a few hundred rows.
@@ -383,7 +553,7 @@ __global__ __launch_bounds__(1024) void f32_grad_kernel(GradJobs jobs, int T, in
     float acc[ZP];
 #pragma unroll
     for (int j = 0; j < ZP; ++j) acc[j] = 0.f;
-#pragma unroll 4
+#pragma unroll(ZP == 4 ? 16 : 4)
     for (int t = hw; t < T; t += 32) {
         const float x = jb.X[(size_t)t * jb.C + cc];
         const float4 *y = (const float4 *)(jb.Y + (size_t)t * ZP);
@@ -417,15 +587,50 @@ void launch_tile(const GemmF32 &a, hipStream_t st)
     const long tiles = (long)((a.M + TM - 1) / TM) * ((a.N + TN - 1) / TN);
     hipLaunchKernelGGL((f32_gemm_kernel<TM, TN, KS, BT, VEC>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256 * KS), 0, st, a);
 }
+template <int TM, int TN, int WM, int WN, int NST, bool BT>
+void launch_ring(const GemmF32 &a, hipStream_t st)
+{
+    const long tiles = (long)((a.M + TM - 1) / TM) * ((a.N + TN - 1) / TN);
+    hipLaunchKernelGGL((f32_tile_kernel<TM, TN, WM, WN, NST, BT>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(512), 0, st, a);
+}
+// The form that costs least, in us as measured (T = 64 to 8192 at five weight shapes): rounds of 256 tiles, or of 512 where two
+// blocks share a CU, at a + b (K / 64) each.  32 x 64 and 64 x 48 fill the chip where 64 x 64 tiles leave a part of it idle
+// (T = 1024, 768 -> 768: 256 tiles of 64 x 48 in 13.5 us, 192 of 64 x 64 in 16.1).
+template <bool BT>
+void launch_ring_forms(const GemmF32 &a, hipStream_t st)
+{
+    struct Form { int tm, tn, per_cu; float a, b; };
+    constexpr Form forms[5] = {{32, 64, 1, 3.1f, .545f}, {64, 48, 1, 3.6f, .765f}, {64, 64, 1, 3.8f, .995f},
+                               {64, 64, 2, 4.6f, 1.90f}, {128, 128, 1, 7.5f, 3.68f}};
+    int best = 0;
+    double least = 0;
+    for (int f = 0; f < 5; ++f) {
+        const long tiles = (long)((a.M + forms[f].tm - 1) / forms[f].tm) * ((a.N + forms[f].tn - 1) / forms[f].tn);
+        const long round = 256 * forms[f].per_cu;
+        const double c = (double)((tiles + round - 1) / round) * (forms[f].a + forms[f].b * (a.K / 64));
+        if (f == 0 || c < least) { best = f; least = c; }
+    }
+    switch (best) {
+    case 0: launch_ring<32, 64, 2, 2, 4, BT>(a, st); break;
+    case 1: launch_ring<64, 48, 4, 1, 4, BT>(a, st); break;
+    case 2: launch_ring<64, 64, 2, 2, 4, BT>(a, st); break;
+    case 3: launch_ring<64, 64, 2, 2, 2, BT>(a, st); break;
+    case 4: launch_ring<128, 128, 2, 2, 2, BT>(a, st); break;
+    }
+}
 template <bool BT, bool VEC>
 int launch_product(const GemmF32 &a, hipStream_t st)
 {
     const long t64 = (long)((a.M + 63) / 64) * ((a.N + 63) / 64), t128 = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-    // 16 x 16 outputs per block while 64 x 64 tiles would leave most CUs without work; 128 x 128 tiles once two of them
-    // per CU are there (below that the idle CUs cost more than the operand traffic saved)
+    // 16 x 16 outputs per block while 64 x 64 tiles would leave most CUs without work.  The ring needs whole stages of 64 and
+    // 32-bit byte offsets; without it 128 x 128 tiles once two of them per CU are there (below that the idle CUs
+    // cost more than the operand traffic saved)
+    const bool ring = VEC && a.K % 64 == 0 && (unsigned long long)a.M * a.K < (1ull << 30) && (unsigned long long)a.N * a.K < (1ull << 30);
     if (t64 < 96) {
         const long tiles = (long)((a.M + 15) / 16) * ((a.N + 15) / 16);
         hipLaunchKernelGGL((f32_gemm_direct_kernel<BT, VEC>), dim3((unsigned)tiles), dim3(512), 0, st, a);
+    } else if (ring) {
+        launch_ring_forms<BT>(a, st);
     } else if (t128 < 512) {
         launch_tile<64, 64, 2, BT, VEC>(a, st);
     } else {

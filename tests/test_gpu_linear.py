@@ -98,6 +98,20 @@ def test_fp32_dispatch_edges(T, n_in, n_out, r, bias):
         assert relerr(g, ref) <= F32_TOL, name
 
 
+# The forms of the ring kernel (contraction a multiple of 64, 96 tiles of 64 x 64 or more), forward (W as [n, k]) and input
+# gradient (W as [k, n]), with ragged rows and columns; 64 is one stage.
+@pytest.mark.parametrize("T,n_in,n_out", [
+    (601, 768, 836), (601, 836, 768),        # 32 x 64
+    (1001, 768, 764), (1001, 764, 768),      # 64 x 48
+    (1001, 1024, 1020), (1001, 1020, 1024),  # 64 x 64
+    (2101, 192, 764), (2101, 764, 192),      # 64 x 64, two to a CU
+    (3900, 320, 1020), (3900, 1020, 320),    # 128 x 128
+    (3900, 64, 1028),                        # one stage
+])
+def test_fp32_ring_forms(T, n_in, n_out):
+    test_fp32_dispatch_edges(T, n_in, n_out, 5, True)
+
+
 # The low-rank term may not cost the fp32 product precision: error (2-norm, against fp64) of y no larger than that of the sums
 # taken one after the other, the frozen product and the low-rank one each on its own (the 5 % cover the sample: some 1e5
 # independent roundings).  Short contractions, where 16 more roundings at the size of the result show most.
