@@ -137,3 +137,59 @@ __device__ __forceinline__ void store_row8(const Args &a, int row, int col, floa
         }
     }
 }
+
+constexpr int EP4 = 68;                      // pitch (floats) of an epilogue staging strip: bank-conflict free
+// Epilogue of one 128 x 128 wave tile: 16 strips of 16 rows x 64 columns, each transposed through the wave's
+// private LDS strip `stg` so that global memory sees 16-byte accesses.  INTERIOR (the tile lies wholly inside
+// the matrix: every tile at the model's shapes) has no branch at all, so the compiler waits for exactly the
+// loads a strip needs (partial vmcnt counts) instead of draining every load and store at each predicated
+// block; the operands that come from global memory are requested four strips ahead.
+template <int EPI, bool INTERIOR, int NI, class Args>
+__device__ __forceinline__ void epilogue4(const Args &a, f32x4 (&acc)[NI][8], float *stg, int m0, int n0,
+                                          int n_end, int wm, int wn, int lane)
+{
+    constexpr int NS = 2 * NI;                           // strips: NI row strips x 2 column halves
+    const int r16 = lane & 15, kg = lane >> 4;
+    const int er = lane >> 3, ec = (lane & 7) * 8;
+    const int row_base = m0 + wm * (16 * NI) + er;
+    constexpr int AHEAD = 4;
+    AuxRow aux[NS][2];
+    float bias8[2][8];
+#pragma unroll
+    for (int jh = 0; jh < 2; ++jh) {
+        const int gcol = n0 + wn * 128 + jh * 64 + ec;
+        bf16x8 b8;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b8[i] = f2bf(0.f);
+        if (a.bias && (INTERIOR || gcol < n_end)) b8 = *(const bf16x8 *)(a.bias + gcol);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) bias8[jh][i] = bf2f(b8[i]);
+    }
+#define E4_AUX(s_)                                                                                     \
+    _Pragma("unroll") for (int it = 0; it < 2; ++it) {                                                 \
+        const int row_ = row_base + ((s_) % NI) * 16 + it * 8, col_ = n0 + wn * 128 + ((s_) / NI) * 64 + ec; \
+        load_aux<EPI>(a, row_, col_, INTERIOR || (row_ < a.M && col_ < n_end), aux[s_][it]);           \
+    }
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) E4_AUX(s)
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {                       // strip s: column half s / NI, rows 16 (s % NI) ..
+        const int jh = s / NI, i = s % NI;
+        if (s + AHEAD < NS) E4_AUX(s + AHEAD)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) stg[(4 * kg + e) * EP4 + j * 16 + r16] = acc[i][jh * 4 + j][e];
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            const int rl = it * 8 + er;
+            const float4 p0 = *(const float4 *)(stg + rl * EP4 + ec);
+            const float4 p1 = *(const float4 *)(stg + rl * EP4 + ec + 4);
+            float v[8] = {p0.x + bias8[jh][0], p0.y + bias8[jh][1], p0.z + bias8[jh][2], p0.w + bias8[jh][3],
+                          p1.x + bias8[jh][4], p1.y + bias8[jh][5], p1.z + bias8[jh][6], p1.w + bias8[jh][7]};
+            const int row = m0 + wm * (16 * NI) + i * 16 + rl, gcol = n0 + wn * 128 + jh * 64 + ec;
+            if (INTERIOR || (row < a.M && gcol < n_end)) store_row8<EPI>(a, row, gcol, v, aux[s][it]);
+        }
+    }
+#undef E4_AUX
+}

@@ -250,6 +250,13 @@ def test_wide_tile_gemm_copies_and_scalars():
     _check_valu_sgpr_to_vmem(text, "gemm_mx.hip")
 
 
+def test_fp32_ring_copies_and_scalars():
+    text = _assembly("f32_linear.hip")
+    assert sum("f32_tile_kernel" in n for n in _functions(text)) == 10      # five tile forms x two orientations of W
+    _check_m0(text, "f32_linear.hip")
+    _check_valu_sgpr_to_vmem(text, "f32_linear.hip")
+
+
 def test_vector_written_scalars_are_settled_before_vector_memory_reads_them(gemm_asm, tile_asm):
     _check_valu_sgpr_to_vmem(gemm_asm, "gemm.hip")
     _check_valu_sgpr_to_vmem(tile_asm, "gemm_tile.hip")
