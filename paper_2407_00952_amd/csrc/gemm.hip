@@ -26,18 +26,25 @@ constexpr int BM = 256, BN = 256, BK = 64, NTHR = 512;
 constexpr int ROWB = BK * 2;                 // bytes per LDS row (one k-slab of a tile row)
 constexpr int XB = BM * ROWB, WB = BN * ROWB;
 
-#define SL_WAIT_VM0() __builtin_amdgcn_s_waitcnt(0x0F70)   // vmcnt(0): this wave's copies have landed
-
 // NZ = number of rank-space columns handled in the K loop: 16 per adapter whose down-projection
-// spans this K range (0, 16, 32 or 48).  K2P = NZ rounded up to the MFMA k-step of 32.
+// spans this K range (16, 32 or 48).  K2P = NZ rounded up to the MFMA k-step of 32.
+//
+// Bound by the matrix pipe's rate under the power limit once nothing waits in front of it; the loop is there to get to that.
+// Fragments are read AHEAD row tiles before their MFMAs, one after each row tile's products, and the copies of the slab
+// after the next go out one or two behind each row tile, so neither the LDS queue nor the copy queue ever holds a wave up;
+// one barrier per slab, where the last fragments of its buffer have been read.  Every LDS read is at one of two lane
+// offsets plus a scalar: with an address register for each, 28 to 96 bytes of the loop's values were spilled, which cost
+// all of the gain.  us at 32768 rows, rank-space columns 16 / 32 / 48, against a loop that read all fragments of a k-step and
+// then multiplied: 4096 -> 1024 254 -> 225, 257 -> 233, 270 -> 262; 1024 -> 4096 285 -> 270, 292 -> 280, 319 -> 312;
+// 10240 x 768 -> 2304 48.0 -> 45.4, 49.9 -> 47.2, 55.8 -> 54.2.
 template <int EPI, int NZ>
 __global__ __launch_bounds__(NTHR) void gemm_kernel(GemmArgs a)
 {
     constexpr int ZB = NZ * ROWB, STAGE = XB + WB + ZB;
-    constexpr int K2P = NZ > 0 ? (NZ + 31) / 32 * 32 : 32;   // (32 keeps array sizes legal when NZ = 0)
-    constexpr int NZT = NZ > 0 ? NZ / 16 : 1;            // 16-column tiles of z
-    // two pipeline stages as separate objects, so that reads of one are not ordered behind the
-    // asynchronous copies into the other
+    constexpr int K2P = (NZ + 31) / 32 * 32;
+    constexpr int NZT = NZ / 16;                         // 16-column tiles of z
+    // 8 where the registers hold them (4: 16 columns 225 -> 239 us at 32768 x 4096 -> 1024; 8: 48 columns spill, 262 -> 392)
+    constexpr int AHEAD = NZ <= 32 ? 8 : 4;
     __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE];
     __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE];
 
@@ -68,7 +75,7 @@ __global__ __launch_bounds__(NTHR) void gemm_kernel(GemmArgs a)
     const int n_end = (seg + 1) * a.seg_n;
     const int m0 = tm * BM;
 
-    const bool has_z = (NZ > 0) && (a.zmat[seg] != nullptr);
+    const bool has_z = a.zmat[seg] != nullptr;
 
     // ---- global -> LDS: every wave copies 32 rows of the X tile and 32 rows of the W tile per
     //      stage, 8 rows (1 KB) per instruction.  Lane l fills 16-byte slot l of the 1 KB chunk:
@@ -83,10 +90,11 @@ __global__ __launch_bounds__(NTHR) void gemm_kernel(GemmArgs a)
         xo[p] = ((unsigned)row * (unsigned)a.ldx + lch * 8) * 2u;
         wo[p] = ((unsigned)n * (unsigned)a.ldw + lch * 8) * 2u;
     }
-    const bool zload = (NZ > 0) && has_z && (wave < NZ / 8);
-    const unsigned zo = zload ? ((unsigned)(wave * 8 + lrow) * (unsigned)a.ldz + lch * 8) * 2u : 0u;
+    // waves 0 .. NZ/8 - 1 copy 8 rows of Z each (all ones there, otherwise no lane is active)
+    const int zlanes = (wave - (has_z ? NZ / 8 : 0)) >> 31;
+    const unsigned zo = ((unsigned)(wave * 8 + lrow) * (unsigned)a.ldz + lch * 8) * 2u;
     const char *Xb = (const char *)a.X, *Wb = (const char *)a.W;
-    const char *Zb = (NZ > 0 && has_z) ? (const char *)a.zmat[seg] : (const char *)a.X;
+    const char *Zb = has_z ? (const char *)a.zmat[seg] : (const char *)a.X;
     const int wofs = wave * 32 * ROWB;
 
     // wave tile 128 x 64 = 8 x 4 MFMA 16x16x32 tiles; lane holds column r16, rows 4 kg + e of each
@@ -106,80 +114,87 @@ __global__ __launch_bounds__(NTHR) void gemm_kernel(GemmArgs a)
 #pragma unroll
             for (int e = 0; e < 4; ++e) zacc[h][q][e] = 0.0f;
 
-    const int a_row = (wm * 128 + r16) * ROWB;
-    const int b_row = (wn * 64 + r16) * ROWB;
-    const int z_row = (wm * 128 + wn * 32 + r16) * ROWB;
-    const int sw = r16 & 7;
-
-#define GEMM_ISSUE1(st, k0, p)                                        \
-    {                                                                 \
-        glds_soff(Xb + (size_t)(k0) * 2, xo[p], lds_addr(st) + wofs + (p) * 1024);     \
-        glds_soff(Wb + (size_t)(k0) * 2, wo[p], lds_addr(st) + XB + wofs + (p) * 1024); \
-        if (NZ > 0 && (p) == 0 && zload) glds_soff(Zb + (size_t)(k0) * 2, zo, lds_addr(st) + XB + WB + wave * 1024); \
-    }
-    // one MFMA k-step of 32: operands in two halves of 4 row tiles to keep the live registers low
-#define GEMM_STEP(st, k2)                                                                              \
-    {                                                                                                  \
-        const unsigned char *Xs = (st), *Ws = (st) + XB, *Zs = (st) + XB + WB;                         \
-        const int co = (((k2) * 4 + kg) ^ sw) << 4;                                                    \
-        bf16x8 bfr[4];                                                                                 \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                  \
-            bfr[j] = *(const bf16x8 *)(Ws + b_row + j * 16 * ROWB + co);                               \
-        _Pragma("unroll") for (int ih = 0; ih < 2; ++ih) {                                             \
-            bf16x8 af[4];                                                                              \
-            _Pragma("unroll") for (int i = 0; i < 4; ++i)                                              \
-                af[i] = *(const bf16x8 *)(Xs + a_row + (ih * 4 + i) * 16 * ROWB + co);                 \
-            _Pragma("unroll") for (int i = 0; i < 4; ++i)                                              \
-                _Pragma("unroll") for (int j = 0; j < 4; ++j)                                          \
-                    acc[ih * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(                      \
-                        af[i], bfr[j], acc[ih * 4 + i][j], 0, 0, 0);                                   \
-            if (NZ > 0) __builtin_amdgcn_sched_barrier(0);                                             \
-        }                                                                                              \
-        if (NZ > 0 && has_z) {                                                                         \
-            bf16x8 za[2];                                                                              \
-            _Pragma("unroll") for (int h = 0; h < 2; ++h)                                              \
-                za[h] = *(const bf16x8 *)(Xs + z_row + h * 16 * ROWB + co);                            \
-            _Pragma("unroll") for (int q = 0; q < NZT; ++q) {                                          \
-                const bf16x8 zb = *(const bf16x8 *)(Zs + (q * 16 + r16) * ROWB + co);                  \
-                _Pragma("unroll") for (int h = 0; h < 2; ++h)                                          \
-                    zacc[h][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(za[h], zb, zacc[h][q], 0, 0, 0); \
-            }                                                                                          \
-        }                                                                                              \
-    }
-    // one k-slab of 64: the copies for the next slab are issued half at a time before the two MFMA
-    // groups so that no wave sits in the memory-issue queue while its MFMAs wait
-#define GEMM_PHASE(cur, nxt, k0, doload)                              \
-    {                                                                 \
-        if (doload) { GEMM_ISSUE1(nxt, k0, 0) GEMM_ISSUE1(nxt, k0, 1) } \
-        GEMM_STEP(cur, 0) __builtin_amdgcn_sched_barrier(0);          \
-        if (doload) { GEMM_ISSUE1(nxt, k0, 2) GEMM_ISSUE1(nxt, k0, 3) } \
-        GEMM_STEP(cur, 1) __builtin_amdgcn_sched_barrier(0);          \
-    }
-
+    // Row tile i of the wave is tile (i + 2 wn) mod 8 of its 128 rows: the two whose rank-space activations it forms come
+    // first, so that their products use the fragments that are there.
+    const int rot = 2 * wn;
+    // lane offsets of k-steps 0 and 1; the tile's place is a scalar
+    const unsigned v0 = r16 * ROWB + ((kg ^ (r16 & 7)) << 4), v1 = v0 ^ 64;
+    const unsigned sa = wm * 128 * ROWB, sb = XB + wn * 64 * ROWB;
+    const unsigned l0 = lds_addr(st0), l1 = lds_addr(st1);
     const int nk = a.K / BK;
-    GEMM_ISSUE1(st0, 0, 0) GEMM_ISSUE1(st0, 0, 1) GEMM_ISSUE1(st0, 0, 2) GEMM_ISSUE1(st0, 0, 3)
-    SL_WAIT_VM0();
+    constexpr int NCP = 9, TURN = 8 - AHEAD;             // copies of a wave per slab; the row tile that reads the next step's first
+    bf16x8 fa[AHEAD], fb[2][4], fz[NZT];
+    auto rd = [&](unsigned v, unsigned s) { return *(const __attribute__((address_space(3))) bf16x8 *)(v + s); };
+    auto copy1 = [&](unsigned st, int kt, int q) {
+        const size_t kb = (size_t)min(kt, nk - 1) * (BK * 2);    // (behind the last slab: it once more, unread)
+        if (q < 4) glds_soff(Xb + kb, xo[q & 3], st + wofs + (q & 3) * 1024);
+        else if (q < 8) glds_soff(Wb + kb, wo[q & 3], st + XB + wofs + (q & 3) * 1024);
+        else glds_soff_if(Zb + kb, zo, st + XB + WB + wave * 1024, zlanes);
+    };
+    // row tile i on the column fragments cb, then the reads that have become free: of row tile i + AHEAD, whose step has its
+    // slab at S and lane offset v, and from TURN on of the next step's columns and rank-space columns
+#define GEMM_ROW(i, cb, S, v)                                                                          \
+    {                                                                                                  \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                  \
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[(i) % AHEAD], fb[cb][j], acc[i][j], 0, 0, 0); \
+        if ((i) < 2 && has_z) {                                                                        \
+            _Pragma("unroll") for (int q = 0; q < NZT; ++q)                                            \
+                zacc[(i) & 1][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[(i) % AHEAD], fz[q], zacc[(i) & 1][q], 0, 0, 0); \
+        }                                                                                              \
+        fa[(i) % AHEAD] = rd(v, (S) + sa + (((i) + AHEAD + rot) & 7) * (16 * ROWB));                   \
+        if ((i) >= TURN && (i) < TURN + 4) fb[1 - (cb)][((i) - TURN) & 3] = rd(v, (S) + sb + (((i) - TURN) & 3) * (16 * ROWB)); \
+        if ((i) >= 4 && (i) - 4 < NZT) fz[((i) & 3) % NZT] = rd(v, (S) + XB + WB + ((i) & 3) * (16 * ROWB)); \
+    }
+    // one slab; behind the barrier its buffer takes the slab after the next, which has until the next slab's barrier to land.
+    // (The scalars are made opaque: else the compiler keeps the sum of each with each lane offset.)
+#define GEMM_SLAB(lc, ln)                                                                              \
+    {                                                                                                  \
+        unsigned sc = lc, sn = ln;                                                                     \
+        asm volatile("" : "+s"(sc));                                                                   \
+        _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                \
+            if (i < TURN) GEMM_ROW(i, 0, sc, v0) else GEMM_ROW(i, 0, sc, v1)                           \
+            __builtin_amdgcn_sched_barrier(0);                                                         \
+        }                                                                                              \
+        _Pragma("unroll") for (int i = 0; i < TURN; ++i) {                                             \
+            GEMM_ROW(i, 1, sc, v1)                                                                     \
+            __builtin_amdgcn_sched_barrier(0);                                                         \
+        }                                                                                              \
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");                                    \
+        __syncthreads();                                                                               \
+        asm volatile("" : "+s"(sn));                                                                   \
+        _Pragma("unroll") for (int i = TURN; i < 8; ++i) {                                             \
+            GEMM_ROW(i, 1, sn, v0)                                                                     \
+            _Pragma("unroll") for (int q = 0; q < NCP; ++q)                                            \
+                if (q >= (i - TURN) * NCP / AHEAD && q < (i - TURN + 1) * NCP / AHEAD) copy1(lc, kt + 2, q); \
+            __builtin_amdgcn_sched_barrier(0);                                                         \
+        }                                                                                              \
+    }
+#pragma unroll
+    for (int q = 0; q < NCP; ++q) copy1(l0, 0, q);
+#pragma unroll
+    for (int q = 0; q < NCP; ++q) copy1(l1, 1, q);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCP) : "memory");
     __syncthreads();
-    int kt = 0;
-    for (; kt + 2 <= nk; kt += 2) {
-        GEMM_PHASE(st0, st1, (kt + 1) * BK, true)
-        SL_WAIT_VM0();
-        __syncthreads();
-        const bool more = kt + 2 < nk;
-        GEMM_PHASE(st1, st0, (kt + 2) * BK, more)
-        SL_WAIT_VM0();
-        __syncthreads();
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) fa[i] = rd(v0, l0 + sa + ((i + rot) & 7) * (16 * ROWB));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) fb[0][j] = rd(v0, l0 + sb + j * (16 * ROWB));
+#pragma unroll
+    for (int q = 0; q < NZT; ++q) fz[q] = rd(v0, l0 + XB + WB + q * (16 * ROWB));
+    for (int kt = 0;;) {
+        GEMM_SLAB(l0, l1)
+        if (++kt >= nk) break;
+        GEMM_SLAB(l1, l0)
+        if (++kt >= nk) break;
     }
-    if (kt < nk) {
-        GEMM_PHASE(st0, st1, 0, false)
-        __syncthreads();
-    }
-#undef GEMM_ISSUE1
-#undef GEMM_STEP
-#undef GEMM_PHASE
+#undef GEMM_ROW
+#undef GEMM_SLAB
+    // the copies and reads behind the last slab are done before its buffers are used for anything else
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
 
     // ---- low-rank tail: acc += (zscale * z)[256,K2P] . T[n,K2P]^T -----------------------------
-    if (NZ > 0 && has_z) {
+    if (has_z) {
         constexpr int ZP = K2P + 8;                      // LDS pitch of the z tile, in elements
         bf16 *zs = (bf16 *)st0;                          // the K loop is over: reuse stage 0
         const bf16 *tm_ = a.tmat[seg];
@@ -219,7 +234,7 @@ __global__ __launch_bounds__(NTHR) void gemm_kernel(GemmArgs a)
                 bf16x8 af[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    af[i] = *(const bf16x8 *)(zs + (wm * 128 + (ih * 4 + i) * 16 + r16) * ZP + ks * 32 + kg * 8);
+                    af[i] = *(const bf16x8 *)(zs + (wm * 128 + ((ih * 4 + i + rot) & 7) * 16 + r16) * ZP + ks * 32 + kg * 8);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -235,7 +250,7 @@ __global__ __launch_bounds__(NTHR) void gemm_kernel(GemmArgs a)
     //      sees 16-byte accesses, 8 rows x 128..256 contiguous bytes per instruction.  Only the
     //      owning wave touches its strip, so no block barrier is needed.
     constexpr int EP = 68;                               // strip pitch in floats (bank-conflict free)
-    if (NZ > 0 && has_z) __syncthreads();                // the z tile in st0 has been consumed
+    if (has_z) __syncthreads();                          // the z tile in st0 has been consumed
     float *stg = (float *)((wave < 4 ? st0 : st1) + (wave & 3) * (32 * EP * 4));
     const int er = lane >> 3, ec = (lane & 7) * 8;
     const int gcol = n0 + wn * 64 + ec;
@@ -250,17 +265,18 @@ __global__ __launch_bounds__(NTHR) void gemm_kernel(GemmArgs a)
     }
     AuxRow aux[2][4];
     const int row_base = m0 + wm * 128 + er;
+    auto strip = [&](int i) { return ((2 * i + rot) & 7) * 16; };      // first row of strip i: its row tiles 2 i and 2 i + 1
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
-        const int row = row_base + it * 8;
+        const int row = row_base + strip(0) + it * 8;
         load_aux<EPI>(a, row, gcol, row < a.M && gcol < n_end, aux[0][it]);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {                        // strip i = rows 32 i .. 32 i + 31 of the wave tile
+    for (int i = 0; i < 4; ++i) {
         if (i + 1 < 4) {
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
-                const int row = row_base + (i + 1) * 32 + it * 8;
+                const int row = row_base + strip(i + 1) + it * 8;
                 load_aux<EPI>(a, row, gcol, row < a.M && gcol < n_end, aux[(i + 1) & 1][it]);
             }
         }
@@ -278,7 +294,7 @@ __global__ __launch_bounds__(NTHR) void gemm_kernel(GemmArgs a)
             const float4 p1 = *(const float4 *)(stg + rl * EP + ec + 4);
             float v[8] = {p0.x + bias8[0], p0.y + bias8[1], p0.z + bias8[2], p0.w + bias8[3],
                           p1.x + bias8[4], p1.y + bias8[5], p1.z + bias8[6], p1.w + bias8[7]};
-            const int row = m0 + wm * 128 + i * 32 + rl;
+            const int row = m0 + wm * 128 + strip(i) + rl;
             if (row < a.M && gcol < n_end) store_row8<EPI>(a, row, gcol, v, aux[i & 1][it]);
         }
     }

@@ -80,7 +80,7 @@ constexpr Form FORMS[3][9] = {
      {192, 128, {5.53f, .424f}, {}, {5.53f, .689f}},
      {256, 128, {6.05f, .591f}, {}, {6.46f, .896f}},
      {},
-     {256, 256, {6.90f, 1.251f}, {}, {5.38f, 1.867f}}},
+     {256, 256, {6.80f, 1.083f}, {}, {5.00f, 1.690f}}},
     {{32, 32, {3.48f, .181f}, {5.18f, .384f}, {3.46f, .371f}},          // 32 or 48
      {32, 64, {2.51f, .355f}, {4.33f, .403f}, {2.00f, .446f}},
      {64, 64, {3.55f, .270f}, {4.37f, .474f}, {2.00f, .552f}},
@@ -89,7 +89,7 @@ constexpr Form FORMS[3][9] = {
      {192, 128, {7.54f, .515f}, {}, {7.47f, .806f}},
      {},
      {},
-     {256, 256, {8.38f, 1.413f}, {}, {8.68f, 1.980f}}}};
+     {256, 256, {8.10f, 1.342f}, {}, {6.20f, 1.950f}}}};
 
 double form_cost(const Form &f, long tiles, int nk)
 {
