@@ -18,6 +18,7 @@
 // probabilities and dP are formed once (see attn_bwd_fused_kernel).
 // No kernel uses floating-point atomics, so results are bit-reproducible.
 #include "common.h"
+#include "gemm_copy.h"
 #include "prof.h"
 
 namespace {
@@ -27,9 +28,10 @@ constexpr int TILE_B = 64 * 128;                             // one 64-row x 64-
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 
-#define AT_GLDS(gp, lp)                                                                            \
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gp),         \
-                                     (__attribute__((address_space(3))) void *)(lp), 16, 0, 0)
+// One 1 KB asynchronous copy: scalar base, the lane's byte offset, LDS place.  (The compiler's own form of it is known to
+// the compiler as a write of LDS: it then waits for the copies in flight, those of the NEXT tile, in front of the first
+// LDS read of every inner iteration of the two backward kernels.)
+#define AT_GLDS(gp, off, lp) glds_soff(gp, off, lds_addr(lp))
 #define AT_WAIT_VM0() __builtin_amdgcn_s_waitcnt(0x0F70)
 
 // XOR mask of a tile row for the 16-byte chunks of its 128-byte LDS row.  Eight consecutive rows get
@@ -55,7 +57,7 @@ __device__ __forceinline__ void tile_copy_async(unsigned char *dst, const bf16 *
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
         const int r0 = (wave * 2 + p) * 8;
-        AT_GLDS(src + (size_t)(r0 + lrow) * ld + lch * 8, dst + r0 * 128);
+        AT_GLDS(src + (size_t)r0 * ld, (unsigned)(lrow * ld + lch * 8) * 2u, dst + r0 * 128);
     }
 }
 
@@ -104,6 +106,15 @@ __device__ __forceinline__ bf16x8 read_tr(const unsigned char *p)
     return u.v;
 }
 
+__device__ __forceinline__ bf16x8 lds_b128(unsigned a) { return *(const __attribute__((address_space(3))) bf16x8 *)a; }
+__device__ __forceinline__ bf16x8 lds_tr(unsigned a)
+{
+    union { v4s s[2]; bf16x8 v; } u;
+    u.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)a);
+    u.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)(a + 1024));
+    return u.v;
+}
+
 constexpr int OST_PITCH = 144;                                // bytes per staged output row (128 + pad: see fwd_store)
 constexpr int OST_B = 32 * OST_PITCH;
 
@@ -113,7 +124,7 @@ __device__ __forceinline__ void rows32_copy_async(unsigned char *dst, const bf16
 {
     const int lrow = lane >> 3, lch = (lane & 7) ^ swm(lane >> 3);
 #pragma unroll
-    for (int p = 0; p < 4; ++p) AT_GLDS(src + (size_t)(p * 8 + lrow) * ld + lch * 8, dst + p * 1024);
+    for (int p = 0; p < 4; ++p) AT_GLDS(src + (size_t)(p * 8) * ld, (unsigned)(lrow * ld + lch * 8) * 2u, dst + p * 1024);
 }
 
 // 32 rows x 64 columns held as two MFMA accumulators (a lane has 4 consecutive columns of row r32 per register group)
@@ -317,10 +328,7 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_kernel(const bf16 *__restrict
     const bf16 *kg = base + d, *vg = base + 2 * d;
     FWD_COPY(K0, V0, 0)
     if (ntB > 0) {                                       // this wave's 32 Q rows of the short tile -> its staging area
-        const int lrow = lane >> 3, lch = (lane & 7) ^ swm(lane >> 3);
-        const bf16 *qsrc = base + (size_t)(qtB * 128 + wave * 32) * ld;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) AT_GLDS(qsrc + (size_t)(p * 8 + lrow) * ld + lch * 8, Ost + wave * OST_B + p * 1024);
+        rows32_copy_async(Ost + wave * OST_B, base + (size_t)(qtB * 128 + wave * 32) * ld, ld, lane);
     }
     AT_WAIT_VM0();
     __syncthreads();
@@ -347,7 +355,9 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_kernel(const bf16 *__restrict
 // the CU's other block.  So: one copy of the 32 x 32 body (all operand reads of a product issued before its first MFMA;
 // a copy per case spilled), LDS offsets formed once per lane, -delta carried into dP as the accumulator's start, the
 // mask only on the diagonal half, and Q, dO, O and dQ moved as whole 128-byte lines.  S = 1024, 32 x 16 heads, with the
-// dK/dV kernel: 412 -> 372 us; three blocks per CU instead of two spill and take 4 us more.
+// dK/dV kernel: 412 -> 372 us; three blocks per CU instead of two spill and take 4 us more.  With copies that the
+// compiler does not wait for in front of the operand reads (see AT_GLDS): 219 -> 187 us, dK/dV 235 -> 210, at S = 1024,
+// 320 heads.
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16 *__restrict__ qkv, const bf16 *__restrict__ o,
                                                           const bf16 *__restrict__ o_lo,
                                                           const bf16 *__restrict__ dout,
@@ -537,8 +547,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(const bf16 *__rest
         const int q0 = q_first + j * 64;
         tile_copy_async(QD[j & 1], base + (size_t)q0 * ld, ld, wave, lane);
         tile_copy_async(QD[j & 1] + TILE_B, dbase + (size_t)q0 * d, d, wave, lane);
-        if (tid < 64) stat = lse_b[q0 + tid];
-        else if (tid < 128) stat = -dl_b[q0 + tid - 64];
+        if (tid < 128) stat = (tid < 64 ? lse_b : dl_b - 64)[q0 + tid];      // (the sign of delta: at the store, behind the wait)
     };
     issue(0);
     // this wave's rows of K (its staging area) and V (the second buffer, still free) as whole lines
@@ -548,7 +557,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(const bf16 *__rest
         rows32_copy_async(stg, base + d + (size_t)kb * ld, ld, lane);
         rows32_copy_async(v_s, base + 2 * d + (size_t)kb * ld, ld, lane);
     }
-    if (tid < 128) st[0][tid] = stat;
+    if (tid < 128) st[0][tid] = tid < 64 ? stat : -stat;
     AT_WAIT_VM0();
     asm volatile("" ::: "memory");
     if (active) {
@@ -622,7 +631,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(const bf16 *__rest
                 }
             }
         }
-        if (j + 1 < ntile && tid < 128) st[(j + 1) & 1][tid] = stat;
+        if (j + 1 < ntile && tid < 128) st[(j + 1) & 1][tid] = tid < 64 ? stat : -stat;
     }
 
     if (active) {
@@ -653,6 +662,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(const bf16 *__rest
 //     compute unit at once, at the memory's speed, with the matrix cores idle; forming delta tile by tile
 //     behind the arithmetic, from rows streamed into LDS, was measured and only moved the same time into the
 //     steps, whose length is set by the latency of the tile copies.)
+//   * The two blocks' accumulators and V fragments leave 96 registers.  With an address register for every buffer and
+//     offset, 84 bytes of V were spilled, and each reload waited for the copies in flight; offsets formed once per lane
+//     and buffers as scalars: 216 -> 189 us (S = 512, 64 x 16 heads), 12.3 -> 9.0 (S = 128, 12 heads).
 constexpr int FB_MAXS = 512;
 
 // XOR mask of the 8-byte slots of a dS^T row (64 bytes = 32 queries): conflict-free both for the
@@ -660,6 +672,7 @@ constexpr int FB_MAXS = 512;
 // (16 lanes = 4 consecutive keys x 4 slots)
 __device__ __forceinline__ int dsm(int key) { return (((key >> 1) & 1) << 2) | ((key >> 2) & 3); }
 
+constexpr int FB_TILE = 32 * 128;
 __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16 *__restrict__ qkv, const bf16 *__restrict__ o,
                                                              const bf16 *__restrict__ o_lo,
                                                              const bf16 *__restrict__ dout,
@@ -668,8 +681,9 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16 *__restr
 {
     __shared__ __attribute__((aligned(1024))) unsigned char Ks[FB_MAXS * 128];
     __shared__ __attribute__((aligned(1024))) unsigned char dS0[FB_MAXS * 64], dS1[FB_MAXS * 64];
-    __shared__ __attribute__((aligned(1024))) unsigned char Qb0[32 * 128], Db0[32 * 128], Qb1[32 * 128], Db1[32 * 128];
-    __shared__ __align__(16) float lse_s[FB_MAXS], dl_s[FB_MAXS];
+    __shared__ __attribute__((aligned(1024))) unsigned char QD0[2 * FB_TILE], QD1[2 * FB_TILE];      // a tile of Q, then of dO
+    __shared__ __align__(16) float lse_s[2 * FB_MAXS];                                               // lse, then delta
+    float *const dl_s = lse_s + FB_MAXS;
     const int a = blockIdx.x, n = blockIdx.y;
     const int d = H * 64, ld = 3 * d;
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
@@ -680,17 +694,18 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16 *__restr
     const int nb = S >> 5;                               // 32-row blocks (even: S is a multiple of 64)
 
     // one 1 KB piece per wave and tile of Q (waves 0-3) and dO (waves 4-7), and the tile's 32 K rows (waves 0-3)
-#define FB_COPY(Qd, Dd, it)                                                                            \
+#define FB_COPY(QD, it)                                                                                \
     {                                                                                                  \
         const int lrow_c = lane >> 3, lch_c = (lane & 7) ^ swm(lane >> 3);                             \
-        const int row_c = 32 * (it) + (wave & 3) * 8 + lrow_c;                                         \
+        const int row_c = 32 * (it) + (wave & 3) * 8;                                                  \
         if (wave < 4) {                                                                                \
-            AT_GLDS(base + (size_t)row_c * ld + lch_c * 8, (Qd) + (wave & 3) * 1024);                  \
-            AT_GLDS(base + d + (size_t)row_c * ld + lch_c * 8, Ks + (it) * 4096 + (wave & 3) * 1024);  \
-        } else AT_GLDS(dbase + (size_t)row_c * d + lch_c * 8, (Dd) + (wave & 3) * 1024);               \
+            const unsigned off_c = (unsigned)(lrow_c * ld + lch_c * 8) * 2u;                           \
+            AT_GLDS(base + (size_t)row_c * ld, off_c, (QD) + (wave & 3) * 1024);                       \
+            AT_GLDS(base + d + (size_t)row_c * ld, off_c, Ks + (it) * 4096 + (wave & 3) * 1024);       \
+        } else AT_GLDS(dbase + (size_t)row_c * d, (unsigned)(lrow_c * d + lch_c * 8) * 2u, (QD) + FB_TILE + (wave & 3) * 1024); \
     }
     // ---- prologue: first tile (Q, dO, K rows), log-sum-exp and delta of all rows, this wave's V fragments
-    FB_COPY(Qb0, Db0, 0)
+    FB_COPY(QD0, 0)
     if (tid < S) lse_s[tid] = lse[((size_t)n * H + a) * S + tid];
     // up to 8 key blocks (256 tokens) every wave owns one at most; waves without a block only do phase 2
     const bool single = nb <= 8;
@@ -734,21 +749,29 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16 *__restr
             }
     }
     f32x16 dkacc[2][2], dvacc[2][2];
+    // lane offsets of the operand reads and of the dS^T stores (row r32: its swizzle does not look above bit 3); the
+    // buffers come in as scalars that the compiler cannot see through, else it keeps the sum of each with each offset
+    int rm[4], tr[2];
+    frag_offsets(lane, rm, tr);
+    const unsigned ds_st = r32 * 64 + ((g ^ dsm(r32)) << 3);
     // phase 1 for query tile `it` (rows 32 it ..) against this wave's blocks that it can see.  Only the
     // block on the diagonal (j == it) needs the causal mask; the blocks below it run a copy without it.
-#define FB_BLOCK(Qs, Ds, dSw, it, b, j, DIAG)                                                          \
+#define FB_BLOCK(QD, dSw, it, b, j, DIAG)                                                              \
     {                                                                                                  \
         f32x16 sacc = zero16(), dpacc = zero16();                                                      \
+        unsigned s_q = lds_addr(QD), s_k = lds_addr(Ks) + (j) * 4096, s_l = lds_addr(lse_s) + (it) * 128, \
+                 s_d = lds_addr(dSw) + (j) * 2048;                                                     \
+        asm volatile("" : "+s"(s_q), "+s"(s_k), "+s"(s_l), "+s"(s_d));                                 \
         _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {                                             \
-            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rm(Qs, r32, ks, g),                    \
-                                                            frag_rm(Ks, 32 * (j) + r32, ks, g), sacc, 0, 0, 0); \
-            dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rm(Ds, r32, ks, g), vf[b][ks],        \
-                                                             dpacc, 0, 0, 0);                          \
+            const unsigned aq = s_q + rm[ks];                                                          \
+            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_b128(aq), lds_b128(s_k + rm[ks]), sacc, 0, 0, 0); \
+            dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_b128(aq + FB_TILE), vf[b][ks], dpacc, 0, 0, 0); \
         }                                                                                              \
+        const unsigned al = s_l + 16 * g, ad = s_d + ds_st;                                            \
         _Pragma("unroll") for (int e4 = 0; e4 < 4; ++e4) {                                             \
             const int ql = 8 * e4 + 4 * g;                                                             \
-            const f32x4 ls = *(const f32x4 *)(lse_s + 32 * (it) + ql);                                 \
-            const f32x4 dd = *(const f32x4 *)(dl_s + 32 * (it) + ql);                                  \
+            const f32x4 ls = *(const __attribute__((address_space(3))) f32x4 *)(al + 32 * e4);         \
+            const f32x4 dd = *(const __attribute__((address_space(3))) f32x4 *)(al + 32 * e4 + FB_MAXS * 4); \
             bf16x4 dst4;                                                                               \
             _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                            \
                 const int e = 4 * e4 + i;                                                              \
@@ -758,8 +781,7 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16 *__restr
                 dpacc[e] = p * (dpacc[e] - dd[i]);                                                     \
                 dst4[i] = f2bf(dpacc[e]);                                                              \
             }                                                                                          \
-            const int key = 32 * (j) + r32;                                                            \
-            *(bf16x4 *)((dSw) + key * 64 + (((2 * e4 + g) ^ dsm(key)) << 3)) = dst4;                   \
+            *(__attribute__((address_space(3))) bf16x4 *)(ad ^ (e4 << 4)) = dst4;                      \
         }                                                                                              \
         _Pragma("unroll") for (int hh = 0; hh < 2; ++hh) {                                             \
             bf16x8 pb, dsb;                                                                            \
@@ -768,18 +790,17 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16 *__restr
                 dsb[i] = f2bf(dpacc[8 * hh + i]);                                                      \
             }                                                                                          \
             _Pragma("unroll") for (int dt = 0; dt < 2; ++dt) {                                         \
-                dvacc[b][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                                \
-                    frag_tr(Ds, 32 * dt, 16 * hh, lane), pb, dvacc[b][dt], 0, 0, 0);                   \
-                dkacc[b][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                                \
-                    frag_tr(Qs, 32 * dt, 16 * hh, lane), dsb, dkacc[b][dt], 0, 0, 0);                  \
+                const unsigned at = s_q + tr[dt] + 2048 * hh;                                          \
+                dvacc[b][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr(at + FB_TILE), pb, dvacc[b][dt], 0, 0, 0); \
+                dkacc[b][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr(at), dsb, dkacc[b][dt], 0, 0, 0); \
             }                                                                                          \
         }                                                                                              \
     }
-#define FB_PHASE1(Qs, Ds, dSw, it)                                                                     \
+#define FB_PHASE1(QD, dSw, it)                                                                         \
     if (owner) {                                                                                       \
         _Pragma("unroll") for (int b = 0; b < 2; ++b) {                                                \
             const int j = jb[b];                                                                       \
-            if (j <= (it)) { const bool diag = j == (it); FB_BLOCK(Qs, Ds, dSw, it, b, j, diag) }      \
+            if (j <= (it)) { const bool diag = j == (it); FB_BLOCK(QD, dSw, it, b, j, diag) }          \
             __builtin_amdgcn_sched_barrier(0);           /* keep the two blocks' live ranges apart */   \
         }                                                                                              \
     }
@@ -818,22 +839,22 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16 *__restr
 
     AT_WAIT_VM0();
     __syncthreads();                                     // tile 0, its K rows and the statistics it needs are in LDS
-    if (nb > 1) FB_COPY(Qb1, Db1, 1)
+    if (nb > 1) FB_COPY(QD1, 1)
 #pragma unroll
     for (int b = 0; b < 2; ++b) { dkacc[b][0] = zero16(); dkacc[b][1] = zero16(); dvacc[b][0] = zero16(); dvacc[b][1] = zero16(); }
-    FB_PHASE1(Qb0, Db0, dS0, 0)
+    FB_PHASE1(QD0, dS0, 0)
     for (int it = 0; it < nb; it += 2) {
         AT_WAIT_VM0();
         __syncthreads();                                 // dS^T of tile it complete; tile it + 1 and its K rows landed
-        if (it + 2 < nb) FB_COPY(Qb0, Db0, it + 2)
+        if (it + 2 < nb) FB_COPY(QD0, it + 2)
         FB_PHASE2(dS0, it)
-        if (it + 1 < nb) FB_PHASE1(Qb1, Db1, dS1, it + 1)
+        if (it + 1 < nb) FB_PHASE1(QD1, dS1, it + 1)
         if (it + 1 < nb) {
             AT_WAIT_VM0();
             __syncthreads();
-            if (it + 3 < nb) FB_COPY(Qb1, Db1, it + 3)
+            if (it + 3 < nb) FB_COPY(QD1, it + 3)
             FB_PHASE2(dS1, it + 1)
-            if (it + 2 < nb) FB_PHASE1(Qb0, Db0, dS0, it + 2)
+            if (it + 2 < nb) FB_PHASE1(QD0, dS0, it + 2)
         }
     }
 #undef FB_COPY

@@ -257,6 +257,20 @@ def test_fp32_ring_copies_and_scalars():
     _check_valu_sgpr_to_vmem(text, "f32_linear.hip")
 
 
+def test_attention_copies_and_scalars():
+    text = _assembly("attention.hip")
+    funcs = _functions(text)
+    assert sum("attn_" in n for n in funcs) == 4
+    _check_m0(text, "attention.hip")
+    _check_valu_sgpr_to_vmem(text, "attention.hip")
+    # the copies of the next tile run beside the products of this one: no wait for memory between a tile's first MFMA
+    # and its last in the backward of long sequences
+    for name, body in funcs.items():
+        if "attn_bwd_dq" in name or "attn_bwd_dkv" in name:
+            mf = [i for i, ins in enumerate(body) if ins.startswith("v_mfma")]
+            assert not any("vmcnt" in ins for ins in body[mf[0]:mf[-1] + 1]), name
+
+
 def test_vector_written_scalars_are_settled_before_vector_memory_reads_them(gemm_asm, tile_asm):
     _check_valu_sgpr_to_vmem(gemm_asm, "gemm.hip")
     _check_valu_sgpr_to_vmem(tile_asm, "gemm_tile.hip")
