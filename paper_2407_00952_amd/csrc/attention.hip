@@ -352,13 +352,15 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_kernel(const bf16 *__restrict
 // ------------------------------------------------------------------------------------------
 // dQ (and delta = rowsum(dO * O), which the dK/dV kernel reads afterwards)
 // Bound by the vector work between the products and by the operand rows of each query tile, which nothing hides but
-// the CU's other block.  So: one copy of the 32 x 32 body (all operand reads of a product issued before its first MFMA;
+// the CU's other blocks.  So: one copy of the 32 x 32 body (all operand reads of a product issued before its first MFMA;
 // a copy per case spilled), LDS offsets formed once per lane, -delta carried into dP as the accumulator's start, the
 // mask only on the diagonal half, and Q, dO, O and dQ moved as whole 128-byte lines.  S = 1024, 32 x 16 heads, with the
-// dK/dV kernel: 412 -> 372 us; three blocks per CU instead of two spill and take 4 us more.  With copies that the
-// compiler does not wait for in front of the operand reads (see AT_GLDS): 219 -> 187 us, dK/dV 235 -> 210, at S = 1024,
-// 320 heads.
-__global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16 *__restrict__ qkv, const bf16 *__restrict__ o,
+// dK/dV kernel: 412 -> 372 us.  With copies that the compiler does not wait for in front of the operand reads (see
+// AT_GLDS), at 32 x 20 heads: 219 -> 187 us, dK/dV 235 -> 210.  A half's 12 MFMAs (384 cycles) and 16 exponentials with
+// what belongs to them (about 520) overlap only between waves, so three blocks share a CU, for which -delta is written to
+// the 16 registers of dP's start anew for each half (held over the loop, they make 44 bytes spill): 187 -> 173 us.  The
+// dK/dV kernel, with four accumulators, would spill 180 bytes.
+__global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(const bf16 *__restrict__ qkv, const bf16 *__restrict__ o,
                                                           const bf16 *__restrict__ o_lo,
                                                           const bf16 *__restrict__ dout,
                                                           const float *__restrict__ lse, float *__restrict__ delta,
@@ -441,10 +443,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16 *__restr
     const int kv_end = min(S, qt * 128 + 128);
     const int ntile = kv_end >> 6;
 
-    // -delta as the addend of the dP product: dP - delta leaves the matrix cores ready
-    f32x16 ndl;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) ndl[e] = -dl;
     for (int j = 0; j < ntile; ++j) {
         AT_WAIT_VM0();
         __syncthreads();                                 // tile j has landed and nobody reads the other buffer any more
@@ -465,7 +463,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16 *__restr
                 fv[ks] = *(const bf16x8 *)(vt_ + rm[ks]);
             }
             __builtin_amdgcn_sched_barrier(0);
-            f32x16 sacc = zero16(), dpacc = ndl;
+            // -delta as the addend of the dP product: dP - delta leaves the matrix cores ready (opaque: else it is written
+            // out ahead of the loop and held)
+            float nd = -dl;
+            asm volatile("" : "+v"(nd));
+            f32x16 sacc = zero16(), dpacc;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) dpacc[e] = nd;
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
                 sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk[ks], qf[ks], sacc, 0, 0, 0);
