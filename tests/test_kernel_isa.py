@@ -16,7 +16,7 @@ test suite instead of corrupting results:
      longest, 16-pass, matrix instruction; the 16x16x32 bf16 one needs fewer) pass before the first
      instruction other than an MFMA that reads or writes an accumulation register;
   4. M0 is written only by the copy sequence (s_mov_b32 m0 / s_nop 0 / global_load_lds_*) and read by
-     nothing else, in gemm.hip, gemm_tile.hip and mx.hip;
+     nothing else, in every source whose kernels issue it;
   5. no vector memory instruction reads a scalar register that a vector instruction (v_readlane,
      v_readfirstlane, a compare with a scalar destination) wrote fewer than 5 wait states earlier.  The
      compiler keeps that distance for its own instructions but does not look into inline assembly, and the
