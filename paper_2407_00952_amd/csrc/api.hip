@@ -939,13 +939,13 @@ LinWs lin_ws(int T, int n_in, int n_out)
     // that a workspace taken for the most tokens serves fewer.
     w.total = w.long_chunks ? own : off;
     const size_t most = off <= own ? own : ~(size_t)0;
-    const int t_fwd = gemm_split_rows(n_out, n_in), t_bwd = gemm_split_rows(n_in, n_out);
+    const SplitPlan pf = plan_gemm_split(T, n_out, n_in, SL_RP), pb = plan_gemm_split(T, n_in, n_out, SL_RP);
     auto end_of = [&](size_t begin, size_t bytes) { return bytes ? begin + al256(gemm_split_counter_bytes()) + al256(bytes) : 0; };
-    const int t = std::min(T, t_bwd);
-    const size_t fwd = end_of(w.B16T, gemm_split_bytes(T, n_out, n_in, SL_RP));
-    const size_t bwd = end_of(at - 2 * (al256(2 * (size_t)T * 16) - al256(2 * (size_t)t * 16)), gemm_split_bytes(T, n_in, n_out, SL_RP));
-    w.share_fwd = T <= t_fwd && fwd && fwd <= most;
-    w.share_bwd = T <= t_bwd && bwd && bwd <= most;
+    const int t = std::min(T, pb.most_rows);
+    const size_t fwd = end_of(w.B16T, pf.bytes);
+    const size_t bwd = end_of(at - 2 * (al256(2 * (size_t)T * 16) - al256(2 * (size_t)t * 16)), pb.bytes);
+    w.share_fwd = pf.shared && fwd <= most;
+    w.share_bwd = pb.shared && bwd <= most;
     w.total = std::max(w.total, std::max(std::min(fwd, most), std::min(bwd, most)));
     return w;
 }

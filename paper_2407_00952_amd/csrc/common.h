@@ -103,7 +103,7 @@ struct GemmArgs {
     unsigned char *oq, *os;
     static constexpr bool kEmitCodes = false;   // the bf16 kernel never does
     // scratch for launches that share the contraction over blocks (null: they do not; contexts never do, so that a
-    // sequence's results do not depend on its batch): gemm_split_bytes(M, N, K, nz) of partial
+    // sequence's results do not depend on its batch): plan_gemm_split(M, N, K, nz).bytes of partial
     // sums, and gemm_split_counter_bytes() of counters, zero before the launch and left zero by it
     float *split_part; unsigned *split_cnt;
     // in device memory, or null: how many of the M rows are wanted, as an earlier kernel counted them (no rank-space branch; one
@@ -118,11 +118,13 @@ inline int gemm_counted_rows(int max_rows) { return max_rows <= 128 ? 128 : 256;
 // the tile of a product's kernel and over how many blocks a tile's contraction is shared: 128 x 256 and 256 x 256 are those
 // of gemm.hip, 128 columns and more than 64 rows those of gemm_wide.hip, the others those of gemm_tile.hip
 struct TilePlan { int tm, tn, splits; };
-TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int epi, int nz, bool can_split, bool whole);
+extern "C" TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int epi, int nz, bool can_split, bool whole);
 int launch_gemm_tile(const GemmArgs &a, int epi, int nz, const TilePlan &p, hipStream_t st);
 int launch_gemm_wide(const GemmArgs &a, int epi, int nz, const TilePlan &p, hipStream_t st);
-int gemm_split_rows(int N, int K);                       // the most rows at which a launch may do so (0: none does)
-size_t gemm_split_bytes(int M, int N, int K, int nz);    // enough for M rows or fewer
+// whether a plain-store launch of M rows (one segment) shares its contraction once it has scratch, the most rows at which one
+// does (0: none), and partial sums enough for M rows or fewer (they never fall as M grows)
+struct SplitPlan { bool shared; int most_rows; size_t bytes; };
+extern "C" SplitPlan plan_gemm_split(int M, int N, int K, int nz);
 size_t gemm_split_counter_bytes();
 // the same call with the frozen product in MXFP8 (a.mx set): converts X, forms the rank-space activations
 // of the adapted segments with a separate projection kernel (into a.zspill), then one fp8 GEMM launch

@@ -103,16 +103,18 @@ double form_cost(const Form &f, long tiles, int nk)
 
 }  // namespace
 
-// Over how many blocks a launch of t64 tiles of 64 x 64 and nk slabs shares its contraction, if it has scratch for that.
-// Combining the partial sums costs about 3 us, so a block keeps 9 slabs or more.
+// Over how many blocks a launch of t64 tiles of 64 x 64 and nk slabs may share its contraction, if it has scratch for that:
+// 32 tiles or fewer over four, 64 over three, 128 over two, so that every block has a CU.  A block keeps 9 slabs or more.
+constexpr long SPLIT_ENDS[3] = {32, 64, SPLIT_TILES};
 static int split_shares(long t64, int nk)
 {
-    const int s = t64 > SPLIT_TILES ? 1 : t64 > 64 ? 2 : t64 > 32 ? 3 : 4;
+    const int s = t64 > SPLIT_ENDS[2] ? 1 : t64 > SPLIT_ENDS[1] ? 2 : t64 > SPLIT_ENDS[0] ? 3 : 4;
     return std::max(1, std::min(s, nk / 9));
 }
 
 // The kernel for a product: the form that costs least (FORMS).  `whole`: the kernels of 256-column tiles may be picked too.
-// A shared contraction costs its blocks 3 us to combine their partial sums.
+// A shared contraction costs its blocks 3 us to combine their partial sums, so it takes 43 slabs or more to beat the forms of
+// 32 rows.
 TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int epi, int nz, bool can_split, bool whole)
 {
     const int nk = K / BK;
@@ -132,20 +134,32 @@ TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int epi, int nz, bool
     return best;
 }
 
-int gemm_split_rows(int N, int K)
+// Scratch by the decision above, so that a layer has none where its launch shares nothing.  The shared form costs the same at
+// every row count of a share count and the others no less at more rows, so a share count that is ever taken is taken at its
+// last row of tiles, and those say what any number of rows needs.
+SplitPlan plan_gemm_split(int M, int N, int K, int nz)
 {
-    return split_shares(1, K / BK) > 1 ? SPLIT_TILES / ((N + 63) / 64) * 64 : 0;
-}
-// a block leaves its 64 x 64 fp32 sums and its 64 rows of rank-space ones
-size_t gemm_split_bytes(int M, int N, int K, int nz)
-{
-    const int cols = (N + 63) / 64, rows = std::min((M + 63) / 64, SPLIT_TILES / cols);
+    SplitPlan p = {false, 0, 0};
+    const int nk = K / BK, cols = (N + 63) / 64, rows = (M + 63) / 64;
+    if (split_shares(1, nk) == 1 || cols > SPLIT_TILES) return p;
+    auto shares = [&](int m) { return plan_gemm_tile(m, N, 1, K, EPI_STORE, nz, true, true).splits; };
     long blocks = 0;
-    for (int r = 1; r <= rows; ++r) {
-        const int s = split_shares((long)r * cols, K / BK);
-        if (s > 1) blocks = std::max(blocks, (long)r * cols * s);
+    auto count = [&](int r, int s) { if (s > 1) blocks = std::max(blocks, (long)r * cols * s); };
+    for (long end : SPLIT_ENDS) {
+        const int last = (int)end / cols;
+        if (last == 0) continue;
+        const int s = shares(last * 64);
+        if (s > 1) p.most_rows = last * 64;
+        if (last * 64 <= M) count(last, s);
     }
-    return (size_t)blocks * 64 * (64 + nz) * sizeof(float);
+    if (M <= p.most_rows) {
+        const int s = shares(M);
+        p.shared = s > 1;
+        count(rows, s);
+    }
+    // a block leaves its 64 x 64 fp32 sums and its 64 rows of rank-space ones
+    p.bytes = (size_t)blocks * 64 * (64 + nz) * sizeof(float);
+    return p;
 }
 size_t gemm_split_counter_bytes() { return SPLIT_TILES * sizeof(unsigned); }
 

@@ -7,6 +7,7 @@ import re
 import numpy as np
 import pytest
 
+import plans
 from paper_2407_00952_amd import binding as B
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -175,15 +176,18 @@ def test_layer_workspace_for_the_most_tokens_serves_fewer(n_in, n_out):
         assert n[0] > 0 and all(a <= b for a, b in zip(n, n[1:]))
 
 
-# A layer asks for room for shared contractions only where one of its products has it (18 slabs of 64 or more, and 128 tiles of
-# 64 x 64 or fewer) and the call has none to spare: the forward's lies behind the operand copies it makes, the backward's where the
+# A layer asks for room for shared contractions only where one of its launches shares one (long contractions over few tiles)
+# and the call has none to spare: the forward's lies behind the operand copies it makes, the backward's where the
 # gradients' partial sums come to lie afterwards.
 @pytest.mark.parametrize("T,n_in,n_out,fwd,bwd", [
-    (1024, 768, 768, 0, 0),                 # 12 slabs both ways
-    (1, 1088, 64, 0, 0),                    # 17 slabs
-    (1, 1152, 64, 2, 0),                    # 18: one tile, two shares
-    (130, 128, 2432, 0, 6 * 4),             # the input gradient: six tiles, four shares
-    (2048, 2048, 256, 128 * 2, 0),          # 128 tiles forward, two shares
+    (1024, 768, 768, 0, 0),                 # 12 slabs of 64 both ways
+    (1, 1152, 64, 0, 0),                    # 18: smaller tiles cost less than combining partial sums
+    (130, 128, 2432, 0, 0),                 # 38
+    (2048, 2048, 256, 0, 0),                # 32
+    (1, 5120, 64, 4, 0),                    # 80: one tile, four shares
+    (130, 128, 5120, 0, 6 * 4),             # the input gradient: six tiles, four shares
+    (160, 4096, 1024, 48 * 3, 0),           # 48 tiles forward, three shares
+    (1024, 5120, 512, 128 * 2, 0),          # 128 tiles forward, two shares
     (64, 64, 8192, 0, 4),                   # one tile, four shares
     (40000, 4096, 1024, 128 * 2, 0),        # far more tiles at this count, and more scratch than fewer tokens need
 ])
@@ -195,6 +199,28 @@ def test_layer_workspace_holds_no_unused_split_scratch(T, n_in, n_out, fwd, bwd)
     need = [grads + max(-(-T // 512), few) * 64 * (n_in + n_out)]
     need += [at + 512 + n * 64 * (64 + 16) * 4 for at, n in ((copies, fwd), (grads, bwd)) if n]
     assert B.slora_lora_linear_ws_bytes(B.DTYPE_BF16, T, n_in, n_out, 4) == max(need)
+
+
+# The scratch follows the launch: a layer has it exactly where its launch shares the contraction, enough for the launch's shares
+# and for those of fewer rows, at every row count where the plan may change (whole 32s, and one more) up to past the
+# last that shares.
+@pytest.mark.parametrize("slabs", [9, 18, 42, 43, 48, 56, 64, 80, 128, 200, 512])
+def test_split_scratch_follows_the_launch(slabs):
+    K, seen = 64 * slabs, 0
+    for cols in list(range(1, 20)) + [32, 33, 48, 64, 65, 96, 127, 128, 129]:
+        N, need, most = 64 * cols, 0, 0
+        plans_of = []
+        for M in sorted({m for e in range(32, 128 // cols * 64 + 129, 32) for m in (e - 31, e)}):
+            shares = plans.tile(M, N, K, nz=16, can_split=True)[2]
+            if shares > 1:
+                need, most = max(need, -(-M // 64) * cols * shares * 64 * (64 + 16) * 4), M
+            plans_of.append((M, (shares > 1, need)))
+        for M, want in plans_of:
+            shared, rows, size = plans.split(M, N, K)
+            assert (shared, size) == want and (not shared or M <= rows), (M, N, K)
+        assert plans.split(1 << 20, N, K)[1:] == (-(-most // 64) * 64, need), (N, K)
+        seen += most > 0
+    assert (seen > 0) == (slabs >= 43)
 
 
 # Layers that the library's own array holds with 512-token partial sums and not with 128-token ones: a wide input into a narrow output,
