@@ -18,6 +18,10 @@
 #include "common.h"
 #include "gemm_copy.h"
 
+// the tile of a product's kernel and the stages of its ring of copies (0: a kernel without one); vec: operands of 16-byte rows
+struct F32Plan { int tm, tn, stages; };
+extern "C" F32Plan plan_f32(int M, int N, int K, bool vec);
+
 namespace {
 
 constexpr int BK = 32;                       // contraction elements per LDS slab
@@ -593,49 +597,31 @@ void launch_ring(const GemmF32 &a, hipStream_t st)
     const long tiles = (long)((a.M + TM - 1) / TM) * ((a.N + TN - 1) / TN);
     hipLaunchKernelGGL((f32_tile_kernel<TM, TN, WM, WN, NST, BT>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(512), 0, st, a);
 }
-// The form that costs least, in us as measured (T = 64 to 8192 at five weight shapes): rounds of 256 tiles, or of 512 where two
-// blocks share a CU, at a + b (K / 64) each.  32 x 64 and 64 x 48 fill the chip where 64 x 64 tiles leave a part of it idle
-// (T = 1024, 768 -> 768: 256 tiles of 64 x 48 in 13.5 us, 192 of 64 x 64 in 16.1).
-template <bool BT>
-void launch_ring_forms(const GemmF32 &a, hipStream_t st)
-{
-    struct Form { int tm, tn, per_cu; float a, b; };
-    constexpr Form forms[5] = {{32, 64, 1, 3.1f, .545f}, {64, 48, 1, 3.6f, .765f}, {64, 64, 1, 3.8f, .995f},
-                               {64, 64, 2, 4.6f, 1.90f}, {128, 128, 1, 7.5f, 3.68f}};
-    int best = 0;
-    double least = 0;
-    for (int f = 0; f < 5; ++f) {
-        const long tiles = (long)((a.M + forms[f].tm - 1) / forms[f].tm) * ((a.N + forms[f].tn - 1) / forms[f].tn);
-        const long round = 256 * forms[f].per_cu;
-        const double c = (double)((tiles + round - 1) / round) * (forms[f].a + forms[f].b * (a.K / 64));
-        if (f == 0 || c < least) { best = f; least = c; }
-    }
-    switch (best) {
-    case 0: launch_ring<32, 64, 2, 2, 4, BT>(a, st); break;
-    case 1: launch_ring<64, 48, 4, 1, 4, BT>(a, st); break;
-    case 2: launch_ring<64, 64, 2, 2, 4, BT>(a, st); break;
-    case 3: launch_ring<64, 64, 2, 2, 2, BT>(a, st); break;
-    case 4: launch_ring<128, 128, 2, 2, 2, BT>(a, st); break;
-    }
-}
+// The kernel for a product.  16 x 16 outputs per block (f32_gemm_direct_kernel) while 64 x 64 tiles would leave most CUs without
+// work.  The ring needs whole stages of 64 and 32-bit byte offsets and runs on the form that costs least, in us as measured
+// (T = 64 to 8192 at five weight shapes): rounds of 256 tiles, or of 512 where two blocks share a CU, at a + b (K / 64) each.
+// 32 x 64 and 64 x 48 fill the chip where 64 x 64 tiles leave a part of it idle (T = 1024, 768 -> 768: 256 tiles of 64 x 48 in
+// 13.5 us, 192 of 64 x 64 in 16.1).  Without the ring (f32_gemm_kernel) 128 x 128 tiles once two of them per CU are there (below
+// that the idle CUs cost more than the operand traffic saved).
 template <bool BT, bool VEC>
-int launch_product(const GemmF32 &a, hipStream_t st)
+int launch_product(const GemmF32 &a, const F32Plan &p, hipStream_t st)
 {
-    const long t64 = (long)((a.M + 63) / 64) * ((a.N + 63) / 64), t128 = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-    // 16 x 16 outputs per block while 64 x 64 tiles would leave most CUs without work.  The ring needs whole stages of 64 and
-    // 32-bit byte offsets; without it 128 x 128 tiles once two of them per CU are there (below that the idle CUs
-    // cost more than the operand traffic saved)
-    const bool ring = VEC && a.K % 64 == 0 && (unsigned long long)a.M * a.K < (1ull << 30) && (unsigned long long)a.N * a.K < (1ull << 30);
-    if (t64 < 96) {
+    if (p.tm == 16) {
         const long tiles = (long)((a.M + 15) / 16) * ((a.N + 15) / 16);
         hipLaunchKernelGGL((f32_gemm_direct_kernel<BT, VEC>), dim3((unsigned)tiles), dim3(512), 0, st, a);
-    } else if (ring) {
-        launch_ring_forms<BT>(a, st);
-    } else if (t128 < 512) {
-        launch_tile<64, 64, 2, BT, VEC>(a, st);
-    } else {
-        launch_tile<128, 128, 1, BT, VEC>(a, st);
-    }
+    } else if (p.stages == 0) {
+        if (p.tm == 64) launch_tile<64, 64, 2, BT, VEC>(a, st);
+        else launch_tile<128, 128, 1, BT, VEC>(a, st);
+    } else if constexpr (VEC) {
+        switch (p.tm * 1000 + p.tn + p.stages) {
+        case 32064 + 4: launch_ring<32, 64, 2, 2, 4, BT>(a, st); break;
+        case 64048 + 4: launch_ring<64, 48, 4, 1, 4, BT>(a, st); break;
+        case 64064 + 4: launch_ring<64, 64, 2, 2, 4, BT>(a, st); break;
+        case 64064 + 2: launch_ring<64, 64, 2, 2, 2, BT>(a, st); break;
+        case 128128 + 2: launch_ring<128, 128, 2, 2, 2, BT>(a, st); break;
+        default: return SL_EINVAL;
+        }
+    } else return SL_EINVAL;
     SL_CHECK_LAUNCH("f32 product");
     return 0;
 }
@@ -643,8 +629,9 @@ int product(const GemmF32 &a, bool bt, hipStream_t st)
 {
     // float4 loads need rows of a multiple of four floats on 16-byte bases
     const bool vec = (a.K % 4) == 0 && aligned16(a.A) && aligned16(a.B) && (bt || (a.N % 4) == 0);
-    if (bt) return vec ? launch_product<true, true>(a, st) : launch_product<true, false>(a, st);
-    return vec ? launch_product<false, true>(a, st) : launch_product<false, false>(a, st);
+    const F32Plan p = plan_f32(a.M, a.N, a.K, vec);
+    if (bt) return vec ? launch_product<true, true>(a, p, st) : launch_product<true, false>(a, p, st);
+    return vec ? launch_product<false, true>(a, p, st) : launch_product<false, false>(a, p, st);
 }
 
 int project(const ProjJob *j, int n, int T, int r, int zp, hipStream_t st)
@@ -663,6 +650,25 @@ int project(const ProjJob *j, int n, int T, int r, int zp, hipStream_t st)
 }
 
 }  // namespace
+
+F32Plan plan_f32(int M, int N, int K, bool vec)
+{
+    struct Form { int tm, tn, stages, per_cu; float a, b; };
+    constexpr Form forms[5] = {{32, 64, 4, 1, 3.1f, .545f}, {64, 48, 4, 1, 3.6f, .765f}, {64, 64, 4, 1, 3.8f, .995f},
+                               {64, 64, 2, 2, 4.6f, 1.90f}, {128, 128, 2, 1, 7.5f, 3.68f}};
+    auto tiles = [&](int tm, int tn) { return (long)((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+    if (tiles(64, 64) < 96) return {16, 16, 0};
+    const bool ring = vec && K % 64 == 0 && (unsigned long long)M * K < (1ull << 30) && (unsigned long long)N * K < (1ull << 30);
+    if (!ring) return tiles(128, 128) < 512 ? F32Plan{64, 64, 0} : F32Plan{128, 128, 0};
+    F32Plan best = {0, 0, 0};
+    double least = 0;
+    for (const Form &f : forms) {
+        const long round = 256 * f.per_cu;
+        const double c = (double)((tiles(f.tm, f.tn) + round - 1) / round) * (f.a + f.b * (K / 64));
+        if (best.tm == 0 || c < least) { best = {f.tm, f.tn, f.stages}; least = c; }
+    }
+    return best;
+}
 
 size_t f32_lora_linear_ws_floats(int T, int r) { return 2 * (size_t)T * pad_rank(r); }
 

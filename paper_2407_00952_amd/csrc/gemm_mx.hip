@@ -14,11 +14,8 @@ __global__ __launch_bounds__(TM <= 64 ? 256 : 512, 2) void gemm_mx_tile_kernel(M
     gemm_mx_body<EPI, TM, TN, WM, WN, (TM > 128 || (TM == 64 && TN == 128) ? 3 : 4)>(a);
 }
 
-// Costs in us as in gemm_tile.hip, fitted to launches of 16 to 32768 rows at eight weight shapes with a rank-space branch (mean
-// error 6 %, the form it picks is 0.1 % slower on average than the fastest), as a + b (K / 128): forms of which two share a CU,
-// `one` for at most 256 tiles, `both` for 257 to 512, `full` for each 512 before; the others between `one` and `full`.
-struct Cost { float a, b; };
-struct Form { int tm, tn; Cost one, both, full; };
+// Fitted to plain-store launches of 16 to 32768 rows at eight weight shapes with a rank-space branch (mean error 6 %, the form it
+// picks is 0.1 % slower on average than the fastest); a slab is 128.
 constexpr Form FORMS[7] = {
     {32, 64, {3.29f, .189f}, {2.71f, .420f}, {0.08f, .458f}},
     {64, 64, {3.51f, .228f}, {2.90f, .552f}, {0.83f, .589f}},
@@ -48,18 +45,12 @@ int launch_e(const MxArgs &a, const TilePlan &p, hipStream_t st)
 
 }  // namespace
 
-TilePlan plan_gemm_mx(const MxArgs &a)
+TilePlan plan_gemm_mx(int M, int seg_n, int nseg, int K)
 {
-    const int nk = a.K / 128;
     TilePlan best = {0, 0, 1};
     double least = 0;
     for (const Form &f : FORMS) {
-        auto us = [&](const Cost &c) { return c.a + (double)c.b * nk; };
-        const long tiles = (long)((a.M + f.tm - 1) / f.tm) * ((a.seg_n + f.tn - 1) / f.tn) * a.nseg;
-        const long round = f.both.b > 0 ? 512 : 256, before = (tiles - 1) / round, last = tiles - before * round;
-        const double fill = last / 256.0;
-        const double c = f.both.b > 0 ? before * us(f.full) + us(last > 256 ? f.both : f.one)
-                                      : (before + fill) * us(f.full) + (1 - fill) * us(f.one);
+        const double c = form_cost(f, (long)((M + f.tm - 1) / f.tm) * ((seg_n + f.tn - 1) / f.tn) * nseg, K / 128);
         if (best.tm == 0 || c < least) { best = {f.tm, f.tn, 1}; least = c; }
     }
     return best;

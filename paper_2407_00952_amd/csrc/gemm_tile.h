@@ -21,6 +21,22 @@ namespace {
 
 constexpr int BK = 64, ROWB = BK * 2;
 
+// What a tile form costs, in us as a + b (slabs of the contraction).  Blocks of 4 waves: `one` for at most 256 tiles, `both` for
+// 257 to 512, `full` for each 512 before those (two of them share a CU, but for 32 x 64 with 16 rank-space columns and 32 x 32
+// with 48, whose 86 KB of LDS leave room for one; those are fitted the same way).  Blocks that own a CU (both.b 0): between `one`
+// for a few tiles and `full` for 256, as full as the last round is, and `full` for each 256 before it.
+struct Cost { float a, b; };
+struct Form { int tm, tn; Cost one, both, full; };
+inline double form_cost(const Form &f, long tiles, int nk)
+{
+    auto us = [&](const Cost &c) { return c.a + (double)c.b * nk; };
+    const bool two = f.both.b > 0;
+    const long round = two ? 512 : 256, before = (tiles - 1) / round, last = tiles - before * round;
+    if (two) return before * us(f.full) + us(last > 256 ? f.both : f.one);
+    const double fill = last / 256.0;
+    return (before + fill) * us(f.full) + (1 - fill) * us(f.one);
+}
+
 // Partial sums cross XCDs (each has its own L2), so they are written and read at device scope: relaxed 8-byte atomics
 // go through to the memory side and need no cache flush; the order is kept by the vmcnt wait before the counter.
 __device__ __forceinline__ void put_partial(float4 *p, f32x4 v)

@@ -56,12 +56,8 @@ int launch_te(const GemmArgs &a, int nz, const TilePlan &p, hipStream_t st)
     return SL_EINVAL;
 }
 
-// What the tile forms cost, in us, fitted to launches of 64 to 32768 rows at seven weight shapes of 768 to 5120 (mean error
-// 2 to 6 %; the form it picks is 0.5 % slower on average than the fastest), each as a + b (K / 64).  Forms of which two share
-// a CU: `one` for at most 256 tiles, `both` for 257 to 512, `full` for each 512 before those.  The others: between `one` for
-// a few tiles and `full` for 256, as full as the last round is, and `full` for each 256 before it.
-struct Cost { float a, b; };
-struct Form { int tm, tn; Cost one, both, full; };       // both.b 0: one block to a CU
+// Fitted to plain-store launches of 64 to 32768 rows at seven weight shapes of 768 to 5120 (mean error 2 to 6 %; the form it picks
+// is 0.5 % slower on average than the fastest), the third group to 32 and 48 columns together.
 constexpr Form FORMS[3][9] = {
     {{32, 32, {2.46f, .093f}, {2.60f, .175f}, {0.97f, .170f}},          // no rank-space branch
      {32, 64, {2.33f, .129f}, {2.49f, .250f}, {0.70f, .269f}},
@@ -90,16 +86,6 @@ constexpr Form FORMS[3][9] = {
      {},
      {},
      {256, 256, {8.10f, 1.342f}, {}, {6.20f, 1.950f}}}};
-
-double form_cost(const Form &f, long tiles, int nk)
-{
-    auto us = [&](const Cost &c) { return c.a + (double)c.b * nk; };
-    const bool two = f.both.b > 0;
-    const long round = two ? 512 : 256, before = (tiles - 1) / round, last = tiles - before * round;
-    if (two) return before * us(f.full) + us(last > 256 ? f.both : f.one);
-    const double fill = last / 256.0;
-    return (before + fill) * us(f.full) + (1 - fill) * us(f.one);
-}
 
 }  // namespace
 
