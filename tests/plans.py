@@ -36,3 +36,37 @@ def split(M, N, K, nz=16):
 def layer(T, n_in, n_out):
     """the plans of a bf16 LoRA layer's two products: forward, input gradient"""
     return [tile(T, n, k, nz=16, can_split=split(T, n, k)[0]) for n, k in ((n_out, n_in), (n_in, n_out))]
+
+
+class F32Plan(ctypes.Structure):
+    _fields_ = [("tm", c_int), ("tn", c_int), ("stages", c_int)]
+
+
+def mx(M, N, K, nseg=1):
+    """(rows, columns) of a product with fp8 weights"""
+    p = _fn("plan_gemm_mx", TilePlan, *[c_int] * 4)(M, N // nseg, nseg, K)
+    return p.tm, p.tn
+
+
+def mx_layer(T, n_in, n_out):
+    return [mx(T, n_out, n_in), mx(T, n_in, n_out)]
+
+
+def f32_layer(T, n_in, n_out):
+    """(rows, columns, stages of the ring of copies or 0) of an fp32 layer's two products, on aligned operands"""
+    f = _fn("plan_f32", F32Plan, c_int, c_int, c_int, c_bool)
+    plan = [f(T, n_out, n_in, n_in % 4 == 0), f(T, n_in, n_out, n_in % 4 == 0 and n_out % 4 == 0)]
+    return [(p.tm, p.tn, p.stages) for p in plan]
+
+
+def stack(T, d, f, proj, seq_len, fp8=False):
+    """{(epilogue, rank-space columns, rows, columns)} of the eight products of a block"""
+    on = {p: p in proj for p in "q k v o fc pr".split()}
+    qkv = sum(on[p] for p in "qkv")
+    ad = lambda p: 16 if on[p] else 0
+    delta = STORE_DELTA if seq_len <= 512 and not on["o"] else STORE
+    prods = [(STORE, 16 if qkv else 0, 3 * d, d, 3), (RESID, ad("o"), d, d, 1), (GELU, ad("fc"), f, d, 1),
+             (RESID, ad("pr"), d, f, 1), (DGELU, ad("pr"), f, d, 1), (STORE, ad("fc"), d, f, 1),
+             (delta, ad("o"), d, d, 1), (STORE, 16 * qkv, d, 3 * d, 1)]
+    return {(epi, nz) + (mx(T, N, K, nseg) if fp8 else tile(T, N, K, epi, nz, nseg=nseg)[:2])
+            for epi, nz, N, K, nseg in prods}

@@ -80,16 +80,17 @@ def test_fp32_ragged_shapes(T, n_in, n_out, r, bias):
 
 
 # Where the fp32 products change kernel, and ragged edges on both sides of each line: 16 x 16 outputs per block up to 95
-# tiles of 64 x 64, 64 x 64 tiles up to 511 tiles of 128 x 128, float4 loads only for rows of a multiple of 4 floats.
+# tiles of 64 x 64; beyond, the ring kernel where rows are whole float4s and the contraction whole 64s, otherwise 64 x 64 tiles
+# up to 511 tiles of 128 x 128, and those.
 # Sums of up to 16 400 fp32 products in whatever order: 1e-4 is the bar of the fp32 path.
 @pytest.mark.parametrize("T,n_in,n_out,r,bias", [
     (1, 768, 768, 4, True),
     (17, 1280, 1288, 5, False),
-    (500, 768, 704, 2, False),       # 88 and 96 tiles of 64 x 64
+    (500, 768, 704, 2, False),       # 88 and 96 tiles of 64 x 64: direct and ring
     (333, 259, 130, 3, True),        # odd rows, direct
     (700, 331, 1027, 9, True),       # odd rows, 64 x 64 tiles
-    (8200, 64, 1030, 16, True),      # 585 tiles of 128 x 128 forward, odd columns
-    (16400, 512, 36, 4, False),      # 516 tiles of 128 x 128 in the input gradient
+    (8200, 64, 1030, 16, True),      # ring forward, odd columns; 64 x 64 tiles back
+    (16400, 512, 36, 4, False),      # ring forward; 516 tiles of 128 x 128 in the input gradient
 ])
 def test_fp32_dispatch_edges(T, n_in, n_out, r, bias):
     c = synth.make_single_layer(T, n_in, n_out, r, seed=17 + T, bias=bias)
@@ -99,15 +100,20 @@ def test_fp32_dispatch_edges(T, n_in, n_out, r, bias):
 
 
 # The forms of the ring kernel (contraction a multiple of 64, 96 tiles of 64 x 64 or more), forward (W as [n, k]) and input
-# gradient (W as [k, n]), with ragged rows and columns; 64 is one stage.
-@pytest.mark.parametrize("T,n_in,n_out", [
-    (601, 768, 836), (601, 836, 768),        # 32 x 64
-    (1001, 768, 764), (1001, 764, 768),      # 64 x 48
-    (1001, 1024, 1020), (1001, 1020, 1024),  # 64 x 64
-    (2101, 192, 764), (2101, 764, 192),      # 64 x 64, two to a CU
-    (3900, 320, 1020), (3900, 1020, 320),    # 128 x 128
-    (3900, 64, 1028),                        # one stage
-])
+# gradient (W as [k, n]), with ragged rows and columns; 64 is one stage.  (The other product of each layer has a contraction
+# that is no multiple of 64.)  T, n_in, n_out: which product, and its tile and ring stages (tests/test_plans.py).
+FP32_RING_FORMS = {
+    (601, 768, 700): ("forward", (32, 64, 4)), (601, 700, 768): ("input gradient", (32, 64, 4)),
+    (601, 768, 836): ("forward", (64, 48, 4)), (601, 836, 768): ("input gradient", (64, 48, 4)),
+    (1001, 768, 764): ("forward", (64, 48, 4)), (1001, 764, 768): ("input gradient", (64, 48, 4)),
+    (1001, 1024, 1020): ("forward", (64, 64, 4)), (1001, 1020, 1024): ("input gradient", (64, 64, 4)),
+    (2101, 192, 764): ("forward", (64, 64, 2)), (2101, 764, 192): ("input gradient", (64, 64, 2)),       # two to a CU
+    (3900, 320, 1020): ("forward", (128, 128, 2)), (3900, 1020, 320): ("input gradient", (128, 128, 2)),
+    (3900, 64, 1028): ("forward", (64, 64, 2)),      # one stage of the contraction
+}
+
+
+@pytest.mark.parametrize("T,n_in,n_out", list(FP32_RING_FORMS))
 def test_fp32_ring_forms(T, n_in, n_out):
     test_fp32_dispatch_edges(T, n_in, n_out, 5, True)
 
@@ -231,15 +237,14 @@ def test_frozen_linear_bf16(T, n_in, n_out, bias):
     assert e <= 2.0 ** -8
 
 
-# Where the bf16 products change kernel (64 x 64 tiles up to 512 of them, 128 x 128 tiles with 8 waves up to 256, with 4
-# where they beat the 256-row tiles), with ragged rows and columns on both sides; one slab and odd numbers of slabs.
+# Products with ragged rows and columns and one or an odd number of slabs.
 @pytest.mark.parametrize("T,n_in,n_out,bias", [
-    (1, 1152, 64, True),             # one tile
-    (130, 2432, 72, False),          # six tiles, columns past a tile
-    (300, 1216, 776, True),          # 65 tiles
-    (1020, 64, 2040, True),          # 512 tiles of 64 x 64, one slab
-    (1030, 192, 2040, False),        # 544: 128 x 128 with 8 waves, three slabs
-    (2050, 320, 2056, True),         # 289 tiles of 128 x 128, five slabs
+    (1, 1152, 64, True),             # one row
+    (130, 2432, 72, False),          # columns past a tile
+    (300, 1216, 776, True),
+    (1020, 64, 2040, True),          # one slab
+    (1030, 192, 2040, False),        # three
+    (2050, 320, 2056, True),         # five
 ])
 def test_frozen_linear_dispatch_edges(T, n_in, n_out, bias):
     import torch
@@ -256,50 +261,69 @@ def test_frozen_linear_dispatch_edges(T, n_in, n_out, bias):
 
 
 # The tile forms of the bf16 products, each with ragged rows and columns and an odd number of slabs (forms with two slabs to
-# a barrier end on a single one).
-@pytest.mark.parametrize("T,n_in,n_out", [
-    (70, 704, 776),                  # 32 x 32
-    (33, 192, 104),                  # 32 x 64, three slabs
-    (200, 448, 4088),                # 64 x 64
-    (450, 192, 3080),                # 64 x 128
-    (1090, 320, 2056),               # 128 x 128
-    (1500, 1088, 3080),              # 192 x 128
-    (2000, 1088, 3080),              # 256 x 128
-    (2100, 192, 3080),               # 128 x 256
-])
+# a barrier end on a single one).  T, n_in, n_out: tile (tests/test_plans.py).
+FROZEN_FORMS = {
+    (70, 704, 776): (32, 32),
+    (33, 192, 104): (32, 64),
+    (200, 448, 4088): (64, 64),
+    (450, 192, 3080): (64, 128),
+    (1090, 320, 2056): (128, 128),
+    (1500, 1088, 3080): (192, 128),
+    (2000, 1088, 3080): (256, 128),
+    (2100, 192, 3080): (128, 256),
+}
+
+
+@pytest.mark.parametrize("T,n_in,n_out", list(FROZEN_FORMS))
 def test_frozen_linear_tile_forms(T, n_in, n_out):
     test_frozen_linear_dispatch_edges(T, n_in, n_out, True)
 
 
-# The same with the rank-space branch (contraction n_in forward, n_out in the input gradient), and contractions long
-# enough to be shared over blocks in either direction, on repeated calls.
-@pytest.mark.parametrize("T,n_in,n_out,r", [
-    (70, 704, 768, 16),              # 32 x 32
-    (130, 704, 2048, 1),             # 32 x 64 forward
-    (450, 192, 3072, 5),             # 64 x 128 forward
-    (1400, 704, 3072, 8),            # 192 x 128 forward
-    (2000, 1088, 3072, 3),           # 256 x 128 forward
-])
-def test_bf16_layer_tile_forms(T, n_in, n_out, r):
-    test_bf16_layer_dispatch_edges(T, n_in, n_out, r)
+# The same with the rank-space branch (contraction n_in forward, n_out in the input gradient).  T, n_in, n_out: tile forward
+# (and in the input gradient: whichever).
+LAYER_FORMS = {
+    (70, 704, 768): (32, 32),
+    (130, 704, 2048): (32, 64),
+    (200, 448, 4096): (64, 64),
+    (450, 192, 3072): (64, 128),
+    (1090, 320, 2048): (128, 128),
+    (1400, 704, 3072): (192, 128),
+    (2000, 1088, 3072): (256, 128),
+}
 
 
-@pytest.mark.parametrize("T,n_in,n_out,r", [
-    (3, 5120, 128, 16),              # forward: two tiles of 64 x 64, four shares
-    (130, 128, 5120, 3),             # input gradient: six tiles, four shares
-    (1024, 5120, 512, 4),            # forward: 128 tiles, two shares
-])
-def test_bf16_layer_long_contractions_are_shared(T, n_in, n_out, r):
+@pytest.mark.parametrize("T,n_in,n_out", list(LAYER_FORMS))
+def test_bf16_layer_tile_forms(T, n_in, n_out):
+    test_bf16_layer_dispatch_edges(T, n_in, n_out, (T // 10) % 16 + 1)
+
+
+# Contractions long enough to be shared over blocks: T, n_in, n_out: blocks to a tile forward, in the input gradient.
+SHARED = {
+    (3, 5120, 128): (4, 1),          # two tiles of 64 x 64
+    (130, 128, 5120): (1, 4),        # six
+    (160, 4096, 1024): (3, 1),       # 48
+    (160, 1024, 4096): (1, 3),
+    (300, 3584, 832): (2, 1),        # 65
+    (1024, 5120, 512): (2, 1),       # 128
+    (2048, 256, 5120): (1, 2),
+    (33, 4160, 2048): (4, 1),        # 65 slabs: shares of 16 and 17
+}
+
+
+@pytest.mark.parametrize("T,n_in,n_out", list(SHARED))
+def test_bf16_layer_long_contractions_are_shared(T, n_in, n_out):
+    r = T % 16 + 1
     test_bf16_layer_dispatch_edges(T, n_in, n_out, r)
     test_bf16_layer_shared_contraction_repeats_itself(T, n_in, n_out, r)
 
 
 @pytest.mark.parametrize("T,n_in,n_out,r", [
-    (3, 2432, 128, 16),              # contraction shared over four blocks (9 and 10 slabs), forward; one row of tiles
+    (3, 2432, 128, 16),              # one row of tiles, an odd number of slabs
     (130, 128, 2432, 3),             # the same in the input gradient
-    (1100, 192, 1984, 5),            # 128 x 128 tiles, 8 waves; odd number of slabs
-    (260, 1216, 832, 2),             # 65 tiles, two shares
-    (2100, 2048, 320, 8),            # 289 tiles of 128 x 128 in the input gradient
+    (1100, 192, 1984, 5),            # odd number of slabs
+    (260, 1216, 832, 2),
+    (2100, 2048, 320, 8),
+    (2048, 2048, 256, 4),
 ])
 def test_bf16_layer_dispatch_edges(T, n_in, n_out, r):
     c = synth.make_single_layer(T, n_in, n_out, r, seed=500 + T + r, quant=True, bias=True)
@@ -313,11 +337,10 @@ def test_bf16_layer_dispatch_edges(T, n_in, n_out, r):
 
 # Products that share their contraction over blocks: the blocks of a tile finish in any order, and their sums are added in
 # share order all the same; the counters are left as the next call expects them; nothing behind the workspace is written.
+# (38 slabs here, which no launch shares: the same must hold.  SHARED has those that do.)
 @pytest.mark.parametrize("T,n_in,n_out,r", [
-    (3, 2432, 128, 16),              # forward: two tiles, four shares
-    (130, 128, 2432, 3),             # input gradient: six tiles, four shares
-    (260, 1216, 832, 2),             # forward: 65 tiles, two shares
-    (2048, 2048, 256, 4),            # forward: 128 tiles, two shares
+    (3, 2432, 128, 16),
+    (130, 128, 2432, 3),
 ])
 def test_bf16_layer_shared_contraction_repeats_itself(T, n_in, n_out, r):
     import torch

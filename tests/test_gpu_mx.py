@@ -114,28 +114,39 @@ def test_linear_on_oracle_codes(T, K, N, with_bias):
     assert rms < 0.06
 
 
-# The tile forms of the fp8 products, each with ragged rows and columns; odd and even numbers of slabs.
-@pytest.mark.parametrize("T,K,N", [
-    (70, 384, 200),               # 32 x 64
-    (300, 256, 4104),             # 64 x 64
-    (500, 640, 4000),             # 64 x 128
-    (1030, 384, 3080),            # 128 x 128
-    (1400, 640, 3080),            # 192 x 128
-    (2000, 640, 3080),            # 256 x 128
-    (5000, 384, 2056),            # 256 x 256
-])
+# The tile forms of the fp8 products, each with ragged rows and columns; odd and even numbers of slabs.  T, K, N: tile
+# (tests/test_plans.py).
+FP8_FORMS = {
+    (70, 384, 200): (32, 64),
+    (300, 256, 4104): (64, 64),
+    (500, 640, 4000): (64, 128),
+    (1030, 384, 3080): (128, 128),
+    (1400, 640, 3080): (192, 128),
+    (2000, 640, 3080): (256, 128),
+    (5000, 384, 2056): (256, 256),
+}
+
+
+@pytest.mark.parametrize("T,K,N", list(FP8_FORMS))
 def test_linear_tile_forms(T, K, N):
     test_linear_on_oracle_codes(T, K, N, True)
 
 
-@pytest.mark.parametrize("T,n_in,n_out,r", [
-    (70, 384, 256, 5),            # 32 x 64
-    (500, 640, 3968, 16),         # 64 x 128 forward
-    (1400, 640, 3072, 1),         # 192 x 128 forward
-    (5000, 384, 2048, 3),         # 256 x 256 forward
-])
-def test_lora_linear_tile_forms(T, n_in, n_out, r):
-    test_lora_linear_mxfp8(T, n_in, n_out, r, True)
+# The same with an adapter: T, n_in, n_out: tile forward, in the input gradient.
+FP8_LAYER_FORMS = {
+    (70, 384, 256): ((32, 64), (32, 64)),
+    (500, 640, 3968): ((64, 128), (32, 64)),
+    (1400, 640, 3072): ((192, 128), (64, 64)),
+    (2000, 640, 3072): ((256, 128), (64, 128)),
+    (5000, 384, 2048): ((64, 128), (64, 128)),
+    (3900, 384, 4096): ((256, 256), (64, 128)),         # three slabs
+    (3900, 4096, 512): ((64, 128), (256, 256)),         # four
+}
+
+
+@pytest.mark.parametrize("T,n_in,n_out", list(FP8_LAYER_FORMS))
+def test_lora_linear_tile_forms(T, n_in, n_out):
+    test_lora_linear_mxfp8(T, n_in, n_out, T // 10 % 16 + 1, True)
 
 
 def test_linear_full_code_range():

@@ -262,8 +262,8 @@ def test_workload5_sampled():
     _sampled_parity(synth.CONFIGS[5], [50, 9])
 
 
-# The kernels a product of a context may run on, chosen by its tile counts: one sequence alone (64 x 64 tiles throughout), three
-# (128 x 128 tiles with 8 waves for q|k|v and the MLP's wide products) and eleven (with 4 waves, or 256-row tiles).
+# The kernels a product of a context may run on, chosen by what their tiles cost: one sequence alone (32 x 64 to 64 x 128), three
+# (64 x 128 to 192 x 128) and eleven (192 x 128 and 256 x 256).
 # Sequences do not interact, so each one's results must be the same bits whichever kernels its batch ran on.
 @pytest.mark.parametrize("proj", [(), synth.PROJ_NAMES])
 def test_results_do_not_depend_on_the_batch(proj):
@@ -277,7 +277,8 @@ def test_results_do_not_depend_on_the_batch(proj):
     srv.close()
 
 
-# The same for short records, from one (32 x 32 and 32 x 64 tiles) to 33 of 128 tokens (128 x 128 and 256 x 256).
+# The same for short records, from one (32 x 32 and 32 x 64 tiles) to 33 of 128 tokens (128 x 128 and 256 x 256), by way of
+# all the others but 128 x 256.
 @pytest.mark.parametrize("proj", [("q", "v"), synth.PROJ_NAMES])
 def test_results_of_short_records_do_not_depend_on_the_batch(proj):
     cfg = synth.tiny_config(d_model=768, n_head=12, d_ff=3072, n_blocks=1, lora_r=5, lora_proj=proj,
@@ -288,6 +289,45 @@ def test_results_of_short_records_do_not_depend_on_the_batch(proj):
         _, y, dx, _ = gpu_round(cfg, inp, clients=inp["clients"][:n], dY=inp["dY"][:n], server=srv)
         assert np.array_equal(y, Y[:n]) and all(np.array_equal(a, b) for a, b in zip(dx, dX[:n])), n
     srv.close()
+
+
+# Every form with every epilogue and width of the rank-space branch that these stacks use it with, of the bf16 products and of
+# the fp8 ones (which also write codes): sequences of 128 tokens in batches that between them run all of these
+# (tests/test_plans.py); a sequence's results are the same bits in each batch, and those of a few sequences are the oracle's.
+FORM_STACK = dict(d_model=256, n_head=4, d_ff=1024, n_blocks=1, lora_r=5, n_clients=1, seq_len=128)
+FORM_BATCHES = {
+    ("bf16", ("q", "v")): (1, 3, 5, 9, 17, 33, 49, 65, 97, 129, 139, 193),
+    ("bf16", synth.PROJ_NAMES): (1, 3, 5, 9, 17, 33, 49, 65, 139, 193),
+    ("mxfp8", ("q", "v")): (1, 9, 17, 20, 33, 49, 65, 97, 129, 193),
+    ("mxfp8", synth.PROJ_NAMES): (1, 9, 22, 43, 49, 65, 97, 129, 193),
+}
+
+
+@pytest.mark.parametrize("dtype,proj", list(FORM_BATCHES))
+def test_every_form_and_epilogue_gives_the_same_bits(dtype, proj):
+    from oracle import mx
+    from test_gpu_mx import MX_STACK_TOL
+    sizes = FORM_BATCHES[dtype, proj]
+    cfg = synth.tiny_config(**FORM_STACK, lora_proj=proj, batch=sizes[-1], seed=synth.BASE_SEED + 160)
+    inp = synth.make_stack_inputs(cfg)
+    if dtype == "bf16":
+        inp = _boost_B(inp, cfg, target=16.0)
+    x = inp["clients"][0]
+    srv = B.Server(cfg, inp["blocks"], inp["adapters"], max_seqs=sizes[-1],
+                   dtype=B.DTYPE_MXFP8 if dtype == "mxfp8" else B.DTYPE_BF16)
+    _, Y, dX, _ = gpu_round(cfg, inp, server=srv)
+    for n in sizes[:-1]:
+        _, y, dx, _ = gpu_round(cfg, inp, clients=[x[:n]], dY=inp["dY"][:n], server=srv)
+        assert np.array_equal(y, Y[:n]) and np.array_equal(dx[0], dX[0][:n]), n
+    srv.close()
+    orc = (mx.make_mx_server_oracle(inp["blocks"], inp["adapters"], cfg.n_head, cfg.lora_alpha, cfg.lora_r, cfg.ln_eps)
+           if dtype == "mxfp8" else oracle_of(cfg, inp))
+    tol = MX_STACK_TOL if dtype == "mxfp8" else BF16_TOL
+    for n in (0, 100, sizes[-1] - 1):
+        y, dx, _ = orc.fwd_bwd_sequence(x[n], inp["dY"][n])
+        ey, ex = relerr(Y[n], y), relerr(dX[0][n], dx)
+        say("   %s %s sequence %d: Y %.2e dx %.2e" % (dtype, ",".join(proj), n, ey, ex))
+        assert ey <= tol and ex <= tol, (n, ey, ex)
 
 
 # One short record: up to 128 tokens the adapter gradients are written without partial sums; up to 256 the attention backward

@@ -1,0 +1,67 @@
+"""The cases of the GPU tests reach the kernels that they are there for: the library's own choice for each, asked on the host.  A
+change of a cost table that moves a case to another kernel fails here."""
+import plans
+import test_gpu_linear as linear
+import test_gpu_mx as mx
+import test_gpu_stack as stack
+from paper_2407_00952_amd import synth
+
+BF16_FORMS = {(32, 32), (32, 64), (64, 64), (64, 128), (128, 128), (192, 128), (256, 128), (128, 256), (256, 256)}
+FP8_FORMS = {(32, 64), (64, 64), (64, 128), (128, 128), (192, 128), (256, 128), (256, 256)}
+
+
+def test_fp32_ring_forms():
+    for case, (which, want) in linear.FP32_RING_FORMS.items():
+        fwd, bwd = plans.f32_layer(*case)
+        assert (fwd if which == "forward" else bwd) == want, case
+    for which in ("forward", "input gradient"):
+        assert {f for w, f in linear.FP32_RING_FORMS.values() if w == which} == {
+            (32, 64, 4), (64, 48, 4), (64, 64, 4), (64, 64, 2), (128, 128, 2)}
+
+
+def test_bf16_forms():
+    for (T, n_in, n_out), want in linear.FROZEN_FORMS.items():
+        assert plans.tile(T, n_out, n_in) == want + (1,), (T, n_in, n_out)
+    assert set(linear.FROZEN_FORMS.values()) == BF16_FORMS - {(256, 256)}
+    for case, want in linear.LAYER_FORMS.items():
+        assert plans.layer(*case)[0] == want + (1,), case
+    assert set(linear.LAYER_FORMS.values()) == BF16_FORMS - {(128, 256), (256, 256)}
+
+
+def test_shared_contractions():
+    for case, want in linear.SHARED.items():
+        assert tuple(p[2] for p in plans.layer(*case)) == want, case
+    assert {w[0] for w in linear.SHARED.values()} == {w[1] for w in linear.SHARED.values()} == {1, 2, 3, 4}
+
+
+def test_fp8_forms():
+    for (T, K, N), want in mx.FP8_FORMS.items():
+        assert plans.mx(T, N, K) == want, (T, K, N)
+    assert set(mx.FP8_FORMS.values()) == FP8_FORMS
+    for case, want in mx.FP8_LAYER_FORMS.items():
+        assert tuple(plans.mx_layer(*case)) == want, case
+
+
+def test_stacks_reach_every_form_and_epilogue():
+    """every (epilogue, rank-space columns, form) that any batch of up to 200 sequences of the test's stack would run on is run on
+    by its batches; and what that leaves out of the forms altogether"""
+    d, f, S = (stack.FORM_STACK[k] for k in ("d_model", "d_ff", "seq_len"))
+    for (dtype, proj), sizes in stack.FORM_BATCHES.items():
+        reached, possible = ([plans.stack(n * S, d, f, proj, S, dtype == "mxfp8") for n in ns] for ns in (sizes, range(1, 201)))
+        assert set().union(*reached) == set().union(*possible), (dtype, proj)
+        forms = {p[2:] for p in set().union(*reached)}
+        if dtype == "mxfp8":
+            assert forms == FP8_FORMS
+        else:                                            # 128 x 256 has no rank-space branch
+            assert forms == BF16_FORMS - ({(128, 256)} if proj == synth.PROJ_NAMES else set())
+
+
+def test_batches_of_the_wider_stack():
+    forms = lambda n, S, proj: {p[2:] for p in plans.stack(n * S, 768, 3072, proj, S)}
+    for proj in ((), synth.PROJ_NAMES):
+        assert {(32, 64), (64, 128)} <= forms(1, 512, proj) <= {(32, 64), (64, 64), (64, 128)}
+        assert forms(3, 512, proj) == {(64, 128), (128, 128), (192, 128)}
+        assert forms(11, 512, proj) == {(192, 128), (256, 256)}
+    for proj in (("q", "v"), synth.PROJ_NAMES):
+        assert forms(1, 128, proj) == {(32, 32), (32, 64)} and forms(33, 128, proj) == {(128, 128), (256, 256)}
+        assert set().union(*(forms(n, 128, proj) for n in (1, 2, 4, 8, 16, 24, 33))) == BF16_FORMS - {(128, 256)}
