@@ -18,7 +18,7 @@ test suite instead of corrupting results:
   4. M0 is written only by the copy sequence (s_mov_b32 m0 / s_nop 0 / global_load_lds_*) and read by
      nothing else, in every source whose kernels issue it;
   5. no vector memory instruction reads a scalar register that a vector instruction (v_readlane,
-     v_readfirstlane, a compare with a scalar destination) wrote fewer than 5 wait states earlier.  The
+     v_readfirstlane, a compare, a carry) wrote fewer than 5 wait states earlier, vcc included.  The
      compiler keeps that distance for its own instructions but does not look into inline assembly, and the
      copies take their base address in scalar registers: a spilled scalar restored right in front of one
      would make it read a stale address.
@@ -182,7 +182,7 @@ def _check_m0(text, what):
         for i, ins in enumerate(code):
             if not re.search(r"\bm0\b", ins):
                 continue
-            if re.match(r"s_mov_b32 m0, s\d+$", ins):
+            if re.match(r"s_mov_b32 m0, (?:s\d+|vcc_lo|vcc_hi)$", ins):        # (a scalar may live in a half of vcc)
                 assert code[i + 1] == "s_nop 0" and code[i + 2].startswith("global_load_lds_dword"), \
                     (what, name, code[i:i + 3])
             else:
@@ -200,7 +200,8 @@ def test_m0_is_only_used_by_the_async_copies(gemm_asm, tile_asm):
     _check_m0(_assembly("mx.hip"), "mx.hip")
 
 
-_SREG = re.compile(r"\bs(\d+)\b|\bs\[(\d+):(\d+)\]")
+_SREG = re.compile(r"\bs(\d+)\b|\bs\[(\d+):(\d+)\]|\b(vcc(?:_lo|_hi)?)\b")
+_VCC = {"vcc": {"vcc_lo", "vcc_hi"}, "vcc_lo": {"vcc_lo"}, "vcc_hi": {"vcc_hi"}}
 _VMEM = ("global_load", "global_store", "global_atomic", "buffer_load", "buffer_store", "scratch_load", "scratch_store")
 
 
@@ -209,17 +210,30 @@ def _sregs(text):
     for m in _SREG.finditer(text):
         if m.group(1) is not None:
             regs.add(int(m.group(1)))
+        elif m.group(4) is not None:
+            regs |= _VCC[m.group(4)]
         else:
             regs.update(range(int(m.group(2)), int(m.group(3)) + 1))
     return regs
 
 
 def _valu_scalar_dest(ins):
-    """Scalar registers written by a vector instruction (empty for everything else)."""
-    op = ins.split()[0]
-    if op.startswith(("v_readlane_b32", "v_readfirstlane_b32")) or (op.startswith("v_cmp") and op.endswith("_e64")):
-        return _sregs(ins.split(None, 1)[1].split(",")[0])
+    """Scalar registers written by a vector instruction (empty for everything else): the first operand of lane reads and
+    compares, the second of what leaves a carry or a scale flag."""
+    op, _, args = ins.partition(" ")
+    args = args.split(",")
+    if op.startswith(("v_readlane_b32", "v_readfirstlane_b32", "v_cmp")):
+        return _sregs(args[0])
+    if re.match(r"v_(?:\w+_co_|div_scale_|mad_[ui]64_[ui]32)", op):
+        return _sregs(args[1])
     return set()
+
+
+def _salu_dest(ins):
+    """Scalar registers written by a scalar arithmetic instruction: what a vector instruction before it left there (the carry
+    of a multiply-add that nobody asked for) is not what is read behind it."""
+    m = re.match(r"s_(?:mov|add|addc|sub|subb|mul|and|or|lshl|lshr|ashr|cselect)\w*\s+([^,]+),", ins)
+    return _sregs(m.group(1)) if m else set()
 
 
 def _check_valu_sgpr_to_vmem(text, what):
@@ -235,6 +249,7 @@ def _check_valu_sgpr_to_vmem(text, what):
             while j >= 0 and ws < 5:
                 hit = _valu_scalar_dest(code[j]) & used
                 assert not hit, (what, name, code[j], ins, "only %d wait states between" % ws)
+                used -= _salu_dest(code[j])
                 ws += _wait_states(code[j])
                 j -= 1
 
@@ -261,8 +276,7 @@ def test_attention_copies_and_scalars():
     text = _assembly("attention.hip")
     funcs = _functions(text)
     assert sum("attn_" in n for n in funcs) == 4
-    # (a scalar may live in a half of vcc)
-    _check_m0(re.sub(r"(s_mov_b32 m0, )vcc_(?:lo|hi)", r"\g<1>s0", text), "attention.hip")
+    _check_m0(text, "attention.hip")
     _check_valu_sgpr_to_vmem(text, "attention.hip")
     # the copies of the next tile run beside the products of this one: no wait for memory between a tile's first MFMA
     # and its last in the backward of long sequences
@@ -285,3 +299,21 @@ def test_the_scalar_hazard_check_sees_a_planted_hazard():
     with pytest.raises(AssertionError):
         _check_valu_sgpr_to_vmem(bad, "planted")
     _check_valu_sgpr_to_vmem(bad.replace("\tglobal_load", "\ts_nop 4\n\tglobal_load"), "planted, with wait states")
+
+
+# the same for a base in vcc, as a whole or by halves, written by each kind of vector instruction that can
+@pytest.mark.parametrize("write", ["v_cmp_gt_i32_e32 vcc, s3, v1", "v_cmp_lt_u32_e64 vcc, v1, v2", "v_readlane_b32 vcc_lo, v255, 16",
+                                   "v_readfirstlane_b32 vcc_hi, v3", "v_add_co_u32_e32 v0, vcc, v1, v2",
+                                   "v_addc_co_u32_e64 v0, vcc, v1, v2, s[4:5]", "v_div_scale_f32 v0, vcc, v1, v2, v1",
+                                   "v_mad_u64_u32 v[0:1], vcc, v2, v3, v[4:5]"])
+def test_the_scalar_hazard_check_knows_vcc(write):
+    bad = "_Z3foov:\n\t%s\n\tglobal_load_lds_dwordx4 v221, vcc\n\ts_endpgm\n.Lfunc_end0:\n" % write
+    with pytest.raises(AssertionError):
+        _check_valu_sgpr_to_vmem(bad, "planted")
+    _check_valu_sgpr_to_vmem(bad.replace("\tglobal_load", "\ts_nop 4\n\tglobal_load"), "planted, with wait states")
+    _check_valu_sgpr_to_vmem(bad.replace("v221, vcc", "v221, s[6:7]"), "another base")
+    half = bad.replace("\tglobal_load", "\ts_add_u32 vcc_lo, s4, 64\n\tglobal_load")
+    if not write.startswith("v_readlane"):               # (that one writes the low half only)
+        with pytest.raises(AssertionError):
+            _check_valu_sgpr_to_vmem(half, "planted, half of it written again")
+    _check_valu_sgpr_to_vmem(half.replace("\tglobal_load", "\ts_addc_u32 vcc_hi, s5, 0\n\tglobal_load"), "written again")
