@@ -660,15 +660,20 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(const bf16 *__rest
 //   * Q / dO tiles (4 KB each) are double buffered asynchronous copies that also bring the tile's 32 K rows,
 //     dS^T is double buffered too, so there is one barrier per query tile: phase 2 of tile i runs next to
 //     phase 1 of tile i + 1.
-//   * Before the arithmetic starts the block waits for one round of memory traffic: the first tile, the
-//     wave's V fragments, and the operands of delta = rowsum(dO * O) of all rows, every load of which is
-//     issued before the first is used.  (All blocks of a launch run in step, so this round is read by every
+//   * Before the arithmetic starts the block waits for two rounds of memory traffic: the first tile with lse (whose LDS store
+//     stands in front of the other loads), then the wave's V fragments and delta, or the operands of delta =
+//     rowsum(dO * O) of all rows, every load of which is issued before the first is used.  (All blocks of a launch run in
+//     step, so these rounds are read by every
 //     compute unit at once, at the memory's speed, with the matrix cores idle; forming delta tile by tile
 //     behind the arithmetic, from rows streamed into LDS, was measured and only moved the same time into the
 //     steps, whose length is set by the latency of the tile copies.)
 //   * The two blocks' accumulators and V fragments leave 96 registers.  With an address register for every buffer and
 //     offset, 84 bytes of V were spilled, and each reload waited for the copies in flight; offsets formed once per lane
 //     and buffers as scalars: 216 -> 189 us (S = 512, 64 x 16 heads), 12.3 -> 9.0 (S = 128, 12 heads).
+//   * The limit of 512 tokens is what K, dS^T and the tiles take of LDS.  From 257 on the split pair could run too (and the product
+//     that forms dO would not have to form delta): whole rounds, 64 x 16 heads of 512 tokens 38.16 ms with this kernel, 38.62
+//     with the pair; 20 x 12 of 512 4.860, 4.867; 12 x 16 of 448 9.88, 10.01; 8 x 16 of 512, a block on every other CU, 2.276,
+//     2.237.  The line may not depend on the number of heads, else a sequence's bits would on its batch.
 constexpr int FB_MAXS = 512;
 
 // XOR mask of the 8-byte slots of a dS^T row (64 bytes = 32 queries): conflict-free both for the

@@ -13,7 +13,7 @@
 //
 // At T = 1024, 768 -> 768, r = 4 (2.5 GFLOP, 15 MB: 16 us at the fp32 matrix rate) forward + backward took 1113 us
 // as nine launches of one vector-FMA kernel: single floats moved one by one, the rank-4 products as mostly empty 64 x 64
-// tiles, the adapter gradients as 12 blocks that walk all tokens.  Five launches of the kernels below: 48 us (59 before the
+// tiles, the adapter gradients as 12 blocks that walk all tokens.  Five launches of the kernels below: 47 us (59 before the
 // products that fill the chip took the ring kernel).
 #include "common.h"
 #include "gemm_copy.h"
@@ -149,10 +149,10 @@ __device__ __forceinline__ float4 up_frag_u(const GemmF32 &a, int n, int g)
 // TM x TN tile per block, KS groups of 4 waves (2 x 2) that take the slabs of the contraction in turn, each with two LDS
 // stages of its own; a group's next slab is on its way from memory in registers while the matrix cores work on the
 // current one, and the groups' accumulators are added in group order at the end.  With one tile per CU a slab costs a
-// memory round trip, not its arithmetic, which a second group hides (T = 1024, 768 -> 768: 64.6 -> 59.2 us forward +
-// backward; four groups: 58.9 there, slower at T = 4096); 128 x 128 tiles halve the operand traffic where there are
-// enough of them.  22 us per product at T = 1024 (55 TFLOP/s; 192 tiles leave a quarter of the CUs idle), 96 TFLOP/s at
-// T = 8192, 1280 -> 5120.
+// memory round trip, not its arithmetic, which a second group hides; 128 x 128 tiles halve the operand traffic where there are
+// enough of them.  For contractions that are no multiple of 64 and rows that are no whole float4s; the figures it was chosen by
+// are from when it ran all products: T = 1024, 768 -> 768 in 64.6 us forward + backward with one group, 59.2 with two (22 us per
+// product, 55 TFLOP/s), 58.9 with four, which were slower at T = 4096; 96 TFLOP/s at T = 8192, 1280 -> 5120.
 template <int TM, int TN, int KS, bool BT, bool VEC>
 __global__ __launch_bounds__(256 * KS) void f32_gemm_kernel(GemmF32 a)
 {
@@ -320,7 +320,8 @@ __global__ __launch_bounds__(256 * KS) void f32_gemm_kernel(GemmF32 a)
 // 32 in turn.  A stage of the LDS ring holds a slab for each group, filled by asynchronous copies NST - 1 stages ahead (a
 // slab's arithmetic is shorter than the round trip that the kernel above has one slab in flight for); operand rows of
 // 128 bytes with the 16-byte chunks XORed with the row, W read as [k, n] as rows of TN floats with the chunks rotated by the
-// k-group, so that the four k-groups of a read meet different banks.  Same sums in the same order.
+// k-group, so that the four k-groups of a read meet different banks.  The sums and their order are those of f32_gemm_kernel with
+// two groups (its 128 x 128 form has one, and one chain of sums instead of two).
 template <int TM, int TN, int WM, int WN, int NST, bool BT>
 __global__ __launch_bounds__(512) void f32_tile_kernel(GemmF32 a)
 {
@@ -598,7 +599,9 @@ void launch_ring(const GemmF32 &a, hipStream_t st)
     hipLaunchKernelGGL((f32_tile_kernel<TM, TN, WM, WN, NST, BT>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(512), 0, st, a);
 }
 // The kernel for a product.  16 x 16 outputs per block (f32_gemm_direct_kernel) while 64 x 64 tiles would leave most CUs without
-// work.  The ring needs whole stages of 64 and 32-bit byte offsets and runs on the form that costs least, in us as measured
+// work: drawn at 96 of them against f32_gemm_kernel.  Against the ring the line would lie at about 36 (projection + product,
+// 1024 -> 1024: 32 tiles 15.3 us direct, 17.2 on the ring; 48: 20.3, 17.4; 80: 27.2, 17.6; 4096 -> 1024: 51.2, 56.0; 66.0, 58.7;
+// 92.3, 59.7).  The ring needs whole stages of 64 and 32-bit byte offsets and runs on the form that costs least, in us as measured
 // (T = 64 to 8192 at five weight shapes): rounds of 256 tiles, or of 512 where two blocks share a CU, at a + b (K / 64) each.
 // 32 x 64 and 64 x 48 fill the chip where 64 x 64 tiles leave a part of it idle (T = 1024, 768 -> 768: 256 tiles of 64 x 48 in
 // 13.5 us, 192 of 64 x 64 in 16.1).  Without the ring (f32_gemm_kernel) 128 x 128 tiles once two of them per CU are there (below

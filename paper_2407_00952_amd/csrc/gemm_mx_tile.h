@@ -66,9 +66,10 @@ __device__ __forceinline__ void gemm_mx_body(const MxArgs &a)
     const int m0 = at.m0, n0 = at.n0, n_end = at.n_end, seg = at.seg;
     const int nk = a.K / BKB;
 
-    // Low-rank operands first (SplitLoRA Sec. II-C: W + BA with the adapter kept in bf16; a few MB: cache hits), so that the
-    // wait for them costs no more than the one for the first stage.  Columns of the rank-space activations beyond K2 and of
-    // the up-projection beyond the ranks are zero.
+    // Low-rank operands first (SplitLoRA Sec. II-C: W + BA with the adapter kept in bf16; a few MB: cache hits).  Columns of the
+    // rank-space activations beyond K2 and of the up-projection beyond the ranks are zero.  Their products stand behind the
+    // first copies of every stage, which the compiler cannot count: it waits for all of these, so a tile with an adapter
+    // begins when the whole ring is filled, not when its first stage is.
     f32x4 acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)

@@ -55,7 +55,7 @@ __device__ __forceinline__ f32x4 get_partial(const float4 *p)
 }
 
 // Epilogue of CR rows staged in LDS, so that memory sees 16-byte accesses.
-// INTERIOR: the rows and columns lie wholly inside the matrix, no branch (see epilogue4 in gemm.hip).
+// INTERIOR: the rows and columns lie wholly inside the matrix, no branch (see epilogue4 in gemm_epilogue.h).
 template <int EPI, int TN, int CR, int NTHR, bool INTERIOR, class Args>
 __device__ __forceinline__ void epilogue_rows(const Args &a, const float *stg, int m0, int n0, int n_end,
                                               const float (&bias8)[8])

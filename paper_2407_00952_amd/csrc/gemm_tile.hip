@@ -57,7 +57,9 @@ int launch_te(const GemmArgs &a, int nz, const TilePlan &p, hipStream_t st)
 }
 
 // Fitted to plain-store launches of 64 to 32768 rows at seven weight shapes of 768 to 5120 (mean error 2 to 6 %; the form it picks
-// is 0.5 % slower on average than the fastest), the third group to 32 and 48 columns together.
+// is 0.5 % slower on average than the fastest of such a launch).  Other epilogues are priced as that one and take up to 45 % more
+// (GELU of 10240 rows of 768 -> 3072: 49 us here, 72 measured).  The third group was fitted to 32 and 48 columns together; its
+// 256 x 256 row is that of 48 (32768 rows of 4096 -> 1024: 262 us, with 32 columns 233).
 constexpr Form FORMS[3][9] = {
     {{32, 32, {2.46f, .093f}, {2.60f, .175f}, {0.97f, .170f}},          // no rank-space branch
      {32, 64, {2.33f, .129f}, {2.49f, .250f}, {0.70f, .269f}},

@@ -275,7 +275,8 @@ __global__ __launch_bounds__(NTHR) void gemm_mx_kernel(MxArgs a)
     MX_ISSUE(st0, 0, 0) MX_ISSUE(st0, 0, 1) MX_ISSUE(st0, 0, 2) MX_ISSUE(st0, 0, 3)
     // ---- low-rank part (SplitLoRA Sec. II-C: W + BA with the adapter kept in bf16), first as in gemm_mx_tile.h: ldt / 32 bf16
     //      MFMA k-steps per tile on operands read straight from global memory (a few MB: cache hits); columns
-    //      of the rank-space activations beyond K2 and of the up-projection beyond the ranks are zero
+    //      of the rank-space activations beyond K2 and of the up-projection beyond the ranks are zero.  (The branch keeps the
+    //      eight loads of rank-space rows apart: each is waited for, with everything in flight, before its MFMAs.)
     if (a.zs[seg] != nullptr) {
         const bf16 *zs_ = a.zs[seg], *tm_ = a.tmat[seg];
         for (int ks = 0; ks < (a.ldt >> 5); ++ks) {
