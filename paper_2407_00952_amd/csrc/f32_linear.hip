@@ -17,6 +17,7 @@
 // products that fill the chip took the ring kernel).
 #include "common.h"
 #include "gemm_copy.h"
+#include <type_traits>
 
 // the tile of a product's kernel and the stages of its ring of copies (0: a kernel without one); vec: operands of 16-byte rows
 struct F32Plan { int tm, tn, stages; };
@@ -543,7 +544,10 @@ __global__ __launch_bounds__(512) void f32_gemm_direct_kernel(GemmF32 a)
 // ---- adapter gradients --------------------------------------------------------------------------------------------
 // G[c,j] = s sum_t X[t,c] Y[t,j], j < r: dA (written [r,C]) from X = x, Y = p and dB (written [C,r]) from X = dy, Y = z.
 // One block per 32 columns walks all tokens with 32 half-waves (a half-wave reads 128 bytes of a row), whose sums
-// are added in order.  Bound by reading X once; no second launch for a reduction.
+// are added in order.  Bound by reading X once; no second launch for a reduction.  A wave's rows are a chain of round trips, so
+// for up to 4 columns of Y 16 of them are in flight, then 4, then single ones (us, backward of a 768 -> 768 layer, r = 4, T = 300,
+// 500, 1000, 8192: 4 rows and single ones 19.4, 20.9, 28.6, 148; 16 and single ones 20.1, 22.3, 29.1, 140; as it is 18.9, 20.7,
+// 27.7, 138); more columns leave registers for 4 rows.
 struct GradJob { const float *X; const float *Y; int C; float *out; int rxC; };
 struct GradJobs { GradJob j[2]; };
 
@@ -558,19 +562,35 @@ __global__ __launch_bounds__(1024) void f32_grad_kernel(GradJobs jobs, int T, in
     float acc[ZP];
 #pragma unroll
     for (int j = 0; j < ZP; ++j) acc[j] = 0.f;
-#pragma unroll(ZP == 4 ? 16 : 4)
-    for (int t = hw; t < T; t += 32) {
-        const float x = jb.X[(size_t)t * jb.C + cc];
-        const float4 *y = (const float4 *)(jb.Y + (size_t)t * ZP);
+    // N rows of this half-wave from t on, all requested before the first is used
+    auto rows = [&](int t, auto n) {
+        constexpr int N = decltype(n)::value;
+        float x[N];
+        float4 y[N][ZP / 4];
 #pragma unroll
-        for (int q = 0; q < ZP / 4; ++q) {
-            const float4 v = y[q];
-            acc[4 * q] = fmaf(x, v.x, acc[4 * q]);
-            acc[4 * q + 1] = fmaf(x, v.y, acc[4 * q + 1]);
-            acc[4 * q + 2] = fmaf(x, v.z, acc[4 * q + 2]);
-            acc[4 * q + 3] = fmaf(x, v.w, acc[4 * q + 3]);
+        for (int u = 0; u < N; ++u) {
+            x[u] = jb.X[(size_t)(t + 32 * u) * jb.C + cc];
+#pragma unroll
+            for (int q = 0; q < ZP / 4; ++q) y[u][q] = ((const float4 *)(jb.Y + (size_t)(t + 32 * u) * ZP))[q];
         }
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int q = 0; q < ZP / 4; ++q) {
+                const float4 v = y[u][q];
+                acc[4 * q] = fmaf(x[u], v.x, acc[4 * q]);
+                acc[4 * q + 1] = fmaf(x[u], v.y, acc[4 * q + 1]);
+                acc[4 * q + 2] = fmaf(x[u], v.z, acc[4 * q + 2]);
+                acc[4 * q + 3] = fmaf(x[u], v.w, acc[4 * q + 3]);
+            }
+    };
+    int t = hw;
+    if (ZP == 4) {
+        for (; t + 15 * 32 < T; t += 16 * 32) rows(t, std::integral_constant<int, 16>());
+        for (; t + 3 * 32 < T; t += 4 * 32) rows(t, std::integral_constant<int, 4>());
     }
+#pragma unroll(ZP == 4 ? 1 : 4)
+    for (; t < T; t += 32) rows(t, std::integral_constant<int, 1>());
 #pragma unroll
     for (int j = 0; j < ZP; ++j) red[hw][j][l] = acc[j];
     __syncthreads();

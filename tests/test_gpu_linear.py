@@ -118,12 +118,23 @@ def test_fp32_ring_forms(T, n_in, n_out):
     test_fp32_dispatch_edges(T, n_in, n_out, 5, True)
 
 
+# The adapter gradients of up to 4 columns take a half-wave's rows 16, 4 and 1 at a time (32 half-waves): none, one and several of
+# each, half-waves with and without the last row.
+@pytest.mark.parametrize("T", [1, 31, 32, 97, 128, 129, 480, 481, 512, 513, 1000, 1024, 1185])
+def test_fp32_adapter_gradient_rows(T):
+    test_fp32_dispatch_edges(T, 72, 40, 3, False)
+
+
 # The low-rank term may not cost the fp32 product precision: error (2-norm, against fp64) of y no larger than that of the sums
 # taken one after the other, the frozen product and the low-rank one each on its own (the 5 % cover the sample: some 1e5
 # independent roundings).  Short contractions, where 16 more roundings at the size of the result show most.
 # A low-rank term that is small beside the frozen product, and one that is larger.
+# T, n_in, n_out: tile and ring stages.
+FP32_PRECISION = {(20, 16, 768): (16, 16, 0), (700, 32, 704): (64, 64, 0), (8200, 16, 1030): (128, 128, 0), (700, 64, 704): (32, 64, 4)}
+
+
 @pytest.mark.parametrize("boost", [1, 30])
-@pytest.mark.parametrize("T,n_in,n_out", [(20, 16, 768), (700, 32, 704), (8200, 16, 1030)])     # direct, 64 and 128 tiles
+@pytest.mark.parametrize("T,n_in,n_out", list(FP32_PRECISION))
 def test_fp32_low_rank_term_costs_no_precision(T, n_in, n_out, boost):
     c = synth.make_single_layer(T, n_in, n_out, 16, seed=23 + T, bias=True)
     c["B"] = c["B"] * np.float32(boost)
@@ -147,7 +158,11 @@ def test_fp32_low_rank_term_costs_no_precision(T, n_in, n_out, boost):
     assert e_got <= 1.05 * e_plain
 
 
-@pytest.mark.parametrize("T,n_in,n_out", [(20, 64, 96), (700, 768, 704)])       # direct, 64 x 64 tiles
+FP32_INFINITY = {(20, 64, 96): ((16, 16, 0),) * 2, (700, 768, 704): ((32, 64, 4), (64, 48, 4)),      # direct, ring
+                 (700, 780, 716): ((64, 64, 0),) * 2, (8200, 100, 1028): ((128, 128, 0), (64, 64, 0))}
+
+
+@pytest.mark.parametrize("T,n_in,n_out", list(FP32_INFINITY))
 def test_fp32_infinity_stays_an_infinity(T, n_in, n_out):
     # rank 3 is kept as 4 columns: the empty one must not turn inf * 0 into a NaN of the result
     c = synth.make_single_layer(T, n_in, n_out, 3, seed=5, bias=False)
@@ -211,9 +226,8 @@ def test_bf16_zero_B_is_bitwise_base():
     assert np.array_equal(y_lora, y_base) and np.array_equal(dx_lora, dx_base)
 
 
-# The frozen product on its own (Sec. II-C without the adapter): this is the launch shape of the stack's
-# products that have no rank-space branch, i.e. the 4-wave GEMM kernel with the plain-store epilogue.  One
-# k-slab, an odd number of slabs, ragged row and column tiles, a single row, with and without bias.
+# The frozen product on its own (Sec. II-C without the adapter), the stack's products that have no rank-space branch with the
+# plain-store epilogue.  One k-slab, an odd number of slabs, ragged row and column tiles, a single row, with and without bias.
 @pytest.mark.parametrize("T,n_in,n_out,bias", [
     (700, 320, 448, True),
     (1, 64, 8, True),
@@ -271,6 +285,7 @@ FROZEN_FORMS = {
     (1500, 1088, 3080): (192, 128),
     (2000, 1088, 3080): (256, 128),
     (2100, 192, 3080): (128, 256),
+    (3700, 192, 4104): (256, 256),
 }
 
 
@@ -289,6 +304,7 @@ LAYER_FORMS = {
     (1090, 320, 2048): (128, 128),
     (1400, 704, 3072): (192, 128),
     (2000, 1088, 3072): (256, 128),
+    (2700, 192, 3072): (256, 256),
 }
 
 

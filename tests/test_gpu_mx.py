@@ -90,7 +90,7 @@ def _linear_gpu(xq, xs, wq, ws, bias):
 
 
 @pytest.mark.parametrize("T,K,N,with_bias", [
-    (256, 128, 256, True),        # one tile, one slab
+    (256, 128, 256, True),        # whole tiles, one slab
     (700, 384, 320, True),        # ragged row and column tiles, odd number of slabs
     (1024, 768, 768, False),      # the single-layer configuration's shape
     (513, 1024, 264, True),       # one row and one column piece past a tile

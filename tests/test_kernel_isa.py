@@ -272,6 +272,29 @@ def test_fp32_ring_copies_and_scalars():
     _check_valu_sgpr_to_vmem(text, "f32_linear.hip")
 
 
+def _loops(body):
+    """[instructions] of every loop without a label inside (a label, its body, a branch back to it)"""
+    loops = []
+    for i, ins in enumerate(body):
+        m = re.match(r"s_c?branch\w*\s+(\S+)", ins)
+        if m and m.group(1) + ":" in body[:i]:
+            inner = body[body.index(m.group(1) + ":") + 1:i]
+            if not any(_is_label(x) for x in inner):
+                loops.append(inner)
+    return loops
+
+
+def test_fp32_adapter_gradient_rows_are_in_flight_together():
+    """the loops over a half-wave's rows (two loads each at up to 4 columns): 16 of them, then 4, then single ones, so that
+    behind the last 16 there are three groups of 4 and three single rows at most"""
+    body = next(b for n, b in _functions(_assembly("f32_linear.hip")).items() if "f32_grad_kernelILi4E" in n)
+    loads = [[i for i, x in enumerate(lp) if x.startswith("global_load")] for lp in _loops(body)]
+    loops = [(lp, ld) for lp, ld in zip(_loops(body), loads) if ld]
+    assert [len(ld) for _, ld in loops] == [32, 8, 2]
+    for (lp, ld), first in zip(loops[:2], (16, 8)):      # loads in front of the first wait for one
+        assert sum(i < next(j for j, x in enumerate(lp) if "vmcnt" in x) for i in ld) >= first
+
+
 def test_attention_copies_and_scalars():
     text = _assembly("attention.hip")
     funcs = _functions(text)

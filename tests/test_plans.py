@@ -4,6 +4,7 @@ import plans
 import test_gpu_linear as linear
 import test_gpu_mx as mx
 import test_gpu_stack as stack
+import test_zz_no_alloc as no_alloc
 from paper_2407_00952_amd import synth
 
 BF16_FORMS = {(32, 32), (32, 64), (64, 64), (64, 128), (128, 128), (192, 128), (256, 128), (128, 256), (256, 256)}
@@ -17,20 +18,26 @@ def test_fp32_ring_forms():
     for which in ("forward", "input gradient"):
         assert {f for w, f in linear.FP32_RING_FORMS.values() if w == which} == {
             (32, 64, 4), (64, 48, 4), (64, 64, 4), (64, 64, 2), (128, 128, 2)}
+    for case, want in linear.FP32_PRECISION.items():
+        assert plans.f32_layer(*case)[0] == want, case
+    for case, want in linear.FP32_INFINITY.items():
+        assert tuple(plans.f32_layer(*case)) == want, case
 
 
 def test_bf16_forms():
     for (T, n_in, n_out), want in linear.FROZEN_FORMS.items():
         assert plans.tile(T, n_out, n_in) == want + (1,), (T, n_in, n_out)
-    assert set(linear.FROZEN_FORMS.values()) == BF16_FORMS - {(256, 256)}
+    assert set(linear.FROZEN_FORMS.values()) == BF16_FORMS
     for case, want in linear.LAYER_FORMS.items():
         assert plans.layer(*case)[0] == want + (1,), case
-    assert set(linear.LAYER_FORMS.values()) == BF16_FORMS - {(128, 256), (256, 256)}
+    assert set(linear.LAYER_FORMS.values()) == BF16_FORMS - {(128, 256)}
 
 
 def test_shared_contractions():
     for case, want in linear.SHARED.items():
         assert tuple(p[2] for p in plans.layer(*case)) == want, case
+    for case, want in no_alloc.SHARED.items():
+        assert plans.layer(*case)[1][2] == want, case
     assert {w[0] for w in linear.SHARED.values()} == {w[1] for w in linear.SHARED.values()} == {1, 2, 3, 4}
 
 

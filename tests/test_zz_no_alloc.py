@@ -12,6 +12,9 @@ from gpu_util import BF16_TOL, relerr, say
 pytestmark = pytest.mark.gpu
 
 
+SHARED = {(130, 128, 5120): 4, (2048, 256, 5120): 2}     # blocks to a tile of the input gradient (tests/test_plans.py)
+
+
 def _both(T, n_in, n_out, r, seed):
     import torch
     c = synth.make_single_layer(T, n_in, n_out, r, seed=seed, quant=True)
@@ -48,7 +51,9 @@ def test_noalloc_backward_equals_the_workspace_backward():
     say("allocation-free single-layer backward, calls in a row")
     _both(2048, 512, 768, 8, seed=901)
     _both(700, 320, 448, 3, seed=902)          # smaller, ragged tiles, lower rank
-    _both(130, 128, 2432, 3, seed=904)         # the input gradient's contraction shared over four blocks
+    _both(130, 128, 2432, 3, seed=904)
+    for T, n_in, n_out in SHARED:              # the input gradient's contraction shared over blocks
+        _both(T, n_in, n_out, 3, seed=905)
 
 
 def test_noalloc_backward_of_a_wide_input():
