@@ -119,6 +119,8 @@ inline int gemm_counted_rows(int max_rows) { return max_rows <= 128 ? 128 : 256;
 // of gemm.hip, 128 columns and more than 64 rows those of gemm_wide.hip, the others those of gemm_tile.hip
 struct TilePlan { int tm, tn, splits; };
 extern "C" TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int epi, int nz, bool can_split, bool whole);
+// the same for a plain store over counted rows (at most M) on a kernel that computes all M; tm 0: on the one that counts
+extern "C" TilePlan plan_gemm_counted(int M, int N, int K);
 int launch_gemm_tile(const GemmArgs &a, int epi, int nz, const TilePlan &p, hipStream_t st);
 int launch_gemm_wide(const GemmArgs &a, int epi, int nz, const TilePlan &p, hipStream_t st);
 // whether a plain-store launch of M rows (one segment) shares its contraction once it has scratch, the most rows at which one

@@ -574,14 +574,13 @@ int launch_e(const GemmArgs &a, int nz, int rows, hipStream_t st)
 
 static int launch_gemm_inner(const GemmArgs &a, int epi, int nz, hipStream_t st);
 static int launch_gemm_counted(const GemmArgs &a, int epi, hipStream_t st);
-static bool counted_on_small_tiles(const GemmArgs &a);
 
 int launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st)
 {
     const bool rec = prof_begin(PK_GEMM, st, a.rows ? &a.rows->rows : nullptr);
     GemmArgs b = a;
     b.clk = prof_clock_words(rec);
-    const int rc = epi == EPI_PARTIAL || (a.rows && !counted_on_small_tiles(a))
+    const int rc = epi == EPI_PARTIAL || (a.rows && plan_gemm_counted(a.M, a.N, a.K).tm == 0)
                        ? launch_gemm_counted(b, epi, st)
                        : launch_gemm_inner(b, epi, nz, st);
     // algorithmic work of this launch: the frozen product only (the rank-r branch adds < 1 % and is left
@@ -603,9 +602,8 @@ static int launch_gemm_inner(const GemmArgs &a, int epi, int nz, hipStream_t st)
     if (nz > 0 && (a.K2 != nz || (a.ldt % 8) || a.ldt < (nz + 31) / 32 * 32 || (a.ldz % 8))) return SL_EINVAL;
     if (epi == EPI_STORE_DELTA && (nz != 0 || !a.dl_o || !a.dl_lo || !a.dl_out || !a.out0 || (a.N % 64) || a.nseg != 1))
         return SL_EINVAL;                                // no rank-space branch, whole heads of 64 columns
-    // (a product over counted rows comes here only to run on the smaller tiles)
-    const TilePlan plan = plan_gemm_tile(a.M, a.seg_n, a.nseg, a.K, epi, nz, a.split_part != nullptr && a.split_cnt != nullptr,
-                                         a.rows == nullptr);
+    const TilePlan plan = a.rows ? plan_gemm_counted(a.M, a.N, a.K)
+                                 : plan_gemm_tile(a.M, a.seg_n, a.nseg, a.K, epi, nz, a.split_part != nullptr && a.split_cnt != nullptr, true);
     if (plan.tn < 256) return launch_gemm_tile(a, epi, nz, plan, st);
     switch (epi) {
     case EPI_STORE: return launch_e<EPI_STORE>(a, nz, plan.tm, st);
@@ -615,14 +613,6 @@ static int launch_gemm_inner(const GemmArgs &a, int epi, int nz, hipStream_t st)
     case EPI_STORE_DELTA: return launch_t4<EPI_STORE_DELTA>(a, plan.tm, st);
     }
     return SL_EINVAL;
-}
-
-// Whether a plain-store product over counted rows runs on the smaller tiles, which compute all M rows: where one round of
-// them does.  (Larger ones would spend rounds on rows that nobody wants: 40 % of a loss head's are prompt tokens.)
-static bool counted_on_small_tiles(const GemmArgs &a)
-{
-    auto tiles = [&](int t) { return (long)((a.M + t - 1) / t) * ((a.N + t - 1) / t); };
-    return a.M <= 128 || tiles(64) <= 512 || tiles(128) <= 256;
 }
 
 // A product over the rows that a kernel before it counted (a.rows; a.M is their upper bound), without rank-space branch.
@@ -638,7 +628,7 @@ static int launch_gemm_counted(const GemmArgs &a, int epi, hipStream_t st)
     const int tiles = ((a.M + bm - 1) / bm) * ((a.N + BN - 1) / BN);
     // shares are chosen where the rows are counted, so that launch always has a block for every CU
     const dim3 grid(epi == EPI_PARTIAL ? 256 : std::min((tiles + 7) / 8 * 8, 256)), block(NTHR4);
-    // (up to 128 rows the plain store runs on the smaller tiles)
+    // (up to 128 rows the plain store runs on kernels that compute all of them: plan_gemm_counted)
     if (epi == EPI_STORE && bm == 256) hipLaunchKernelGGL((gemm_counted4<EPI_STORE, 8>), grid, block, 0, st, a);
     else if (epi == EPI_PARTIAL && bm == 256) hipLaunchKernelGGL((gemm_counted4<EPI_PARTIAL, 8>), grid, block, 0, st, a);
     else if (epi == EPI_PARTIAL) hipLaunchKernelGGL((gemm_counted4<EPI_PARTIAL, 4>), grid, block, 0, st, a);

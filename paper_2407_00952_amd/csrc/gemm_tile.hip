@@ -122,6 +122,17 @@ TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int epi, int nz, bool
     return best;
 }
 
+// A plain store over counted rows (at most M) on a kernel that computes all M: up to 512 tiles of 128 x 128, which the smaller forms
+// take at once, and for at most 128 rows, of which the counting kernel's 256-row tiles would fill half.  Larger launches would
+// spend rounds on rows that nobody wants (40 % of a loss head's are prompt tokens).  Whole loss heads of 768 columns, us, on the
+// smaller forms and on the counting kernel: 2315 tokens, V = 2000 (304 tiles) 59, 69; 1024, 8000 (504) 78.5, 86; 1500, 8000
+// (756) 90, 92, with 1280 columns 112, 110; 1500, 31118 (2928; 1280 columns) 273, 220.
+TilePlan plan_gemm_counted(int M, int N, int K)
+{
+    if (M > 128 && (long)((M + 127) / 128) * ((N + 127) / 128) > 512) return {0, 0, 0};
+    return plan_gemm_tile(M, N, 1, K, EPI_STORE, 0, false, M <= 128);
+}
+
 // Scratch by the decision above, so that a layer has none where its launch shares nothing.  The shared form costs the same at
 // every row count of a share count and the others no less at more rows, so a share count that is ever taken is taken at its
 // last row of tiles, and those say what any number of rows needs.

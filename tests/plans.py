@@ -70,3 +70,9 @@ def stack(T, d, f, proj, seq_len, fp8=False):
              (delta, ad("o"), d, d, 1), (STORE, 16 * qkv, d, 3 * d, 1)]
     return {(epi, nz) + (mx(T, N, K, nseg) if fp8 else tile(T, N, K, epi, nz, nseg=nseg)[:2])
             for epi, nz, N, K, nseg in prods}
+
+
+def counted(M, N, K):
+    """(rows, columns) of a plain store over counted rows on a kernel that computes all M, None for the one that counts"""
+    p = _fn("plan_gemm_counted", TilePlan, c_int, c_int, c_int)(M, N, K)
+    return (p.tm, p.tn) if p.tm else None

@@ -115,6 +115,18 @@ def test_loss_head_listed_rows(T, d, V, n_labeled):
     check_full(inp, d, V, "listed rows")
 
 
+# Where the logits' product goes from the kernels that compute all rows to the one that counts them (None): 512 and 513 tiles of
+# 128 x 128, 128 and 129 rows of a wide vocabulary; few labeled rows and all.  T, d, V: tile (tests/test_plans.py).
+LOGIT_FORMS = {(1000, 64, 8190): (64, 128), (1030, 64, 7290): None, (128, 768, 50257): (128, 256), (129, 64, 50257): None,
+               (600, 768, 12013): (128, 128), (700, 512, 9001): (256, 128), (100, 64, 1003): (32, 64)}
+
+
+@pytest.mark.parametrize("T,d,V", list(LOGIT_FORMS))
+@pytest.mark.parametrize("share", [0.1, 1.0])
+def test_loss_head_logit_forms(T, d, V, share):
+    test_loss_head_listed_rows(T, d, V, round(share * T))
+
+
 def test_loss_head_nan_stays_in_its_row():
     """A NaN in an unlabeled row of y reaches that row of dy (as the LayerNorm gradient has it) and nothing else."""
     T, d, V = 300, 128, 1003

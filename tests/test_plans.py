@@ -2,6 +2,7 @@
 change of a cost table that moves a case to another kernel fails here."""
 import plans
 import test_gpu_linear as linear
+import test_gpu_loss_head as head
 import test_gpu_mx as mx
 import test_gpu_stack as stack
 import test_zz_no_alloc as no_alloc
@@ -72,3 +73,15 @@ def test_batches_of_the_wider_stack():
     for proj in (("q", "v"), synth.PROJ_NAMES):
         assert forms(1, 128, proj) == {(32, 32), (32, 64)} and forms(33, 128, proj) == {(128, 128), (256, 256)}
         assert set().union(*(forms(n, 128, proj) for n in (1, 2, 4, 8, 16, 24, 33))) == BF16_FORMS - {(128, 256)}
+
+
+def test_logits_of_a_loss_head():
+    """all rows are computed where 512 tiles of 128 x 128 or fewer hold them, and up to 128 rows; elsewhere they are counted"""
+    for (T, d, V), want in head.LOGIT_FORMS.items():
+        assert plans.counted(T, -(-V // 64) * 64, d) == want, (T, d, V)
+    for d in (64, 768, 1280, 2048):
+        for T in (1, 64, 128, 129, 256, 300, 600, 1000, 1500, 4096, 16384):
+            for Vp in (64, 1024, 1344, 4288, 8000, 12032, 20032, 31168, 50304, 65536):
+                few = T <= 128 or -(-T // 128) * -(-Vp // 128) <= 512
+                plan = plans.counted(T, Vp, d)
+                assert (plan is not None) == few and (not few or plan == plans.tile(T, Vp, d, whole=T <= 128)[:2]), (T, Vp, d)
