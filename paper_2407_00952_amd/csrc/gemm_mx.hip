@@ -14,16 +14,25 @@ __global__ __launch_bounds__(TM <= 64 ? 256 : 512, 2) void gemm_mx_tile_kernel(M
     gemm_mx_body<EPI, TM, TN, WM, WN, (TM > 128 || (TM == 64 && TN == 128) ? 3 : 4)>(a);
 }
 
-// Fitted to plain-store launches of 16 to 32768 rows at eight weight shapes with a rank-space branch (mean error 6 %, the form it
-// picks is 0.1 % slower on average than the fastest); a slab is 128.
-constexpr Form FORMS[7] = {
-    {32, 64, {3.29f, .189f}, {2.71f, .420f}, {0.08f, .458f}},
-    {64, 64, {3.51f, .228f}, {2.90f, .552f}, {0.83f, .589f}},
-    {64, 128, {3.74f, .326f}, {3.07f, .837f}, {0.68f, .942f}},
-    {128, 128, {4.97f, .401f}, {}, {2.55f, .775f}},
-    {192, 128, {5.27f, .532f}, {}, {3.38f, .980f}},
-    {256, 128, {5.82f, .641f}, {}, {4.87f, 1.196f}},
-    {256, 256, {5.83f, 1.388f}, {}, {6.79f, 2.063f}}};
+// Fitted to plain-store launches of 16 to 32768 rows; a slab is 128.  Without a low-rank branch: 1318 shapes of 128 to 5120 columns,
+// the form it picks is 0.2 % slower on average than the fastest.  With one: eight weight shapes (mean error 6 %; 0.1 % slower than
+// the fastest there).  The branch costs the 256 x 256 kernel most (see mx.hip), so priced by the second table products without one
+// were taken off it too early (8192 rows of 1024 -> 3072: 42 us on 256 x 128, 37 on 256 x 256).
+constexpr Form FORMS[2][7] = {
+    {{32, 64, {3.712f, .177f}, {4.127f, .305f}, {0.f, .419f}},                 // no low-rank branch
+     {64, 64, {4.033f, .198f}, {4.738f, .403f}, {.576f, .573f}},
+     {64, 128, {4.391f, .265f}, {5.402f, .667f}, {.049f, .907f}},
+     {128, 128, {5.154f, .334f}, {}, {4.425f, .652f}},
+     {192, 128, {5.494f, .454f}, {}, {4.968f, .835f}},
+     {256, 128, {6.320f, .550f}, {}, {5.886f, 1.036f}},
+     {256, 256, {5.932f, 1.292f}, {}, {6.131f, 1.897f}}},
+    {{32, 64, {3.29f, .189f}, {2.71f, .420f}, {0.08f, .458f}},
+     {64, 64, {3.51f, .228f}, {2.90f, .552f}, {0.83f, .589f}},
+     {64, 128, {3.74f, .326f}, {3.07f, .837f}, {0.68f, .942f}},
+     {128, 128, {4.97f, .401f}, {}, {2.55f, .775f}},
+     {192, 128, {5.27f, .532f}, {}, {3.38f, .980f}},
+     {256, 128, {5.82f, .641f}, {}, {4.87f, 1.196f}},
+     {256, 256, {5.83f, 1.388f}, {}, {6.79f, 2.063f}}}};
 
 template <int EPI>
 int launch_e(const MxArgs &a, const TilePlan &p, hipStream_t st)
@@ -45,11 +54,11 @@ int launch_e(const MxArgs &a, const TilePlan &p, hipStream_t st)
 
 }  // namespace
 
-TilePlan plan_gemm_mx(int M, int seg_n, int nseg, int K)
+TilePlan plan_gemm_mx(int M, int seg_n, int nseg, int K, bool low_rank)
 {
     TilePlan best = {0, 0, 1};
     double least = 0;
-    for (const Form &f : FORMS) {
+    for (const Form &f : FORMS[low_rank]) {
         const double c = form_cost(f, (long)((M + f.tm - 1) / f.tm) * ((seg_n + f.tn - 1) / f.tn) * nseg, K / 128);
         if (best.tm == 0 || c < least) { best = {f.tm, f.tn, 1}; least = c; }
     }

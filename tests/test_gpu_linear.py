@@ -286,6 +286,7 @@ FROZEN_FORMS = {
     (2000, 1088, 3080): (256, 128),
     (2100, 192, 3080): (128, 256),
     (3700, 192, 4104): (256, 256),
+    (10803, 64, 4040): (256, 256),   # one slab
 }
 
 

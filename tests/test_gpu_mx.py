@@ -118,12 +118,13 @@ def test_linear_on_oracle_codes(T, K, N, with_bias):
 # (tests/test_plans.py).
 FP8_FORMS = {
     (70, 384, 200): (32, 64),
-    (300, 256, 4104): (64, 64),
+    (150, 256, 4104): (64, 64),
     (500, 640, 4000): (64, 128),
     (1030, 384, 3080): (128, 128),
     (1400, 640, 3080): (192, 128),
     (2000, 640, 3080): (256, 128),
     (5000, 384, 2056): (256, 256),
+    (10803, 128, 4232): (256, 256),      # one slab
 }
 
 
@@ -138,7 +139,7 @@ FP8_LAYER_FORMS = {
     (500, 640, 3968): ((64, 128), (32, 64)),
     (1400, 640, 3072): ((192, 128), (64, 64)),
     (2000, 640, 3072): ((256, 128), (64, 128)),
-    (5000, 384, 2048): ((64, 128), (64, 128)),
+    (5000, 384, 2048): ((256, 256), (64, 128)),
     (3900, 384, 4096): ((256, 256), (64, 128)),         # three slabs
     (3900, 4096, 512): ((64, 128), (256, 256)),         # four
 }

@@ -85,3 +85,12 @@ def test_logits_of_a_loss_head():
                 few = T <= 128 or -(-T // 128) * -(-Vp // 128) <= 512
                 plan = plans.counted(T, Vp, d)
                 assert (plan is not None) == few and (not few or plan == plans.tile(T, Vp, d, whole=T <= 128)[:2]), (T, Vp, d)
+
+
+def test_short_contractions():
+    """one to six slabs over many rows: a small tile's price is not the line through the long contractions alone"""
+    for T, K, N in ((10803, 128, 4224), (20820, 128, 1024), (13197, 256, 4320), (20820, 256, 2048), (8192, 384, 4320), (8192, 512, 4696),
+                    (8192, 1024, 3072), (20820, 1024, 1024)):           # (and eight, without a low-rank branch)
+        assert plans.mx(T, N, K) == (256, 256), (T, K, N)
+    for T, K, N in ((20820, 64, 3072), (13197, 64, 4320), (20820, 128, 3072), (13197, 192, 4320), (20820, 192, 4696)):
+        assert plans.tile(T, N, K)[:2] in ((256, 256), (128, 256)), (T, K, N)
