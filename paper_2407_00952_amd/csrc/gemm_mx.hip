@@ -17,9 +17,10 @@ __global__ __launch_bounds__(TM <= 64 ? 256 : 512, 2) void gemm_mx_tile_kernel(M
 // Fitted to plain-store launches of 16 to 32768 rows; a slab is 128.  Without a low-rank branch: 1318 shapes of 128 to 5120 columns,
 // the form it picks is 0.2 % slower on average than the fastest.  With one: eight weight shapes (mean error 6 %; 0.1 % slower than
 // the fastest there).  The branch costs the 256 x 256 kernel most (see mx.hip), so priced by the second table products without one
-// were taken off it too early (8192 rows of 1024 -> 3072: 42 us on 256 x 128, 37 on 256 x 256).
+// were taken off it too early (8192 rows of 1024 -> 3072: 42 us on 256 x 128, 37 on 256 x 256).  Other epilogues than the plain
+// store cost it as well: they are priced by the second.
 constexpr Form FORMS[2][7] = {
-    {{32, 64, {3.712f, .177f}, {4.127f, .305f}, {0.f, .419f}},                 // no low-rank branch
+    {{32, 64, {3.712f, .177f}, {4.127f, .305f}, {0.f, .419f}},                 // plain store, no low-rank branch
      {64, 64, {4.033f, .198f}, {4.738f, .403f}, {.576f, .573f}},
      {64, 128, {4.391f, .265f}, {5.402f, .667f}, {.049f, .907f}},
      {128, 128, {5.154f, .334f}, {}, {4.425f, .652f}},
@@ -54,12 +55,12 @@ int launch_e(const MxArgs &a, const TilePlan &p, hipStream_t st)
 
 }  // namespace
 
-TilePlan plan_gemm_mx(int M, int seg_n, int nseg, int K, bool low_rank)
+TilePlan plan_gemm_mx(int M, int seg_n, int nseg, int K, int epi, bool low_rank)
 {
     TilePlan best = {0, 0, 1};
     double least = 0;
-    for (const Form &f : FORMS[low_rank]) {
-        const double c = form_cost(f, (long)((M + f.tm - 1) / f.tm) * ((seg_n + f.tn - 1) / f.tn) * nseg, K / 128);
+    for (const Form &f : FORMS[low_rank || epi != EPI_STORE]) {
+        const double c = form_cost(f, (long)((M + f.tm - 1) / f.tm) * ((seg_n + f.tn - 1) / f.tn) * nseg, K / 128, epi == EPI_STORE ? 16 : 0);
         if (best.tm == 0 || c < least) { best = {f.tm, f.tn, 1}; least = c; }
     }
     return best;

@@ -27,7 +27,7 @@ struct MxArgs {
 };
 
 // the tile of a product with fp8 weights: 256 x 256 is that of mx.hip, the others those of gemm_mx.hip
-extern "C" TilePlan plan_gemm_mx(int M, int seg_n, int nseg, int K, bool low_rank);
+extern "C" TilePlan plan_gemm_mx(int M, int seg_n, int nseg, int K, int epi, bool low_rank);
 int launch_gemm_mx_tile(const MxArgs &a, int epi, const TilePlan &p, hipStream_t st);
 
 namespace {

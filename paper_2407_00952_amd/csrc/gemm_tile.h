@@ -25,22 +25,24 @@ constexpr int BK = 64, ROWB = BK * 2;
 // 257 to 512, `full` for each 512 before those (two of them share a CU, but for 32 x 64 with 16 rank-space columns and 32 x 32
 // with 48, whose 86 KB of LDS leave room for one; those are fitted the same way).  Blocks that own a CU (both.b 0): between `one`
 // for a few tiles and `full` for 256, as full as the last round is, and `full` for each 256 before it.
-// A full round of two blocks to a CU is priced at sqrt(nk^2 + 16) slabs: the line through the long contractions the table was
+// A full round of two blocks to a CU is priced at sqrt(nk^2 + fill) slabs: the line through the long contractions the table was
 // fitted to leaves out what a tile costs at any length (its ring is filled whatever there is to fill it with: 0.65 us for
 // 64 x 128 by the line, 3.0 measured at one slab and 3.8 at three), and small tiles were picked where a few large ones cost half
-// (fp8, 10803 rows of 128 -> 4224: 42 us on 64 x 128, 24 on 256 x 256; bf16, 20820 of 64 -> 3072: 46, 34).  Over 996 shapes of
-// 16 to 32768 rows and 64 to 5120 columns the form picked is then 1.0 % (bf16) and 0.5 % (fp8) slower on average than the fastest,
-// 2.7 and 4.7 % without; for contractions from 768 on the picks are the same but for six of the fp8 ones.
+// (fp8, 10803 rows of 128 -> 4224: 42 us on 64 x 128, 24 on 256 x 256; bf16, 20820 of 64 -> 3072: 46, 34).  `fill`: the largest of
+// 0 to 25 (bf16, 12) and of 8 to 16 (fp8, 16) that takes no shape of 1894 off a form by more than 3 and 5 %.  The form picked is
+// then 0.9 % (bf16) and 0.2 % (fp8) slower on average than the fastest, 2.1 and 4.7 % without.  Plain stores only (else `fill` is 0):
+// the others' epilogues take longer, most of all on large tiles, where nothing runs beside them, and narrow stacks lost by it
+// (two blocks of 256 -> 4032 columns, 9472 tokens: 605 -> 631 us; fp8, 256 -> 1024, 17856 tokens: 677 -> 720).
 struct Cost { float a, b; };
 struct Form { int tm, tn; Cost one, both, full; };
-inline double form_cost(const Form &f, long tiles, int nk)
+inline double form_cost(const Form &f, long tiles, int nk, double fill)
 {
     auto us = [&](const Cost &c) { return c.a + (double)c.b * nk; };
     const bool two = f.both.b > 0;
     const long round = two ? 512 : 256, before = (tiles - 1) / round, last = tiles - before * round;
-    if (two) return before * (f.full.a + f.full.b * sqrt((double)nk * nk + 16.0)) + us(last > 256 ? f.both : f.one);
-    const double fill = last / 256.0;
-    return (before + fill) * us(f.full) + (1 - fill) * us(f.one);
+    if (two) return before * (f.full.a + f.full.b * sqrt((double)nk * nk + fill)) + us(last > 256 ? f.both : f.one);
+    const double part = last / 256.0;
+    return (before + part) * us(f.full) + (1 - part) * us(f.one);
 }
 
 // Partial sums cross XCDs (each has its own L2), so they are written and read at device scope: relaxed 8-byte atomics

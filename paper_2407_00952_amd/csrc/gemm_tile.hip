@@ -60,6 +60,7 @@ int launch_te(const GemmArgs &a, int nz, const TilePlan &p, hipStream_t st)
 // is 0.5 % slower on average than the fastest of such a launch).  Other epilogues are priced as that one and take up to 45 % more
 // (GELU of 10240 rows of 768 -> 3072: 49 us here, 72 measured).  The third group was fitted to 32 and 48 columns together; its
 // 256 x 256 row is that of 48 (32768 rows of 4096 -> 1024: 262 us, with 32 columns 233).
+constexpr double FILL = 12;                              // (form_cost)
 constexpr Form FORMS[3][9] = {
     {{32, 32, {2.46f, .093f}, {2.60f, .175f}, {0.97f, .170f}},          // no rank-space branch
      {32, 64, {2.33f, .129f}, {2.49f, .250f}, {0.70f, .269f}},
@@ -112,12 +113,12 @@ TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int epi, int nz, bool
     for (const Form &f : FORMS[nz == 0 ? 0 : nz == 16 ? 1 : 2]) {
         if (f.tm == 0 || (!whole && f.tn == 256)) continue;
         if (epi == EPI_STORE_DELTA && f.tn < 64) continue;               // a head's columns in one tile
-        const double c = form_cost(f, tiles(f.tm, f.tn), nk);
+        const double c = form_cost(f, tiles(f.tm, f.tn), nk, epi == EPI_STORE ? FILL : 0);
         if (best.tm == 0 || c < least) { best = {f.tm, f.tn, 1}; least = c; }
     }
     if (can_split && epi == EPI_STORE && nz <= 16) {
         const int s = split_shares(tiles(64, 64), nk);
-        if (s > 1 && form_cost(FORMS[nz == 0 ? 0 : 1][2], tiles(64, 64) * s, (nk + s - 1) / s) + 3.0 < least) best = {64, 64, s};
+        if (s > 1 && form_cost(FORMS[nz == 0 ? 0 : 1][2], tiles(64, 64) * s, (nk + s - 1) / s, FILL) + 3.0 < least) best = {64, 64, s};
     }
     return best;
 }

@@ -449,7 +449,7 @@ int launch_gemm_mx(const MxArgs &a, hipStream_t st, bool w4 = false, int epi = E
 {
     if (epi == EPI_STORE_DELTA && (!a.dl_o || !a.dl_lo || !a.dl_out || !a.out0 || (a.N % 64) || a.nseg != 1)) return SL_EINVAL;
     if (!w4) {
-        const TilePlan p = plan_gemm_mx(a.M, a.seg_n, a.nseg, a.K, a.zs[0] || a.zs[1] || a.zs[2]);
+        const TilePlan p = plan_gemm_mx(a.M, a.seg_n, a.nseg, a.K, epi, a.zs[0] || a.zs[1] || a.zs[2]);
         if (p.tn < 256) return launch_gemm_mx_tile(a, epi, p, st);
     }
     const int nb = ((a.M + BM - 1) / BM) * (((a.seg_n + BN - 1) / BN) * a.nseg);

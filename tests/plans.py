@@ -42,9 +42,9 @@ class F32Plan(ctypes.Structure):
     _fields_ = [("tm", c_int), ("tn", c_int), ("stages", c_int)]
 
 
-def mx(M, N, K, nseg=1, low_rank=False):
+def mx(M, N, K, nseg=1, epi=STORE, low_rank=False):
     """(rows, columns) of a product with fp8 weights"""
-    p = _fn("plan_gemm_mx", TilePlan, *[c_int] * 4, c_bool)(M, N // nseg, nseg, K, low_rank)
+    p = _fn("plan_gemm_mx", TilePlan, *[c_int] * 5, c_bool)(M, N // nseg, nseg, K, epi, low_rank)
     return p.tm, p.tn
 
 
@@ -68,7 +68,7 @@ def stack(T, d, f, proj, seq_len, fp8=False):
     prods = [(STORE, 16 if qkv else 0, 3 * d, d, 3), (RESID, ad("o"), d, d, 1), (GELU, ad("fc"), f, d, 1),
              (RESID, ad("pr"), d, f, 1), (DGELU, ad("pr"), f, d, 1), (STORE, ad("fc"), d, f, 1),
              (delta, ad("o"), d, d, 1), (STORE, 16 * qkv, d, 3 * d, 1)]
-    return {(epi, nz) + (mx(T, N, K, nseg, nz > 0) if fp8 else tile(T, N, K, epi, nz, nseg=nseg)[:2])
+    return {(epi, nz) + (mx(T, N, K, nseg, epi, nz > 0) if fp8 else tile(T, N, K, epi, nz, nseg=nseg)[:2])
             for epi, nz, N, K, nseg in prods}
 
 

@@ -296,10 +296,10 @@ def test_results_of_short_records_do_not_depend_on_the_batch(proj):
 # (tests/test_plans.py); a sequence's results are the same bits in each batch, and those of a few sequences are the oracle's.
 FORM_STACK = dict(d_model=256, n_head=4, d_ff=1024, n_blocks=1, lora_r=5, n_clients=1, seq_len=128)
 FORM_BATCHES = {
-    ("bf16", ("q", "v")): (1, 3, 5, 9, 17, 33, 43, 65, 161, 193),
-    ("bf16", synth.PROJ_NAMES): (1, 3, 5, 9, 17, 43, 49, 65, 129, 193),
-    ("mxfp8", ("q", "v")): (1, 5, 9, 17, 22, 33, 49, 65, 129, 193),
-    ("mxfp8", synth.PROJ_NAMES): (1, 9, 17, 22, 49, 65, 129, 193),
+    ("bf16", ("q", "v")): (1, 3, 5, 9, 17, 33, 49, 64, 97, 129, 139, 193),
+    ("bf16", synth.PROJ_NAMES): (1, 3, 5, 9, 17, 33, 49, 65, 139, 193),
+    ("mxfp8", ("q", "v")): (1, 9, 17, 22, 33, 64, 65, 97, 171, 193),
+    ("mxfp8", synth.PROJ_NAMES): (1, 9, 22, 43, 49, 65, 97, 129, 193),
 }
 
 
