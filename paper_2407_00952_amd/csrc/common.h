@@ -115,9 +115,10 @@ struct GemmArgs {
 int launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st);
 // rows of the tiles (256 columns) of a product over counted rows: 128 only where no more can come
 inline int gemm_counted_rows(int max_rows) { return max_rows <= 128 ? 128 : 256; }
-// the tile of a product's kernel and over how many blocks a tile's contraction is shared: 128 x 256 and 256 x 256 are those
-// of gemm.hip, 128 columns and more than 64 rows those of gemm_wide.hip, the others those of gemm_tile.hip
-struct TilePlan { int tm, tn, splits; };
+// the tile of a product's kernel, over how many blocks a tile's contraction is shared, and whether blocks of 4 waves share a CU
+// (pair; for 128 x 128, which has both): 128 x 256 and 256 x 256 are those of gemm.hip, 128 columns and more than 64 rows those
+// of gemm_wide.hip, the others and the pair form those of gemm_tile.hip
+struct TilePlan { int tm, tn, splits, pair; };
 extern "C" TilePlan plan_gemm_tile(int M, int seg_n, int nseg, int K, int epi, int nz, bool can_split, bool whole);
 // the same for a plain store over counted rows (at most M) on a kernel that computes all M; tm 0: on the one that counts
 extern "C" TilePlan plan_gemm_counted(int M, int N, int K);

@@ -57,11 +57,11 @@ int launch_e(const MxArgs &a, const TilePlan &p, hipStream_t st)
 
 TilePlan plan_gemm_mx(int M, int seg_n, int nseg, int K, int epi, bool low_rank)
 {
-    TilePlan best = {0, 0, 1};
+    TilePlan best = {0, 0, 1, 0};
     double least = 0;
     for (const Form &f : FORMS[low_rank || epi != EPI_STORE]) {
         const double c = form_cost(f, (long)((M + f.tm - 1) / f.tm) * ((seg_n + f.tn - 1) / f.tn) * nseg, K / 128, epi == EPI_STORE ? 16 : 0);
-        if (best.tm == 0 || c < least) { best = {f.tm, f.tn, 1}; least = c; }
+        if (best.tm == 0 || c < least) { best = {f.tm, f.tn, 1, 0}; least = c; }
     }
     return best;
 }

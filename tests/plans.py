@@ -9,7 +9,10 @@ STORE, RESID, GELU, DGELU, STORE_DELTA = range(5)        # epilogues (csrc/commo
 
 
 class TilePlan(ctypes.Structure):
-    _fields_ = [("tm", c_int), ("tn", c_int), ("splits", c_int)]
+    _fields_ = [("tm", c_int), ("tn", c_int), ("splits", c_int), ("pair", c_int)]
+
+    def form(self):
+        return (self.tm, self.tn) + (("pair",) if self.pair else ())
 
 
 class SplitPlan(ctypes.Structure):
@@ -23,9 +26,9 @@ def _fn(name, res, *args):
 
 
 def tile(M, N, K, epi=STORE, nz=0, can_split=False, nseg=1, whole=True):
-    """(rows, columns, blocks that share a tile's contraction) of a bf16 product with nseg segments of N / nseg columns"""
+    """((rows, columns[, "pair"]), blocks that share a tile's contraction) of a bf16 product with nseg segments of N / nseg columns"""
     p = _fn("plan_gemm_tile", TilePlan, *[c_int] * 6, c_bool, c_bool)(M, N // nseg, nseg, K, epi, nz, can_split, whole)
-    return p.tm, p.tn, p.splits
+    return p.form(), p.splits
 
 
 def split(M, N, K, nz=16):
@@ -68,11 +71,11 @@ def stack(T, d, f, proj, seq_len, fp8=False):
     prods = [(STORE, 16 if qkv else 0, 3 * d, d, 3), (RESID, ad("o"), d, d, 1), (GELU, ad("fc"), f, d, 1),
              (RESID, ad("pr"), d, f, 1), (DGELU, ad("pr"), f, d, 1), (STORE, ad("fc"), d, f, 1),
              (delta, ad("o"), d, d, 1), (STORE, 16 * qkv, d, 3 * d, 1)]
-    return {(epi, nz) + (mx(T, N, K, nseg, epi, nz > 0) if fp8 else tile(T, N, K, epi, nz, nseg=nseg)[:2])
+    return {(epi, nz) + (mx(T, N, K, nseg, epi, nz > 0) if fp8 else tile(T, N, K, epi, nz, nseg=nseg)[0])
             for epi, nz, N, K, nseg in prods}
 
 
 def counted(M, N, K):
     """(rows, columns) of a plain store over counted rows on a kernel that computes all M, None for the one that counts"""
     p = _fn("plan_gemm_counted", TilePlan, c_int, c_int, c_int)(M, N, K)
-    return (p.tm, p.tn) if p.tm else None
+    return p.form() if p.tm else None

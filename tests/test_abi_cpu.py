@@ -211,7 +211,7 @@ def test_split_scratch_follows_the_launch(slabs):
         N, need, most = 64 * cols, 0, 0
         plans_of = []
         for M in sorted({m for e in range(32, 128 // cols * 64 + 129, 32) for m in (e - 31, e)}):
-            shares = plans.tile(M, N, K, nz=16, can_split=True)[2]
+            shares = plans.tile(M, N, K, nz=16, can_split=True)[1]
             if shares > 1:
                 need, most = max(need, -(-M // 64) * cols * shares * 64 * (64 + 16) * 4), M
             plans_of.append((M, (shares > 1, need)))

@@ -284,15 +284,31 @@ FROZEN_FORMS = {
     (1090, 320, 2056): (128, 128),
     (1500, 1088, 3080): (192, 128),
     (2000, 1088, 3080): (256, 128),
-    (2100, 192, 3080): (128, 256),
+    (2100, 192, 3080): (128, 128, "pair"),
+    (1818, 832, 4104): (128, 256),
     (3700, 192, 4104): (256, 256),
-    (10803, 64, 4040): (256, 256),   # one slab
+    (10803, 64, 4040): (128, 128, "pair"),       # one slab
 }
 
 
 @pytest.mark.parametrize("T,n_in,n_out", list(FROZEN_FORMS))
 def test_frozen_linear_tile_forms(T, n_in, n_out):
     test_frozen_linear_dispatch_edges(T, n_in, n_out, True)
+
+
+# A row's bits are the same on whichever form its call ran.
+@pytest.mark.parametrize("T,n_in,n_out", [(10803, 64, 4040), (2100, 192, 3080), (2900, 640, 2568)])      # pair forms
+def test_frozen_linear_rows_are_the_same_on_every_form(T, n_in, n_out):
+    import torch
+    c = synth.make_single_layer(T, n_in, n_out, 1, seed=450 + T, quant=True, bias=True)
+    x, W, b = (B.to_device_bf16(c[k]) for k in ("x", "W", "b"))
+    y = torch.empty((T, n_out), dtype=torch.bfloat16, device="cuda")
+    B.slora_frozen_linear_bf16(T, n_in, n_out, x, W, b, y)
+    for rows in (1, 33, 200, 450, 1090, 1500, 2000):
+        part = torch.empty((rows, n_out), dtype=torch.bfloat16, device="cuda")
+        B.slora_frozen_linear_bf16(rows, n_in, n_out, x, W, b, part)
+        torch.cuda.synchronize()
+        assert torch.equal(part, y[:rows]), rows
 
 
 # The same with the rank-space branch (contraction n_in forward, n_out in the input gradient).  T, n_in, n_out: tile forward

@@ -117,7 +117,7 @@ def test_loss_head_listed_rows(T, d, V, n_labeled):
 
 # Where the logits' product goes from the kernels that compute all rows to the one that counts them (None): 512 and 513 tiles of
 # 128 x 128, 128 and 129 rows of a wide vocabulary; few labeled rows and all.  T, d, V: tile (tests/test_plans.py).
-LOGIT_FORMS = {(1000, 64, 8190): (256, 128), (1030, 64, 7290): None, (128, 768, 50257): (128, 256), (129, 64, 50257): None,
+LOGIT_FORMS = {(1000, 64, 8190): (128, 128, "pair"), (1030, 64, 7290): None, (128, 768, 50257): (128, 256), (129, 64, 50257): None,
                (600, 768, 12013): (128, 128), (700, 512, 9001): (256, 128), (300, 64, 4099): (64, 128), (100, 64, 1003): (32, 64)}
 
 

@@ -100,6 +100,7 @@ def gemm_asm():
 def tile_asm():
     text = _assembly("gemm_tile.hip")
     assert sum("gemm_tile_kernel" in n for n in _functions(text)) == 33     # 11 epilogues and ranks x three tile forms
+    assert sum("gemm_tile128_kernel" in n for n in _functions(text)) == 1   # plain store
     return text
 
 

@@ -27,18 +27,27 @@ def test_fp32_ring_forms():
 
 def test_bf16_forms():
     for (T, n_in, n_out), want in linear.FROZEN_FORMS.items():
-        assert plans.tile(T, n_out, n_in) == want + (1,), (T, n_in, n_out)
-    assert set(linear.FROZEN_FORMS.values()) == BF16_FORMS
+        assert plans.tile(T, n_out, n_in) == (want, 1), (T, n_in, n_out)
+    assert set(linear.FROZEN_FORMS.values()) == BF16_FORMS | {(128, 128, "pair")}
     for case, want in linear.LAYER_FORMS.items():
-        assert plans.layer(*case)[0] == want + (1,), case
+        assert plans.layer(*case)[0] == (want, 1), case
     assert set(linear.LAYER_FORMS.values()) == BF16_FORMS - {(128, 256)}
+
+
+def test_pair_forms():
+    """up to the rows of which the pair form takes all at once, other forms take fewer"""
+    for T, n_in, n_out in ((10803, 64, 4040), (2100, 192, 3080), (2900, 640, 2568)):
+        assert plans.tile(T, n_out, n_in)[0] == (128, 128, "pair"), (T, n_in, n_out)
+        assert len({plans.tile(rows, n_out, n_in)[0] for rows in (1, 33, 200, 450, 1090, 1500, 2000)} - {(128, 128, "pair")}) >= 3
+    assert plans.tile(10803, 4040, 64, epi=plans.RESID)[0] != (128, 128, "pair") != plans.tile(10803, 4040, 64, nz=16)[0]
+    assert plans.tile(13197, 2520, 768)[0] != (128, 128, "pair")             # 12 slabs
 
 
 def test_shared_contractions():
     for case, want in linear.SHARED.items():
-        assert tuple(p[2] for p in plans.layer(*case)) == want, case
+        assert tuple(p[1] for p in plans.layer(*case)) == want, case
     for case, want in no_alloc.SHARED.items():
-        assert plans.layer(*case)[1][2] == want, case
+        assert plans.layer(*case)[1][1] == want, case
     assert {w[0] for w in linear.SHARED.values()} == {w[1] for w in linear.SHARED.values()} == {1, 2, 3, 4}
 
 
@@ -84,7 +93,7 @@ def test_logits_of_a_loss_head():
             for Vp in (64, 1024, 1344, 4288, 8000, 12032, 20032, 31168, 50304, 65536):
                 few = T <= 128 or -(-T // 128) * -(-Vp // 128) <= 512
                 plan = plans.counted(T, Vp, d)
-                assert (plan is not None) == few and (not few or plan == plans.tile(T, Vp, d, whole=T <= 128)[:2]), (T, Vp, d)
+                assert (plan is not None) == few and (not few or plan == plans.tile(T, Vp, d, whole=T <= 128)[0]), (T, Vp, d)
 
 
 def test_short_contractions():
@@ -93,4 +102,4 @@ def test_short_contractions():
                     (8192, 1024, 3072), (20820, 1024, 1024)):           # (and eight, without a low-rank branch)
         assert plans.mx(T, N, K) == (256, 256), (T, K, N)
     for T, K, N in ((20820, 64, 3072), (13197, 64, 4320), (20820, 128, 3072), (13197, 192, 4320), (20820, 192, 4696)):
-        assert plans.tile(T, N, K)[:2] in ((256, 256), (128, 256)), (T, K, N)
+        assert plans.tile(T, N, K)[0] in ((256, 256), (128, 256), (128, 128, "pair")), (T, K, N)
