@@ -309,8 +309,12 @@ __global__ __launch_bounds__(NTHR) void gemm_kernel(GemmArgs a)
 // fragments one k-step ahead.  Per 32-deep k-step a wave reads 8 + 8 fragments for 64 MFMAs, a third less
 // LDS traffic per MFMA than the 8 + 4 for 32 of the 8-wave kernel.  LDS is a ring of five 32 KB half
 // stages: three for the X tile and two for the W tile, so the X copies run two slabs ahead and the W
-// copies one; the 16 copies a wave issues per slab are spread two to a row of 8 MFMAs, because with a
-// single wave per SIMD a burst of copies that fills the memory-issue queue stalls the MFMAs behind it.
+// copies one.  With a single wave per SIMD whatever the wave issues in a clump is time the matrix pipe idles: the 32 fragment
+// reads and 16 copies of a slab go one by one behind MFMAs of their own, and the fragments of a k-step have a register set of
+// their own, so that the last read is 32 MFMAs old at the barrier.  Against three reads and two copies behind each row of 8
+// MFMAs: 3300 -> 2920 shader cycles a slab of 2048 MFMA cycles, of which the chip, at its power limit, takes back more than half
+// as clock (2.10 -> 1.94 GHz between copies).  us at 32768 x 4096 -> 1024 200.3 -> 195.0, 32768 x 1024 -> 4096 235.4 -> 231.2;
+// a round of 18 blocks of width 1024 at 32768 tokens 39.47 -> 38.27 ms, the loss head at 32768 x 1024 -> 50257 4.27 -> 3.99 ms.
 // The grid is one block per CU and a block walks its tiles itself, so that the first copies of the next
 // tile are in flight under the epilogue of the current one.
 // The MFMA hazards the compiler can no longer see (inline assembly) are covered by construction: every MFMA
@@ -330,6 +334,10 @@ __device__ __forceinline__ void gemm4_body(GemmArgs a)
 {
     constexpr int BM4 = 32 * NI;                         // rows of a block tile
     constexpr bool SHARED = EPI == EPI_PARTIAL;
+    // Spacing, in MFMAs of a k-step, of the fragment reads and of the copies, and how many of the X copies of a slab go out
+    // beside the W copies before it (the others one k-step later).  (CP, NX1) = (5, 4), (6, 2), (7, 1) are within 0.5 % of each
+    // other on whole rounds; all X copies behind the W copies, (4, 8), are 1 to 4 % slower.
+    constexpr int RD = 2, CP = NI == 8 ? 6 : 3, NX1 = 2;
     if constexpr (COUNTED) a.M = a.rows->rows;
     const int shares = SHARED ? a.rows->shares : 1;
     __shared__ __attribute__((aligned(1024))) unsigned char ring[5 * HB];   // X: 0, HB, 2HB;  W: 3HB, 4HB
@@ -417,49 +425,36 @@ __device__ __forceinline__ void gemm4_body(GemmArgs a)
         _Pragma("unroll") for (int p = 0; p < 8; ++p) G4_COPYW(k1, 4 * HB, p)                          \
         _Pragma("unroll") for (int p = 0; p < NI; ++p) G4_COPYX(k1, HB, p)                             \
     }
-#define G4_HEAD5 { _Pragma("unroll") for (int p = 0; p < NI; ++p) G4_COPYX(k2, 2 * HB, p) }
-#define G4_LDA(i, xs, k2_) fa[i] = *(const bf16x8 *)(ring + (xs) + a_row + (i) * 16 * ROWB + ((((k2_) * 4 + kg) ^ sw) << 4));
+#define G4_HEAD5 { _Pragma("unroll") for (int p = 0; p < NX1; ++p) G4_COPYX(k2, 2 * HB, p) }
+#define G4_LDA(nb_, i, xs, k2_) fa[nb_][i] = *(const bf16x8 *)(ring + (xs) + a_row + (i) * 16 * ROWB + ((((k2_) * 4 + kg) ^ sw) << 4));
 #define G4_LDB(nb_, j, ws, k2_) fb[nb_][j] = *(const bf16x8 *)(ring + (ws) + b_row + (j) * 16 * ROWB + ((((k2_) * 4 + kg) ^ sw) << 4));
-#define G4_ROW(cb, i)                                                                                  \
-    _Pragma("unroll") for (int j = 0; j < 8; ++j)                                                      \
-        asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fa[i]), "v"(fb[cb][j]));
-    // one k-step: row i of MFMAs on fragment set cb, then the fragments of the next k-step that have
-    // become free to load (A fragment i, B fragments 2i and 2i+1 of set nb_)
-#define G4_STEP(cb, nb_, xs, ws, k2_)                                                                  \
+    // One k-step: 8 NI MFMAs on fragment set cb.  Behind an MFMA goes at most one fragment read of the next k-step (set nb_)
+    // or one copy, so that the wave has its next MFMA ready before the matrix pipe has finished this one.
+#define G4_STEP(cb, nb_, xs, ws, k2_, COPIES)                                                          \
     {                                                                                                  \
-        _Pragma("unroll") for (int i = 0; i < NI; ++i) {                                               \
-            G4_ROW(cb, i)                                                                              \
-            if (i < 4) { G4_LDB(nb_, 2 * i, ws, k2_) G4_LDB(nb_, 2 * i + 1, ws, k2_) }                 \
-            G4_LDA(i, xs, k2_)                                                                         \
+        _Pragma("unroll") for (int i = 0; i < NI; ++i) _Pragma("unroll") for (int j = 0; j < 8; ++j) { \
+            asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fa[cb][i]), "v"(fb[cb][j])); \
+            const int s_ = 8 * i + j;                                                                  \
+            if (s_ % RD == 0 && s_ / RD < 8) G4_LDB(nb_, (s_ / RD) & 7, ws, k2_)                       \
+            if (s_ % RD == 0 && s_ / RD >= 8 && s_ / RD < 8 + NI) G4_LDA(nb_, (s_ / RD - 8) & (NI - 1), xs, k2_) \
+            COPIES(s_)                                                                                 \
             __builtin_amdgcn_sched_barrier(0);                                                         \
         }                                                                                              \
     }
-    // the same with this slab's copies: W of slab +2 (rows 0..3), then X of slab +3 (rows 4..7; with four rows
-    // all of them behind the last W copy), into the buffers the slab being finished has just released.  The X
-    // copies must be the LAST ones issued: the wait in front of the barrier lets exactly NI copies stay in
-    // flight, and those must be X of slab +3, never W of slab +2
-#define G4_STEPC(cb, nb_, xs, ws, k2_, kw, kx)                                                         \
-    {                                                                                                  \
-        _Pragma("unroll") for (int i = 0; i < NI; ++i) {                                               \
-            G4_ROW(cb, i)                                                                              \
-            if (i < 4) { G4_LDB(nb_, 2 * i, ws, k2_) G4_LDB(nb_, 2 * i + 1, ws, k2_) }                 \
-            G4_LDA(i, xs, k2_)                                                                         \
-            if (i < 4) { G4_COPYW(kw, wcur, 2 * i) G4_COPYW(kw, wcur, 2 * i + 1) }                     \
-            if (NI == 8 && i >= 4) { G4_COPYX(kx, xcur, 2 * i - 8) G4_COPYX(kx, xcur, 2 * i - 7) }     \
-            if (NI == 4 && i == 3) { G4_COPYX(kx, xcur, 0) G4_COPYX(kx, xcur, 1)                       \
-                                     G4_COPYX(kx, xcur, 2) G4_COPYX(kx, xcur, 3) }                     \
-            __builtin_amdgcn_sched_barrier(0);                                                         \
-        }                                                                                              \
-    }
+    // k-step 0 of slab kt: the rest of X of slab kt + 2; k-step 1, behind the barrier that frees the slab's buffers: W of slab
+    // kt + 2, then the first NX1 copies of X of slab kt + 3
+#define G4_COPIES0(s_) { if ((s_) % CP == 1 && (s_) / CP < NI - NX1) glds_soff(x2, xo[((s_) / CP + NX1) & (NI - 1)], lx2 + (((s_) / CP + NX1) & (NI - 1)) * 1024); }
+#define G4_COPIES1(s_) { if ((s_) % CP == 1 && (s_) / CP < 8) glds_soff(w2, wo[((s_) / CP) & 7], lw + (((s_) / CP) & 7) * 1024); \
+                         if ((s_) % CP == 1 && (s_) / CP >= 8 && (s_) / CP < 8 + NX1) glds_soff(x3, xo[((s_) / CP - 8) & (NI - 1)], lx + (((s_) / CP - 8) & (NI - 1)) * 1024); }
 
     G4_TILE(logical)
     G4_HEAD4                                             // copy queue: W0 X0 W1 X1 ...
     for (;;) {
         G4_HEAD5                                         // ... X2
-        // Everything but X2 (NI copies) has landed: W0, X0 (and W1, X1, requested just before them or, from the second
+        // Everything but X2 (NX1 copies) has landed: W0, X0 (and W1, X1, requested just before them or, from the second
         // tile on, before the previous tile's epilogue).  The counter is in order, so this also waits for
         // the previous tile's stores to be acknowledged, which they are within 0.2 us of being issued.
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NX1) : "memory");
         __syncthreads();
         f32x4 acc[NI][8];
 #pragma unroll
@@ -468,17 +463,20 @@ __device__ __forceinline__ void gemm4_body(GemmArgs a)
             for (int j = 0; j < 8; ++j)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.0f;
-        bf16x8 fa[NI], fb[2][8];
+        bf16x8 fa[2][NI], fb[2][8];
         int xcur = 0, wcur = 3 * HB;                     // buffers of the slab being computed
 #pragma unroll
-        for (int i = 0; i < 8; ++i) { if (i < NI) { G4_LDA(i, 0, 0) } G4_LDB(0, i, 3 * HB, 0) }
+        for (int i = 0; i < 8; ++i) { G4_LDB(0, i, 3 * HB, 0) if (i < NI) { G4_LDA(0, i & (NI - 1), 0, 0) } }
         for (int kt = 0;; ++kt) {                        // nk >= 1 (checked by the launcher)
             const int xnxt = xcur == 2 * HB ? 0 : xcur + HB, wnxt = wcur ^ (3 * HB ^ 4 * HB);
-            G4_STEP(0, 1, xcur, wcur, 1)                 // MFMAs (slab kt, step 0); fetch (kt, step 1)
+            const int c2 = min((kt + 2) * BK, klast), c3 = min((kt + 3) * BK, klast);
+            const char *x2 = Xb + (size_t)c2 * 2, *w2 = Wb + (size_t)c2 * 2, *x3 = Xb + (size_t)c3 * 2;
+            const unsigned lx2 = ringa_x + (xcur == 0 ? 2 * HB : xcur - HB), lx = ringa_x + xcur, lw = ringa_w + wcur;
+            G4_STEP(0, 1, xcur, wcur, 1, G4_COPIES0)     // MFMAs (slab kt, step 0); fetch (kt, step 1)
             // slab kt+1 has landed (X of kt+2 may still be in flight); nobody reads slab kt's buffers any more
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NI) : "memory");
             __syncthreads();
-            G4_STEPC(1, 0, xnxt, wnxt, 0, min((kt + 2) * BK, klast), min((kt + 3) * BK, klast))
+            G4_STEP(1, 0, xnxt, wnxt, 0, G4_COPIES1)
             xcur = xnxt; wcur = wnxt;
             // The compiler takes an accumulator for finished where its MFMA is issued, and it moves
             // accumulators between registers right where the loop ends.  The only way out of the loop is
@@ -519,9 +517,9 @@ __device__ __forceinline__ void gemm4_body(GemmArgs a)
 #undef G4_COPYW
 #undef G4_LDA
 #undef G4_LDB
-#undef G4_ROW
 #undef G4_STEP
-#undef G4_STEPC
+#undef G4_COPIES0
+#undef G4_COPIES1
 }
 
 template <int EPI, int NI>
