@@ -1,25 +1,26 @@
 // Single-precision LoRA-adapted linear layer (SplitLoRA Sec. II-C), forward and backward.
 //
-// Every operand and every sum is fp32: the frozen product and the rank-space projections run on the fp32 matrix
-// instruction (V_MFMA_F32_16X16X4_F32: fp32 operands, fp32 accumulation, the same rate as packed vector FMAs but
-// one instruction per 1024 of them), the adapter gradients on vector FMAs.  Each sum has one fixed order, so
-// results are reproducible.
+// Every operand and every sum is fp32.  Products whose shapes allow it run on the bf16 matrix instruction with each operand
+// as the exact sum of three bf16 numbers (f32_tile_kernel; closer to the sum in 64 bits than the fp32 instruction), the others and
+// the rank-space projections on the fp32 one (V_MFMA_F32_16X16X4_F32), the adapter gradients on vector FMAs.  Each sum has one
+// fixed order, so results are reproducible.
 //
-//   forward   z = x A^T                                 f32_project_kernel
+//   forward   z = x A^T                                 f32_tile_kernel on small tiles forms z itself; else f32_project_kernel
 //             y = x W^T + bias + s z B^T                f32_tile_kernel / f32_gemm_kernel / f32_gemm_direct_kernel
-//   backward  z = x A^T, p = dy B                       f32_project_kernel (both in one launch)
+//   backward  z = x A^T, p = dy B                       as in the forward
 //             dx = dy W + s p A                         the same product kernels, W read as [k, n]
 //             dA = s p^T x, dB = s dy^T z               f32_grad_kernel (both in one launch)
 //
-// At T = 1024, 768 -> 768, r = 4 (2.5 GFLOP, 15 MB: 16 us at the fp32 matrix rate) forward + backward took 1113 us
-// as nine launches of one vector-FMA kernel: single floats moved one by one, the rank-4 products as mostly empty 64 x 64
-// tiles, the adapter gradients as 12 blocks that walk all tokens.  Five launches of the kernels below: 47 us (59 before the
-// products that fill the chip took the ring kernel).
+// At T = 1024, 768 -> 768, r = 4 (2.5 GFLOP, 15 MB) forward + backward take three launches and 38 us; with the products on the fp32
+// instruction (64 x 48 tiles on a ring in LDS, 0.64 of 0.77 us a stage of 64 being matrix time) and projections of their own
+// five launches and 46 us.  Whole layers in us, before and now: 64 rows of 1024 -> 3072, r = 16, 63.2 and 49.6; 200 of
+// 1280 -> 5120, r = 8, 164 and 90; 1024 of 3072 -> 768 133 and 99; 2048 of 1280 -> 1280, r = 16, 208 and 168; 8192 of 1280 -> 5120
+// 1719 and 1350.
 #include "common.h"
 #include "gemm_copy.h"
 #include <type_traits>
 
-// the tile of a product's kernel and the stages of its ring of copies (0: a kernel without one); vec: operands of 16-byte rows
+// the tile of a product's kernel and the last argument of f32_tile_kernel (0: another kernel); vec: operands of 16-byte rows
 struct F32Plan { int tm, tn, stages; };
 extern "C" F32Plan plan_f32(int M, int N, int K, bool vec);
 
@@ -125,6 +126,13 @@ struct GemmF32 {
     int M, N, K, zp, r;
     long uj, un;
     float s;
+    // f32_wave_tile forms z itself where Z is there ([r,K] beside a B of [N,K], [K,r] beside one of [K,N]), and stores it to
+    // zout if that is there; and z2 [M,zp] = x2 A2^T, if asked for, with x2 [M,K2], A2 [r,K2]
+    const float *Z;
+    float *zout;
+    const float *x2, *A2;
+    float *z2;
+    int K2;
 };
 
 // The low-rank term is one more step of 16 contraction elements: operand fragments z[m, 4g ..] and U(4g .., n), zero
@@ -317,22 +325,335 @@ __global__ __launch_bounds__(256 * KS) void f32_gemm_kernel(GemmF32 a)
             }
 }
 
-// The same product where the contraction is a multiple of 64: TM x TN tile, two groups of WM x WN waves that take the slabs of
-// 32 in turn.  A stage of the LDS ring holds a slab for each group, filled by asynchronous copies NST - 1 stages ahead (a
-// slab's arithmetic is shorter than the round trip that the kernel above has one slab in flight for); operand rows of
-// 128 bytes with the 16-byte chunks XORed with the row, W read as [k, n] as rows of TN floats with the chunks rotated by the
-// k-group, so that the four k-groups of a read meet different banks.  The sums and their order are those of f32_gemm_kernel with
-// two groups (its 128 x 128 form has one, and one chain of sums instead of two).
-template <int TM, int TN, int WM, int WN, int NST, bool BT>
-__global__ __launch_bounds__(512) void f32_tile_kernel(GemmF32 a)
+// ---- products on the bf16 matrix instruction ----------------------------------------------------------------------
+// An fp32 number is the sum of three bf16 ones (8 bits each: round to nearest, subtract exactly, again), so a product of two
+// is six bf16 products, exact in fp32, and three left out that are below 2^-24 of it.  V_MFMA_F32_16X16X32_BF16 does sixteen times
+// the work of V_MFMA_F32_16X16X4_F32 in a pass and rounds its sum once where that rounds eight times: six of them take 0.375
+// of the time, and the result is closer to the sum in 64 bits (errors in the 2-norm, chains of 768 and 5120 products of normal
+// numbers: 4.1e-7 against 5.1e-7, 1.1e-6 against 1.3e-6; of absolute values 3.0e-7, 4.3e-7 and 6.0e-7, 9.7e-7).  Rounded, not
+// cut: cut pieces all have the sign of their number, and what is left out adds up (5120 absolute values: 1.1e-5).
+// Infinities and NaN, and numbers that bf16 rounds to an infinity, come out as NaN or infinity: a wave that finds one among
+// its sums forms them again with the fp32 instruction.  Below 2^-102 the smallest of the three pieces loses bits.
+__device__ __forceinline__ void split3(const float4 &u, const float4 &v, bf16x8 (&p)[3])
 {
-    static_assert(WM * WN == 4, "four waves in a group");
-    constexpr int MI = TM / 16 / WM, NI = TN / 16 / WN;
+    float x[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        union { unsigned w[4]; bf16x8 v; } c;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            // (the instruction by name: the compiler would convert each of the two once more to take them apart)
+            asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(c.w[e]) : "v"(x[2 * e]), "v"(x[2 * e + 1]));
+            if (q < 2) {
+                x[2 * e] -= __uint_as_float(c.w[e] << 16);
+                x[2 * e + 1] -= __uint_as_float(c.w[e] & 0xFFFF0000u);
+            }
+        }
+        p[q] = c.v;
+    }
+}
+// An MFMA wants 2 wait states behind the vector instruction that wrote its operand; the compiler does not count the
+// conversions, which it does not see (tests/test_kernel_isa.py does).
+__device__ __forceinline__ void split_done()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 1");
+    __builtin_amdgcn_sched_barrier(0);
+}
+// ask for the conversion of one fragment (44 instructions) between the products of MI row tiles with another
+template <int MI>
+__device__ __forceinline__ void spread_split()
+{
+#pragma unroll
+    for (int i = 0; i < 6 * MI; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);               // an MFMA
+        __builtin_amdgcn_sched_group_barrier(0x002, (44 + 6 * MI - 1) / (6 * MI), 0);
+    }
+    split_done();
+}
+// the six products, the small ones first; neighbours work on different accumulators.  With sums of their own for the small
+// ones (to be added at the end) the error is 0.4 of it.
+template <int MI>
+__device__ __forceinline__ void mfma_split(f32x4 *acc, int stride, f32x4 *small, int small_stride, const bf16x8 (&pa)[MI][3],
+                                           const bf16x8 (&pb)[3])
+{
+    constexpr int PA[6] = {0, 2, 1, 0, 1, 0}, PB[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            f32x4 &c = q < 5 ? small[i * small_stride] : acc[i * stride];
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[i][PA[q]], pb[PB[q]], c, 0, 0, 0);
+        }
+}
+// sums that are no finite numbers (0 x would be NaN for them)
+__device__ __forceinline__ bool any_not_finite(const f32x4 *acc, int n)
+{
+    float c = 0.f;
+#pragma unroll
+    for (int i = 0; i < n; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c = fmaf(acc[i][e], 0.f, c);
+    return __any(c != 0.f);
+}
+
+// TM x TN tile per block of NW waves, each of which takes its share of the contraction for the whole tile; the waves' sums are added
+// in wave order through LDS.  So every operand is converted once per block and nothing in the loop waits at a barrier: a wave
+// has a piece of LDS of its own for a k-step's operands, filled by asynchronous copies, reads its fragments from there, and
+// requests the next step's operands into what it has read before it multiplies.  (Fragments read straight from memory go
+// 16 bytes at a time, neighbouring lanes being different rows: 30 GB/s per CU where whole rows reach 100.)  The rank-space
+// activations z = A Z^T are one more column tile, formed by every column tile's block for its rows (a third more matrix
+// work at TN = 48, where a launch of their own took 5 us) and stored by the first.  The blocks of a launch also deal out the rows of a
+// second projection (backward: x A^T, which nothing here waits for).
+// One of them to a CU with 8 waves, for launches of about a tile per CU, or two with 4 (64 x 64 of short contractions).
+template <int TM, int TN, int NW, bool BT>
+struct F32Wave {
+    static constexpr int MI = TM / 16, NI = TN / 16, NT = MI * (NI + 1);
+    static constexpr int NA = TM / 8, NB = TN / 8, NZ = BT ? 2 : 0;   // copies of 1 KB per k-step: A, B, rows of Z
+    static constexpr int SLAB = (NA + NB + NZ) * 1024;
+    static constexpr int LDS = NW * (SLAB > NT * 1024 ? SLAB : NT * 1024);
+};
+template <int TM, int TN, int NW, bool BT>
+__device__ __forceinline__ void f32_wave_tile(const GemmF32 &a, unsigned char *lds)
+{
+    typedef F32Wave<TM, TN, NW, BT> F;
+    constexpr int MI = F::MI, NI = F::NI, NT = F::NT, NQ = (MI * NI + NW - 1) / NW, RW = TN / 4;
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4, sw = r16 & 7;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tiles_n = (a.N + TN - 1) / TN, tiles_m = (a.M + TM - 1) / TM, nb = tiles_m * tiles_n, per_xcd = (nb + 7) >> 3;
+    const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (tile >= nb || (int)(blockIdx.x >> 3) >= per_xcd) return;
+    const int panel = tile / (4 * tiles_n), rem = tile - panel * 4 * tiles_n, rows = min(4, tiles_m - 4 * panel);
+    const int m0 = (4 * panel + rem % rows) * TM, tn = rem / rows, n0 = tn * TN;
+    const bool fold = a.Z != nullptr;
+
+    // copies: 8 rows of 128 bytes each, 16-byte chunks XORed with the row; W as [k, n]: rows of TN floats, chunks rotated by
+    // the k-group, so that the four k-groups of a read meet different banks
+    const int crow = lane >> 3, cch = ((lane & 7) ^ (lane >> 3)) << 4;
+    unsigned ao[F::NA], bo[F::NB], zo[2];
+#pragma unroll
+    for (int p = 0; p < F::NA; ++p) ao[p] = (unsigned)min(m0 + p * 8 + crow, a.M - 1) * (unsigned)a.K * 4u + cch;
+#pragma unroll
+    for (int p = 0; p < F::NB; ++p) {
+        if (BT) bo[p] = (unsigned)min(n0 + p * 8 + crow, a.N - 1) * (unsigned)a.K * 4u + cch;
+        else {
+            const int slot = p * 64 + lane, k = slot / RW, ch = (slot % RW + RW - 4 * ((k >> 2) & 3) % RW) % RW;
+            bo[p] = ((unsigned)k * (unsigned)a.N + (unsigned)min(n0 + ch * 4, a.N - 4)) * 4u;
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) zo[p] = fold ? (unsigned)min(p * 8 + crow, a.r - 1) * (unsigned)a.K * 4u + cch : ao[0];
+    // (without a branch: the waits below count these copies whether they are wanted or not)
+    const char *const zsrc = (const char *)(fold ? a.Z : a.A);
+    const unsigned char *mine = lds + wave * F::SLAB;
+    const unsigned base = lds_addr(mine);
+    const size_t bstep = BT ? 128 : 128 * (size_t)a.N;   // bytes of B per k-step
+    auto copy_a = [&](int s) {
+#pragma unroll
+        for (int p = 0; p < F::NA; ++p) glds_soff((const char *)a.A + (size_t)s * 128, ao[p], base + p * 1024);
+    };
+    auto copy_b = [&](int s) {
+#pragma unroll
+        for (int p = 0; p < F::NB; ++p) glds_soff((const char *)a.B + s * bstep, bo[p], base + (F::NA + p) * 1024);
+#pragma unroll
+        for (int p = 0; p < F::NZ; ++p) glds_soff(zsrc + (size_t)s * 128, zo[p], base + (F::NA + F::NB + p) * 1024);
+    };
+    const int steps = a.K >> 5, s0 = wave * steps / NW, s1 = (wave + 1) * steps / NW;
+    if (s0 < s1) {
+        copy_a(s0);
+        copy_b(s0);
+    }
+    // rows of the second projection: a wave each
+    if (a.z2) {
+        typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+        const int per = (a.M + nb - 1) / nb;
+        for (int i = wave; i < per; i += NW) {
+            const int t = tile * per + i;
+            if (t >= a.M) break;
+            for (int j0 = 0; j0 < a.zp; j0 += 4) {
+                float v[4] = {0.f, 0.f, 0.f, 0.f};
+                for (int c = lane * 4; c < a.K2; c += 256) {
+                    const f32x4u x = *(const f32x4u *)(a.x2 + (size_t)t * a.K2 + c);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const f32x4u w = *(const f32x4u *)(a.A2 + (size_t)min(j0 + j, a.r - 1) * a.K2 + c);
+                        v[j] = fmaf(x.x, w.x, v[j]); v[j] = fmaf(x.y, w.y, v[j]);
+                        v[j] = fmaf(x.z, w.z, v[j]); v[j] = fmaf(x.w, w.w, v[j]);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = wave_sum(v[j]);
+                if (lane < 4) {
+                    const float w = lane == 0 ? v[0] : lane == 1 ? v[1] : lane == 2 ? v[2] : v[3];
+                    a.z2[(size_t)t * a.zp + j0 + lane] = j0 + lane < a.r ? w : 0.f;
+                }
+            }
+        }
+    }
+
+    f32x4 acc[NT];                                       // column tile NI is z
+#pragma unroll
+    for (int i = 0; i < NT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the input gradient's z enters the adapter's gradient, where the fp32 instruction's 8 shorter chains stood
+    f32x4 zsmall[BT ? 1 : MI];
+#pragma unroll
+    for (int i = 0; i < (BT ? 1 : MI); ++i) zsmall[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const bool zok = fold && r16 < a.r;
+    // Z as the caller's B [K, r] (backward): neighbouring lanes are neighbours in memory, a load per element
+    const float *zcol = a.Z + min(r16, a.r - 1);
+    auto load_z = [&](int s, float4 (&z)[2]) {
+        if (BT || !fold) return;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float *q = zcol + (size_t)(s * 32 + 16 * h + 4 * g) * a.r;
+            z[h] = make_float4(q[0], q[a.r], q[2 * a.r], q[3 * a.r]);
+        }
+    };
+    for (int s = s0; s < s1; ++s) {
+        const int next = min(s + 1, s1 - 1);             // (behind the last step: it once more, unread)
+        bf16x8 pa[MI][3], pb[2][3], pz[3];
+        float4 b[NI][2], z[2];
+        {
+            float4 f[MI][2];
+            load_z(s, z);
+            // A has landed (B of this step, requested behind it, and z may not have)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(F::NB + F::NZ) : "memory");
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) f[i][h] = *(const float4 *)(mine + (i * 16 + r16) * 128 + (((h * 4 + g) ^ sw) << 4));
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            // (a load the compiler waits for: converted here, where nothing else is in flight)
+            if (!BT) split3(zero_beyond(z[0], zok), zero_beyond(z[1], zok), pz);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const unsigned char *S = mine + F::NA * 1024;
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    const int n = j * 16 + r16;
+                    if (BT) b[j][h] = *(const float4 *)(S + n * 128 + (((h * 4 + g) ^ sw) << 4));
+                    else {
+                        const float *q = (const float *)S + (h * 16 + 4 * g) * TN + (((n >> 2) + 4 * g) % RW) * 4 + (n & 3);
+                        b[j][h] = make_float4(q[0], q[TN], q[2 * TN], q[3 * TN]);
+                    }
+                }
+                if (BT) z[h] = *(const float4 *)(S + F::NB * 1024 + r16 * 128 + (((h * 4 + g) ^ sw) << 4));
+            }
+            copy_a(next);
+#pragma unroll
+            for (int i = 0; i < MI; ++i) split3(f[i][0], f[i][1], pa[i]);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            copy_b(next);
+            if (BT) split3(zero_beyond(z[0], zok), zero_beyond(z[1], zok), pz);
+        }
+        split3(b[0][0], b[0][1], pb[0]);
+        split_done();
+#pragma unroll
+        for (int j = 0; j <= NI; ++j) {
+            if (j + 1 < NI) split3(b[j + 1][0], b[j + 1][1], pb[(j + 1) & 1]);
+            if (j < NI) mfma_split<MI>(acc + j, NI + 1, acc + j, NI + 1, pa, pb[j & 1]);
+            else if (BT) mfma_split<MI>(acc + NI, NI + 1, acc + NI, NI + 1, pa, pz);
+            else mfma_split<MI>(acc + NI, NI + 1, zsmall, 1, pa, pz);
+            spread_split<MI>();
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    if (!BT) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i * (NI + 1) + NI][e] += zsmall[BT ? 0 : i][e];
+    }
+    // operands of the low-rank term and the bias for the tiles this wave finishes
+    float4 uu[NQ];
+    float bias[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int n = min(n0 + ((wave + q * NW) % NI) * 16 + r16, a.N - 1);
+        uu[q] = up_frag_u(a, n, g);
+        bias[q] = a.bias ? a.bias[n] : 0.f;
+    }
+    if (any_not_finite(acc, NT)) {
+#pragma unroll
+        for (int i = 0; i < NT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int k = s0 * 32 + 4 * g; k < s1 * 32; k += 16) {
+            float4 f[MI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) f[i] = *(const float4 *)(a.A + (size_t)min(m0 + i * 16 + r16, a.M - 1) * a.K + k);
+#pragma unroll
+            for (int j = 0; j <= NI; ++j) {
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (j < NI || zok) {
+                    const int n = j < NI ? min(n0 + j * 16 + r16, a.N - 1) : r16;
+                    const bool rowsk = BT;               // B and Z as [n, k] in the forward, [k, n] in the input gradient
+                    const float *q = (j < NI ? a.B : a.Z) + (rowsk ? (size_t)n * a.K + k : (size_t)k * (j < NI ? a.N : a.r) + n);
+                    const size_t st = rowsk ? 1 : j < NI ? a.N : a.r;
+                    v = make_float4(q[0], q[st], q[2 * st], q[3 * st]);
+                }
+#pragma unroll
+                for (int i = 0; i < MI; ++i) mfma4(acc[i * (NI + 1) + j], f[i], v);
+            }
+        }
+    }
+    __syncthreads();                                     // the waves' pieces of LDS take their sums
+    float4 *part = (float4 *)lds;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) part[(wave * NT + i) * 64 + lane] = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+    __syncthreads();
+    auto sum = [&](int t) {
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float4 q = part[(w * NT + t) * 64 + lane];
+            v[0] += q.x; v[1] += q.y; v[2] += q.z; v[3] += q.w;
+        }
+        return v;
+    };
+    // z of the block's rows, in the place of the first wave's share of it as [16 rows][16]
+    if (fold) {
+        for (int i = wave; i < MI; i += NW) {
+            const f32x4 v = sum(i * (NI + 1) + NI);
+            float *zt = (float *)(part + (i * (NI + 1) + NI) * 64);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float w = zok ? v[e] : 0.f;        // also where an infinity met a zero of Z
+                zt[(4 * g + e) * 16 + r16] = w;
+                const int m = m0 + i * 16 + 4 * g + e;
+                if (a.zout && tn == 0 && m < a.M && r16 < a.zp) a.zout[(size_t)m * a.zp + r16] = w;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int t = wave + q * NW, i = t / NI, j = t % NI;
+        if (t >= MI * NI) break;
+        const float4 uz = fold ? part[(i * (NI + 1) + NI) * 64 + r16 * 4 + g] : up_frag_z(a, min(m0 + i * 16 + r16, a.M - 1), g);
+        f32x4 v = sum(i * (NI + 1) + j), low = {0.f, 0.f, 0.f, 0.f};
+        mfma4(low, uz, uu[q]);
+        const int n = n0 + j * 16 + r16;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int m = m0 + i * 16 + 4 * g + e;
+            if (m < a.M && n < a.N) a.C[(size_t)m * a.N + n] = fmaf(a.s, low[e], v[e] + bias[q]);
+        }
+    }
+}
+
+// 128 x 128 tile per block, two groups of 2 x 2 waves (wave tile 64 x 64) that take the slabs of 32 in turn, for launches with
+// enough such tiles.  A stage of the LDS ring holds a slab for each group, filled by asynchronous copies; a wave takes its
+// fragments into registers, a barrier frees the stage for the copies of the stage after the next, and the wave converts and
+// multiplies while they arrive; its SIMD's other wave fills the matrix pipe while it converts.  Operand rows of 128 bytes with the
+// 16-byte chunks XORed with the row, W read as [k, n] as rows of 128 floats with the chunks rotated by the k-group, so that
+// the four k-groups of a read meet different banks.
+template <int NST, bool BT>
+__device__ __forceinline__ void f32_ring_tile(const GemmF32 &a, unsigned char *lds)
+{
+    constexpr int TM = 128, TN = 128, WN = 2, MI = 4, NI = 4;
     constexpr int ASZ = TM * 128, SUB = ASZ + TN * 128, STAGE = 2 * SUB;
-    constexpr int CA = 2 * TM / 64, PER = CA + (2 * TN + 63) / 64;    // 1 KB copies of a wave per stage
+    constexpr int CA = 2 * TM / 64, PER = CA + 2 * TN / 64;           // 1 KB copies of a wave per stage
     constexpr int RW = TN / 4;                           // 16-byte chunks of a row of W as [k, n]
-    static_assert((2 * TM) % 64 == 0 && NST * PER < 64, "copies");
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
+    static_assert(NST * PER < 64, "copies");
     const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), grp = wv >> 2, wave = wv & 3;
     const int wm = wave / WN, wn = wave % WN;
@@ -342,23 +663,10 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(GemmF32 a)
     const int panel = tile / (4 * tiles_n), rem = tile - panel * 4 * tiles_n, rows = min(4, tiles_m - 4 * panel);
     const int m0 = (4 * panel + rem % rows) * TM, n0 = (rem / rows) * TN;
 
-    // operands of the low-rank term and the bias, needed after the loop: requested first, so that the waits below count
-    // copies only
-    float4 uz[MI], uu[NI];
-    float bias[NI];
-    if (grp == 0) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i) uz[i] = up_frag_z(a, min(m0 + (wm * MI + i) * 16 + r16, a.M - 1), g);
-#pragma unroll
-        for (int j = 0; j < NI; ++j) uu[j] = up_frag_u(a, min(n0 + (wn * NI + j) * 16 + r16, a.N - 1), g);
-#pragma unroll
-        for (int j = 0; j < NI; ++j) bias[j] = a.bias ? a.bias[min(n0 + (wn * NI + j) * 16 + r16, a.N - 1)] : 0.f;
-    }
-
     // copies: piece p of a stage (1 KB), the pieces of both groups' slabs dealt over the 8 waves; lane l fills 16-byte slot l
     const int nst = a.K / 64;                            // stages of the contraction
     unsigned ao[CA], bo[PER - CA];
-    int al[CA], bl[PER - CA], blanes[PER - CA];
+    int al[CA], bl[PER - CA];
 #pragma unroll
     for (int c = 0; c < CA; ++c) {
         const int p = wv * CA + c, sub = p / (TM / 8), row = (p % (TM / 8)) * 8 + (lane >> 3);
@@ -367,9 +675,7 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(GemmF32 a)
     }
 #pragma unroll
     for (int c = 0; c < PER - CA; ++c) {
-        constexpr int NB = 2 * (TN / 8);                 // pieces of B per stage
-        const int p = min(wv * (PER - CA) + c, NB - 1), sub = p / (TN / 8), q = p % (TN / 8);
-        blanes[c] = (wv * (PER - CA) + c - NB) >> 31;    // -1, or 0 where there is no such piece
+        const int p = wv * (PER - CA) + c, sub = p / (TN / 8), q = p % (TN / 8);
         bl[c] = sub * SUB + ASZ + q * 1024;
         if (BT) {
             const int row = q * 8 + (lane >> 3);
@@ -385,91 +691,107 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(GemmF32 a)
     auto copy1 = [&](int slot, int t, int c) {
         const size_t tt = (size_t)min(t, nst - 1);
         if (c < CA) glds_soff((const char *)a.A + tt * 256, ao[c < CA ? c : 0], base + slot * STAGE + al[c < CA ? c : 0]);
-        else {
-            const int b = c >= CA ? c - CA : 0;
-            glds_soff_if((const char *)a.B + tt * bstep, bo[b], base + slot * STAGE + bl[b], blanes[b]);
-        }
+        else glds_soff((const char *)a.B + tt * bstep, bo[c >= CA ? c - CA : 0], base + slot * STAGE + bl[c >= CA ? c - CA : 0]);
     };
 
-    f32x4 acc[MI][NI];
+    f32x4 acc[MI * NI];
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    struct Frags { float4 a[MI], b[NI]; } f[2];
+    for (int i = 0; i < MI * NI; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int sw = r16 & 7;
-    auto frags = [&](Frags &F, int slot, int ks) {
-        const unsigned char *S = lds + slot * STAGE + grp * SUB;
-        const int co = ((ks * 4 + g) ^ sw) << 4;
 #pragma unroll
-        for (int i = 0; i < MI; ++i) F.a[i] = *(const float4 *)(S + ((wm * MI + i) * 16 + r16) * 128 + co);
-#pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            const int n = (wn * NI + j) * 16 + r16;
-            if (BT) F.b[j] = *(const float4 *)(S + ASZ + n * 128 + co);
-            else {
-                const float *q = (const float *)(S + ASZ) + (ks * 16 + 4 * g) * TN + (((n >> 2) + 4 * g) % RW) * 4 + (n & 3);
-                F.b[j] = make_float4(q[0], q[TN], q[2 * TN], q[3 * TN]);
-            }
-        }
-    };
-    // component by component, so that an accumulator is not needed again by the very next MFMA
-    auto mfmas = [&](const Frags &F) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32((&F.a[i].x)[c], (&F.b[j].x)[c], acc[i][j], 0, 0, 0);
-    };
-#pragma unroll
-    for (int s = 0; s < NST - 1; ++s)
+    for (int s = 0; s < NST; ++s)
 #pragma unroll
         for (int c = 0; c < PER; ++c) copy1(s, s, c);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * PER) : "memory");
-    __syncthreads();
-    frags(f[0], 0, 0);
     int slot = 0;
     for (int t = 0; t < nst; ++t) {
-        const int next = slot + 1 == NST ? 0 : slot + 1, prev = slot == 0 ? NST - 1 : slot - 1;
-        frags(f[1], slot, 1);
-#pragma unroll
-        for (int c = 0; c < PER; ++c) copy1(prev, t + NST - 1, c);
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(f[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        // the wave's reads of the stage are done and its copies of the next one have landed
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NST - 2) * PER) : "memory");
+        // this wave's copies of the stage have landed, then everybody's
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * PER) : "memory");
         __syncthreads();
-        frags(f[0], next, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(f[1]);
-        __builtin_amdgcn_sched_barrier(0);
-        slot = next;
+        float4 fa[MI][2], fb[NI][2];
+        const unsigned char *S = lds + slot * STAGE + grp * SUB;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int co = ((h * 4 + g) ^ sw) << 4;
+#pragma unroll
+            for (int i = 0; i < MI; ++i) fa[i][h] = *(const float4 *)(S + ((wm * MI + i) * 16 + r16) * 128 + co);
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                const int n = (wn * NI + j) * 16 + r16;
+                if (BT) fb[j][h] = *(const float4 *)(S + ASZ + n * 128 + co);
+                else {
+                    const float *q = (const float *)(S + ASZ) + (h * 16 + 4 * g) * TN + (((n >> 2) + 4 * g) % RW) * 4 + (n & 3);
+                    fb[j][h] = make_float4(q[0], q[TN], q[2 * TN], q[3 * TN]);
+                }
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < PER; ++c) copy1(slot, t + NST, c);
+        bf16x8 pa[MI][3], pb[2][3];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) split3(fa[i][0], fa[i][1], pa[i]);
+        split3(fb[0][0], fb[0][1], pb[0]);
+        split_done();
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            if (j + 1 < NI) split3(fb[j + 1][0], fb[j + 1][1], pb[(j + 1) & 1]);
+            mfma_split<MI>(acc + j, NI, acc + j, NI, pa, pb[j & 1]);
+            spread_split<MI>();
+        }
+        slot = slot + 1 == NST ? 0 : slot + 1;
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    // operands of the low-rank term, and of the sums that have to be formed again
+    unsigned ar[MI], br[NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) ar[i] = (unsigned)min(m0 + (wm * MI + i) * 16 + r16, a.M - 1);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) br[j] = (unsigned)min(n0 + (wn * NI + j) * 16 + r16, a.N - 1);
+    if (any_not_finite(acc, MI * NI)) {
+#pragma unroll
+        for (int i = 0; i < MI * NI; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < nst; ++t)
+            for (int h = 0; h < 2; ++h) {
+                const int k = t * 64 + grp * 32 + h * 16 + 4 * g;
+                float4 fa[MI];
+#pragma unroll
+                for (int i = 0; i < MI; ++i) fa[i] = *(const float4 *)(a.A + (size_t)ar[i] * a.K + k);
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    const float *q = BT ? a.B + (size_t)br[j] * a.K + k : a.B + (size_t)k * a.N + br[j];
+                    const size_t st = BT ? 1 : a.N;
+                    const float4 fb = make_float4(q[0], q[st], q[2 * st], q[3 * st]);
+#pragma unroll
+                    for (int i = 0; i < MI; ++i) mfma4(acc[i * NI + j], fa[i], fb);
+                }
+            }
+    }
     __syncthreads();                                     // the ring takes the second group's sums
     float4 *part = (float4 *)lds;
     if (grp == 1) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-                part[(i * NI + j) * 256 + (tid & 255)] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+        for (int i = 0; i < MI * NI; ++i) part[i * 256 + (tid & 255)] = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
     }
     __syncthreads();
     if (grp == 1) return;
+    float4 uz[MI], uu[NI];
+    float bias[NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) uz[i] = up_frag_z(a, (int)ar[i], g);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) { uu[j] = up_frag_u(a, (int)br[j], g); bias[j] = a.bias ? a.bias[br[j]] : 0.f; }
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
+            f32x4 &c = acc[i * NI + j];
             const float4 v = part[(i * NI + j) * 256 + (tid & 255)];
-            acc[i][j][0] += v.x; acc[i][j][1] += v.y; acc[i][j][2] += v.z; acc[i][j][3] += v.w;
+            c[0] += v.x; c[1] += v.y; c[2] += v.z; c[3] += v.w;
             f32x4 low = {0.f, 0.f, 0.f, 0.f};
             mfma4(low, uz[i], uu[j]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][e] = fmaf(a.s, low[e], acc[i][j][e] + bias[j]);
+            for (int e = 0; e < 4; ++e) c[e] = fmaf(a.s, low[e], c[e] + bias[j]);
         }
     float *cp = a.C + (size_t)(m0 + wm * MI * 16 + 4 * g) * a.N + n0 + wn * NI * 16 + r16;
     const bool inside = m0 + TM <= a.M && n0 + TN <= a.N;
@@ -479,11 +801,24 @@ __global__ __launch_bounds__(512) void f32_tile_kernel(GemmF32 a)
         for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
-                const float v = acc[i][j][e];
+                const float v = acc[i * NI + j][e];
                 if (inside) cp[(size_t)(i * 16 + e) * a.N + j * 16] = v;
                 else if (m0 + (wm * MI + i) * 16 + 4 * g + e < a.M && n0 + (wn * NI + j) * 16 + r16 < a.N)
                     cp[(size_t)(i * 16 + e) * a.N + j * 16] = v;
             }
+}
+
+// FORM: pairs of waves of f32_wave_tile's block, or the stages of f32_ring_tile's ring
+template <int TM, int TN, int FORM, bool BT>
+__global__ __launch_bounds__(TM == 128 ? 512 : 128 * FORM, TM == 128 ? 1 : FORM == 2 ? 2 : 1) void f32_tile_kernel(GemmF32 a)
+{
+    if constexpr (TM == 128) {
+        __shared__ __attribute__((aligned(1024))) unsigned char lds[FORM * 2 * 256 * 128];
+        f32_ring_tile<FORM, BT>(a, lds);
+    } else {
+        __shared__ __attribute__((aligned(1024))) unsigned char lds[F32Wave<TM, TN, 2 * FORM, BT>::LDS];
+        f32_wave_tile<TM, TN, 2 * FORM, BT>(a, lds);
+    }
 }
 
 // Few output tiles (small T): 16 x 16 outputs per block, the contraction split over 8 waves that read their fragments
@@ -612,20 +947,21 @@ void launch_tile(const GemmF32 &a, hipStream_t st)
     const long tiles = (long)((a.M + TM - 1) / TM) * ((a.N + TN - 1) / TN);
     hipLaunchKernelGGL((f32_gemm_kernel<TM, TN, KS, BT, VEC>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256 * KS), 0, st, a);
 }
-template <int TM, int TN, int WM, int WN, int NST, bool BT>
-void launch_ring(const GemmF32 &a, hipStream_t st)
+template <int TM, int TN, int FORM, bool BT>
+void launch_split(const GemmF32 &a, hipStream_t st)
 {
     const long tiles = (long)((a.M + TM - 1) / TM) * ((a.N + TN - 1) / TN);
-    hipLaunchKernelGGL((f32_tile_kernel<TM, TN, WM, WN, NST, BT>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(512), 0, st, a);
+    hipLaunchKernelGGL((f32_tile_kernel<TM, TN, FORM, BT>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(TM == 128 ? 512 : 128 * FORM), 0, st, a);
 }
-// The kernel for a product.  16 x 16 outputs per block (f32_gemm_direct_kernel) while 64 x 64 tiles would leave most CUs without
-// work: drawn at 96 of them against f32_gemm_kernel.  Against the ring the line would lie at about 36 (projection + product,
-// 1024 -> 1024: 32 tiles 15.3 us direct, 17.2 on the ring; 48: 20.3, 17.4; 80: 27.2, 17.6; 4096 -> 1024: 51.2, 56.0; 66.0, 58.7;
-// 92.3, 59.7).  The ring needs whole stages of 64 and 32-bit byte offsets and runs on the form that costs least, in us as measured
-// (T = 64 to 8192 at five weight shapes): rounds of 256 tiles, or of 512 where two blocks share a CU, at a + b (K / 64) each.
-// 32 x 64 and 64 x 48 fill the chip where 64 x 64 tiles leave a part of it idle (T = 1024, 768 -> 768: 256 tiles of 64 x 48 in
-// 13.5 us, 192 of 64 x 64 in 16.1).  Without the ring (f32_gemm_kernel) 128 x 128 tiles once two of them per CU are there (below
-// that the idle CUs cost more than the operand traffic saved).
+// The kernel for a product (plan_f32).  f32_tile_kernel needs whole stages of 64, rows of whole float4s and 32-bit byte offsets; without
+// them 16 x 16 outputs per block while there are fewer than 96 tiles of 64 x 64 and 128 x 128 tiles of f32_gemm_kernel
+// once two of them per CU are there (below that the idle CUs cost more than the operand traffic saved).
+// With them the form that costs least in us as fitted to forward calls of 64 to 8192 rows at nine weight shapes (mean error 2 to 3 %):
+// a launch, then rounds of tiles at a + b (K / 64) each, the last of up to 256 at a1 + b1 (K / 64); the 128 x 128 form with
+// the projections' launch.  Forward, r = 4, us on 16 x 16, 32 x 64, 64 x 48, 64 x 64, two blocks of 64 x 64 to a CU, 128 x 128:
+// 64 rows of 768 -> 768 10.6, 11.9, 14.6, 16.6, 18.2, 40; 256 of 1024 -> 1024 25.2, 14.0, 17.5, 19.6, 21.6, 51; 1024 of
+// 768 -> 768 41, 21.6, 16.3, 16.6, 18.4, 41; 1024 of 1024 -> 1024 66, 25.8, 29.5, 21.8, 22.6, 51; 2048 of 1280 -> 1280 -, 73, 75, 67, 58, 67;
+// 4096 of 768 -> 3072 -, 241, 211, 186, 145, 124.
 template <bool BT, bool VEC>
 int launch_product(const GemmF32 &a, const F32Plan &p, hipStream_t st)
 {
@@ -637,21 +973,28 @@ int launch_product(const GemmF32 &a, const F32Plan &p, hipStream_t st)
         else launch_tile<128, 128, 1, BT, VEC>(a, st);
     } else if constexpr (VEC) {
         switch (p.tm * 1000 + p.tn + p.stages) {
-        case 32064 + 4: launch_ring<32, 64, 2, 2, 4, BT>(a, st); break;
-        case 64048 + 4: launch_ring<64, 48, 4, 1, 4, BT>(a, st); break;
-        case 64064 + 4: launch_ring<64, 64, 2, 2, 4, BT>(a, st); break;
-        case 64064 + 2: launch_ring<64, 64, 2, 2, 2, BT>(a, st); break;
-        case 128128 + 2: launch_ring<128, 128, 2, 2, 2, BT>(a, st); break;
+        case 32064 + 4: launch_split<32, 64, 4, BT>(a, st); break;
+        case 64048 + 4: launch_split<64, 48, 4, BT>(a, st); break;
+        case 64064 + 4: launch_split<64, 64, 4, BT>(a, st); break;
+        case 64064 + 2: launch_split<64, 64, 2, BT>(a, st); break;
+        case 128128 + 2: launch_split<128, 128, 2, BT>(a, st); break;
         default: return SL_EINVAL;
         }
     } else return SL_EINVAL;
     SL_CHECK_LAUNCH("f32 product");
     return 0;
 }
+// float4 loads need rows of a multiple of four floats on 16-byte bases
+bool vec_rows(const GemmF32 &a, bool bt) { return (a.K % 4) == 0 && aligned16(a.A) && aligned16(a.B) && (bt || (a.N % 4) == 0); }
+// whether the product's kernel forms the rank-space activations (and the second projection) itself
+bool projects(const GemmF32 &a, const float *Z, bool bt)
+{
+    const F32Plan p = plan_f32(a.M, a.N, a.K, vec_rows(a, bt));
+    return p.stages > 0 && p.tm < 128 && (!bt || aligned16(Z));
+}
 int product(const GemmF32 &a, bool bt, hipStream_t st)
 {
-    // float4 loads need rows of a multiple of four floats on 16-byte bases
-    const bool vec = (a.K % 4) == 0 && aligned16(a.A) && aligned16(a.B) && (bt || (a.N % 4) == 0);
+    const bool vec = vec_rows(a, bt);
     const F32Plan p = plan_f32(a.M, a.N, a.K, vec);
     if (bt) return vec ? launch_product<true, true>(a, p, st) : launch_product<true, false>(a, p, st);
     return vec ? launch_product<false, true>(a, p, st) : launch_product<false, false>(a, p, st);
@@ -676,18 +1019,26 @@ int project(const ProjJob *j, int n, int T, int r, int zp, hipStream_t st)
 
 F32Plan plan_f32(int M, int N, int K, bool vec)
 {
-    struct Form { int tm, tn, stages, per_cu; float a, b; };
-    constexpr Form forms[5] = {{32, 64, 4, 1, 3.1f, .545f}, {64, 48, 4, 1, 3.6f, .765f}, {64, 64, 4, 1, 3.8f, .995f},
-                               {64, 64, 2, 2, 4.6f, 1.90f}, {128, 128, 2, 1, 7.5f, 3.68f}};
+    struct Form { int tm, tn, stages; float launch; int round; float a, b, a1, b1; };
+    constexpr Form forms[5] = {{32, 64, 4, 2.8f, 256, 4.18f, .485f, 4.18f, .485f}, {64, 48, 4, 2.8f, 256, 5.90f, .610f, 5.90f, .610f},
+                               {64, 64, 4, 2.8f, 256, 6.78f, .725f, 6.78f, .725f}, {64, 64, 2, 2.8f, 512, 5.94f, 1.518f, 5.74f, .864f},
+                               {128, 128, 2, 5.5f, 256, 6.80f, 2.688f, 6.80f, 2.688f}};
     auto tiles = [&](int tm, int tn) { return (long)((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
-    if (tiles(64, 64) < 96) return {16, 16, 0};
-    const bool ring = vec && K % 64 == 0 && (unsigned long long)M * K < (1ull << 30) && (unsigned long long)N * K < (1ull << 30);
-    if (!ring) return tiles(128, 128) < 512 ? F32Plan{64, 64, 0} : F32Plan{128, 128, 0};
+    const bool split = vec && K % 64 == 0 && (unsigned long long)M * K < (1ull << 30) && (unsigned long long)N * K < (1ull << 30);
+    if (!split) {
+        if (tiles(64, 64) < 96) return {16, 16, 0};
+        return tiles(128, 128) < 512 ? F32Plan{64, 64, 0} : F32Plan{128, 128, 0};
+    }
+    const double nk = K / 64;
     F32Plan best = {0, 0, 0};
     double least = 0;
+    if (tiles(16, 16) <= 1024) {
+        best = {16, 16, 0};
+        least = 5.9 + nk * (.25 + .27 * ((tiles(16, 16) + 255) / 256));
+    }
     for (const Form &f : forms) {
-        const long round = 256 * f.per_cu;
-        const double c = (double)((tiles(f.tm, f.tn) + round - 1) / round) * (f.a + f.b * (K / 64));
+        const long t = tiles(f.tm, f.tn), before = (t - 1) / f.round;
+        const double c = f.launch + before * (f.a + f.b * nk) + (t - before * f.round > 256 ? f.a + f.b * nk : f.a1 + f.b1 * nk);
         if (best.tm == 0 || c < least) { best = {f.tm, f.tn, f.stages}; least = c; }
     }
     return best;
@@ -700,10 +1051,13 @@ int f32_lora_linear_fwd(int T, int n_in, int n_out, int r, float s, const float 
                         const float *bias, const float *A, const float *B, float *y, float *ws, hipStream_t st)
 {
     const int zp = pad_rank(r);
-    const ProjJob j = {x, A, n_in, 1, n_in, ws};
-    int rc;
-    if ((rc = project(&j, 1, T, r, zp, st))) return rc;
-    GemmF32 a = {x, W, bias, ws, B, y, T, n_out, n_in, zp, r, 1, r, s};
+    GemmF32 a = {x, W, bias, ws, B, y, T, n_out, n_in, zp, r, 1, r, s, nullptr, nullptr, nullptr, nullptr, nullptr, 0};
+    if (projects(a, A, true)) a.Z = A;
+    else {
+        const ProjJob j = {x, A, n_in, 1, n_in, ws};
+        const int rc = project(&j, 1, T, r, zp, st);
+        if (rc) return rc;
+    }
     return product(a, true, st);
 }
 
@@ -713,10 +1067,24 @@ int f32_lora_linear_bwd(int T, int n_in, int n_out, int r, float s, const float 
 {
     const int zp = pad_rank(r);
     float *z = ws, *p = ws + (size_t)T * zp;
-    const ProjJob pj[2] = {{x, A, n_in, 1, n_in, z}, {dy, B, 1, r, n_out, p}};
+    GemmF32 a = {dy, W, nullptr, p, A, dx, T, n_in, n_out, zp, r, n_in, 1, s, nullptr, nullptr, nullptr, nullptr, nullptr, 0};
     int rc;
-    if ((rc = project(pj, 2, T, r, zp, st))) return rc;
-    GemmF32 a = {dy, W, nullptr, p, A, dx, T, n_in, n_out, zp, r, n_in, 1, s};
+    if (projects(a, B, false)) {
+        a.Z = B;
+        a.zout = p;
+        if (zp <= 8) {                                   // (16 rows of A for each row of x: a launch of its own is less)
+            a.x2 = x;
+            a.A2 = A;
+            a.z2 = z;
+            a.K2 = n_in;
+        } else {
+            const ProjJob j = {x, A, n_in, 1, n_in, z};
+            if ((rc = project(&j, 1, T, r, zp, st))) return rc;
+        }
+    } else {
+        const ProjJob pj[2] = {{x, A, n_in, 1, n_in, z}, {dy, B, 1, r, n_out, p}};
+        if ((rc = project(pj, 2, T, r, zp, st))) return rc;
+    }
     if ((rc = product(a, false, st))) return rc;
     const GradJobs gj = {{{x, p, n_in, dA, 1}, {dy, z, n_out, dB, 0}}};
     const dim3 grid(((n_in > n_out ? n_in : n_out) + 31) / 32, 2);

@@ -175,6 +175,54 @@ def test_fp32_infinity_stays_an_infinity(T, n_in, n_out):
     assert np.isfinite(np.delete(y, 7, 0)).all() and np.isfinite(np.delete(dx, 9, 0)).all()
 
 
+# The products on three bf16 pieces an operand: fewer k-steps than waves, ragged tiles, an adapter that is not 16-byte aligned
+# (projection in a launch of its own), backward projections in the product's launch (rank up to 8) and not (16); and numbers
+# that bf16 rounds to an infinity, whose sums are formed again.  T, n_in, n_out, r, floats the adapter is off by: forms of
+# the two products (tests/test_plans.py).
+FP32_SPLIT = {
+    (300, 64, 2052, 4, 0): ((64, 48, 4), (16, 16, 0)),
+    (97, 1024, 1536, 16, 1): ((32, 64, 4), (32, 64, 4)),
+    (300, 576, 1152, 8, 0): ((32, 64, 4), (32, 64, 4)),
+    (300, 1152, 576, 16, 0): ((32, 64, 4), (32, 64, 4)),
+    (2050, 192, 772, 5, 0): ((64, 64, 2), (64, 64, 0)),
+    (2100, 384, 1984, 3, 0): ((64, 64, 2), (64, 64, 4)),
+    (4100, 256, 1988, 2, 0): ((128, 128, 2), (64, 64, 0)),
+}
+
+
+@pytest.mark.parametrize("huge", [False, True])
+@pytest.mark.parametrize("T,n_in,n_out,r,off", list(FP32_SPLIT))
+def test_fp32_split_products(T, n_in, n_out, r, off, huge):
+    import torch
+    c = synth.make_single_layer(T, n_in, n_out, r, seed=31 + T, bias=True)
+    if huge:                                             # (3.39e38 and above have no bf16 neighbour but infinity)
+        for k in ("W", "A", "B"):
+            c[k] = c[k] * np.float32(1e-3)
+        c["x"][T // 2, 3] = c["dy"][T // 3, 5] = np.float32(3.4e38)
+    flat = torch.empty(r * n_in + off, dtype=torch.float32, device="cuda")
+    A = flat[off:].view(r, n_in)
+    A.copy_(torch.from_numpy(c["A"]))
+    x, W, dy, bias, Bm = (torch.from_numpy(c[k]).cuda() for k in ("x", "W", "dy", "b", "B"))
+    nws = B.slora_lora_linear_ws_bytes(B.DTYPE_F32, T, n_in, n_out, r)
+    ws = torch.empty(nws, dtype=torch.uint8, device="cuda")
+    y, dx, dA, dB = (torch.empty(s, dtype=torch.float32, device="cuda") for s in ((T, n_out), (T, n_in), (r, n_in), (n_out, r)))
+    say("fp32 split", T, n_in, n_out, r, off, huge)
+    B.slora_lora_linear_fwd(B.DTYPE_F32, T, n_in, n_out, r, c["alpha"], x, W, bias, A, Bm, y, ws, nws)
+    B.slora_lora_linear_bwd(B.DTYPE_F32, T, n_in, n_out, r, c["alpha"], x, dy, W, A, Bm, dx, dA, dB, ws, nws)
+    torch.cuda.synchronize()
+    # element by element: no more roundings of half an ulp (of the sum of magnitudes) than 6 sums for 32 products, each
+    # with up to 3 more inside the instruction, and 32 for the pieces left out, the low-rank term, the bias and the waves
+    a = {k: np.abs(c[k].astype(np.float64)) for k in ("x", "dy", "W", "A", "B")}
+    s = c["alpha"] / c["r"]
+    size = [a["x"] @ a["W"].T + np.abs(c["b"]) + s * (a["x"] @ a["A"].T) @ a["B"].T, a["dy"] @ a["W"] + s * (a["dy"] @ a["B"]) @ a["A"],
+            s * (a["dy"] @ a["B"]).T @ a["x"], s * a["dy"].T @ (a["x"] @ a["A"].T)]
+    sums = [24 * n_in / 32, 24 * n_out / 32, 24 * n_out / 32 + T, 24 * n_in / 32 + T]
+    for name, got, ref, m, n in zip(("y", "dx", "dA", "dB"), (y, dx, dA, dB), _oracle(c), size, sums):
+        got = got.cpu().numpy().astype(np.float64)
+        assert np.isfinite(got).all(), name
+        assert (np.abs(got - ref) <= (n + 32) * 2.0 ** -24 * m).all(), (name, np.max(np.abs(got - ref) / m) * 2 ** 24)
+
+
 def test_fp32_zero_B_is_bitwise_base():
     import torch
     c = synth.make_single_layer(300, 128, 192, 4, seed=11)

@@ -273,6 +273,42 @@ def test_fp32_ring_copies_and_scalars():
     _check_valu_sgpr_to_vmem(text, "f32_linear.hip")
 
 
+_VGPR = re.compile(r"\bv(\d+)\b|\bv\[(\d+):(\d+)\]")
+
+
+def _vgprs(text):
+    regs = set()
+    for m in _VGPR.finditer(text):
+        regs.update([int(m.group(1))] if m.group(1) is not None else range(int(m.group(2)), int(m.group(3)) + 1))
+    return regs
+
+
+def _conversions_too_close(body):
+    """(conversion, MFMA) pairs of which the second reads what the first wrote fewer than 2 wait states earlier"""
+    code = [ins for ins in body if not _is_label(ins)]
+    found = []
+    for i, ins in enumerate(code):
+        if not ins.startswith("v_mfma"):
+            continue
+        used, ws, j = _vgprs(ins.split(",", 1)[1]), 0, i - 1
+        while j >= 0 and ws < 2:
+            if code[j].startswith("v_cvt_pk_bf16_f32") and _vgprs(code[j].split(",")[0]) & used:
+                found.append((code[j], ins))
+            ws += _wait_states(code[j])
+            j -= 1
+    return found
+
+
+def test_fp32_pieces_are_settled_before_the_products():
+    """the conversions are inline assembly, whose results the compiler keeps no distance to"""
+    funcs = {n: b for n, b in _functions(_assembly("f32_linear.hip")).items() if "f32_tile_kernel" in n}
+    assert all(sum(x.startswith("v_cvt_pk_bf16_f32") for x in b) >= 60 for b in funcs.values())
+    for name, body in funcs.items():
+        assert not _conversions_too_close(body), (name, _conversions_too_close(body)[:2])
+    bad = ["v_cvt_pk_bf16_f32 v5, v1, v2", "s_mov_b32 s1, s2", "v_mfma_f32_16x16x32_bf16 v[8:11], v[4:7], v[0:3], v[8:11]"]
+    assert _conversions_too_close(bad) and not _conversions_too_close(bad[:1] + ["s_nop 1"] + bad[2:])
+
+
 def _loops(body):
     """[instructions] of every loop without a label inside (a label, its body, a branch back to it)"""
     loops = []

@@ -25,6 +25,11 @@ def test_fp32_ring_forms():
         assert tuple(plans.f32_layer(*case)) == want, case
 
 
+def test_fp32_split_forms():
+    for (T, n_in, n_out, _, _), want in linear.FP32_SPLIT.items():
+        assert tuple(plans.f32_layer(T, n_in, n_out)) == want, (T, n_in, n_out)
+
+
 def test_bf16_forms():
     for (T, n_in, n_out), want in linear.FROZEN_FORMS.items():
         assert plans.tile(T, n_out, n_in) == (want, 1), (T, n_in, n_out)
