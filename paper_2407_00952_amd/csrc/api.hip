@@ -374,7 +374,7 @@ int lora_grads(slora_ctx *c, int l, int p, const bf16 *x, int ldx, const bf16 *d
     float *part = at<float>(c, c->t_part);
     // dA [r,in] = ps^T x and dB [out,r] = dy^T zs, one launch for the two
     const LoraGradDesc jobs[2] = {
-        {x, ps, part, ab.dA, nullptr, ldx, ldps, n_in, false, 1},
+        {x, ps, part, ab.dA, nullptr, ldx, ldps, n_in, false, 1, 0},
         {dy, at<bf16>(c, c->bw[l].zs[p]), part + lora_grad_partial_floats(c->maxT, n_in), ab.dB, nullptr, ldy_, SL_RP, n_out,
          false, 0}};
     return launch_lora_grad_jobs(jobs, 2, c->r, c->T, st);
@@ -1052,8 +1052,8 @@ int slora_lora_linear_bwd(int dtype, int T, int n_in, int n_out, int r, float al
     if ((rc = launch_layer_front(f, st))) return rc;
     if ((rc = launch_gemm(a, EPI_STORE, 16, st))) return rc;
     const LoraGradDesc jobs[2] = {
-        {(const bf16 *)x, (bf16 *)(base + w.ps), (float *)(base + w.part_a), dA, nullptr, n_in, 16, n_in, false, 1},
-        {(const bf16 *)dy, (bf16 *)(base + w.zs), (float *)(base + w.part_b), dB, nullptr, n_out, 16, n_out, false, 0}};
+        {(const bf16 *)x, (bf16 *)(base + w.ps), (float *)(base + w.part_a), dA, nullptr, n_in, 16, n_in, false, 1, 0},
+        {(const bf16 *)dy, (bf16 *)(base + w.zs), (float *)(base + w.part_b), dB, nullptr, n_out, 16, n_out, false, 0, 0}};
     return launch_lora_grad_jobs(jobs, 2, r, T, st, w.long_chunks);
 }
 

@@ -159,8 +159,22 @@ struct LoraGradDesc {
     float *partials;                 // lora_grad_partial_floats(T, C) floats
     float *out_a, *out_b;            // out_b: the second adapter of a dual job, else null
     int ldx, ldy, C; bool dual; int out_is_rxC;
+    int summed_rows;                 // tokens of each chunk of partial sums that is there already (launch_rank_grad), or 0
 };
 int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStream_t st, bool long_chunks = false);
+// One pass over the gradient X [T,C] of an adapted projection's output: its rank-space gradient and the partial sums of
+// dB; C a multiple of 256 (chunks of rank_grad_rows(r) tokens, [chunk][r][C] floats), optionally X's MXFP8 codes and scales; up to three in one launch
+struct RankGradDesc {
+    const bf16 *X; int ldx, C;       // [T,C] (pitch ldx)
+    const bf16 *Z; int ldz;          // [16,C]: B transposed, rows past the rank zero
+    const bf16 *zs;                  // [T,16]: the forward's rank-space activations
+    bf16 *ps; int ldp;               // [T,16] = s X Z^T (pitch ldp)
+    float *partials;
+    unsigned char *codes, *scales;   // [T,C], [T,C/32], or null
+};
+int rank_grad_rows(int r);
+bool rank_grad_fills(int T, int njobs, int r);           // whether that launch has a block for most CUs
+int launch_rank_grad(const RankGradDesc *d, int njobs, int r, float s, int T, hipStream_t st);
 int launch_fedavg(int K, const float *const *x, const float *w, size_t n, float *out, hipStream_t st);
 int launch_sgd(float *p, const float *g, float lr, size_t n, hipStream_t st);
 int launch_adamw(float *p, const float *g, float *m, float *v, size_t n, float b1, float b2, float eps, float decay,

@@ -71,6 +71,7 @@ struct LoraGradJob {
     float *partials;                 // this job's chunk partial sums
     float *out_a, *out_b;            // result(s); out_b only for a dual job
     int ldx, ldy, C, dual, out_is_rxC;
+    int nchunk;                      // chunks of partial sums
 };
 constexpr int LG_MAX_JOBS = 6;
 struct LoraGradJobs { LoraGradJob j[LG_MAX_JOBS]; };
@@ -197,12 +198,12 @@ __global__ __launch_bounds__(256) void lora_grad_partial_kernel(LoraGradJobs job
 // out[j, c] = sum over chunks, in a fixed order: each of the 4 wavefronts of a block sums a
 // contiguous quarter of the chunks in increasing order, then the four are added in order.
 // With a second output, rows r..2r-1 of every chunk belong to it (two adapters reduced in one launch).
-__global__ __launch_bounds__(256) void lora_grad_reduce_kernel(LoraGradJobs jobs, int nchunk, int r)
+__global__ __launch_bounds__(256) void lora_grad_reduce_kernel(LoraGradJobs jobs, int r)
 {
     __shared__ float red[3][64];
     const LoraGradJob &jb = jobs.j[blockIdx.z];
     const float *__restrict__ partials = jb.partials;
-    const int C = jb.C, out_is_rxC = jb.out_is_rxC;
+    const int C = jb.C, out_is_rxC = jb.out_is_rxC, nchunk = jb.nchunk;
     float *__restrict__ out = jb.out_a;
     float *__restrict__ out_second = jb.dual ? jb.out_b : nullptr;
     if ((int)blockIdx.x * 64 >= (jb.dual ? 2 * r : r) * C) return;      // (uniform: before the barrier)
@@ -440,26 +441,33 @@ int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStr
 {
     if (njobs < 1 || njobs > LG_MAX_JOBS || T <= 0 || r < 1 || r > 16) return SL_EINVAL;
     LoraGradJobs jobs;
-    int max_c = 0, max_red = 0;
+    int max_c = 0, widest = 0, max_red = 0;                // (the scratch was sized for chunks by the widest of all jobs)
+    int todo = 0;                    // jobs whose partial sums are not there yet; they come first
     double bytes = 0.0;
     for (int k = 0; k < njobs; ++k) {
         const LoraGradDesc &q = d[k];
         if (!q.X || !q.Y || !q.partials || !q.out_a || (q.dual && !q.out_b)) return SL_EINVAL;
         if (q.C <= 0 || (q.C % 64) || (q.ldx % 8) || (q.ldy % 8) || (q.dual && q.ldy < 32)) return SL_EINVAL;
-        jobs.j[k] = {q.X, q.Y, q.partials, q.out_a, q.out_b, q.ldx, q.ldy, q.C, q.dual ? 1 : 0, q.out_is_rxC};
-        max_c = q.C > max_c ? q.C : max_c;
+        jobs.j[k] = {q.X, q.Y, q.partials, q.out_a, q.out_b, q.ldx, q.ldy, q.C, q.dual ? 1 : 0, q.out_is_rxC, 0};
+        if (q.summed_rows == 0) {
+            if (todo++ != k) return SL_EINVAL;
+            max_c = q.C > max_c ? q.C : max_c;
+        }
+        widest = q.C > widest ? q.C : widest;
         const int red = (q.dual ? 2 * r : r) * q.C;
         max_red = red > max_red ? red : max_red;
-        bytes += 2.0 * T * (double)q.C;                  // the streaming pass: the tall operand once
+        if (q.summed_rows == 0) bytes += 2.0 * T * (double)q.C;          // the streaming pass: the tall operand once
     }
-    const int rows = long_chunks ? GR_ROWS : grad_rows(T, max_c), nchunk = (T + rows - 1) / rows;
+    const int rows = long_chunks ? GR_ROWS : grad_rows(T, widest), nchunk = (T + rows - 1) / rows;
+    if (todo == 0 || (todo < njobs && nchunk == 1)) return SL_EINVAL;    // (a single chunk is written as the result)
+    for (int k = 0; k < njobs; ++k) jobs.j[k].nchunk = k < todo ? nchunk : (T + d[k].summed_rows - 1) / d[k].summed_rows;
     const bool rec = prof_begin(PK_LORA_GRAD, st);
-    hipLaunchKernelGGL(lora_grad_partial_kernel, dim3((max_c + GR_COLS - 1) / GR_COLS, nchunk, njobs), dim3(256), 0, st,
+    hipLaunchKernelGGL(lora_grad_partial_kernel, dim3((max_c + GR_COLS - 1) / GR_COLS, nchunk, todo), dim3(256), 0, st,
                        jobs, r, T, rows);
     prof_end(rec, PK_LORA_GRAD, bytes, st);
     SL_CHECK_LAUNCH("lora_grad_partial");
     if (nchunk == 1) return 0;                           // (one record of 128 tokens: 3.3 us of its 104 a block)
-    hipLaunchKernelGGL(lora_grad_reduce_kernel, dim3((max_red + 63) / 64, 1, njobs), dim3(256), 0, st, jobs, nchunk, r);
+    hipLaunchKernelGGL(lora_grad_reduce_kernel, dim3((max_red + 63) / 64, 1, njobs), dim3(256), 0, st, jobs, r);
     SL_CHECK_LAUNCH("lora_grad_reduce");
     return 0;
 }

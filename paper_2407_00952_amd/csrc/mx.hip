@@ -742,14 +742,22 @@ int slora_mx_lora_linear_bwd(int32_t T, int32_t n_in, int32_t n_out, int32_t r, 
     f.T = T; f.n_in = n_in; f.n_out = n_out; f.r = r;
     f.project_blocks = (T + 15) / 16;
     if ((rc = launch_layer_front(f, st))) return rc;
-    if ((rc = launch_quantize_project((const bf16 *)dy, T, n_out, base + w.q, base + w.qs, (const bf16 *)(base + w.B16T), s,
-                                      (bf16 *)(base + w.ps), st)))
+    // one pass over dy for its codes, ps and the partial sums of dB, where they fit the scratch (rank up to 8) and there are
+    // blocks enough
+    const bool one_pass = r <= 8 && n_out % 256 == 0 && rank_grad_fills(T, 1, r);
+    if (one_pass) {
+        const RankGradDesc g = {(const bf16 *)dy, n_out, n_out, (const bf16 *)(base + w.B16T), n_out, (const bf16 *)(base + w.zs),
+                                (bf16 *)(base + w.ps), 16, (float *)(base + w.part_b), base + w.q, base + w.qs};
+        if ((rc = launch_rank_grad(&g, 1, r, s, T, st))) return rc;
+    } else if ((rc = launch_quantize_project((const bf16 *)dy, T, n_out, base + w.q, base + w.qs, (const bf16 *)(base + w.B16T), s,
+                                             (bf16 *)(base + w.ps), st)))
         return rc;
     MxArgs a = mx_plain(base + w.q, base + w.qs, pw + p.tq, pw + p.ts, nullptr, dx, T, n_in, n_out);
     a.zs[0] = (const bf16 *)(base + w.ps); a.tmat[0] = (const bf16 *)(base + w.A32T);
     if ((rc = launch_gemm_mx(a, st))) return rc;
     const LoraGradDesc jobs[2] = {
-        {(const bf16 *)x, (bf16 *)(base + w.ps), (float *)(base + w.part_a), dA, nullptr, n_in, 16, n_in, false, 1},
-        {(const bf16 *)dy, (bf16 *)(base + w.zs), (float *)(base + w.part_b), dB, nullptr, n_out, 16, n_out, false, 0}};
+        {(const bf16 *)x, (bf16 *)(base + w.ps), (float *)(base + w.part_a), dA, nullptr, n_in, 16, n_in, false, 1, 0},
+        {(const bf16 *)dy, (bf16 *)(base + w.zs), (float *)(base + w.part_b), dB, nullptr, n_out, 16, n_out, false, 0,
+         one_pass ? rank_grad_rows(r) : 0}};
     return launch_lora_grad_jobs(jobs, 2, r, T, st);
 }

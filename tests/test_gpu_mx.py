@@ -269,6 +269,13 @@ def test_lora_linear_mxfp8(T, n_in, n_out, r, with_bias):
     assert relerr(y0, yo) > 4 * BF16_TOL
 
 
+# dy's codes, rank-space gradients and dB in one pass: blocks of 128 tokens (rank up to 4) and of 256, the last one ragged, one slab
+# of 256 columns and two; 28600 tokens (224 blocks, the last of 56 tokens) are the fewest of rank 3 that take it, 28544 do not.
+@pytest.mark.parametrize("T,n_in,n_out,r", [(28600, 128, 512, 3), (28544, 128, 256, 4), (57200, 128, 256, 8)])
+def test_lora_linear_mxfp8_one_pass(T, n_in, n_out, r):
+    test_lora_linear_mxfp8(T, n_in, n_out, r, False)
+
+
 @pytest.mark.parametrize("ctx_type,d_model,n_head,d_ff", [("bf16", 320, 5, 704), ("mxfp8", 384, 6, 640)])
 def test_server_round_with_compressed_cut_traffic(ctx_type, d_model, n_head, d_ff):
     """slora_server_fwd_mx / slora_server_bwd_mx: the clients' activations arrive as MXFP8 and their gradients

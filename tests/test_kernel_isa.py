@@ -332,6 +332,18 @@ def test_fp32_adapter_gradient_rows_are_in_flight_together():
         assert sum(i < next(j for j, x in enumerate(lp) if "vmcnt" in x) for i in ld) >= first
 
 
+def test_rank_gradient_pass_copies_and_stores():
+    """copies and scalars as elsewhere; and each unit of 64 tokens stores codes and scales as often as its wait allows for: 4
+    of either where all rows are tokens (and one in the loop for the last block)"""
+    text = _assembly("rank_grad.hip")
+    _check_m0(text, "rank_grad.hip")
+    _check_valu_sgpr_to_vmem(text, "rank_grad.hip")
+    for ht in (1, 2):
+        body = next(b for n, b in _functions(text).items() if "rank_grad_kernelILi%dELb1E" % ht in n)
+        assert sum(x.startswith("global_store_dwordx2") for x in body) == 2 * ht * 5
+        assert sum(x.startswith("global_store_byte") for x in body) == 2 * ht * 5
+
+
 def test_attention_copies_and_scalars():
     text = _assembly("attention.hip")
     funcs = _functions(text)
