@@ -365,8 +365,20 @@ inline void set_mx(const slora_ctx *c, int l, int which, GemmArgs &a, MxOperands
 inline unsigned char *qa(const slora_ctx *c) { return c->mx ? at<unsigned char>(c, c->t_qa) : nullptr; }
 inline unsigned char *qas(const slora_ctx *c) { return c->mx ? at<unsigned char>(c, c->t_qas) : nullptr; }
 
+// Whether the rank-space gradients of an input-gradient product are formed by a pass of their own over its operand, together with
+// dB (launch_rank_grad), and follow the product's main loop instead of running in it: where the product runs on 256 x 256 tiles
+// and the pass has blocks enough (njobs adapters).  us at 32768 rows, main loop with the branch and without: 4096 -> 1024 229, 193;
+// 3072 -> 1024 with 48 columns 207, 156; 1024 -> 4096 with the saved GELU' 331, 273.
+bool one_pass(const slora_ctx *c, const GemmArgs &a, int epi, int nz, int njobs)
+{
+    if (c->mx || nz == 0 || (a.K % 256) || !rank_grad_fills(c->T, njobs, c->r)) return false;
+    const TilePlan p = plan_gemm_tile(a.M, a.seg_n, a.nseg, a.K, epi, nz, false, true);
+    return p.tm == 256 && p.tn == 256;
+}
+
+// summed: dB's partial sums are there already (launch_rank_grad)
 int lora_grads(slora_ctx *c, int l, int p, const bf16 *x, int ldx, const bf16 *dy, int ldy_, const bf16 *ps, int ldps,
-               hipStream_t st)
+               bool summed, hipStream_t st)
 {
     int n_in, n_out, rc;
     proj_shape(c, p, n_in, n_out);
@@ -376,8 +388,19 @@ int lora_grads(slora_ctx *c, int l, int p, const bf16 *x, int ldx, const bf16 *d
     const LoraGradDesc jobs[2] = {
         {x, ps, part, ab.dA, nullptr, ldx, ldps, n_in, false, 1, 0},
         {dy, at<bf16>(c, c->bw[l].zs[p]), part + lora_grad_partial_floats(c->maxT, n_in), ab.dB, nullptr, ldy_, SL_RP, n_out,
-         false, 0}};
+         false, 0, summed ? rank_grad_rows(c->r) : 0}};
     return launch_lora_grad_jobs(jobs, 2, c->r, c->T, st);
+}
+
+// One adapter's share of the pass before its product `a` (whose operand is dy and whose rank-space gradients become a.zspill[0])
+int rank_grad(slora_ctx *c, int l, int p, GemmArgs &a, hipStream_t st)
+{
+    int n_in, n_out;
+    proj_shape(c, p, n_in, n_out);
+    const RankGradDesc g = {a.X, a.ldx, n_out, a.zmat[0], a.ldz, at<bf16>(c, c->bw[l].zs[p]), a.zspill[0], a.K2,
+                            at<float>(c, c->t_part) + lora_grad_partial_floats(c->maxT, n_in), nullptr, nullptr};
+    a.z_ready = true;
+    return launch_rank_grad(&g, 1, c->r, c->s, c->T, st);
 }
 
 }  // namespace
@@ -690,8 +713,10 @@ static int stack_bwd(slora_ctx *c, const void *dy, const ClientTable *tabp, hipS
             MxOperands mxo;
             set_mx(c, l, MXW_PRT, a, mxo, 1);
             if (c->mx) { a.oq = at<unsigned char>(c, c->t_qb); a.os = at<unsigned char>(c, c->t_qbs); }   // codes of df
+            const bool pass = one_pass(c, a, EPI_DGELU, ad ? 16 : 0, 1);
+            if (pass && (rc = rank_grad(c, l, SLORA_PROJ_PR, a, st))) return rc;
             if ((rc = launch_gemm(a, EPI_DGELU, ad ? 16 : 0, st))) return rc;
-            if (ad && (rc = lora_grads(c, l, SLORA_PROJ_PR, at<bf16>(c, b.g), dff, dh2_16, d, ps, SL_RP, st)))
+            if (ad && (rc = lora_grads(c, l, SLORA_PROJ_PR, at<bf16>(c, b.g), dff, dh2_16, d, ps, SL_RP, pass, st)))
                 return rc;
         }
         // du2 = df Wfc (+ adapter)
@@ -706,8 +731,10 @@ static int stack_bwd(slora_ctx *c, const void *dy, const ClientTable *tabp, hipS
             }
             MxOperands mxo;
             set_mx(c, l, MXW_FCT, a, mxo, 2);
+            const bool pass = one_pass(c, a, EPI_STORE, ad ? 16 : 0, 1);
+            if (pass && (rc = rank_grad(c, l, SLORA_PROJ_FC, a, st))) return rc;
             if ((rc = launch_gemm(a, EPI_STORE, ad ? 16 : 0, st))) return rc;
-            if (ad && (rc = lora_grads(c, l, SLORA_PROJ_FC, at<bf16>(c, b.u2), d, df, dff, ps, SL_RP, st))) return rc;
+            if (ad && (rc = lora_grads(c, l, SLORA_PROJ_FC, at<bf16>(c, b.u2), d, df, dff, ps, SL_RP, pass, st))) return rc;
         }
         // dh' = dh'' + LN2^T(du2)
         float *dh1_32 = at<float>(c, c->t_dh32[1]);
@@ -734,8 +761,10 @@ static int stack_bwd(slora_ctx *c, const void *dy, const ClientTable *tabp, hipS
             if (gemm_delta) {
                 a.dl_o = at<bf16>(c, b.o); a.dl_lo = at<bf16>(c, b.o_lo); a.dl_out = at<float>(c, c->t_delta);
             }
+            const bool pass = one_pass(c, a, EPI_STORE, ad ? 16 : 0, 1);
+            if (pass && (rc = rank_grad(c, l, SLORA_PROJ_O, a, st))) return rc;
             if ((rc = launch_gemm(a, gemm_delta ? EPI_STORE_DELTA : EPI_STORE, ad ? 16 : 0, st))) return rc;
-            if (ad && (rc = lora_grads(c, l, SLORA_PROJ_O, at<bf16>(c, b.o), d, dh1_16, d, ps, SL_RP, st))) return rc;
+            if (ad && (rc = lora_grads(c, l, SLORA_PROJ_O, at<bf16>(c, b.o), d, dh1_16, d, ps, SL_RP, pass, st))) return rc;
         }
         // attention backward
         bf16 *dqkv = at<bf16>(c, c->t_dqkv);
@@ -753,30 +782,42 @@ static int stack_bwd(slora_ctx *c, const void *dy, const ClientTable *tabp, hipS
             }
             MxOperands mxo;
             set_mx(c, l, MXW_QKVT, a, mxo);
+            const size_t part_stride = lora_grad_partial_floats(c->maxT, d);
+            float *part = at<float>(c, c->t_part);
+            const int n_da = (c->n_qkv + 1) / 2;         // jobs of dA, in front of those of dB
+            // (one slice of dq|dk|dv per adapter, with its rows and columns of the block-diagonal operand; d a multiple of 256)
+            const bool pass = d % 256 == 0 && one_pass(c, a, EPI_STORE, c->n_qkv ? c->nz_qkv : 0, c->n_qkv);
+            if (pass) {
+                RankGradDesc g[3];
+                for (int p = 0; p < 3; ++p)
+                    if (adapted(c, p)) {
+                        const int i = c->qkv_idx[p];
+                        g[i] = {dqkv + (size_t)p * d, 3 * d, d, at<bf16>(c, b.bz_qkv) + (size_t)16 * i * 3 * d + (size_t)p * d, 3 * d,
+                                at<bf16>(c, b.zs[p]), ps + 16 * i, c->k2_qkv, part + (n_da + i) * part_stride, nullptr, nullptr};
+                    }
+                if ((rc = launch_rank_grad(g, c->n_qkv, c->r, c->s, T, st))) return rc;
+                a.z_ready = true;
+            }
             if ((rc = launch_gemm(a, EPI_STORE, c->n_qkv ? c->nz_qkv : 0, st))) return rc;
             // dB per adapted projection (its own slice of dq|dk|dv against its own zs); dA for the adapters
             // two at a time: they share the operand u, and their rank-space gradients sit side by side in ps.
             // All of them go out as one launch (each with partial-sum scratch of its own).
             if (c->n_qkv) {
-                const size_t part_stride = lora_grad_partial_floats(c->maxT, d);
-                float *part = at<float>(c, c->t_part);
                 LoraGradDesc jobs[5];
-                int nj = 0, slot_proj[3], nslot = 0;
+                int slot_proj[3];
                 for (int p = 0; p < 3; ++p)
                     if (adapted(c, p)) {
-                        slot_proj[c->qkv_idx[p]] = p;
-                        ++nslot;
-                        jobs[nj] = {dqkv + (size_t)p * d, at<bf16>(c, b.zs[p]), part + nj * part_stride,
-                                    c->adapters[l][p].dB, nullptr, 3 * d, SL_RP, d, false, 0};
-                        ++nj;
+                        const int i = c->qkv_idx[p];
+                        slot_proj[i] = p;
+                        jobs[n_da + i] = {dqkv + (size_t)p * d, at<bf16>(c, b.zs[p]), part + (n_da + i) * part_stride,
+                                          c->adapters[l][p].dB, nullptr, 3 * d, SL_RP, d, false, 0, pass ? rank_grad_rows(c->r) : 0};
                     }
-                for (int sl = 0; sl < nslot; sl += 2) {
-                    const bool pair = sl + 1 < nslot;
-                    jobs[nj] = {at<bf16>(c, b.u), ps + 16 * sl, part + nj * part_stride, c->adapters[l][slot_proj[sl]].dA,
-                                pair ? c->adapters[l][slot_proj[sl + 1]].dA : nullptr, d, c->k2_qkv, d, pair, 1};
-                    ++nj;
+                for (int j = 0; j < n_da; ++j) {
+                    const bool pair = 2 * j + 1 < c->n_qkv;
+                    jobs[j] = {at<bf16>(c, b.u), ps + 32 * j, part + j * part_stride, c->adapters[l][slot_proj[2 * j]].dA,
+                               pair ? c->adapters[l][slot_proj[2 * j + 1]].dA : nullptr, d, c->k2_qkv, d, pair, 1, 0};
                 }
-                if ((rc = launch_lora_grad_jobs(jobs, nj, c->r, T, st))) return rc;
+                if ((rc = launch_lora_grad_jobs(jobs, n_da + c->n_qkv, c->r, T, st))) return rc;
             }
         }
         // dh = dh' + LN1^T(du): next block's incoming gradient, or the clients' activation gradients

@@ -94,6 +94,7 @@ struct GemmArgs {
     const bf16 *tmat[3]; int ldt;    // [seg_n,ldt]: up-projection, ldt = NZ rounded up to 32, zero beyond the rank
     bf16 *zspill[3];                 // [M,K2] or null: scaled bf16 copy of the rank-space activations
     int K2; float zscale;            // K2 = NZ
+    bool z_ready;                    // zspill holds the rank-space activations already (a kernel may form them again: same bits)
     // epilogue
     void *out0; void *out1; const void *aux; int ldo;
     const bf16 *dl_o, *dl_lo; float *dl_out;   // EPI_STORE_DELTA: the two bf16 terms of O [M,ldo], delta [M,N/64] fp32

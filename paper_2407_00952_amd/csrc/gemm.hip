@@ -329,9 +329,12 @@ constexpr int NTHR4 = 256, HB = 32768;       // HB: one operand's k-slab (256 ro
 // tile 64 x 128) for launches that have fewer 256-row tiles than the chip has CUs.
 // COUNTED: the number of rows, and (EPI_PARTIAL) over how many blocks a tile's contraction is shared, are read from
 // device memory (a.rows); share s of a tile leaves its fp32 sums in the s-th [rows, ldo] block of out0.
-template <int EPI, int NI, bool COUNTED>
+// TAIL: a rank-space branch whose activations are there (a.zspill): its one or two k-steps of 32 follow the main loop, on operands
+// read straight into fragments while the last two slabs are multiplied.
+template <int EPI, int NI, bool COUNTED, bool TAIL = false>
 __device__ __forceinline__ void gemm4_body(GemmArgs a)
 {
+    static_assert(!TAIL || NI == 8, "the tail is for 256 x 256 tiles");
     constexpr int BM4 = 32 * NI;                         // rows of a block tile
     constexpr bool SHARED = EPI == EPI_PARTIAL;
     // Spacing, in MFMAs of a k-step, of the fragment reads and of the copies, and how many of the X copies of a slab go out
@@ -379,7 +382,7 @@ __device__ __forceinline__ void gemm4_body(GemmArgs a)
     // the epilogue's staging strips live in the third X buffer, the one the next tile's early copies leave alone
     float *stg = (float *)(ring + 2 * HB + wave * (16 * EP4 * 4));
 
-    int m0, n0, n_end, share = 0;
+    int m0, n0, n_end, share = 0, zseg = 0;
     float *const part0 = (float *)a.out0;
     unsigned xo[8], wo[8];
     // tile `t` of the panel walk: its origin, and this wave's copy offsets (every wave copies a quarter of the
@@ -404,6 +407,7 @@ __device__ __forceinline__ void gemm4_body(GemmArgs a)
         const int prow = min(PANEL, tiles_m - pidx * PANEL);                                           \
         const int tn = prem / prow, tm = pidx * PANEL + prem - tn * prow;                              \
         const int seg = tn / tiles_n_seg, tns = tn % tiles_n_seg;                                      \
+        zseg = seg;                                                                                    \
         n0 = seg * a.seg_n + tns * BN;                                                                 \
         n_end = (seg + 1) * a.seg_n;                                                                   \
         m0 = tm * BM4;                                                                                 \
@@ -467,7 +471,27 @@ __device__ __forceinline__ void gemm4_body(GemmArgs a)
         int xcur = 0, wcur = 3 * HB;                     // buffers of the slab being computed
 #pragma unroll
         for (int i = 0; i < 8; ++i) { G4_LDB(0, i, 3 * HB, 0) if (i < NI) { G4_LDA(0, i & (NI - 1), 0, 0) } }
+        // rows of z and of the up-projection: k-step ks of the tail
+        bf16x8 za[TAIL ? 8 : 1], tb[TAIL ? 8 : 1];
+        auto tail_operands = [&](int ks) {
+            const char *zp = (const char *)a.zspill[zseg], *tp = (const char *)a.tmat[zseg];
+            int lane_ = lane;
+            asm volatile("" : "+v"(lane_));              // (else 16 addresses are held in registers through the loop)
+            const int r_ = lane_ & 15, k_ = ks * 32 + (lane_ >> 4) * 8;
+            const bool zok = k_ < a.K2;                  // columns past K2 count as zero
+#pragma unroll
+            for (int i = 0; i < (TAIL ? 8 : 0); ++i) {
+                const int row = min(m0 + wm * 128 + i * 16 + r_, a.M - 1), n = min(n0 + wn * 128 + i * 16 + r_, n_end - 1) - zseg * a.seg_n;
+                za[i] = *(const bf16x8 *)(zp + ((unsigned)row * (unsigned)a.K2 + (zok ? k_ : 0)) * 2u);
+                tb[i] = *(const bf16x8 *)(tp + ((unsigned)n * (unsigned)a.ldt + k_) * 2u);
+            }
+        };
+        const bool has_z = TAIL && a.zmat[zseg] != nullptr;
+        const int kt_tail = max(nk - 2, 0);
         for (int kt = 0;; ++kt) {                        // nk >= 1 (checked by the launcher)
+            if (TAIL) {
+                if (has_z && kt == kt_tail) tail_operands(0);
+            }
             const int xnxt = xcur == 2 * HB ? 0 : xcur + HB, wnxt = wcur ^ (3 * HB ^ 4 * HB);
             const int c2 = min((kt + 2) * BK, klast), c3 = min((kt + 3) * BK, klast);
             const char *x2 = Xb + (size_t)c2 * 2, *w2 = Wb + (size_t)c2 * 2, *x3 = Xb + (size_t)c3 * 2;
@@ -490,6 +514,27 @@ __device__ __forceinline__ void gemm4_body(GemmArgs a)
         // all copies have landed and every wave is out of the loop before the ring is reused
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __syncthreads();
+        if (TAIL) {
+            if (has_z) {
+                for (int ks = 0;;) {
+                    if (ks * 32 + kg * 8 >= a.K2) {
+#pragma unroll
+                        for (int i = 0; i < (TAIL ? 8 : 0); ++i)
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) za[i][e] = f2bf(0.f);
+                    }
+                    asm volatile("s_nop 1" ::: "memory");                    // (a vector write, then an MFMA the compiler does not see)
+#pragma unroll
+                    for (int i = 0; i < NI; ++i)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j)
+                            asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(za[TAIL ? i : 0]), "v"(tb[TAIL ? j : 0]));
+                    if (++ks * 32 >= a.K2) break;
+                    tail_operands(ks);
+                }
+                asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");          // (as behind the main loop)
+            }
+        }
         // the next tile's first four half stages are requested now and arrive under this tile's epilogue
         const int em0 = m0, en0 = n0, en_end = n_end;
         if constexpr (SHARED) a.out0 = part0 + (size_t)share * a.M * a.ldo;
@@ -534,6 +579,21 @@ __global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 }
 
 template <int EPI>
+__global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_tail4(GemmArgs a)
+{
+    gemm4_body<EPI, 8, false, true>(a);
+}
+
+template <int EPI>
+int launch_tail4(const GemmArgs &a, hipStream_t st)
+{
+    const int nb = ((a.M + 255) / 256) * ((a.seg_n + BN - 1) / BN) * a.nseg;
+    hipLaunchKernelGGL(gemm_tail4<EPI>, dim3(std::min(((nb + 7) / 8) * 8, 256)), dim3(NTHR4), 0, st, a);
+    SL_CHECK_LAUNCH("gemm");
+    return 0;
+}
+
+template <int EPI>
 int launch_t4(const GemmArgs &a, int rows, hipStream_t st)
 {
     const int nb = ((a.M + rows - 1) / rows) * ((a.seg_n + BN - 1) / BN) * a.nseg;
@@ -559,6 +619,9 @@ int launch_t(const GemmArgs &a, hipStream_t st)
 template <int EPI>
 int launch_e(const GemmArgs &a, int nz, int rows, hipStream_t st)
 {
+    if constexpr (EPI == EPI_STORE || EPI == EPI_DGELU) {
+        if (nz > 0 && a.z_ready && rows == 256) return launch_tail4<EPI>(a, st);
+    }
     switch (nz) {
     case 0: return launch_t4<EPI>(a, rows, st);          // no rank-space branch: the 4-wave kernel
     case 16: return launch_t<EPI, 16>(a, st);

@@ -388,6 +388,34 @@ def test_adapter_gradients_in_long_chunks():
     srv.close()
 
 
+# Input-gradient products on 256 x 256 tiles whose rank-space gradients come from a pass of their own with dB (28800 tokens: 225 blocks of
+# 128 for every projection at rank 4; at rank 16, 113 of 256, for q, k and v together) against the same clients one by one (5760
+# tokens), where they are formed in the main loop: the same bits for every sequence, the same products in the gradients' sums.
+@pytest.mark.parametrize("r", [4, 16])
+def test_rank_gradients_ahead_of_the_products(r):
+    cfg = synth.tiny_config(d_model=512, n_head=8, d_ff=1024, n_blocks=2, lora_r=r, lora_proj=synth.PROJ_NAMES,
+                            n_clients=5, batch=90, seq_len=64, seed=synth.BASE_SEED + 170 + r)
+    say("rank gradients ahead:", cfg)
+    inp = _boost_B(synth.make_stack_inputs(cfg), cfg, target=16.0)
+    srv, Y, dX, grads = gpu_round(cfg, inp)
+    sums = [{p: [0.0, 0.0] for p in ad} for ad in grads]
+    at = 0
+    for i, x in enumerate(inp["clients"]):
+        n = x.shape[0]
+        _, y1, dx1, g1 = gpu_round(cfg, inp, clients=[x], dY=inp["dY"][at:at + n], server=srv)
+        assert np.array_equal(y1, Y[at:at + n]) and np.array_equal(dx1[0], dX[i]), i
+        for l, ad in enumerate(g1):
+            for p, (dA, dB) in ad.items():
+                sums[l][p][0] = sums[l][p][0] + dA.astype(np.float64)
+                sums[l][p][1] = sums[l][p][1] + dB.astype(np.float64)
+        at += n
+    srv.close()
+    # fp32 sums of 28800 products, in chunks of 128 to 512 and then over those: the bound of the sums over clients elsewhere
+    worst = max(relerr(g, s) for l, ad in enumerate(grads) for p in ad for g, s in zip(ad[p], sums[l][p]))
+    say("   worst gradient against the clients' sum: %.2e" % worst)
+    assert worst <= 1e-4
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "mxfp8"])
 def test_round_replays_from_a_hip_graph(dtype):
     """Forward + backward + adapter step captured once into a HIP graph and replayed: every replay must

@@ -116,6 +116,28 @@ def test_counted_gemm_mfma_hazards(gemm_asm):
     _check_mfma_hazards(funcs)
 
 
+def test_tail_gemm_mfma_hazards(gemm_asm):
+    """the main loop of gemm_kernel4 and the rank-space tail behind it: MFMAs in place, nothing else on an accumulator inside
+    either, and wait states behind the last of each before anything else reads one"""
+    funcs = {n: b for n, b in _functions(gemm_asm).items() if "gemm_tail4" in n}
+    assert len(funcs) == 2, sorted(funcs)          # plain store, saved GELU'
+    for name, body in funcs.items():
+        mf = [i for i, ins in enumerate(body) if ins.startswith("v_mfma")]
+        assert len(mf) == 3 * 64, (name, len(mf))  # two k-steps of a slab, one of the tail
+        for first, last in ((mf[0], mf[127]), (mf[128], mf[191])):
+            acc = set()
+            for ins in body[first:last + 1]:
+                if ins.startswith("v_mfma"):
+                    m = re.match(r"v_mfma_f32_16x16x32_bf16 a\[(\d+):(\d+)\], v\[\d+:\d+\], v\[\d+:\d+\], a\[(\d+):(\d+)\]$", ins)
+                    assert m and m.group(1, 2) == m.group(3, 4) and int(m.group(1)) % 4 == 0, (name, ins)
+                    acc.add(m.group(1))
+                else:
+                    assert not _agprs(ins), (name, ins)
+            assert len(acc) == 64, name
+            worst, where = _min_wait_states_to_acc_access(body, last)
+            assert worst >= MIN_WAIT_STATES, (name, worst, where)
+
+
 def _check_mfma_hazards(funcs):
     for name, body in funcs.items():
         ni = int(re.search(r"gemm_(?:kernel|counted)4ILi\d+ELi(\d+)E", name).group(1))      # 16-row MFMA tiles per wave along M

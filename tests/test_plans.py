@@ -89,6 +89,12 @@ def test_batches_of_the_wider_stack():
         assert set().union(*(forms(n, 128, proj) for n in (1, 2, 4, 8, 16, 24, 33))) == BF16_FORMS - {(128, 256)}
 
 
+def test_stack_of_the_rank_gradient_pass():
+    """every input gradient of 28800 tokens on 256 x 256 tiles, where the rank-space tail is; of a client's 5760 on others"""
+    for N, K, epi, nz in ((1024, 512, plans.DGELU, 16), (512, 1024, plans.STORE, 16), (512, 512, plans.STORE, 16), (512, 1536, plans.STORE, 48)):
+        assert plans.tile(28800, N, K, epi, nz)[0] == (256, 256) != plans.tile(5760, N, K, epi, nz)[0], (N, K)
+
+
 def test_logits_of_a_loss_head():
     """all rows are computed where 512 tiles of 128 x 128 or fewer hold them, and up to 128 rows; elsewhere they are counted"""
     for (T, d, V), want in head.LOGIT_FORMS.items():
