@@ -195,12 +195,18 @@ __global__ __launch_bounds__(256) void lora_grad_partial_kernel(LoraGradJobs job
     else lora_grad_partial_body<false>(jb.X, jb.ldx, jb.C, jb.Y, jb.ldy, r, T, rows, jb, X0, X1, Y0, Y1);
 }
 
-// out[j, c] = sum over chunks, in a fixed order: each of the 4 wavefronts of a block sums a
-// contiguous quarter of the chunks in increasing order, then the four are added in order.
+// out[j, c] = sum over chunks, in a fixed order: each of the W wavefronts of a block sums a
+// contiguous W-th of the chunks in increasing order, then the W are added in order.
 // With a second output, rows r..2r-1 of every chunk belong to it (two adapters reduced in one launch).
-__global__ __launch_bounds__(256) void lora_grad_reduce_kernel(LoraGradJobs jobs, int r)
+// Bound by round trips (a wave has eight loads in flight) on the one or two hundred blocks that an adapter gives, so 16 waves share
+// the chunks where there are two for each.  us with 4 and 16: 256 and 64 chunks, [1024, 4] each, 8.8, 5.7; 256 and 64, [4096, 4] and
+// [1024, 4], 8.6, 6.6; 256 and 128, [1024..4096, 16], 15.7, 14.2 (35 MB of partial sums: 2.5 TB/s).  With 11 chunks of
+// [3072 + 1024, 8] a launch is 3.9 either way.
+constexpr int GR_MANY = 32;
+template <int W>
+__global__ __launch_bounds__(W * 64) void lora_grad_reduce_kernel(LoraGradJobs jobs, int r)
 {
-    __shared__ float red[3][64];
+    __shared__ float red[W - 1][64];
     const LoraGradJob &jb = jobs.j[blockIdx.z];
     const float *__restrict__ partials = jb.partials;
     const int C = jb.C, out_is_rxC = jb.out_is_rxC, nchunk = jb.nchunk;
@@ -212,7 +218,7 @@ __global__ __launch_bounds__(256) void lora_grad_reduce_kernel(LoraGradJobs jobs
     const int idx = blockIdx.x * 64 + lane;              // over nrows*C, c fastest
     const bool ok = idx < nrows * C;
     const int j = ok ? idx / C : 0, c = ok ? idx - j * C : 0;
-    const int per = (nchunk + 3) >> 2;
+    const int per = (nchunk + W - 1) / W;
     const int k0 = wave * per, k1 = min(k0 + per, nchunk);
     float s = 0.f;
     if (ok) {
@@ -232,9 +238,8 @@ __global__ __launch_bounds__(256) void lora_grad_reduce_kernel(LoraGradJobs jobs
     if (wave > 0) red[wave - 1][lane] = s;
     __syncthreads();
     if (wave == 0 && ok) {
-        s += red[0][lane];
-        s += red[1][lane];
-        s += red[2][lane];
+#pragma unroll
+        for (int w = 0; w < W - 1; ++w) s += red[w][lane];
         float *dst = j < r ? out : out_second;
         const int jj = j < r ? j : j - r;
         if (out_is_rxC) dst[(size_t)jj * C + c] = s;
@@ -467,7 +472,11 @@ int launch_lora_grad_jobs(const LoraGradDesc *d, int njobs, int r, int T, hipStr
     prof_end(rec, PK_LORA_GRAD, bytes, st);
     SL_CHECK_LAUNCH("lora_grad_partial");
     if (nchunk == 1) return 0;                           // (one record of 128 tokens: 3.3 us of its 104 a block)
-    hipLaunchKernelGGL(lora_grad_reduce_kernel, dim3((max_red + 63) / 64, 1, njobs), dim3(256), 0, st, jobs, r);
+    int most = 0;
+    for (int k = 0; k < njobs; ++k) most = std::max(most, jobs.j[k].nchunk);
+    const dim3 grid((max_red + 63) / 64, 1, njobs);
+    if (most >= GR_MANY) hipLaunchKernelGGL(lora_grad_reduce_kernel<16>, grid, dim3(1024), 0, st, jobs, r);
+    else hipLaunchKernelGGL(lora_grad_reduce_kernel<4>, grid, dim3(256), 0, st, jobs, r);
     SL_CHECK_LAUNCH("lora_grad_reduce");
     return 0;
 }

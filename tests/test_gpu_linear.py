@@ -243,12 +243,12 @@ def test_fp32_zero_B_is_bitwise_base():
     (64, 128, 128, 1, False),
     (512, 768, 768, 2, True),        # the remaining ranks of the paper's sweep r in {1, 2, 4, 8} (Sec. IV)
     (512, 768, 2304, 8, False),
-    # 133 chunks of 128 tokens, the last one ragged: 34 for each wavefront of the adapter-gradient reduction, 31 for the
-    # last (the body with eight loads in flight, and its tail)
+    # 133 chunks of 128 tokens, the last one ragged: nine for each wavefront of the adapter-gradient reduction (the body with
+    # eight loads in flight, and its tail), seven for the 15th, none for the last
     (16960, 256, 64, 4, True),
     (16960, 64, 256, 16, False),
     # both sides of tokens x the wider side = 2^24, where chunks of 128 tokens become chunks of 512 (for both gradients): 128 short
-    # chunks, the last one ragged; 33 long ones, the last of 16 tokens, nine for each wavefront and six for the last (tail only)
+    # chunks, the last one ragged; 33 long ones, the last of 16 tokens, three for each of 11 wavefronts (tail only)
     (16383, 1024, 64, 4, False),
     (16400, 1024, 64, 4, True),
     (16400, 64, 1024, 16, False),
@@ -263,6 +263,18 @@ def test_bf16_layer(T, n_in, n_out, r, bias):
         e = relerr(g, rf)
         say("   %s rel err %.2e" % (name, e))
         assert e <= BF16_TOL, (name, e)
+
+
+# chunks of 128 tokens: 31 (4 waves of the reduction share them), 32 and 33 (16 waves; the last of 11 with 33), 49, 160
+@pytest.mark.parametrize("T", [3968, 3969, 4096, 4097, 6145, 20480])
+def test_bf16_adapter_gradient_chunks(T):
+    c = synth.make_single_layer(T, 64, 128, 3, seed=53, quant=True)
+    c["B"] = synth.round_bf16(c["B"] * 10)
+    _, _, dA, dB = _run_bf16(c)
+    _, _, rdA, rdB = _oracle(c)
+    say("bf16 gradient chunks", T, relerr(dA, rdA), relerr(dB, rdB))
+    # (each chunk is 1/T of the sum: one left out or read twice is an error of 1/sqrt(160) = 8e-2 or more)
+    assert relerr(dA, rdA) <= BF16_TOL and relerr(dB, rdB) <= BF16_TOL
 
 
 def test_bf16_zero_B_is_bitwise_base():
