@@ -371,7 +371,7 @@ inline unsigned char *qas(const slora_ctx *c) { return c->mx ? at<unsigned char>
 // 3072 -> 1024 with 48 columns 207, 156; 1024 -> 4096 with the saved GELU' 331, 273.
 bool one_pass(const slora_ctx *c, const GemmArgs &a, int epi, int nz, int njobs)
 {
-    if (c->mx || nz == 0 || (a.K % 256) || !rank_grad_fills(c->T, njobs, c->r)) return false;
+    if (c->mx || nz == 0 || (a.K % 256) || !rank_grad_fills(c->T, njobs, c->r, a.K)) return false;
     const TilePlan p = plan_gemm_tile(a.M, a.seg_n, a.nseg, a.K, epi, nz, false, true);
     return p.tm == 256 && p.tn == 256;
 }

@@ -174,7 +174,7 @@ struct RankGradDesc {
     unsigned char *codes, *scales;   // [T,C], [T,C/32], or null
 };
 int rank_grad_rows(int r);
-bool rank_grad_fills(int T, int njobs, int r);           // whether that launch has a block for most CUs
+extern "C" bool rank_grad_fills(int T, int njobs, int r, int width);      // whether that launch has blocks enough for a product of that contraction
 int launch_rank_grad(const RankGradDesc *d, int njobs, int r, float s, int T, hipStream_t st);
 int launch_fedavg(int K, const float *const *x, const float *w, size_t n, float *out, hipStream_t st);
 int launch_sgd(float *p, const float *g, float lr, size_t n, hipStream_t st);

@@ -744,7 +744,7 @@ int slora_mx_lora_linear_bwd(int32_t T, int32_t n_in, int32_t n_out, int32_t r, 
     if ((rc = launch_layer_front(f, st))) return rc;
     // one pass over dy for its codes, ps and the partial sums of dB, where they fit the scratch (rank up to 8) and there are
     // blocks enough
-    const bool one_pass = r <= 8 && n_out % 256 == 0 && rank_grad_fills(T, 1, r);
+    const bool one_pass = r <= 8 && n_out % 256 == 0 && rank_grad_fills(T, 1, r, n_out);
     if (one_pass) {
         const RankGradDesc g = {(const bf16 *)dy, n_out, n_out, (const bf16 *)(base + w.B16T), n_out, (const bf16 *)(base + w.zs),
                                 (bf16 *)(base + w.ps), 16, (float *)(base + w.part_b), base + w.q, base + w.qs};

@@ -190,9 +190,14 @@ __global__ __launch_bounds__(512, 1) void rank_grad_kernel(RankGradJobs jobs, in
 
 int rank_grad_rows(int r) { return r <= 4 ? 128 : 256; }
 // Layers with MXFP8 weights, forward + backward in us, as separate passes and as this one: 8192 x 1024 -> 4096 (64 blocks) 156, 184;
-// 16384 x 1024 -> 3072 (128) 229, 227; 30001 x 1280 -> 3840 (235) 605, 550; 32768 x 1024 -> 4096 (256) 584, 521; rank 8: 12000 x
-// 1280 -> 5120 (47) 318, 408; 32768 x 4096 -> 1024 (128) 628, 617.
-bool rank_grad_fills(int T, int njobs, int r) { return (long)((T + rank_grad_rows(r) - 1) / rank_grad_rows(r)) * njobs >= 224; }
+// 18432 x 768 -> 2304 (144) 171, 179; 20480 x 768 -> 2304 (160) 191, 185; 20480 x 4096 -> 1024 407, 397; 20480 x 1024 -> 4096 384, 354;
+// 32768 x 1024 -> 4096 (256) 584, 521; rank 8: 12000 x 1280 -> 5120 (47) 318, 408; 40960 x 1280 -> 3840 (160) 769, 717.  Stacks of two
+// layers: 1280 wide, q, v, 20480 tokens, rank 8 (160 blocks) 4130, 4066; all six, rank 4 4755, 4691; 24576 tokens (192) 5341, 5250;
+// 768 wide, all six, 20480 tokens, rank 4, passes of 768 columns among them, 2237, 2254: what a narrow product saves, a pass costs.
+bool rank_grad_fills(int T, int njobs, int r, int width)
+{
+    return (long)((T + rank_grad_rows(r) - 1) / rank_grad_rows(r)) * njobs >= (width >= 1024 ? 160 : 224);
+}
 
 int launch_rank_grad(const RankGradDesc *d, int njobs, int r, float s, int T, hipStream_t st)
 {

@@ -75,6 +75,11 @@ def stack(T, d, f, proj, seq_len, fp8=False):
             for epi, nz, N, K, nseg in prods}
 
 
+def one_pass(T, jobs, r, width):
+    """whether rank-space gradients of `jobs` adapters and their dB come from one pass over a gradient of that width"""
+    return _fn("rank_grad_fills", c_bool, c_int, c_int, c_int, c_int)(T, jobs, r, width)
+
+
 def counted(M, N, K):
     """(rows, columns) of a plain store over counted rows on a kernel that computes all M, None for the one that counts"""
     p = _fn("plan_gemm_counted", TilePlan, c_int, c_int, c_int)(M, N, K)

@@ -93,6 +93,9 @@ def test_stack_of_the_rank_gradient_pass():
     """every input gradient of 28800 tokens on 256 x 256 tiles, where the rank-space tail is; of a client's 5760 on others"""
     for N, K, epi, nz in ((1024, 512, plans.DGELU, 16), (512, 1024, plans.STORE, 16), (512, 512, plans.STORE, 16), (512, 1536, plans.STORE, 48)):
         assert plans.tile(28800, N, K, epi, nz)[0] == (256, 256) != plans.tile(5760, N, K, epi, nz)[0], (N, K)
+    assert all(plans.one_pass(28800, 1, 4, K) for K in (512, 1024)) and plans.one_pass(28800, 3, 16, 1536)
+    for (T, r, width), want in mx.ONE_PASS.items():
+        assert plans.one_pass(T, 1, r, width) == want, (T, r, width)
 
 
 def test_logits_of_a_loss_head():
