@@ -8,7 +8,7 @@
 // The rank-space product X.Z^T is accumulated inside the K loop from the X tile that is
 // already in LDS, scaled, rounded to bf16, staged through LDS and applied as K2/16 extra
 // MFMA steps; the first column tile of a segment also spills it ([M,K2] bf16) because the
-// adapter-gradient kernels need it.
+// adapter-gradient kernels need it.  Input gradients of large batches find it spilled already (gemm_tail4).
 //
 // Tiling: 256x256x64 block tile, 8 waves (2 x 4), wave tile 128x64 = 8x4 MFMA 16x16x32
 // tiles (measured ~8 % faster than 32x32x16 on this power-limited part); two LDS stages filled
@@ -578,6 +578,11 @@ __global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     gemm4_body<EPI, NI, true>(a);
 }
 
+// The 4-wave kernel for a product whose rank-space activations are there (rank_grad.hip forms them in the pass that forms dB):
+// bound as gemm_kernel4; there is no room in LDS to form them in its loop, and the loop that forms them (gemm_kernel) reads
+// half as much again from LDS.  The tail adds 32 or 64 to the contraction, its operands come under way two slabs before the end.
+// us at 32768 rows, gemm_kernel and this: 3072 -> 1024 with 32 columns 178, 150; 4096 -> 1024 229, 193; 1024 -> 4096 with the
+// saved GELU' 331, 273 (no branch at all: 194 and 273).
 template <int EPI>
 __global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_tail4(GemmArgs a)
 {

@@ -6,7 +6,8 @@
 //    Both are G[c,j] = sum_t X[t,c] Y[t,j] with a tall X [T,C] and a skinny Y [T,16]: one
 //    streaming pass over X (HBM-bound) feeding MFMAs whose operands are read along the token
 //    axis with the LDS transpose read, per-chunk partial sums, then a fixed-order reduction
-//    over chunks -- no floating-point atomics, so results are reproducible.  Y must have 16
+//    over chunks -- no floating-point atomics, so results are reproducible (dB's partial sums of
+//    large batches come from the pass of rank_grad.hip).  Y must have 16
 //    readable columns per row (the spilled rank-space activations are padded with zeros).
 //  * SGD (Eq. 4-5): p = fmaf(-lr, g, p).
 //  * FedAvg (Sec. III-B step b2, Eq. 8-9): acc = fmaf(w_i, x_i[j], acc), i = 0..K-1.
