@@ -332,8 +332,9 @@ __global__ __launch_bounds__(256 * KS) void f32_gemm_kernel(GemmF32 a)
 // of the time, and the result is closer to the sum in 64 bits (errors in the 2-norm, chains of 768 and 5120 products of normal
 // numbers: 4.1e-7 against 5.1e-7, 1.1e-6 against 1.3e-6; of absolute values 3.0e-7, 4.3e-7 and 6.0e-7, 9.7e-7).  Rounded, not
 // cut: cut pieces all have the sign of their number, and what is left out adds up (5120 absolute values: 1.1e-5).
-// Infinities and NaN, and numbers that bf16 rounds to an infinity, come out as NaN or infinity: a wave that finds one among
-// its sums forms them again with the fp32 instruction.  Below 2^-102 the smallest of the three pieces loses bits.
+// Infinities and NaN, and numbers that bf16 rounds to an infinity, come out as NaN or infinity: such a sum is formed again with the
+// fp32 instruction, and only that one, so that a row's bits are the same whatever its neighbours hold.  Below 2^-102 the smallest
+// of the three pieces loses bits.
 __device__ __forceinline__ void split3(const float4 &u, const float4 &v, bf16x8 (&p)[3])
 {
     float x[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
@@ -386,7 +387,7 @@ __device__ __forceinline__ void mfma_split(f32x4 *acc, int stride, f32x4 *small,
             c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[i][PA[q]], pb[PB[q]], c, 0, 0, 0);
         }
 }
-// sums that are no finite numbers (0 x would be NaN for them)
+// whether the wave holds a sum that is no finite number (0 times it is NaN)
 __device__ __forceinline__ bool any_not_finite(const f32x4 *acc, int n)
 {
     float c = 0.f;
@@ -395,6 +396,29 @@ __device__ __forceinline__ bool any_not_finite(const f32x4 *acc, int n)
 #pragma unroll
         for (int e = 0; e < 4; ++e) c = fmaf(acc[i][e], 0.f, c);
     return __any(c != 0.f);
+}
+// those sums of a 16 x 16 tile formed again: `chains` sums of the fp32 instruction, one for each k in [at(c), at(c + 1)), added in
+// order.  x: the lane's row of A; y: its column of B, elements ys apart, zeros unless yok
+template <class At>
+__device__ __forceinline__ void sum_again(f32x4 &v, const float *x, const float *y, size_t ys, bool yok, int chains, At at, int g)
+{
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < chains; ++c) {
+        f32x4 part = {0.f, 0.f, 0.f, 0.f};
+        at(c, [&](int k) {
+            float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (yok) {
+                const float *q = y + (size_t)(k + 4 * g) * ys;
+                b = make_float4(q[0], q[ys], q[2 * ys], q[3 * ys]);
+            }
+            mfma4(part, *(const float4 *)(x + k + 4 * g), b);
+        });
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] += part[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (v[e] * 0.f != 0.f) v[e] = sum[e];
 }
 
 // TM x TN tile per block of NW waves, each of which takes its share of the contraction for the whole tile; the waves' sums are added
@@ -573,28 +597,6 @@ __device__ __forceinline__ void f32_wave_tile(const GemmF32 &a, unsigned char *l
         uu[q] = up_frag_u(a, n, g);
         bias[q] = a.bias ? a.bias[n] : 0.f;
     }
-    if (any_not_finite(acc, NT)) {
-#pragma unroll
-        for (int i = 0; i < NT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int k = s0 * 32 + 4 * g; k < s1 * 32; k += 16) {
-            float4 f[MI];
-#pragma unroll
-            for (int i = 0; i < MI; ++i) f[i] = *(const float4 *)(a.A + (size_t)min(m0 + i * 16 + r16, a.M - 1) * a.K + k);
-#pragma unroll
-            for (int j = 0; j <= NI; ++j) {
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (j < NI || zok) {
-                    const int n = j < NI ? min(n0 + j * 16 + r16, a.N - 1) : r16;
-                    const bool rowsk = BT;               // B and Z as [n, k] in the forward, [k, n] in the input gradient
-                    const float *q = (j < NI ? a.B : a.Z) + (rowsk ? (size_t)n * a.K + k : (size_t)k * (j < NI ? a.N : a.r) + n);
-                    const size_t st = rowsk ? 1 : j < NI ? a.N : a.r;
-                    v = make_float4(q[0], q[st], q[2 * st], q[3 * st]);
-                }
-#pragma unroll
-                for (int i = 0; i < MI; ++i) mfma4(acc[i * (NI + 1) + j], f[i], v);
-            }
-        }
-    }
     __syncthreads();                                     // the waves' pieces of LDS take their sums
     float4 *part = (float4 *)lds;
 #pragma unroll
@@ -606,6 +608,13 @@ __device__ __forceinline__ void f32_wave_tile(const GemmF32 &a, unsigned char *l
         for (int w = 0; w < NW; ++w) {
             const float4 q = part[(w * NT + t) * 64 + lane];
             v[0] += q.x; v[1] += q.y; v[2] += q.z; v[3] += q.w;
+        }
+        if (any_not_finite(&v, 1)) {
+            const int i = t / (NI + 1), j = t % (NI + 1), n = j < NI ? min(n0 + j * 16 + r16, a.N - 1) : r16;
+            const float *y = j < NI ? a.B : a.Z;         // as [n, k] in the forward, [k, n] in the input gradient
+            const size_t ld = BT ? a.K : j < NI ? a.N : a.r;
+            sum_again(v, a.A + (size_t)min(m0 + i * 16 + r16, a.M - 1) * a.K, y + (BT ? n * ld : n), BT ? 1 : ld, j < NI || zok, NW,
+                      [&](int w, auto step) { for (int k = w * steps / NW * 32; k < (w + 1) * steps / NW * 32; k += 16) step(k); }, g);
         }
         return v;
     };
@@ -748,25 +757,6 @@ __device__ __forceinline__ void f32_ring_tile(const GemmF32 &a, unsigned char *l
     for (int i = 0; i < MI; ++i) ar[i] = (unsigned)min(m0 + (wm * MI + i) * 16 + r16, a.M - 1);
 #pragma unroll
     for (int j = 0; j < NI; ++j) br[j] = (unsigned)min(n0 + (wn * NI + j) * 16 + r16, a.N - 1);
-    if (any_not_finite(acc, MI * NI)) {
-#pragma unroll
-        for (int i = 0; i < MI * NI; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int t = 0; t < nst; ++t)
-            for (int h = 0; h < 2; ++h) {
-                const int k = t * 64 + grp * 32 + h * 16 + 4 * g;
-                float4 fa[MI];
-#pragma unroll
-                for (int i = 0; i < MI; ++i) fa[i] = *(const float4 *)(a.A + (size_t)ar[i] * a.K + k);
-#pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    const float *q = BT ? a.B + (size_t)br[j] * a.K + k : a.B + (size_t)k * a.N + br[j];
-                    const size_t st = BT ? 1 : a.N;
-                    const float4 fb = make_float4(q[0], q[st], q[2 * st], q[3 * st]);
-#pragma unroll
-                    for (int i = 0; i < MI; ++i) mfma4(acc[i * NI + j], fa[i], fb);
-                }
-            }
-    }
     __syncthreads();                                     // the ring takes the second group's sums
     float4 *part = (float4 *)lds;
     if (grp == 1) {
@@ -778,6 +768,28 @@ __device__ __forceinline__ void f32_ring_tile(const GemmF32 &a, unsigned char *l
     float4 uz[MI], uu[NI];
     float bias[NI];
 #pragma unroll
+    for (int i = 0; i < MI * NI; ++i) {
+        const float4 v = part[i * 256 + (tid & 255)];
+        acc[i][0] += v.x; acc[i][1] += v.y; acc[i][2] += v.z; acc[i][3] += v.w;
+    }
+    if (any_not_finite(acc, MI * NI)) {                  // (tile by tile: through the half of the ring that is free)
+        static_assert(NST * STAGE >= 2 * 256 * MI * NI * 16, "room for both groups' sums");
+        f32x4 *own = (f32x4 *)(part + 256 * MI * NI) + wave * MI * NI * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < MI * NI; ++i) own[i * 64] = acc[i];
+#pragma unroll 1
+        for (int i = 0; i < MI * NI; ++i) {
+            f32x4 v = own[i * 64];
+            if (!any_not_finite(&v, 1)) continue;
+            const size_t m = min(m0 + (wm * MI + i / NI) * 16 + r16, a.M - 1), n = min(n0 + (wn * NI + i % NI) * 16 + r16, a.N - 1);
+            sum_again(v, a.A + m * a.K, a.B + (BT ? n * a.K : n), BT ? 1 : a.N, true, 2,
+                      [&](int c, auto step) { for (int k = c * 32; k < a.K; k += k & 16 ? 48 : 16) step(k); }, g);
+            own[i * 64] = v;
+        }
+#pragma unroll
+        for (int i = 0; i < MI * NI; ++i) acc[i] = own[i * 64];
+    }
+#pragma unroll
     for (int i = 0; i < MI; ++i) uz[i] = up_frag_z(a, (int)ar[i], g);
 #pragma unroll
     for (int j = 0; j < NI; ++j) { uu[j] = up_frag_u(a, (int)br[j], g); bias[j] = a.bias ? a.bias[br[j]] : 0.f; }
@@ -786,8 +798,6 @@ __device__ __forceinline__ void f32_ring_tile(const GemmF32 &a, unsigned char *l
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             f32x4 &c = acc[i * NI + j];
-            const float4 v = part[(i * NI + j) * 256 + (tid & 255)];
-            c[0] += v.x; c[1] += v.y; c[2] += v.z; c[3] += v.w;
             f32x4 low = {0.f, 0.f, 0.f, 0.f};
             mfma4(low, uz[i], uu[j]);
 #pragma unroll

@@ -175,6 +175,28 @@ def test_fp32_infinity_stays_an_infinity(T, n_in, n_out):
     assert np.isfinite(np.delete(y, 7, 0)).all() and np.isfinite(np.delete(dx, 9, 0)).all()
 
 
+# A sum that is formed again because an operand is infinite, or has no bf16 neighbour but infinity (3.39e38 and above), leaves the
+# sums beside it alone: the same bits as without that operand, in every form of the kernel on bf16 pieces and both directions.
+@pytest.mark.parametrize("value", [np.inf, 3.4e38])
+@pytest.mark.parametrize("T,n_in,n_out", list(FP32_RING_FORMS))
+def test_fp32_sums_do_not_depend_on_their_neighbours(T, n_in, n_out, value):
+    c = synth.make_single_layer(T, n_in, n_out, 5, seed=19 + T, bias=True)
+    for k in ("W", "A", "B"):
+        c[k] = c[k] * np.float32(1e-3)
+    y, dx = _run_f32(c)[:2]
+    say("fp32 layer with one", value, T, n_in, n_out)
+    rows = dict(c, x=c["x"].copy(), dy=c["dy"].copy())   # an element of a row each
+    rows["x"][7, 5] = rows["dy"][9, 11] = value
+    y1, dx1 = _run_f32(rows)[:2]
+    assert not np.array_equal(y1[7], y[7]) and not np.array_equal(dx1[9], dx[9])
+    assert np.array_equal(np.delete(y1, 7, 0), np.delete(y, 7, 0)) and np.array_equal(np.delete(dx1, 9, 0), np.delete(dx, 9, 0))
+    cols = dict(c, W=c["W"].copy())                      # of a column of either product
+    cols["W"][13, 6] = value
+    y2, dx2 = _run_f32(cols)[:2]
+    assert not np.array_equal(y2[:, 13], y[:, 13]) and not np.array_equal(dx2[:, 6], dx[:, 6])
+    assert np.array_equal(np.delete(y2, 13, 1), np.delete(y, 13, 1)) and np.array_equal(np.delete(dx2, 6, 1), np.delete(dx, 6, 1))
+
+
 # The products on three bf16 pieces an operand: fewer k-steps than waves, ragged tiles, an adapter that is not 16-byte aligned
 # (projection in a launch of its own), backward projections in the product's launch (rank up to 8) and not (16); and numbers
 # that bf16 rounds to an infinity, whose sums are formed again.  T, n_in, n_out, r, floats the adapter is off by: forms of
