@@ -332,12 +332,17 @@ __global__ __launch_bounds__(256 * KS) void f32_gemm_kernel(GemmF32 a)
 // of the time, and the result is closer to the sum in 64 bits (errors in the 2-norm, chains of 768 and 5120 products of normal
 // numbers: 4.1e-7 against 5.1e-7, 1.1e-6 against 1.3e-6; of absolute values 3.0e-7, 4.3e-7 and 6.0e-7, 9.7e-7).  Rounded, not
 // cut: cut pieces all have the sign of their number, and what is left out adds up (5120 absolute values: 1.1e-5).
-// Infinities and NaN, and numbers that bf16 rounds to an infinity, come out as NaN or infinity: such a sum is formed again with the
-// fp32 instruction, and only that one, so that a row's bits are the same whatever its neighbours hold.  Below 2^-102 the smallest
-// of the three pieces loses bits.
+// The pieces are those of 2^24 times the number, which are normal numbers or zero whatever it was (its last bit is 2^-149 or more:
+// unscaled, the last piece loses bits below 2^-102 and nothing is left at 2^-134); a sum gets its own scale back where the waves'
+// shares of it have been added.
+// Infinities and NaN, numbers that bf16 rounds to an infinity (from 2^104 on) and sums from 2^80 on come out as NaN or infinity:
+// such a sum is formed again with the fp32 instruction, and only that one, so that a row's bits are the same whatever its neighbours hold.
+constexpr float PIECES = 0x1p24f, SUM_SCALE = 0x1p-48f;
 __device__ __forceinline__ void split3(const float4 &u, const float4 &v, bf16x8 (&p)[3])
 {
     float x[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] *= PIECES;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
         union { unsigned w[4]; bf16x8 v; } c;
@@ -361,16 +366,18 @@ __device__ __forceinline__ void split_done()
     asm volatile("s_nop 1");
     __builtin_amdgcn_sched_barrier(0);
 }
-// ask for the conversion of one fragment (44 instructions) between the products of MI row tiles with another
-template <int MI>
+// Ask for the conversion of one fragment (52 instructions) between the products of MI row tiles with another, 44 of them spaced
+// evenly: us of forward products 4096 x 768 -> 3072 and 8192 x 1280 -> 5120 with 3 behind each product, all 52 spaced evenly and
+// these 44 132.3, 129.4, 127.1 and 653, 641, 638 (unscaled pieces, 44 instructions, 2 behind each: 131.5 and 611).
+template <int MI, int I = 0>
 __device__ __forceinline__ void spread_split()
 {
-#pragma unroll
-    for (int i = 0; i < 6 * MI; ++i) {
+    if constexpr (I < 6 * MI) {
+        constexpr int before = I * 44 / (6 * MI), upto = (I + 1) * 44 / (6 * MI);
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);               // an MFMA
-        __builtin_amdgcn_sched_group_barrier(0x002, (44 + 6 * MI - 1) / (6 * MI), 0);
-    }
-    split_done();
+        __builtin_amdgcn_sched_group_barrier(0x002, upto - before, 0);
+        spread_split<MI, I + 1>();
+    } else split_done();
 }
 // the six products, the small ones first; neighbours work on different accumulators.  With sums of their own for the small
 // ones (to be added at the end) the error is 0.4 of it.
@@ -609,6 +616,8 @@ __device__ __forceinline__ void f32_wave_tile(const GemmF32 &a, unsigned char *l
             const float4 q = part[(w * NT + t) * 64 + lane];
             v[0] += q.x; v[1] += q.y; v[2] += q.z; v[3] += q.w;
         }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] *= SUM_SCALE;
         if (any_not_finite(&v, 1)) {
             const int i = t / (NI + 1), j = t % (NI + 1), n = j < NI ? min(n0 + j * 16 + r16, a.N - 1) : r16;
             const float *y = j < NI ? a.B : a.Z;         // as [n, k] in the forward, [k, n] in the input gradient
@@ -771,6 +780,8 @@ __device__ __forceinline__ void f32_ring_tile(const GemmF32 &a, unsigned char *l
     for (int i = 0; i < MI * NI; ++i) {
         const float4 v = part[i * 256 + (tid & 255)];
         acc[i][0] += v.x; acc[i][1] += v.y; acc[i][2] += v.z; acc[i][3] += v.w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][e] *= SUM_SCALE;
     }
     if (any_not_finite(acc, MI * NI)) {                  // (tile by tile: through the half of the ring that is free)
         static_assert(NST * STAGE >= 2 * 256 * MI * NI * 16, "room for both groups' sums");

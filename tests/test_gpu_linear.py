@@ -197,6 +197,30 @@ def test_fp32_sums_do_not_depend_on_their_neighbours(T, n_in, n_out, value):
     assert np.array_equal(np.delete(y2, 13, 1), np.delete(y, 13, 1)) and np.array_equal(np.delete(dx2, 6, 1), np.delete(dx, 6, 1))
 
 
+# Operands times powers of two are sums times powers of two, bit by bit, while nothing rounds at the edge of the range: x and dy at
+# 2^-118, where a bf16 piece of 16 bits less would be no normal number, against W at 2^60; W at 2^-118 against x and dy at 2^60; and
+# subnormal ones at 2^-140.
+@pytest.mark.parametrize("tiny", ["x", "W", "subnormal x", "subnormal W"])
+@pytest.mark.parametrize("T,n_in,n_out", list(FP32_RING_FORMS))
+def test_fp32_tiny_operands_keep_their_bits(T, n_in, n_out, tiny):
+    c = synth.make_single_layer(T, n_in, n_out, 5, seed=29 + T, bias=False)
+    down = -140 if "subnormal" in tiny else -118
+    ex = {k: down if tiny.endswith("x") == (k != "W") else 60 - down - 118 for k in ("x", "dy", "W")}
+    for k in ("x", "dy") if tiny.endswith("x") else ("W",):         # whole multiples of 2^-149 there
+        c[k] = np.ldexp(np.round(np.ldexp(c[k].astype(np.float64), 149 + down + (k == "W") * 5)), -149 - down).astype(np.float32)
+    z = 40 if ex["x"] < 0 else -60                       # (the rank-space activations between 2^-100 and 2^22)
+    ex["A"], ex["B"] = z, ex["W"] - z                    # (both terms of a result in one scale)
+    t = dict(c)
+    for k, e in ex.items():
+        t[k] = np.ldexp(c[k], e).astype(np.float32)
+        assert np.array_equal(np.ldexp(t[k].astype(np.float64), -e), c[k]), k
+    say("fp32 layer, tiny", tiny, T, n_in, n_out, ex)
+    (y, dx), (ty, tdx) = _run_f32(c)[:2], _run_f32(t)[:2]
+    for name, got, want, e in (("y", ty, y, ex["x"] + ex["W"]), ("dx", tdx, dx, ex["dy"] + ex["W"])):
+        want = np.ldexp(want, e).astype(np.float32)
+        assert np.array_equal(got, want), (name, relerr(got, want))
+
+
 # The products on three bf16 pieces an operand: fewer k-steps than waves, ragged tiles, an adapter that is not 16-byte aligned
 # (projection in a launch of its own), backward projections in the product's launch (rank up to 8) and not (16); and numbers
 # that bf16 rounds to an infinity, whose sums are formed again.  T, n_in, n_out, r, floats the adapter is off by: forms of
