@@ -523,7 +523,11 @@ __device__ __forceinline__ void gemm4_body(GemmArgs a)
 #pragma unroll
                             for (int e = 0; e < 8; ++e) za[i][e] = f2bf(0.f);
                     }
-                    asm volatile("s_nop 1" ::: "memory");                    // (a vector write, then an MFMA the compiler does not see)
+                    // a vector write, then an MFMA the compiler does not see: 2 wait states (tests/test_kernel_isa.py); the barriers,
+                    // because nothing else ties the zeros above to this side of them
+                    __builtin_amdgcn_sched_barrier(0);
+                    asm volatile("s_nop 1" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -582,7 +586,7 @@ __global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 // bound as gemm_kernel4; there is no room in LDS to form them in its loop, and the loop that forms them (gemm_kernel) reads
 // half as much again from LDS.  The tail adds 32 or 64 to the contraction, its operands come under way two slabs before the end.
 // us at 32768 rows, gemm_kernel and this: 3072 -> 1024 with 32 columns 178, 150; 4096 -> 1024 229, 193; 1024 -> 4096 with the
-// saved GELU' 331, 273 (no branch at all: 194 and 273).
+// saved GELU' 331, 273 (no branch at all: 194 and 273).  It has all 512 registers and spills three of the epilogue's, read back once a tile.
 template <int EPI>
 __global__ __launch_bounds__(NTHR4) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_tail4(GemmArgs a)
 {

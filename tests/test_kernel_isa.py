@@ -136,6 +136,10 @@ def test_tail_gemm_mfma_hazards(gemm_asm):
             assert len(acc) == 64, name
             worst, where = _min_wait_states_to_acc_access(body, last)
             assert worst >= MIN_WAIT_STATES, (name, worst, where)
+            # what the kernel spills (it has all 512 registers) stays out of both loops
+            assert not any("scratch_" in ins for ins in body[first:last]), name
+        # the tail's operands are zeroed by vector instructions; the main loop's come from LDS alone
+        assert not _operands_too_close(body, "v_"), (name, _operands_too_close(body, "v_")[:2])
 
 
 def _check_mfma_hazards(funcs):
@@ -305,8 +309,9 @@ def _vgprs(text):
     return regs
 
 
-def _conversions_too_close(body):
-    """(conversion, MFMA) pairs of which the second reads what the first wrote fewer than 2 wait states earlier"""
+def _operands_too_close(body, writer):
+    """(vector instruction, MFMA) pairs of which the second reads as an operand what the first, one that starts with `writer`,
+    wrote fewer than 2 wait states earlier"""
     code = [ins for ins in body if not _is_label(ins)]
     found = []
     for i, ins in enumerate(code):
@@ -314,7 +319,7 @@ def _conversions_too_close(body):
             continue
         used, ws, j = _vgprs(ins.split(",", 1)[1]), 0, i - 1
         while j >= 0 and ws < 2:
-            if code[j].startswith("v_cvt_pk_bf16_f32") and _vgprs(code[j].split(",")[0]) & used:
+            if code[j].startswith(writer) and not code[j].startswith("v_mfma") and _vgprs(code[j].split(",")[0]) & used:
                 found.append((code[j], ins))
             ws += _wait_states(code[j])
             j -= 1
@@ -326,9 +331,11 @@ def test_fp32_pieces_are_settled_before_the_products():
     funcs = {n: b for n, b in _functions(_assembly("f32_linear.hip")).items() if "f32_tile_kernel" in n}
     assert all(sum(x.startswith("v_cvt_pk_bf16_f32") for x in b) >= 60 for b in funcs.values())
     for name, body in funcs.items():
-        assert not _conversions_too_close(body), (name, _conversions_too_close(body)[:2])
+        assert not _operands_too_close(body, "v_cvt_pk_bf16_f32"), (name, _operands_too_close(body, "v_cvt_pk_bf16_f32")[:2])
     bad = ["v_cvt_pk_bf16_f32 v5, v1, v2", "s_mov_b32 s1, s2", "v_mfma_f32_16x16x32_bf16 v[8:11], v[4:7], v[0:3], v[8:11]"]
-    assert _conversions_too_close(bad) and not _conversions_too_close(bad[:1] + ["s_nop 1"] + bad[2:])
+    for writer in ("v_cvt_pk_bf16_f32", "v_"):
+        assert _operands_too_close(bad, writer) and not _operands_too_close(bad[:1] + ["s_nop 1"] + bad[2:], writer)
+    assert _operands_too_close(["v_mov_b64_e32 v[6:7], v[0:1]"] + bad[1:], "v_")
 
 
 def _loops(body):
