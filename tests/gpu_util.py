@@ -22,6 +22,19 @@ def relerr(got, ref):
     return float(np.abs(got - ref).max() / (den if den > 0 else 1.0))
 
 
+def one_by_one(X, Y):
+    """sum_k X[:, k] Y[:, k]^T in fp32, a fused multiply-add for each k in order"""
+    acc = np.zeros((X.shape[0], Y.shape[0]), np.float32)
+    for k in range(X.shape[1]):
+        acc = (X[:, k, None].astype(np.float64) * Y[None, :, k].astype(np.float64) + acc).astype(np.float32)
+    return acc
+
+
+def norm_err(got, ref):
+    """2-norm of the difference over the 2-norm of ref, in 64 bits"""
+    return float(np.linalg.norm(np.asarray(got, np.float64) - ref) / np.linalg.norm(ref))
+
+
 def say(*a):
     print(*a, flush=True)
     sys.stdout.flush()

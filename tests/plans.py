@@ -56,7 +56,8 @@ def mx_layer(T, n_in, n_out):
 
 
 def f32_layer(T, n_in, n_out):
-    """(rows, columns, stages of the ring of copies or 0) of an fp32 layer's two products, on aligned operands"""
+    """(rows, columns, pairs of waves or ring stages of the kernel on bf16 pieces, or 0) of an fp32 layer's two products, on aligned
+    operands"""
     f = _fn("plan_f32", F32Plan, c_int, c_int, c_int, c_bool)
     plan = [f(T, n_out, n_in, n_in % 4 == 0), f(T, n_in, n_out, n_in % 4 == 0 and n_out % 4 == 0)]
     return [(p.tm, p.tn, p.stages) for p in plan]

@@ -292,7 +292,7 @@ def test_wide_tile_gemm_copies_and_scalars():
     _check_valu_sgpr_to_vmem(text, "gemm_mx.hip")
 
 
-def test_fp32_ring_copies_and_scalars():
+def test_fp32_tile_copies_and_scalars():
     text = _assembly("f32_linear.hip")
     assert sum("f32_tile_kernel" in n for n in _functions(text)) == 10      # five tile forms x two orientations of W
     _check_m0(text, "f32_linear.hip")

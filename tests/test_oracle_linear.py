@@ -2,6 +2,7 @@
 import numpy as np
 import torch
 
+from gpu_util import norm_err, one_by_one
 from oracle import slora_oracle as so
 from paper_2407_00952_amd import synth
 
@@ -79,3 +80,24 @@ def test_planted_mistakes_are_caught():
     for bad in (wrong_scale, transposed, no_bias):
         assert np.abs(bad - good).max() > 1e-3
     assert np.abs(y - good).max() < 1e-12
+
+
+def test_a_lost_piece_exceeds_the_fp32_precision_bound():
+    """fp32 products as six products of three bf16 pieces each: all six are closer to the sum in 64 bits than a fused multiply-add for
+    each product in turn, any five are at least 3 times as far, from the shortest to the longest contraction that the GPU tests
+    hold to that bound."""
+    rng = np.random.default_rng(1)
+    for K in (64, 192, 1152, 1536):
+        x, w = rng.standard_normal((32, K)).astype(np.float32), (rng.standard_normal((256, K)) * 0.02).astype(np.float32)
+        ref = x.astype(np.float64) @ w.T.astype(np.float64)
+        plain = norm_err(one_by_one(x, w), ref)
+        px, pw = ([], [])
+        for out, v in ((px, x), (pw, w)):
+            for _ in range(3):
+                out.append(synth.round_bf16(v))
+                v = v - out[-1]
+            assert not v.any()
+        prods = [px[i].astype(np.float64) @ pw[j].T for i in range(3) for j in range(3 - i)]
+        assert len(prods) == 6 and norm_err(sum(prods), ref) < 0.1 * plain
+        for left_out in prods:
+            assert norm_err(sum(prods) - left_out, ref) > 3 * plain

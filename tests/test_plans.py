@@ -12,12 +12,12 @@ BF16_FORMS = {(32, 32), (32, 64), (64, 64), (64, 128), (128, 128), (192, 128), (
 FP8_FORMS = {(32, 64), (64, 64), (64, 128), (128, 128), (192, 128), (256, 128), (256, 256)}
 
 
-def test_fp32_ring_forms():
-    for case, (which, want) in linear.FP32_RING_FORMS.items():
+def test_fp32_tile_forms():
+    for case, (which, want) in linear.FP32_TILE_FORMS.items():
         fwd, bwd = plans.f32_layer(*case)
         assert (fwd if which == "forward" else bwd) == want, case
     for which in ("forward", "input gradient"):
-        assert {f for w, f in linear.FP32_RING_FORMS.values() if w == which} == {
+        assert {f for w, f in linear.FP32_TILE_FORMS.values() if w == which} == {
             (32, 64, 4), (64, 48, 4), (64, 64, 4), (64, 64, 2), (128, 128, 2)}
     for case, want in linear.FP32_PRECISION.items():
         assert plans.f32_layer(*case)[0] == want, case
