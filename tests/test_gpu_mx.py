@@ -271,11 +271,13 @@ def test_lora_linear_mxfp8(T, n_in, n_out, r, with_bias):
 
 # dy's codes, rank-space gradients and dB in one pass: blocks of 128 tokens (rank up to 4) and of 256, the last one ragged, one slab
 # of 256 columns, two and four; 28600 tokens (224 blocks, the last of 56 tokens) are the fewest of rank 3 that take it, 28544 do not;
-# from 1024 columns on 160 blocks do.
-ONE_PASS = {(28600, 3, 512): True, (28544, 4, 256): False, (57200, 8, 256): True, (20460, 4, 1024): True, (20352, 4, 1024): False}
+# from 1024 columns on 160 blocks do (of 256 tokens: with 41000 tokens 161, five slabs, the last block of 40 tokens).
+ONE_PASS = {(28600, 3, 512): True, (28544, 4, 256): False, (57200, 8, 256): True, (20460, 4, 1024): True, (20352, 4, 1024): False,
+            (41000, 8, 1280): True}
 
 
-@pytest.mark.parametrize("T,n_in,n_out,r", [(28600, 128, 512, 3), (28544, 128, 256, 4), (57200, 128, 256, 8), (20460, 128, 1024, 4)])
+@pytest.mark.parametrize("T,n_in,n_out,r", [(28600, 128, 512, 3), (28544, 128, 256, 4), (57200, 128, 256, 8), (20460, 128, 1024, 4),
+                                              (41000, 128, 1280, 8)])
 def test_lora_linear_mxfp8_one_pass(T, n_in, n_out, r):
     test_lora_linear_mxfp8(T, n_in, n_out, r, False)
 

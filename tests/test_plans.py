@@ -89,11 +89,17 @@ def test_batches_of_the_wider_stack():
         assert set().union(*(forms(n, 128, proj) for n in (1, 2, 4, 8, 16, 24, 33))) == BF16_FORMS - {(128, 256)}
 
 
-def test_stack_of_the_rank_gradient_pass():
-    """every input gradient of 28800 tokens on 256 x 256 tiles, where the rank-space tail is; of a client's 5760 on others"""
-    for N, K, epi, nz in ((1024, 512, plans.DGELU, 16), (512, 1024, plans.STORE, 16), (512, 512, plans.STORE, 16), (512, 1536, plans.STORE, 48)):
-        assert plans.tile(28800, N, K, epi, nz)[0] == (256, 256) != plans.tile(5760, N, K, epi, nz)[0], (N, K)
-    assert all(plans.one_pass(28800, 1, 4, K) for K in (512, 1024)) and plans.one_pass(28800, 3, 16, 1536)
+def test_stacks_of_the_rank_gradient_pass():
+    """input gradients of the adapted projections on 256 x 256 tiles, where the rank-space tail is, behind a pass; of a client's tokens
+    on other tiles, without one"""
+    for name, (d, f, r, proj, batch) in stack.AHEAD.items():
+        n = sum(p in proj for p in "qkv")
+        prods = {"pr": (f, d, plans.DGELU, 16, 1), "fc": (d, f, plans.STORE, 16, 1), "o": (d, d, plans.STORE, 16, 1)}
+        prods = [v for k, v in prods.items() if k in proj] + ([(d, 3 * d, plans.STORE, 16 * n, n)] if n else [])
+        for N, K, epi, nz, jobs in prods:
+            few = name == "rank 16" and jobs == 1        # (113 blocks: only q, k and v together are enough)
+            assert plans.one_pass(320 * batch, jobs, r, K) != few and not plans.one_pass(64 * batch, jobs, r, K), (name, N, K)
+            assert plans.tile(320 * batch, N, K, epi, nz)[0] == (256, 256) != plans.tile(64 * batch, N, K, epi, nz)[0], (name, N, K)
     for (T, r, width), want in mx.ONE_PASS.items():
         assert plans.one_pass(T, 1, r, width) == want, (T, r, width)
 
