@@ -1,9 +1,9 @@
 // Single-precision LoRA-adapted linear layer (SplitLoRA Sec. II-C), forward and backward.
 //
-// Every operand and every sum is fp32.  Products whose shapes allow it run on the bf16 matrix instruction with each operand
-// as the exact sum of three bf16 numbers (f32_tile_kernel; closer to the sum in 64 bits than the fp32 instruction), the others and
-// the rank-space projections on the fp32 one (V_MFMA_F32_16X16X4_F32), the adapter gradients on vector FMAs.  Each sum has one
-// fixed order, so results are reproducible.
+// Every operand and every sum is fp32.  Products whose shapes allow it run on the bf16 matrix instruction with each operand, times
+// 2^24, as the exact sum of three bf16 numbers (f32_tile_kernel; closer to the sum in 64 bits than the fp32 instruction; operands
+// and sums too large for that on the fp32 one), the others and the rank-space projections on the fp32 one
+// (V_MFMA_F32_16X16X4_F32), the adapter gradients on vector FMAs.  Each sum has one fixed order, so results are reproducible.
 //
 //   forward   z = x A^T                                 f32_tile_kernel on small tiles forms z itself; else f32_project_kernel
 //             y = x W^T + bias + s z B^T                f32_tile_kernel / f32_gemm_kernel / f32_gemm_direct_kernel
@@ -13,9 +13,9 @@
 //
 // At T = 1024, 768 -> 768, r = 4 (2.5 GFLOP, 15 MB) forward + backward take three launches and 38 us; with the products on the fp32
 // instruction (64 x 48 tiles on a ring in LDS, 0.64 of 0.77 us a stage of 64 being matrix time) and projections of their own
-// five launches and 46 us.  Whole layers in us, before and now: 64 rows of 1024 -> 3072, r = 16, 63.2 and 49.6; 200 of
-// 1280 -> 5120, r = 8, 164 and 90; 1024 of 3072 -> 768 133 and 99; 2048 of 1280 -> 1280, r = 16, 208 and 168; 8192 of 1280 -> 5120
-// 1719 and 1350.
+// five launches and 46 us.  Whole layers in us, before and now: 64 rows of 1024 -> 3072, r = 16, 63.2 and 50.4; 200 of
+// 1280 -> 5120, r = 8, 164 and 95; 1024 of 3072 -> 768 133 and 99; 2048 of 1280 -> 1280, r = 16, 208 and 167; 8192 of 1280 -> 5120
+// 1719 and 1390.
 #include "common.h"
 #include "gemm_copy.h"
 #include <type_traits>
@@ -137,8 +137,8 @@ struct GemmF32 {
 
 // The low-rank term is one more step of 16 contraction elements: operand fragments z[m, 4g ..] and U(4g .., n), zero
 // beyond the rank.  They are requested before the main loop, whose last step they follow.  Its sum is formed on its own and
-// added, scaled, in one rounding, after the bias: in the accumulators it would cost one more rounding at the size of the result for every element of the rank
-// (r = 16: 1.37 times the error at n_in = 16, 1.016 times at 768).
+// added, scaled, in one rounding, after the bias: in the accumulators it would cost one more rounding at the size of the result
+// for every element of the rank (r = 16: 1.37 times the error at n_in = 16, 1.016 times at 768).
 __device__ __forceinline__ float4 up_frag_z(const GemmF32 &a, int m, int g)
 {
     if (4 * g >= a.zp) return make_float4(0.f, 0.f, 0.f, 0.f);
@@ -326,14 +326,15 @@ __global__ __launch_bounds__(256 * KS) void f32_gemm_kernel(GemmF32 a)
 }
 
 // ---- products on the bf16 matrix instruction ----------------------------------------------------------------------
-// An fp32 number is the sum of three bf16 ones (8 bits each: round to nearest, subtract exactly, again), so a product of two
-// is six bf16 products, exact in fp32, and three left out that are below 2^-24 of it.  V_MFMA_F32_16X16X32_BF16 does sixteen times
+// An fp32 number is the sum of three bf16 ones (8 bits each: round to nearest, subtract exactly, again; Henry, Tang and Heinecke,
+// "Leveraging the bfloat16 artificial intelligence datatype for higher-precision computations", 2019), so a product of two is
+// six bf16 products, exact in fp32, and three left out that are below 2^-24 of it.  V_MFMA_F32_16X16X32_BF16 does sixteen times
 // the work of V_MFMA_F32_16X16X4_F32 in a pass and rounds its sum once where that rounds eight times: six of them take 0.375
 // of the time, and the result is closer to the sum in 64 bits (errors in the 2-norm, chains of 768 and 5120 products of normal
 // numbers: 4.1e-7 against 5.1e-7, 1.1e-6 against 1.3e-6; of absolute values 3.0e-7, 4.3e-7 and 6.0e-7, 9.7e-7).  Rounded, not
 // cut: cut pieces all have the sign of their number, and what is left out adds up (5120 absolute values: 1.1e-5).
 // The pieces are those of 2^24 times the number, which are normal numbers or zero whatever it was (its last bit is 2^-149 or more:
-// unscaled, the last piece loses bits below 2^-102 and nothing is left at 2^-134); a sum gets its own scale back where the waves'
+// unscaled, the last piece loses bits below 2^-110 and nothing is left at 2^-134); a sum gets its own scale back where the waves'
 // shares of it have been added.
 // Infinities and NaN, numbers that bf16 rounds to an infinity (from 2^104 on) and sums from 2^80 on come out as NaN or infinity:
 // such a sum is formed again with the fp32 instruction, and only that one, so that a row's bits are the same whatever its neighbours hold.

@@ -312,8 +312,8 @@ __global__ __launch_bounds__(NTHR) void gemm_kernel(GemmArgs a)
 // copies one.  With a single wave per SIMD whatever the wave issues in a clump is time the matrix pipe idles: the 32 fragment
 // reads and 16 copies of a slab go one by one behind MFMAs of their own, and the fragments of a k-step have a register set of
 // their own, so that the last read is 32 MFMAs old at the barrier.  Against three reads and two copies behind each row of 8
-// MFMAs: 3300 -> 2920 shader cycles a slab of 2048 MFMA cycles, of which the chip, at its power limit, takes back more than half
-// as clock (2.10 -> 1.94 GHz between copies).  us at 32768 x 4096 -> 1024 200.3 -> 195.0, 32768 x 1024 -> 4096 235.4 -> 231.2;
+// MFMAs: 3300 -> 2920 shader cycles a slab of 2048 MFMA cycles, of which the chip, at its power limit, takes back a part
+// as clock: 2.10 -> 1.94 GHz in launches with copies between them, 2.15 -> 2.06 in rounds of 18 blocks of width 1024.  us at 32768 x 4096 -> 1024 200.3 -> 195.0, 32768 x 1024 -> 4096 235.4 -> 231.2;
 // a round of 18 blocks of width 1024 at 32768 tokens 39.47 -> 38.27 ms, the loss head at 32768 x 1024 -> 50257 4.27 -> 3.99 ms.
 // The grid is one block per CU and a block walks its tiles itself, so that the first copies of the next
 // tile are in flight under the epilogue of the current one.

@@ -193,7 +193,9 @@ int rank_grad_rows(int r) { return r <= 4 ? 128 : 256; }
 // 18432 x 768 -> 2304 (144) 171, 179; 20480 x 768 -> 2304 (160) 191, 185; 20480 x 4096 -> 1024 407, 397; 20480 x 1024 -> 4096 384, 354;
 // 32768 x 1024 -> 4096 (256) 584, 521; rank 8: 12000 x 1280 -> 5120 (47) 318, 408; 40960 x 1280 -> 3840 (160) 769, 717.  Stacks of two
 // layers: 1280 wide, q, v, 20480 tokens, rank 8 (160 blocks) 4130, 4066; all six, rank 4 4755, 4691; 24576 tokens (192) 5341, 5250;
-// 768 wide, all six, 20480 tokens, rank 4, passes of 768 columns among them, 2237, 2254: what a narrow product saves, a pass costs.
+// 768 wide, all six, 20480 tokens, rank 4, passes in front of products of 768 among them, 2237, 2254: what a narrow product saves, a pass
+// costs.  `width` is the product's contraction, for q, k and v that of the three slices though a pass reads one: three layers 768
+// wide, 12800 tokens, q and v, rank 4 (200 blocks) 2101, 2090; 16384, q, k and v, rank 8 (192) 2446, 2411; 40960, q, rank 8 (160) 5341, 5310.
 bool rank_grad_fills(int T, int njobs, int r, int width)
 {
     return (long)((T + rank_grad_rows(r) - 1) / rank_grad_rows(r)) * njobs >= (width >= 1024 ? 160 : 224);
